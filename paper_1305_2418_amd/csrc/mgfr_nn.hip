@@ -20,8 +20,8 @@
 // 27 taps and its channels in steps of 32 (8 consecutive channels of one tap
 // per lane).  The backward-data pass is the same kernel on
 // the output gradient with the taps mirrored and the weight matrix transposed;
-// the backward-weight pass reduces over voxels with LDS-transposed tiles and
-// float32 atomics.
+// the backward-weight pass reduces over voxels, its fragments read from LDS by
+// the transpose load.
 #include "mgfr_internal.h"
 #include "mgfr_ops.h"
 
@@ -208,85 +208,145 @@ void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 
     }
 }
 
-// dW[t][o][c] += sum_v dZ[v][o] X[v + off(t)][c];  Cin, Cout % 16 == 0.
-// Grid (27, chunks); each workgroup reduces kWChunk voxels for one tap.
-constexpr int kWChunk = 2048, kWStage = 64;
+// dW[t][o][c] += sum_v dZ[v][o] X[v + off(t)][c] and db[o] += sum_v dZ[v][o];
+// Cin, Cout % 16 == 0, S >= 8.
+//
+// A GEMM per tap whose reduction runs over voxels, with both operands stored
+// channels-last, i.e. the wrong way round for the MFMA fragments (8
+// consecutive k = voxels per lane).  A workgroup owns one 16 x 16 block of
+// (output, input) channels for all 27 taps and walks over tiles of 512
+// voxels (TX x 8 x TZ): the tile of dZ and the tile plus halo of X are staged
+// once, as they lie in memory, and every tap's fragments are read from there
+// by the LDS transpose load (ds_read_b64_tr_b16: 16 lanes read 4 voxels x 16
+// channels and get 4 voxels of one channel each).  The order of the voxels
+// within a k-step is free, as long as both operands use the same: the 16
+// lanes of a group and the two halves of a fragment are laid out so that one
+// load of a wave reads 16 consecutive voxels of a row (512 contiguous bytes,
+// no bank conflict).  Wave w accumulates the taps w, w + 4, ...; the 28th slot
+// is the bias gradient (a product with ones).  The sums stay in registers
+// over all tiles and are added to dW once per workgroup.
+// Bound: the LDS reads (two per MFMA, 8 LDS cycles against 16 / 4 matrix
+// cycles per CU) and the staging between barriers.  16 -> 16 channels on 2.1 M
+// voxels: 2163 -> 87 us (333 TFLOP/s); the ten layers of one gradient of eight
+// 64^3 volumes: 14.4 -> 0.78 ms (before: a scalar transpose into LDS for each
+// tap, atomics per 2048 voxels), and the separate bias pass's 3.9 ms are gone.
+#ifndef MGFR_WG_SPLIT
+#define MGFR_WG_SPLIT 512
+#endif
+constexpr int kWgTile = 512;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-__global__ __launch_bounds__(256) void k_conv3d_wgrad(const __bf16 *__restrict__ X, const __bf16 *__restrict__ dZ,
-                                                       int lgS, int Cin, int Cout, size_t nvox,
-                                                       float *__restrict__ dW)
+__device__ __forceinline__ bf16x8 tr_pair(const __bf16 *p0, const __bf16 *p1)
 {
-    __shared__ __bf16 sA[96][kWStage + 8];
-    __shared__ __bf16 sB[96][kWStage + 8];
-    const int tap = blockIdx.x;
-    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-    const int S = 1 << lgS, sm = S - 1;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p0);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p1);
+    const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// grid (Cout / 16 * Cin / 16, splits of the tiles)
+template <int LGX>
+__global__ __launch_bounds__(256) void k_conv3d_wgrad(const __bf16 *__restrict__ X, const __bf16 *__restrict__ dZ,
+                                                       int lgS, int Cin, int Cout, unsigned ntiles,
+                                                       float *__restrict__ dW, float *__restrict__ db)
+{
+    constexpr int TX = 1 << LGX, TZ = kWgTile / (8 * TX);
+    constexpr int HX = TX + 2, HY = 10, HV = HX * HY * (TZ + 2);
+    __shared__ __attribute__((aligned(16))) __bf16 sX[HV * 16];
+    __shared__ __attribute__((aligned(16))) __bf16 sZ[kWgTile * 16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, r16 = lane & 15;
-    const int OT = Cout >> 4, CT = Cin >> 4, ntiles = OT * CT;
-    f32x4 acc[6];
+    const int S = 1 << lgS, sm = S - 1;
+    const int CT = Cin >> 4;
+    const int o0 = 16 * ((int)blockIdx.x / CT), c0 = 16 * ((int)blockIdx.x % CT);
+    const bool bias = db != nullptr && c0 == 0 && w == 3;
+    const unsigned ntx = (unsigned)S / TX, nty = (unsigned)S / 8, ntz = (unsigned)S / TZ;
+    // this lane's part of a row of voxels: voxel 4 g + r16 / 4 of 16, channels 4 (r16 & 3) ..
+    const int v0 = 4 * g + (r16 >> 2), c4 = 4 * (r16 & 3);
+    const __bf16 *pz = sZ + v0 * 16 + c4;
+    const __bf16 *px = sX + (((HY + 1 + (v0 >> LGX)) * HX) + 1 + (v0 & (TX - 1))) * 16 + c4;
+    f32x4 acc[7];
+    const __bf16 *pt[7];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const size_t vbeg = (size_t)blockIdx.y * kWChunk;
-    for (size_t vs = vbeg; vs < vbeg + kWChunk && vs < nvox; vs += kWStage) {
-        __syncthreads();
-        // stage dZ[vs..vs+63][0..Cout) -> sA[o][v] and X[shifted][0..Cin) -> sB[c][v]
-        for (int idx = threadIdx.x; idx < kWStage * Cout; idx += 256) {
-            const int v = idx / Cout, o = idx - v * Cout;
-            sA[o][v] = dZ[(vs + v) * Cout + o];
+    for (int q = 0; q < 7; ++q) {
+        acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int t = w + 4 * q < 27 ? w + 4 * q : 0;
+        pt[q] = px + (((t / 9 - 1) * HY + ((t / 3) % 3 - 1)) * HX + (t % 3 - 1)) * 16;
+    }
+    const __bf16 one = (__bf16)1.0f;
+    const bf16x8 ones = {one, one, one, one, one, one, one, one};
+    for (unsigned tile = blockIdx.y; tile < ntiles; tile += gridDim.y) {
+        unsigned b = tile;
+        const int x0 = (int)(b % ntx) * TX;
+        b /= ntx;
+        const int y0 = (int)(b % nty) * 8;
+        b /= nty;
+        const int z0 = (int)(b % ntz) * TZ;
+        const size_t vol = (size_t)(b / ntz) << (3 * lgS);
+        __syncthreads();  // the previous tile's readers are done
+#pragma unroll
+        for (int i = 0; i < kWgTile * 2 / 256; ++i) {
+            const int idx = tid + 256 * i, v = idx >> 1, h = idx & 1;
+            const int x = v & (TX - 1), y = (v >> LGX) & 7, z = v >> (LGX + 3);
+            const size_t src = vol + ((((size_t)(z0 + z) << lgS) + (size_t)(y0 + y)) << lgS) + (size_t)(x0 + x);
+            *(bf16x8 *)(sZ + v * 16 + 8 * h) = *(const bf16x8 *)(dZ + src * Cout + o0 + 8 * h);
         }
-        for (int idx = threadIdx.x; idx < kWStage * Cin; idx += 256) {
-            const int v = idx / Cin, c = idx - v * Cin;
-            const size_t vv = vs + v;
-            const int x = (int)(vv & sm), y = (int)((vv >> lgS) & sm), z = (int)((vv >> (2 * lgS)) & sm);
-            const size_t b = vv >> (3 * lgS);
-            const size_t src = (((b << lgS) + ((z + dz) & sm)) << (2 * lgS)) + ((size_t)((y + dy) & sm) << lgS) +
-                               ((x + dx) & sm);
-            sB[c][v] = X[src * Cin + c];
-        }
-        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            const int tile = w + 4 * q;
-            if (tile < ntiles) {
-                const int ot = tile / CT, ct = tile - ot * CT;
-#pragma unroll
-                for (int kk = 0; kk < kWStage; kk += 32) {
-                    bf16x8 a, b;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        a[j] = sA[16 * ot + r16][kk + 8 * g + j];
-                        b[j] = sB[16 * ct + r16][kk + 8 * g + j];
-                    }
-                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[q], 0, 0, 0);
-                }
+        for (int i = 0; i < (HV * 2 + 255) / 256; ++i) {
+            const int idx = tid + 256 * i, v = idx >> 1, h = idx & 1;
+            if (v < HV) {
+                const int x = v % HX, y = (v / HX) % HY, z = v / (HX * HY);
+                const size_t src = vol + ((((size_t)((z0 + z - 1) & sm) << lgS) + (size_t)((y0 + y - 1) & sm)) << lgS) +
+                                   (size_t)((x0 + x - 1) & sm);
+                *(bf16x8 *)(sX + v * 16 + 8 * h) = *(const bf16x8 *)(X + src * Cin + c0 + 8 * h);
             }
+        }
+        __syncthreads();
+        // k-steps of 32 voxels: two groups of 16, each one row of 16 or two rows of 8
+#pragma unroll 4
+        for (int ks = 0; ks < kWgTile / 32; ++ks) {
+            constexpr int RG = 16 / TX;  // rows per group
+            const int r0 = 2 * ks * RG, r1 = r0 + RG;
+            const int off0 = ((r0 >> 3) * HY + (r0 & 7)) * HX * 16, off1 = ((r1 >> 3) * HY + (r1 & 7)) * HX * 16;
+            const bf16x8 a = tr_pair(pz + ks * 512, pz + ks * 512 + 256);
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, tr_pair(pt[q] + off0, pt[q] + off1), acc[q], 0, 0, 0);
+            if (w < 3)
+                acc[6] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, tr_pair(pt[6] + off0, pt[6] + off1), acc[6], 0, 0, 0);
+            else if (bias)
+                acc[6] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[6], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        const int tile = w + 4 * q;
-        if (tile < ntiles) {
-            const int ot = tile / CT, ct = tile - ot * CT;
+    for (int q = 0; q < 7; ++q) {
+        const int t = w + 4 * q;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int o = 16 * ot + 4 * g + j, c = 16 * ct + r16;
-                unsafeAtomicAdd(&dW[((size_t)tap * Cout + o) * Cin + c], acc[q][j]);
-            }
+        for (int j = 0; j < 4; ++j) {
+            const int o = o0 + 4 * g + j;
+            if (t < 27) unsafeAtomicAdd(&dW[((size_t)t * Cout + o) * Cin + c0 + r16], acc[q][j]);
+            else if (bias && r16 == 0) unsafeAtomicAdd(&db[o], acc[q][j]);
         }
     }
 }
 
-// db[o] += sum_v dZ[v][o]
-__global__ __launch_bounds__(256) void k_bias_grad(const __bf16 *__restrict__ dZ, int C, size_t nvox, float *__restrict__ db)
+// Launch k_conv3d_wgrad over nvox = B S^3 voxels (a multiple of 512: S >= 8).
+// Two workgroups per CU over all channel blocks: each adds a whole channel
+// block to dW with atomics, so more of them cost more than they hide (the ten
+// layers of a gradient of eight 64^3 volumes with 256, 512, 768, 1024
+// workgroups: 0.98, 0.78, 0.80, 0.91 ms).
+void launch_wgrad(const __bf16 *X, const __bf16 *dZ, size_t nvox, int lgS, int Cin, int Cout, float *dW, float *db,
+                  hipStream_t s)
 {
-    const int o = threadIdx.x % C;
-    const int lanes = 256 / C;
-    const int sub = threadIdx.x / C;
-    if (sub >= lanes) return;
-    float s = 0.f;
-    for (size_t v = (size_t)blockIdx.x * lanes + sub; v < nvox; v += (size_t)gridDim.x * lanes) s += bf2f(dZ[v * C + o]);
-    unsafeAtomicAdd(&db[o], s);
+    const unsigned ntiles = (unsigned)(nvox / kWgTile), pairs = (unsigned)((Cin >> 4) * (Cout >> 4));
+    const dim3 grid(pairs, std::max(1u, std::min(ntiles, (unsigned)MGFR_WG_SPLIT / pairs)));
+    if (lgS == 3)
+        k_conv3d_wgrad<3><<<grid, 256, 0, s>>>(X, dZ, lgS, Cin, Cout, ntiles, dW, db);
+    else
+        k_conv3d_wgrad<4><<<grid, 256, 0, s>>>(X, dZ, lgS, Cin, Cout, ntiles, dW, db);
 }
 
 // Wt[t'][c][o] = W[26 - t'][o][c]: weights of the backward-data convolution
@@ -416,42 +476,51 @@ __global__ void k_head(const __bf16 *__restrict__ h, size_t nvox, const float *_
     }
 }
 
-// loss = mean (y - u/kUScale)^2 accumulated into loss[0]; dy = 2 (y - t) / n
-__global__ __launch_bounds__(256) void k_loss(const float *__restrict__ y, const double *__restrict__ u, size_t n,
-                                               float *__restrict__ dy, float *__restrict__ loss)
+// Loss and the head's backward pass in one: with d = 2 (y - u / kUScale) / n,
+// loss[0] += sum (y - u / kUScale)^2 / n, dh[v][c] = d wh[c],
+// dwh[c] += sum_v d h[v][c], dwh[16] += sum_v d.  The sums are formed per
+// workgroup first: atomics on these 18 addresses cost 12 ns each one after
+// the other (one per wave and sum: 1.78 ms on 2.1 M voxels; 256 workgroups,
+// two instructions each: 36 us, the traffic of h, dh, y and u).
+constexpr int kHeadBlocks = 256;
+__global__ __launch_bounds__(256) void k_loss_head_bwd(const __bf16 *__restrict__ h, const float *__restrict__ y,
+                                                        const double *__restrict__ u, size_t n,
+                                                        const float *__restrict__ wh, __bf16 *__restrict__ dh,
+                                                        float *__restrict__ dwh, float *__restrict__ loss)
 {
-    float s = 0.f;
-    for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (size_t)gridDim.x * 256) {
-        const float d = y[v] - (float)u[v] / kUScale;
-        dy[v] = 2.f * d / (float)n;
-        s += d * d;
-    }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(loss, s / (float)n);
-}
-
-// head backward: dh[v][c] = dy[v] wh[c]; dwh[c] += sum_v dy[v] h[v][c]; dbh += sum dy
-__global__ __launch_bounds__(256) void k_head_bwd(const __bf16 *__restrict__ h, const float *__restrict__ dy, size_t n,
-                                                   const float *__restrict__ wh, __bf16 *__restrict__ dh,
-                                                   float *__restrict__ dwh)
-{
-    float s[17];
+    __shared__ float sh[4][18];
+    float s[18], w[16];
 #pragma unroll
-    for (int c = 0; c < 17; ++c) s[c] = 0.f;
-    for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (size_t)gridDim.x * 256) {
-        const float d = dy[v];
+    for (int c = 0; c < 18; ++c) s[c] = 0.f;
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            s[c] += d * bf2f(h[v * 16 + c]);
-            dh[v * 16 + c] = f2bf(d * wh[c]);
-        }
+    for (int c = 0; c < 16; ++c) w[c] = wh[c];
+    for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (size_t)gridDim.x * 256) {
+        const float e = y[v] - (float)u[v] / kUScale, d = 2.f * e / (float)n;
+        s[17] += e * e;
         s[16] += d;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bf16x8 a = *(const bf16x8 *)(h + v * 16 + 8 * q);
+            bf16x8 b;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                s[8 * q + c] += d * bf2f(a[c]);
+                b[c] = f2bf(d * w[8 * q + c]);
+            }
+            *(bf16x8 *)(dh + v * 16 + 8 * q) = b;
+        }
     }
 #pragma unroll
-    for (int c = 0; c < 17; ++c) {
+    for (int c = 0; c < 18; ++c) {
         float x = s[c];
         for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(&dwh[c], x);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][c] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < 18) {
+        const float x = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
+        if (threadIdx.x < 17) unsafeAtomicAdd(&dwh[threadIdx.x], x);
+        else unsafeAtomicAdd(loss, x / (float)n);
     }
 }
 
@@ -571,7 +640,7 @@ struct mgfr_net {
     int fwd_B = 0, fwd_lg = 0;  // shape of the last forward pass (0: none yet)
     // activations
     __bf16 *x0, *h1a, *s1, *p1, *h2a, *s2, *p2, *h3a, *h3, *cat4, *h4a, *h4, *cat5, *h5a, *h5;
-    float *y32, *dy32, *cond, *loss;
+    float *y32, *cond, *loss;
     // gradient scratch
     __bf16 *gA, *gB, *gC, *gD;
     float *hcond = nullptr, *hloss = nullptr;
@@ -614,7 +683,6 @@ int net_alloc(mgfr_net *n)
         (rc = A(&n->gA, V * 48)) || (rc = A(&n->gB, V * 48)) || (rc = A(&n->gC, V * 16)) || (rc = A(&n->gD, V * 16)))
         return rc;
     MGFR_HIP(hipMalloc(&n->y32, V * sizeof(float)));
-    MGFR_HIP(hipMalloc(&n->dy32, V * sizeof(float)));
     MGFR_HIP(hipMalloc(&n->cond, 2 * 4096 * sizeof(float)));
     MGFR_HIP(hipMalloc(&n->loss, sizeof(float)));
     MGFR_HIP(hipHostMalloc(&n->hcond, 2 * 4096 * sizeof(float), hipHostMallocDefault));
@@ -627,7 +695,7 @@ void net_free(mgfr_net *n)
     if (!n) return;
     void *ptrs[] = {n->p, n->g, n->m, n->v, n->wbf, n->wt, n->x0, n->h1a, n->s1, n->p1, n->h2a, n->s2, n->p2,
                     n->h3a, n->h3, n->cat4, n->h4a, n->h4, n->cat5, n->h5a, n->h5, n->gA, n->gB, n->gC, n->gD,
-                    n->y32, n->dy32, n->cond, n->loss};
+                    n->y32, n->cond, n->loss};
     for (void *q : ptrs) (void)hipFree(q);
     if (n->hcond) (void)hipHostFree(n->hcond);
     if (n->hloss) (void)hipHostFree(n->hloss);
@@ -660,9 +728,7 @@ int conv_bwd(mgfr_net *n, const __bf16 *dy, int Ctot, int off, const __bf16 *y, 
 {
     const ConvSpec &L = n->L[layer];
     k_relu_bwd<<<gridn(nvox * L.cout), 256, 0, n->stream>>>(dy, Ctot, off, y, nvox, L.cout, dz_scratch);
-    const unsigned chunks = (unsigned)((nvox + kWChunk - 1) / kWChunk);
-    k_conv3d_wgrad<<<dim3(27, chunks), 256, 0, n->stream>>>(x, dz_scratch, lgS, L.cin, L.cout, nvox, n->g + L.woff);
-    k_bias_grad<<<gridn(nvox, 1024), 256, 0, n->stream>>>(dz_scratch, L.cout, nvox, n->g + L.boff);
+    launch_wgrad(x, dz_scratch, nvox, lgS, L.cin, L.cout, n->g + L.woff, n->g + L.boff, n->stream);
     if (dx) {
         launch_conv3d(dz_scratch, nvox, lgS, L.cout, n->wt + L.woff, nullptr, L.cin, 0, dx, nullptr, n->stream);
     }
@@ -695,13 +761,16 @@ int net_forward(mgfr_net *n, const double *delta, int B, int lgS)
     return MGFR_OK;
 }
 
-int net_backward(mgfr_net *n, int B, int lgS)
+// Loss against u_target (into n->loss) and the gradient of every parameter.
+int net_backward(mgfr_net *n, const double *u_target, int B, int lgS)
 {
     const size_t V = (size_t)B << (3 * lgS), V2 = V / 8, V3 = V / 64;
     int rc;
     MGFR_HIP(hipMemsetAsync(n->g, 0, n->nparam * sizeof(float), n->stream));
-    // head
-    k_head_bwd<<<gridn(V, 2048), 256, 0, n->stream>>>(n->h5, n->dy32, V, n->p + n->head_off, n->gC, n->g + n->head_off);
+    MGFR_HIP(hipMemsetAsync(n->loss, 0, sizeof(float), n->stream));
+    // loss and head
+    k_loss_head_bwd<<<gridn(V, kHeadBlocks), 256, 0, n->stream>>>(n->h5, n->y32, u_target, V, n->p + n->head_off, n->gC,
+                                                                  n->g + n->head_off, n->loss);
     // level 1 decoder: c5b (dy = gC) -> d(h5a) in gD; c5a -> d(cat5) in gA [V][48]
     if ((rc = conv_bwd(n, n->gC, 16, 0, n->h5, n->h5a, V, lgS, 9, n->gB, n->gD))) return rc;
     if ((rc = conv_bwd(n, n->gD, 16, 0, n->h5a, n->cat5, V, lgS, 8, n->gB, n->gA))) return rc;
@@ -928,10 +997,7 @@ extern "C" int mgfr_net_train_step(mgfr_net *n, const double *delta, const doubl
     if ((rc = check_shape(n, B, S, &lgS))) return rc;
     set_cond(n, cond, B);
     if ((rc = net_forward(n, delta, B, lgS))) return rc;
-    const size_t V = (size_t)B << (3 * lgS);
-    MGFR_HIP(hipMemsetAsync(n->loss, 0, sizeof(float), n->stream));
-    k_loss<<<gridn(V, 2048), 256, 0, n->stream>>>(n->y32, u_target, V, n->dy32, n->loss);
-    if ((rc = net_backward(n, B, lgS))) return rc;
+    if ((rc = net_backward(n, u_target, B, lgS))) return rc;
     n->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - std::pow(b1, (float)n->step), c2 = 1.f - std::pow(b2, (float)n->step);
@@ -952,10 +1018,7 @@ extern "C" int mgfr_net_grads(mgfr_net *n, const double *delta, const double *u_
     if ((rc = check_shape(n, B, S, &lgS))) return rc;
     set_cond(n, cond, B);
     if ((rc = net_forward(n, delta, B, lgS))) return rc;
-    const size_t V = (size_t)B << (3 * lgS);
-    MGFR_HIP(hipMemsetAsync(n->loss, 0, sizeof(float), n->stream));
-    k_loss<<<gridn(V, 2048), 256, 0, n->stream>>>(n->y32, u_target, V, n->dy32, n->loss);
-    if ((rc = net_backward(n, B, lgS))) return rc;
+    if ((rc = net_backward(n, u_target, B, lgS))) return rc;
     MGFR_HIP(hipMemcpyAsync(grad_host, n->g, n->nparam * sizeof(float), hipMemcpyDeviceToHost, n->stream));
     MGFR_HIP(hipMemcpyAsync(n->hloss, n->loss, sizeof(float), hipMemcpyDeviceToHost, n->stream));
     MGFR_HIP(hipStreamSynchronize(n->stream));
@@ -1014,9 +1077,7 @@ extern "C" int mgfr_conv3d_bwd_weight(const void *x, const void *dz, int B, int 
     if (!x || !dz || !dw) return set_error(MGFR_ERR_ARG, "null argument");
     hipStream_t s = (hipStream_t)stream;
     const size_t V = (size_t)B << (3 * lgS);
-    k_conv3d_wgrad<<<dim3(27, (unsigned)((V + kWChunk - 1) / kWChunk)), 256, 0, s>>>(
-        (const __bf16 *)x, (const __bf16 *)dz, lgS, Cin, Cout, V, dw);
-    if (db) k_bias_grad<<<gridn(V, 1024), 256, 0, s>>>((const __bf16 *)dz, Cout, V, db);
+    launch_wgrad((const __bf16 *)x, (const __bf16 *)dz, V, lgS, Cin, Cout, dw, db, s);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }

@@ -70,6 +70,34 @@ def test_conv_backward_data_and_weight_match_reference(B, S, Cin, Cout):
     assert torch.abs(db - db_ref).max() <= 1e-4 * db_ref.abs().max()
 
 
+@pytest.mark.parametrize("B,S,Cin,Cout,with_db", [(1, 8, 16, 16, True), (3, 8, 16, 96, True), (1, 8, 96, 16, False),
+                                                  (1, 16, 64, 64, True), (2, 32, 48, 16, True), (1, 32, 16, 32, True)])
+def test_conv_backward_weight_exact_on_integers(B, S, Cin, Cout, with_db):
+    """Weight and bias gradients on small integers: every product and every
+    float32 partial sum is an integer below 2^24, so any order of the sums is
+    exact (|x|, |dz| <= 3: 9 B S^3 < 2^20).  Sides with tiles of 8 and of 16
+    voxels, one tile and several per workgroup, one and many channel blocks."""
+    mg = _mg()
+    print(f"[case] conv wgrad B={B} S={S} Cin={Cin} Cout={Cout}", flush=True)
+    g = torch.Generator().manual_seed(S * 1000 + Cin + Cout)
+    x = torch.randint(-3, 4, (B, S, S, S, Cin), generator=g)
+    dz = torch.randint(-3, 4, (B, S, S, S, Cout), generator=g)
+    ref = torch.empty((27, Cout, Cin), dtype=torch.float64)
+    zf = dz.reshape(-1, Cout).double().t().contiguous()
+    for t in range(27):
+        sh = (1 - t // 9, 1 - (t // 3) % 3, 1 - t % 3)
+        ref[t] = zf @ torch.roll(x, sh, (1, 2, 3)).reshape(-1, Cin).double()
+    xb, zb = x.to(torch.bfloat16).to(DEV), dz.to(torch.bfloat16).to(DEV)
+    if with_db:
+        dw, db = mg.conv3d_bwd_weight(xb, zb)
+        assert torch.equal(db.double().cpu(), zf.sum(1))
+    else:  # no bias gradient asked for
+        dw = torch.zeros((27, Cout, Cin), dtype=torch.float32, device=DEV)
+        assert mg.lib().mgfr_conv3d_bwd_weight(xb.data_ptr(), zb.data_ptr(), B, S, Cin, Cout, dw.data_ptr(), None,
+                                               mg._stream_ptr()) == 0
+    assert torch.equal(dw.double().cpu(), ref)
+
+
 def _pairs(n, S=32, seed0=100, device=DEV):
     """(delta, u) training pairs generated by the solver itself on S^3 meshes."""
     mg = _mg()

@@ -176,50 +176,6 @@ __device__ __forceinline__ void mx_restrict_block(const float *__restrict__ e, c
     rm = 0.125f * sr;
 }
 
-// daughter means of e, u and of the residual r - N(e) for coarse cell (I,J,K)
-__device__ __forceinline__ void mx_restrict_cell(const float *__restrict__ e, const float *__restrict__ u,
-                                                 const float *__restrict__ r, int I, int J, int K, int lg,
-                                                 const MxConst &kc, float &em, float &um, float &rm)
-{
-    float se = 0.f, su = 0.f, sr = 0.f;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int i = 2 * I + a, j = 2 * J + b, k = 2 * K + c;
-                const size_t cc = ix(i, j, k, lg);
-                se += e[cc];
-                su += u[cc];
-                sr += r[cc] - mx_value_at(e, u, i, j, k, lg, kc);
-            }
-    em = 0.125f * se;
-    um = 0.125f * su;
-    rm = 0.125f * sr;
-}
-
-__device__ __forceinline__ float mx_prolong(const float *__restrict__ ec, const float *__restrict__ eb, int i,
-                                            int j, int k, int lgc, int mode)
-{
-    const int m = (1 << lgc) - 1;
-    const int I = i >> 1, J = j >> 1, K = k >> 1;
-    const size_t P = ix(I, J, K, lgc);
-    float v = ec[P] - eb[P];
-    if (mode == 0) {
-        const size_t xp = ix((I + 1) & m, J, K, lgc), xm = ix((I - 1) & m, J, K, lgc);
-        const size_t yp = ix(I, (J + 1) & m, K, lgc), ym = ix(I, (J - 1) & m, K, lgc);
-        const size_t zp = ix(I, J, (K + 1) & m, lgc), zm = ix(I, J, (K - 1) & m, lgc);
-        const float gx = (ec[xp] - eb[xp]) - (ec[xm] - eb[xm]);
-        const float gy = (ec[yp] - eb[yp]) - (ec[ym] - eb[ym]);
-        const float gz = (ec[zp] - eb[zp]) - (ec[zm] - eb[zm]);
-        v += ((i & 1) ? 0.125f : -0.125f) * gx;
-        v += ((j & 1) ? 0.125f : -0.125f) * gy;
-        v += ((k & 1) ? 0.125f : -0.125f) * gz;
-    }
-    return v;
-}
-
 // Element at a wave-uniform row pointer plus a 32-bit byte offset (lets the
 // compiler address with a scalar base and one 32-bit lane offset).
 template <typename T>
@@ -939,121 +895,230 @@ __global__ __launch_bounds__(kBlock) void k_mx_prolong_add(float *__restrict__ e
             }
 }
 
+// The tail (16^3, 8^3, 4^3) in one workgroup, every level in LDS as
+// (e, expm1 e, u, e^u) per cell, so that an update reads its neighbours'
+// exponentials and evaluates one of its own.  Layout and threads: TailGrid;
+// the arithmetic is that of the other float32 levels (mx_step, mx_value).
+// Bound: the latency of some 100 dependent half-sweeps.  V(4,4) cycle: 104 us
+// with e, u and r alone in LDS (14 exponentials per update), now 36 us.
 struct MxTail {
-    float *e[kMaxLevels];
-    float *u[kMaxLevels];
-    float *r[kMaxLevels];
-    float *eb[kMaxLevels];
-    float ih2[kMaxLevels];
-    int lg[kMaxLevels];
-    int l0, nlev, pre, post, coarse, mode;
+    float *e;             // top level, in and out
+    const float *u, *r;
+    float ih2[3];         // 16^3, 8^3, 4^3
+    int lg0, pre, post, coarse, mode;
     float bC, q, max_du, omega;
 };
 
-// The tail (levels with N <= kTailN: 16^3, 8^3, 4^3) runs in one workgroup
-// with every array in LDS: e, u and r of its top level are copied in and e is
-// copied out at the end; the coarser levels' arrays (e, u, r and the restricted
-// e) live only here.  Level l0 + k holds 2^(3 (lg0 - k)) cells; its arrays sit
-// after those of the finer levels (three at l0, four below).
-constexpr int kTailLdsFloats = 3 * (1 << 12) + 4 * (1 << 9) + 4 * (1 << 6);
-static_assert(kTailN <= 16, "the tail's LDS holds levels up to 16^3");
-
-struct TailLds {
-    float *lds;
-    int l0, lg0;
-    __device__ int cells(int l) const { return 1 << (3 * (lg0 - (l - l0))); }
-    __device__ float *base(int l) const
-    {
-        int off = 0;
-        if (l > l0) {
-            off = 3 * cells(l0);
-            for (int k = l0 + 1; k < l; ++k) off += 4 * cells(k);
-        }
-        return lds + off;
-    }
-    __device__ float *e(int l) const { return base(l); }
-    __device__ float *u(int l) const { return base(l) + cells(l); }
-    __device__ float *r(int l) const { return base(l) + 2 * cells(l); }
-    __device__ float *eb(int l) const { return base(l) + 3 * cells(l); }  // l > l0
+template <int LG>
+struct MxTailLevel : TailGrid<LG> {
+    float4 *c;      // (e, expm1 e, u, e^u)
+    float *r, *eb;
 };
 
-// Red-black sweeps of one tail level.  The 4^3 level (32 cells per colour) is
-// swept by the first wave alone: within one wave the LDS accesses of a
-// half-sweep are done before the next one's, and the fences keep the compiler
-// from moving them, so no workgroup barrier is needed per half-sweep.
-__device__ void mx_tail_sweeps(const MxTail &A, const TailLds &T, int l, int sweeps)
+__device__ __forceinline__ float mx_tail_step(const float4 &c, const float4 n[6], float r, const MxConst &kc)
 {
-    const MxConst kc{A.ih2[l], A.bC, A.q, A.max_du, A.omega};
-    const int lg = A.lg[l];
-    const int half = 1 << (3 * lg - 1);
-    float *e = T.e(l);
-    const float *u = T.u(l), *r = T.r(l);
-    if (half <= 32) {  // uniform
-        if (threadIdx.x < 64)
-            for (int s = 0; s < sweeps; ++s)
-                for (int colour = 0; colour < 2; ++colour) {
-                    if ((int)threadIdx.x < half) mx_sweep_cell(e, u, r, threadIdx.x, lg, colour, kc);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                }
-        __syncthreads();
-        return;
-    }
-    for (int s = 0; s < sweeps; ++s)
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int t = threadIdx.x; t < half; t += kTailThreads) mx_sweep_cell(e, u, r, t, lg, colour, kc);
-            __syncthreads();
+    const float en[6] = {n[0].x, n[1].x, n[2].x, n[3].x, n[4].x, n[5].x};
+    const float Xn[6] = {n[0].y, n[1].y, n[2].y, n[3].y, n[4].y, n[5].y};
+    const float un[6] = {n[0].z, n[1].z, n[2].z, n[3].z, n[4].z, n[5].z};
+    const float wn[6] = {n[0].w, n[1].w, n[2].w, n[3].w, n[4].w, n[5].w};
+    return c.x + mx_step(c.x, c.y, c.z, c.w, en, Xn, un, wn, r, kc);
+}
+
+// N(e) at a cell of a tail level
+template <int LG>
+__device__ __forceinline__ float mx_tail_value(const MxTailLevel<LG> &T, int i, int j, int k, const float4 &c,
+                                               const MxConst &kc)
+{
+    using G = TailGrid<LG>;
+    constexpr int M = G::M;
+    const float4 n[6] = {T.c[G::slot((i + 1) & M, j, k)], T.c[G::slot((i - 1) & M, j, k)],
+                         T.c[G::slot(i, (j + 1) & M, k)], T.c[G::slot(i, (j - 1) & M, k)],
+                         T.c[G::slot(i, j, (k + 1) & M)], T.c[G::slot(i, j, (k - 1) & M)]};
+    const float en[6] = {n[0].x, n[1].x, n[2].x, n[3].x, n[4].x, n[5].x};
+    const float Xn[6] = {n[0].y, n[1].y, n[2].y, n[3].y, n[4].y, n[5].y};
+    const float un[6] = {n[0].z, n[1].z, n[2].z, n[3].z, n[4].z, n[5].z};
+    const float wn[6] = {n[0].w, n[1].w, n[2].w, n[3].w, n[4].w, n[5].w};
+    return mx_value(c.x, c.y, c.z, c.w, en, Xn, un, wn, kc);
+}
+
+// Red-black sweeps of the 16^3 or 8^3 level.
+template <int LG>
+__device__ __forceinline__ void mx_tail_sweeps(const MxTailLevel<LG> &T, int sweeps, const MxConst &kc)
+{
+    using G = TailGrid<LG>;
+    constexpr int W = G::W, M = G::M;
+    const bool own = threadIdx.x < G::THREADS;
+    int i = 0, j = 0, k0 = 0;
+    float4 x[W];
+    float r[W];
+    if (own) {
+        G::cell(threadIdx.x, i, j, k0);
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+            x[c] = T.c[G::slot(i, j, k0 + c)];
+            r[c] = T.r[G::slot(i, j, k0 + c)];
         }
+    }
+    const int par = __builtin_amdgcn_readfirstlane((i + j) & 1);  // uniform over the wave
+    const int ip = (i + 1) & M, im = (i - 1) & M, jp = (j + 1) & M, jm = (j - 1) & M;
+    // update columns B, B + 2, ... of the thread's cells
+    auto half = [&](auto Bc) {
+        constexpr int B = decltype(Bc)::value;
+        const float4 out = T.c[G::slot(i, j, B ? (k0 + W) & M : (k0 - 1) & M)];
+#pragma unroll
+        for (int c = B; c < W; c += 2) {
+            const int k = k0 + c;
+            const float4 n[6] = {T.c[G::slot(ip, j, k)], T.c[G::slot(im, j, k)], T.c[G::slot(i, jp, k)],
+                                 T.c[G::slot(i, jm, k)], c == W - 1 ? out : x[(c + 1) % W], c == 0 ? out : x[(c + W - 1) % W]};
+            x[c].x = mx_tail_step(x[c], n, r[c], kc);
+            x[c].y = fexpm1(x[c].x);
+        }
+#pragma unroll
+        for (int c = B; c < W; c += 2) T.c[G::slot(i, j, k0 + c)] = x[c];
+    };
+    for (int h = 0; h < 2 * sweeps; ++h) {
+        if (own) {
+            if ((par ^ h) & 1)
+                half(std::integral_constant<int, 1>{});
+            else
+                half(std::integral_constant<int, 0>{});
+        }
+        __syncthreads();
+    }
+}
+
+// Sweeps of the 4^3 level by the first wave: within one wave the LDS accesses
+// of a half-sweep are done before the next one's, and the fences keep the
+// compiler from moving them.
+__device__ __forceinline__ void mx_tail_sweeps4(const MxTailLevel<2> &T, int sweeps, const MxConst &kc)
+{
+    using G = TailGrid<2>;
+    if (threadIdx.x < 64) {
+        int i, j, k;
+        G::cell(threadIdx.x, i, j, k);
+        const int c = G::slot(i, j, k), par = (i + j + k) & 1;
+        const int s[6] = {G::slot((i + 1) & 3, j, k), G::slot((i - 1) & 3, j, k), G::slot(i, (j + 1) & 3, k),
+                          G::slot(i, (j - 1) & 3, k), G::slot(i, j, (k + 1) & 3), G::slot(i, j, (k - 1) & 3)};
+        float4 x = T.c[c];
+        const float r = T.r[c];
+        for (int h = 0; h < 2 * sweeps; ++h) {
+            if (par == (h & 1)) {
+                const float4 n[6] = {T.c[s[0]], T.c[s[1]], T.c[s[2]], T.c[s[3]], T.c[s[4]], T.c[s[5]]};
+                x.x = mx_tail_step(x, n, r, kc);
+                x.y = fexpm1(x.x);
+                T.c[c] = x;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+}
+
+// Means of e, u and r - N(e) over the eight daughters, then the coarse source
+// r_c += N_c(eb) and e_c = eb.
+template <int LG>
+__device__ __forceinline__ void mx_tail_restrict(const MxTailLevel<LG> &T, const MxTailLevel<LG - 1> &C,
+                                                 const MxConst &kf, const MxConst &kcc)
+{
+    using G = TailGrid<LG>;
+    using GC = TailGrid<LG - 1>;
+    const int t = threadIdx.x;
+    const int I = t >> (2 * LG - 2), J = (t >> (LG - 1)) & GC::M, K = t & GC::M;
+    float se = 0.f, su = 0.f, sr = 0.f;
+    if (t < GC::CELLS) {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            const int i = 2 * I + (d >> 2), j = 2 * J + ((d >> 1) & 1), k = 2 * K + (d & 1), c = G::slot(i, j, k);
+            const float4 x = T.c[c];
+            se += x.x;
+            su += x.z;
+            sr += T.r[c] - mx_tail_value(T, i, j, k, x, kf);
+        }
+        const int c = GC::slot(I, J, K);
+        const float em = 0.125f * se, um = 0.125f * su;
+        C.eb[c] = em;
+        C.c[c] = make_float4(em, fexpm1(em), um, fexp(um));
+    }
+    __syncthreads();
+    if (t < GC::CELLS) {
+        const int c = GC::slot(I, J, K);
+        const float rm = 0.125f * sr;
+        C.r[c] = rm + mx_tail_value(C, I, J, K, C.c[c], kcc);
+    }
+    __syncthreads();
+}
+
+// e += P(e_c - eb): the thread's cells from their W / 2 parents
+template <int LG>
+__device__ __forceinline__ void mx_tail_prolong(const MxTailLevel<LG> &T, const MxTailLevel<LG - 1> &C, int mode)
+{
+    using G = TailGrid<LG>;
+    using GC = TailGrid<LG - 1>;
+    constexpr int MC = GC::M;
+    if (threadIdx.x < G::THREADS) {
+        int i, j, k0;
+        G::cell(threadIdx.x, i, j, k0);
+        auto d = [&](int a, int b, int c) {
+            const int s = GC::slot(a & MC, b & MC, c & MC);
+            return C.c[s].x - C.eb[s];
+        };
+#pragma unroll
+        for (int h = 0; h < G::W / 2; ++h) {
+            const int I = i >> 1, J = j >> 1, K = (k0 >> 1) + h;
+            float v0 = d(I, J, K), gz = 0.f;
+            if (mode == 0) {
+                v0 += ((i & 1) ? 0.125f : -0.125f) * (d(I + 1, J, K) - d(I - 1, J, K));
+                v0 += ((j & 1) ? 0.125f : -0.125f) * (d(I, J + 1, K) - d(I, J - 1, K));
+                gz = 0.125f * (d(I, J, K + 1) - d(I, J, K - 1));
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int s = G::slot(i, j, k0 + 2 * h + c);
+                float4 x = T.c[s];
+                x.x += c ? v0 + gz : v0 - gz;
+                x.y = fexpm1(x.x);
+                T.c[s] = x;
+            }
+        }
+    }
+    __syncthreads();
 }
 
 __global__ __launch_bounds__(kTailThreads) void k_mx_tail(MxTail A)
 {
-    __shared__ float lds[kTailLdsFloats];
-    const TailLds T{lds, A.l0, A.lg[A.l0]};
-    const int n0 = T.cells(A.l0);
-    for (int t = threadIdx.x; t < n0; t += kTailThreads) {
-        T.e(A.l0)[t] = A.e[A.l0][t];
-        T.u(A.l0)[t] = A.u[A.l0][t];
-        T.r(A.l0)[t] = A.r[A.l0][t];
+    __shared__ float4 s_c[4096 + 512 + 64];
+    __shared__ float s_r[4096 + 512 + 64], s_eb[512 + 64];
+    const MxTailLevel<4> T4{{}, s_c, s_r, nullptr};
+    const MxTailLevel<3> T3{{}, s_c + 4096, s_r + 4096, s_eb};
+    const MxTailLevel<2> T2{{}, s_c + 4608, s_r + 4608, s_eb + 512};
+    const MxConst k4{A.ih2[0], A.bC, A.q, A.max_du, A.omega}, k3{A.ih2[1], A.bC, A.q, A.max_du, A.omega},
+        k2{A.ih2[2], A.bC, A.q, A.max_du, A.omega};
+    const int lg = A.lg0, n0 = 1 << (3 * lg), m = (1 << lg) - 1;
+    auto slot0 = [&](int c) {
+        const int i = c >> (2 * lg), j = (c >> lg) & m, k = c & m;
+        return lg == 4 ? TailGrid<4>::slot(i, j, k) : 4096 + TailGrid<3>::slot(i, j, k);
+    };
+    for (int c = threadIdx.x; c < n0; c += kTailThreads) {
+        const float e = A.e[c], u = A.u[c];
+        s_c[slot0(c)] = make_float4(e, fexpm1(e), u, fexp(u));
+        s_r[slot0(c)] = A.r[c];
     }
     __syncthreads();
-    for (int l = A.l0; l < A.nlev - 1; ++l) {
-        mx_tail_sweeps(A, T, l, A.pre);
-        const MxConst kc{A.ih2[l], A.bC, A.q, A.max_du};
-        const int lg = A.lg[l], lgc = lg - 1;
-        const int nc = 1 << (3 * lgc);
-        for (int t = threadIdx.x; t < nc; t += kTailThreads) {
-            const int K = t & ((1 << lgc) - 1), J = (t >> lgc) & ((1 << lgc) - 1), I = t >> (2 * lgc);
-            float em, um, rm;
-            mx_restrict_cell(T.e(l), T.u(l), T.r(l), I, J, K, lg, kc, em, um, rm);
-            T.eb(l + 1)[t] = em;
-            T.u(l + 1)[t] = um;
-            T.r(l + 1)[t] = rm;
-        }
-        __syncthreads();
-        const MxConst kcc{A.ih2[l + 1], A.bC, A.q, A.max_du};
-        const int mc = (1 << lgc) - 1;
-        for (int t = threadIdx.x; t < nc; t += kTailThreads) {
-            const int k = t & mc, j = (t >> lgc) & mc, i = t >> (2 * lgc);
-            T.r(l + 1)[t] += mx_value_at(T.eb(l + 1), T.u(l + 1), i, j, k, lgc, kcc);
-        }
-        __syncthreads();
-        for (int t = threadIdx.x; t < nc; t += kTailThreads) T.e(l + 1)[t] = T.eb(l + 1)[t];
-        __syncthreads();
+    if (lg == 4) {
+        mx_tail_sweeps(T4, A.pre, k4);
+        mx_tail_restrict(T4, T3, k4, k3);
     }
-    mx_tail_sweeps(A, T, A.nlev - 1, A.coarse);
-    for (int l = A.nlev - 2; l >= A.l0; --l) {
-        const int lg = A.lg[l];
-        const int n = 1 << (3 * lg);
-        const int m = (1 << lg) - 1;
-        for (int t = threadIdx.x; t < n; t += kTailThreads) {
-            const int k = t & m, j = (t >> lg) & m, i = t >> (2 * lg);
-            T.e(l)[t] += mx_prolong(T.e(l + 1), T.eb(l + 1), i, j, k, lg - 1, A.mode);
-        }
-        __syncthreads();
-        mx_tail_sweeps(A, T, l, A.post);
+    mx_tail_sweeps(T3, A.pre, k3);
+    mx_tail_restrict(T3, T2, k3, k2);
+    mx_tail_sweeps4(T2, A.coarse, k2);
+    mx_tail_prolong(T3, T2, A.mode);
+    mx_tail_sweeps(T3, A.post, k3);
+    if (lg == 4) {
+        mx_tail_prolong(T4, T3, A.mode);
+        mx_tail_sweeps(T4, A.post, k4);
     }
-    for (int t = threadIdx.x; t < n0; t += kTailThreads) A.e[A.l0][t] = T.e(A.l0)[t];
+    for (int c = threadIdx.x; c < n0; c += kTailThreads) A.e[c] = s_c[slot0(c)].x;
 }
 
 // float64 residual of u on the finest level, its float32 copies for the inner
@@ -1363,18 +1428,16 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
 
 int mx_launch_tail(mgfr_ctx *c, int l0)
 {
+    const Level &L = c->lev[l0];
     MxTail A;
-    memset(&A, 0, sizeof A);
-    for (int l = 0; l < c->nlev; ++l) {
-        A.e[l] = c->lev[l].e32;
-        A.u[l] = c->lev[l].u32;
-        A.r[l] = c->lev[l].r32;
-        A.eb[l] = c->lev[l].ebar32;
-        A.ih2[l] = (float)(1.0 / (c->lev[l].h * c->lev[l].h));
-        A.lg[l] = c->lev[l].lg;
+    A.e = L.e32;
+    A.u = L.u32;
+    A.r = L.r32;
+    A.lg0 = L.lg;  // 4 or 3: meshes have at least 8 cells a side
+    for (int k = 0; k < 3; ++k) {
+        const double h = c->p.box / (16 >> k);
+        A.ih2[k] = (float)(1.0 / (h * h));
     }
-    A.l0 = l0;
-    A.nlev = c->nlev;
     A.pre = c->p.pre_smooth;
     A.post = c->p.post_smooth;
     A.coarse = c->p.coarse_sweeps;

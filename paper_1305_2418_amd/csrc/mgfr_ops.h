@@ -121,34 +121,9 @@ __device__ __forceinline__ void block_residuals(const double *__restrict__ u, co
     out.rmean = sr / 8.0;
 }
 
-// Linear (mode 0) or injected (mode 1) correction at fine cell (i,j,k):
-// P(uc - ubar) with the central-difference gradient at the parent centre.
-__device__ __forceinline__ double prolong_value(const double *__restrict__ uc, const double *__restrict__ ub,
-                                                int i, int j, int k, int lgc, int mode)
-{
-    const int m = (1 << lgc) - 1;
-    int I = i >> 1, J = j >> 1, K = k >> 1;
-    size_t P = cidx(I, J, K, lgc);
-    double v = uc[P] - ub[P];
-    if (mode == 0) {
-        size_t xp = cidx((I + 1) & m, J, K, lgc), xm = cidx((I - 1) & m, J, K, lgc);
-        size_t yp = cidx(I, (J + 1) & m, K, lgc), ym = cidx(I, (J - 1) & m, K, lgc);
-        size_t zp = cidx(I, J, (K + 1) & m, lgc), zm = cidx(I, J, (K - 1) & m, lgc);
-        double gx = (uc[xp] - ub[xp]) - (uc[xm] - ub[xm]);
-        double gy = (uc[yp] - ub[yp]) - (uc[ym] - ub[ym]);
-        double gz = (uc[zp] - ub[zp]) - (uc[zm] - ub[zm]);
-        double sx = (i & 1) ? 0.125 : -0.125, sy = (j & 1) ? 0.125 : -0.125, sz = (k & 1) ? 0.125 : -0.125;
-        v += sx * gx;
-        v += sy * gy;
-        v += sz * gz;
-    }
-    return v;
-}
-
-
-// Correction u += P(uc - ub) for the 8 daughters of coarse cell (I,J,K) of a
-// 2^lgc mesh: the parent value and gradient are formed once (same arithmetic
-// order as prolong_value).
+// Linear (mode 0) or injected (mode 1) correction u += P(uc - ub) for the 8
+// daughters of coarse cell (I,J,K) of a 2^lgc mesh: the parent value and the
+// central-difference gradient at the parent centre are formed once.
 template <typename T>
 __device__ __forceinline__ void prolong_block(T *__restrict__ u, const T *__restrict__ uc, const T *__restrict__ ub,
                                               int I, int J, int K, int lgc, int mode)
@@ -182,6 +157,44 @@ __device__ __forceinline__ void prolong_block(T *__restrict__ u, const T *__rest
                 u[cidx(2 * I + a, 2 * J + b, 2 * K + c, lg)] += v;
             }
 }
+
+// ---------------------------------------------------- tail levels (16^3, 8^3, 4^3)
+// How one workgroup of 1024 threads holds the coarsest levels in LDS.  A
+// thread owns W consecutive cells of a row: 4 on 16^3 (all threads), 2 on 8^3
+// (four waves, one per SIMD), 1 on 4^3 (one wave, which needs no workgroup
+// barriers).  The rows of a wave all have the same parity, so the column it
+// updates in a half-sweep is uniform.  Cells are 16 bytes.
+template <int LG>
+struct TailGrid {
+    static constexpr int N = 1 << LG, M = N - 1, CELLS = N * N * N;
+    static constexpr int W = LG == 4 ? 4 : LG == 3 ? 2 : 1;  // cells per thread
+    static constexpr int THREADS = CELLS / W;
+    // LDS slot of a cell: on 16^3 the four cells of a quad are rotated by j, so
+    // that the lanes of a wave (four quads by rows) reading the same column of
+    // their quads touch all banks
+    __device__ __forceinline__ static int slot(int i, int j, int k)
+    {
+        const int row = ((i << LG) + j) << LG;
+        return LG == 4 ? row + (k & 12) + ((k + j) & 3) : row + k;
+    }
+    // first cell of thread t: the rows of a wave have i + j even (even waves) or odd
+    __device__ __forceinline__ static void cell(int t, int &i, int &j, int &k0)
+    {
+        constexpr int Q = N / W;  // threads per row
+        k0 = W * (t % Q);
+        const int r = t / Q;  // row
+        if constexpr (LG == 2) {
+            i = r >> LG;
+            j = r & M;
+        } else {
+            // 64 / Q rows per wave: the N / 2 rows of one parity of each of several planes
+            constexpr int RW = 64 / Q, H = N / 2, P = RW / H;
+            const int wv = r / RW, s = r % RW;
+            i = P * (wv / 2) + s / H;
+            j = 2 * (s % H) + ((wv + i) & 1);
+        }
+    }
+};
 
 // ------------------------------------------------ float32 correction cycle
 // Shared by the uniform mixed-precision solve and the refined levels.

@@ -18,6 +18,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 
 namespace mgfr {
 
@@ -454,74 +455,240 @@ __global__ __launch_bounds__(kBlock) void k_dfr(const double *__restrict__ u, do
 }
 
 // ------------------------------------------------------------- tail kernel
-// All levels with N <= kTailN inside one workgroup: the V-cycle from level l0
-// down to the 4^3 grid and back, with workgroup barriers between steps.
+// All levels with N <= kTailN inside one workgroup: the V-cycle from the 16^3
+// (or 8^3) level down to the 4^3 grid and back.
+//
+// Bound: a serial chain of some 100 half-sweeps of few cells, so what counts
+// is the latency of each.  Every level lives in LDS as (u, e^u) pairs, so that
+// an update reads its neighbours' exponentials and evaluates one of its own
+// (in global memory, with eight exponentials and a division per update, the
+// cycle took 137 us for V(2,2) and 192 us for V(4,4); now 42 and 57 us).  A
+// thread owns W consecutive cells of a row (TailGrid) and keeps their values
+// and f in registers through a smoothing phase.
 
 struct TailArgs {
-    double *u[kMaxLevels];
-    double *f[kMaxLevels];
-    double *ub[kMaxLevels];
-    double ih2[kMaxLevels];
-    int lg[kMaxLevels];
-    int l0, nlev, pre, post, coarse, mode;
+    double *u;        // top level, in and out
+    const double *f;
+    double ih2[3];    // 16^3, 8^3, 4^3
+    int lg0;          // 4 or 3
+    int pre, post, coarse, mode;
     double bC, q, max_du;
     const double *tab;  // exponential's table (the kernel points it at its LDS copy)
 };
 
-__device__ void tail_sweeps(const TailArgs &A, int l, int sweeps)
+template <int LG>
+struct TailLevel : TailGrid<LG> {
+    double2 *ue;  // (u, e^u)
+    double *f, *ub;
+};
+
+template <bool N1, int LG>
+__device__ __forceinline__ double2 tail_update(double2 c, double2 n0, double2 n1, double2 n2, double2 n3, double2 n4,
+                                               double2 n5, double f, const OpConst &kc)
 {
-    OpConst kc{A.ih2[l], A.bC, A.q, A.max_du, A.tab};
-    const int lg = A.lg[l];
-    const size_t half = (size_t)1 << (3 * lg - 1);
-    for (int s = 0; s < sweeps; ++s)
-        for (int colour = 0; colour < 2; ++colour) {
-            for (size_t t = threadIdx.x; t < half; t += kTailThreads) sweep_cell(A.u[l], A.f[l], t, lg, colour, kc);
-            __syncthreads();
-        }
+    const double un = c.x + ngs_step_e(c.x, c.y, curv_em<N1>(c.x, c.y, kc.q, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y,
+                                       n3.x, n3.y, n4.x, n4.y, n5.x, n5.y, f, kc);
+    return make_double2(un, exp64(un, kc.tab));
 }
 
+// Red-black sweeps of the 16^3 or 8^3 level.
+template <bool N1, int LG>
+__device__ __forceinline__ void tail_sweeps(const TailLevel<LG> &T, int sweeps, const OpConst &kc)
+{
+    using L = TailLevel<LG>;
+    constexpr int W = L::W, M = L::M;
+    const int t = threadIdx.x;
+    const bool own = t < L::THREADS;
+    int i = 0, j = 0, k0 = 0;
+    double2 x[W];
+    double f[W];
+    if (own) {
+        L::cell(t, i, j, k0);
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+            x[c] = T.ue[L::slot(i, j, k0 + c)];
+            f[c] = T.f[L::slot(i, j, k0 + c)];
+        }
+    }
+    const int par = __builtin_amdgcn_readfirstlane((i + j) & 1);  // uniform over the wave
+    const int ip = (i + 1) & M, im = (i - 1) & M, jp = (j + 1) & M, jm = (j - 1) & M;
+    // update columns B, B + 2, ... of the thread's cells
+    auto half = [&](auto Bc) {
+        constexpr int B = decltype(Bc)::value;
+        const double2 out = T.ue[L::slot(i, j, B ? (k0 + W) & M : (k0 - 1) & M)];
+        double2 y[W];
+#pragma unroll
+        for (int c = B; c < W; c += 2) {
+            const int k = k0 + c;
+            const double2 l = c == 0 ? out : x[c - 1], r = c == W - 1 ? out : x[(c + 1) % W];
+            y[c] = tail_update<N1, LG>(x[c], T.ue[L::slot(ip, j, k)], T.ue[L::slot(im, j, k)], T.ue[L::slot(i, jp, k)],
+                                       T.ue[L::slot(i, jm, k)], r, l, f[c], kc);
+        }
+#pragma unroll
+        for (int c = B; c < W; c += 2) {
+            x[c] = y[c];
+            T.ue[L::slot(i, j, k0 + c)] = y[c];
+        }
+    };
+    for (int h = 0; h < 2 * sweeps; ++h) {
+        if (own) {
+            if ((par ^ h) & 1)
+                half(std::integral_constant<int, 1>{});
+            else
+                half(std::integral_constant<int, 0>{});
+        }
+        __syncthreads();
+    }
+}
+
+// Sweeps of the 4^3 level by the first wave: within one wave the LDS accesses
+// of a half-sweep are done before the next one's, and the fences keep the
+// compiler from moving them.
+template <bool N1>
+__device__ __forceinline__ void tail_sweeps4(const TailLevel<2> &T, int sweeps, const OpConst &kc)
+{
+    using L = TailLevel<2>;
+    if (threadIdx.x < 64) {
+        int i, j, k;
+        L::cell(threadIdx.x, i, j, k);
+        const int c = L::slot(i, j, k), par = (i + j + k) & 1;
+        const int n0 = L::slot((i + 1) & 3, j, k), n1 = L::slot((i - 1) & 3, j, k), n2 = L::slot(i, (j + 1) & 3, k),
+                  n3 = L::slot(i, (j - 1) & 3, k), n4 = L::slot(i, j, (k + 1) & 3), n5 = L::slot(i, j, (k - 1) & 3);
+        double2 x = T.ue[c];
+        const double f = T.f[c];
+        for (int h = 0; h < 2 * sweeps; ++h) {
+            if (par == (h & 1)) {
+                x = tail_update<N1, 2>(x, T.ue[n0], T.ue[n1], T.ue[n2], T.ue[n3], T.ue[n4], T.ue[n5], f, kc);
+                T.ue[c] = x;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+}
+
+// L(u) at a cell of a tail level
+template <int LG>
+__device__ __forceinline__ double tail_op(const TailLevel<LG> &T, int i, int j, int k, double2 c, const OpConst &kc)
+{
+    using L = TailLevel<LG>;
+    constexpr int M = L::M;
+    const double2 n0 = T.ue[L::slot((i + 1) & M, j, k)], n1 = T.ue[L::slot((i - 1) & M, j, k)],
+                  n2 = T.ue[L::slot(i, (j + 1) & M, k)], n3 = T.ue[L::slot(i, (j - 1) & M, k)],
+                  n4 = T.ue[L::slot(i, j, (k + 1) & M)], n5 = T.ue[L::slot(i, j, (k - 1) & M)];
+    const double d0 = n0.x - c.x, d1 = n1.x - c.x, d2 = n2.x - c.x, d3 = n3.x - c.x, d4 = n4.x - c.x, d5 = n5.x - c.x;
+    const double S1 = ((d0 + d1) + (d2 + d3)) + (d4 + d5);
+    const double S3 = ((n0.y * d0 + n1.y * d1) + (n2.y * d2 + n3.y * d3)) + (n4.y * d4 + n5.y * d5);
+    return kc.ih2 * 0.5 * (S3 + c.y * S1) + kc.bC * expm1_64(-kc.q * c.x, kc.tab);
+}
+
+// Restriction to the next level: means of u and of the residual over the eight
+// daughters, then the coarse source f_c = L_c(R u) + R(f - L u), u_c = R u.
+template <int LG>
+__device__ __forceinline__ void tail_restrict(const TailLevel<LG> &T, const TailLevel<LG - 1> &C, const OpConst &kf,
+                                              const OpConst &kcc)
+{
+    using L = TailLevel<LG>;
+    using LC = TailLevel<LG - 1>;
+    const int t = threadIdx.x;
+    const int I = t >> (2 * LG - 2), J = (t >> (LG - 1)) & LC::M, K = t & LC::M;
+    double r = 0.0, ub = 0.0;
+    if (t < LC::CELLS) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = 2 * I + (e >> 2), j = 2 * J + ((e >> 1) & 1), k = 2 * K + (e & 1), c = L::slot(i, j, k);
+            const double2 x = T.ue[c];
+            ub += x.x;
+            r += T.f[c] - tail_op(T, i, j, k, x, kf);
+        }
+        ub *= 0.125;
+        r *= 0.125;
+        const int c = LC::slot(I, J, K);
+        C.ub[c] = ub;
+        C.ue[c] = make_double2(ub, exp64(ub, kf.tab));
+    }
+    __syncthreads();
+    if (t < LC::CELLS) {
+        const int c = LC::slot(I, J, K);
+        C.f[c] = r + tail_op(C, I, J, K, C.ue[c], kcc);
+    }
+    __syncthreads();
+}
+
+// u += P(u_c - R u): the thread's cells from their W / 2 parents
+template <int LG>
+__device__ __forceinline__ void tail_prolong(const TailLevel<LG> &T, const TailLevel<LG - 1> &C, int mode,
+                                             const double *tab)
+{
+    using L = TailLevel<LG>;
+    using LC = TailLevel<LG - 1>;
+    constexpr int MC = LC::M;
+    if (threadIdx.x < L::THREADS) {
+        int i, j, k0;
+        L::cell(threadIdx.x, i, j, k0);
+        auto d = [&](int a, int b, int c) {
+            const int s = LC::slot(a & MC, b & MC, c & MC);
+            return C.ue[s].x - C.ub[s];
+        };
+#pragma unroll
+        for (int h = 0; h < L::W / 2; ++h) {
+            const int I = i >> 1, J = j >> 1, K = (k0 >> 1) + h;
+            double v0 = d(I, J, K), gz = 0.0;
+            if (mode == 0) {
+                v0 += ((i & 1) ? 0.125 : -0.125) * (d(I + 1, J, K) - d(I - 1, J, K));
+                v0 += ((j & 1) ? 0.125 : -0.125) * (d(I, J + 1, K) - d(I, J - 1, K));
+                gz = 0.125 * (d(I, J, K + 1) - d(I, J, K - 1));
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int s = L::slot(i, j, k0 + 2 * h + c);
+                const double u = T.ue[s].x + (c ? v0 + gz : v0 - gz);
+                T.ue[s] = make_double2(u, exp64(u, tab));
+            }
+        }
+    }
+    __syncthreads();
+}
+
+template <bool N1>
 __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs A)
 {
-    __shared__ double s_tab[64];
-    if (threadIdx.x < 64) s_tab[threadIdx.x] = A.tab[threadIdx.x];
+    __shared__ double2 s_ue[4096 + 512 + 64];
+    __shared__ double s_f[4096 + 512 + 64], s_ub[512 + 64], s_tab[64];
+    const int t = threadIdx.x;
+    if (t < 64) s_tab[t] = A.tab[t];
+    const TailLevel<4> T4{{}, s_ue, s_f, nullptr};
+    const TailLevel<3> T3{{}, s_ue + 4096, s_f + 4096, s_ub};
+    const TailLevel<2> T2{{}, s_ue + 4608, s_f + 4608, s_ub + 512};
+    const OpConst k4{A.ih2[0], A.bC, A.q, A.max_du, s_tab}, k3{A.ih2[1], A.bC, A.q, A.max_du, s_tab},
+        k2{A.ih2[2], A.bC, A.q, A.max_du, s_tab};
     __syncthreads();
-    A.tab = s_tab;
-    for (int l = A.l0; l < A.nlev - 1; ++l) {
-        tail_sweeps(A, l, A.pre);
-        OpConst kc{A.ih2[l], A.bC, A.q, A.max_du, A.tab};
-        const int lg = A.lg[l], lgc = lg - 1;
-        const size_t nc = (size_t)1 << (3 * lgc);
-        for (size_t t = threadIdx.x; t < nc; t += kTailThreads) {
-            int K = (int)(t & ((1u << lgc) - 1));
-            int J = (int)((t >> lgc) & ((1u << lgc) - 1));
-            int I = (int)(t >> (2 * lgc));
-            BlockRes br;
-            block_residuals(A.u[l], A.f[l], I, J, K, lg, kc, br);
-            A.ub[l + 1][t] = br.umean;
-            A.f[l + 1][t] = br.rmean;
-        }
-        __syncthreads();
-        OpConst kcc{A.ih2[l + 1], A.bC, A.q, A.max_du, A.tab};
-        const int mc = (1 << lgc) - 1;
-        for (size_t t = threadIdx.x; t < nc; t += kTailThreads) {
-            int k = (int)(t & mc), j = (int)((t >> lgc) & mc), i = (int)(t >> (2 * lgc));
-            A.f[l + 1][t] += op_at(A.ub[l + 1], i, j, k, lgc, kcc);
-            A.u[l + 1][t] = A.ub[l + 1][t];
-        }
-        __syncthreads();
+    const int lg = A.lg0, n0 = 1 << (3 * lg), m = (1 << lg) - 1;
+    auto slot0 = [&](int c) {
+        const int i = c >> (2 * lg), j = (c >> lg) & m, k = c & m;
+        return lg == 4 ? TailLevel<4>::slot(i, j, k) : 4096 + TailLevel<3>::slot(i, j, k);
+    };
+    for (int c = t; c < n0; c += kTailThreads) {
+        const double u = A.u[c];
+        s_ue[slot0(c)] = make_double2(u, exp64(u, s_tab));
+        s_f[slot0(c)] = A.f[c];
     }
-    tail_sweeps(A, A.nlev - 1, A.coarse);
-    for (int l = A.nlev - 2; l >= A.l0; --l) {
-        const int lg = A.lg[l];
-        const size_t n = (size_t)1 << (3 * lg);
-        const int m = (1 << lg) - 1;
-        for (size_t t = threadIdx.x; t < n; t += kTailThreads) {
-            int k = (int)(t & m), j = (int)((t >> lg) & m), i = (int)(t >> (2 * lg));
-            A.u[l][t] += prolong_value(A.u[l + 1], A.ub[l + 1], i, j, k, lg - 1, A.mode);
-        }
-        __syncthreads();
-        tail_sweeps(A, l, A.post);
+    __syncthreads();
+    if (lg == 4) {
+        tail_sweeps<N1>(T4, A.pre, k4);
+        tail_restrict(T4, T3, k4, k3);
     }
+    tail_sweeps<N1>(T3, A.pre, k3);
+    tail_restrict(T3, T2, k3, k2);
+    tail_sweeps4<N1>(T2, A.coarse, k2);
+    tail_prolong(T3, T2, A.mode, s_tab);
+    tail_sweeps<N1>(T3, A.post, k3);
+    if (lg == 4) {
+        tail_prolong(T4, T3, A.mode, s_tab);
+        tail_sweeps<N1>(T4, A.post, k4);
+    }
+    for (int c = t; c < n0; c += kTailThreads) A.u[c] = s_ue[slot0(c)].x;
 }
 
 // ------------------------------------------------------------ host launches
@@ -592,17 +759,15 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
 
 static int launch_tail(mgfr_ctx *c, int l0)
 {
+    const Level &L = c->lev[l0];
     TailArgs A;
-    memset(&A, 0, sizeof A);
-    for (int l = 0; l < c->nlev; ++l) {
-        A.u[l] = c->lev[l].u;
-        A.f[l] = c->lev[l].f;
-        A.ub[l] = c->lev[l].ubar;
-        A.ih2[l] = 1.0 / (c->lev[l].h * c->lev[l].h);
-        A.lg[l] = c->lev[l].lg;
+    A.u = L.u;
+    A.f = L.f;
+    A.lg0 = L.lg;  // 4 or 3: meshes have at least 8 cells a side
+    for (int k = 0; k < 3; ++k) {
+        const double h = c->p.box / (16 >> k);
+        A.ih2[k] = 1.0 / (h * h);
     }
-    A.l0 = l0;
-    A.nlev = c->nlev;
     A.pre = c->p.pre_smooth;
     A.post = c->p.post_smooth;
     A.coarse = c->p.coarse_sweeps;
@@ -611,7 +776,10 @@ static int launch_tail(mgfr_ctx *c, int l0)
     A.q = c->q;
     A.max_du = c->p.max_du;
     A.tab = c->exp2tab;
-    k_tail<<<1, kTailThreads, 0, c->stream>>>(A);
+    if (c->p.n == 1)
+        k_tail<true><<<1, kTailThreads, 0, c->stream>>>(A);
+    else
+        k_tail<false><<<1, kTailThreads, 0, c->stream>>>(A);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }

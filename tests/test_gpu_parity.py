@@ -281,6 +281,27 @@ def test_small_meshes_all_in_tail():
         assert _rel(dfr.cpu().numpy(), dfr_o) < 1e-10
 
 
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("prolong", [0, 1])
+@pytest.mark.parametrize("N,pre,post,coarse", [(8, 2, 2, 30), (8, 0, 1, 1), (16, 4, 4, 30), (16, 3, 0, 2), (32, 1, 2, 7)])
+def test_tail_cycle_matches_oracle(N, pre, post, coarse, prolong, n):
+    """One V-cycle on the meshes that live in the tail kernel (8^3, 16^3) and one
+    level above it, from a rough field: every smoothing count, both
+    reconstructions, n = 1 and n = 2.  A cycle is some 1e2 dependent updates of
+    O(1) values, each rounded at 1e-16 and contracting: 1e-12 relative."""
+    mg = _mg()
+    d = _delta(N, 1.0, 7)
+    kw = dict(fr0_abs=1e-5, n=n, pre_smooth=pre, post_smooth=post, coarse_sweeps=coarse, prolong=prolong)
+    p = _oparams(N, **kw)
+    _, beta, _ = O.background(p)
+    f = np.ascontiguousarray(beta * 0.3 * d)
+    u0 = np.random.default_rng(N + n).normal(-0.5, 0.3, (N, N, N))
+    ref = O.vcycle_once(p, f, u0)
+    s = mg.Solver(_params(mg, N, **kw))
+    u = s.vcycle(torch.tensor(u0, device=DEV), torch.tensor(f, device=DEV)).cpu().numpy()
+    assert _rel(u, ref) < 1e-12
+
+
 # ------------------------------------------------------------------ mass assignment
 
 @pytest.mark.parametrize("binning", [True, False])

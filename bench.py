@@ -507,7 +507,7 @@ def main():
     # algorithmic bytes of a red-black sweep: float64, read u and f, write u
     # (24 B/cell); float32 correction sweep, read e, r and u, write e (16 B/cell)
     if args.mode.startswith("fp64"):
-        kernel, bpc, design_bpc = ("k_sweep_fused" if N >= 512 else "k_sweep_half (x2 per sweep)"), 24.0, 24.0
+        kernel, bpc, design_bpc = ("k_sweep_rows" if N >= 128 else "k_sweep_half (x2 per sweep)"), 24.0, 24.0
         src = KERNEL_SRC["fp64"]
     else:
         # one colour pass is half a sweep (8 B/cell of the sweep's 16); by its own

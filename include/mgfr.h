@@ -132,7 +132,7 @@ int mgfr_set_timing(mgfr_ctx *ctx, int on);
 
 /* Float64 sweeps: smallest level size N at which a red-black sweep runs as
  * one fused, out-of-place kernel (both colours per launch, LDS-staged tiles);
- * smaller levels use one in-place kernel per colour.  Default 512; 0 = never;
+ * smaller levels use one in-place kernel per colour.  Default 128; 0 = never;
  * otherwise n >= 64.  Results agree to rounding either way. */
 int mgfr_set_fused_min_mesh(mgfr_ctx *ctx, int n);
 

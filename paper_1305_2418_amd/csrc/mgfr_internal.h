@@ -53,7 +53,10 @@ struct mgfr_ctx {
     int nlev = 0;
     mgfr::Level lev[mgfr::kMaxLevels];
     double *alt0 = nullptr;  // level-0 second buffer (owned)
-    int fused_min_n = 512;   // levels with N >= this use the fused out-of-place sweep (0: never)
+    // Levels with N >= this use the fused out-of-place sweep (0: never).  Fused
+    // against one launch per colour, us per sweep: 64^3 16 and 8, 128^3 22 and
+    // 26, 256^3 99 and 187, 512^3 755 and 1771.
+    int fused_min_n = 128;
     int colour32_min_n = 128; // float32 sweeps on levels with N >= this by one-colour pass kernels (0: never)
     int fused32 = 0;          // those sweeps as one fused red-black kernel per sweep instead
     double omega32 = 1.0;     // relaxation factor of the float32 correction sweeps (mixed solve)

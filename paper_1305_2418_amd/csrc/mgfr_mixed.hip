@@ -899,8 +899,8 @@ __global__ __launch_bounds__(kBlock) void k_mx_prolong_add(float *__restrict__ e
 // (e, expm1 e, u, e^u) per cell, so that an update reads its neighbours'
 // exponentials and evaluates one of its own.  Layout and threads: TailGrid;
 // the arithmetic is that of the other float32 levels (mx_step, mx_value).
-// Bound: the latency of some 100 dependent half-sweeps.  V(4,4) cycle: 104 us
-// with e, u and r alone in LDS (14 exponentials per update), now 36 us.
+// Bound: the latency of some 100 dependent half-sweeps.  V(4,4) cycle: 103 us
+// with e, u and r alone in LDS (14 exponentials per update), now 58 us.
 struct MxTail {
     float *e;             // top level, in and out
     const float *u, *r;

@@ -52,6 +52,30 @@ __device__ __forceinline__ double expm1_64(double x, const double *tab)
     return fma(e.S, e.p, e.S - 1.0);
 }
 
+// Plane accesses of the marching kernels: a buffer descriptor per plane (scalar
+// registers) and a byte offset within the plane per lane, so that a wave keeps
+// one 32-bit register per address instead of a 64-bit pointer that it advances.
+struct PlaneBuf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ PlaneBuf(const void *base, uint32_t bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00027000))
+    {
+    }
+    __device__ __forceinline__ double ld(uint32_t off) const
+    {
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    }
+    __device__ __forceinline__ double2 ld2(uint32_t off) const
+    {
+        return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    }
+    __device__ __forceinline__ void st2(uint32_t off, double2 v) const
+    {
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, 0);
+    }
+};
+
 __device__ __forceinline__ double nanmax(double a, double b)
 {
     return (a != a || a > b) ? a : b;

@@ -510,10 +510,10 @@ def main():
         kernel, bpc, design_bpc = ("k_sweep_rows" if N >= 128 else "k_sweep_half (x2 per sweep)"), 24.0, 24.0
         src = KERNEL_SRC["fp64"]
     else:
-        # one colour pass is half a sweep (8 B/cell of the sweep's 16); by its own
-        # design it reads u and e of every cell, r of the updated half and
-        # writes that half (12 B/cell)
-        kernel, bpc, design_bpc = "k_mx_colour (x2 per sweep)", 8.0, 12.0
+        # levels from 256^3 on: one fused kernel per sweep; below, one pass per
+        # colour, half a sweep each (8 B/cell of its 16), which by its own design
+        # reads u and e of every cell, r of the updated half and writes that half
+        kernel, bpc, design_bpc = ("k_mx_sweep_rows", 16.0, 16.0) if N >= 256 else ("k_mx_colour (x2 per sweep)", 8.0, 12.0)
         src = KERNEL_SRC["mixed"]
     alg_bytes = bpc * N ** 3
     achieved = alg_bytes / (head["sweep_launch_ms"] * 1e-3) / 1e9

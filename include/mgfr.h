@@ -145,12 +145,12 @@ int mgfr_set_fused_min_mesh(mgfr_ctx *ctx, int n);
 int mgfr_set_colour_min_mesh(mgfr_ctx *ctx, int n);
 
 /* Float32 correction sweeps on the levels that use the pass kernels (see
- * mgfr_set_colour_min_mesh): on = 1 runs each red-black sweep (Sec. 3.3) as
- * one fused, out-of-place kernel that updates the red cells of plane i + 1
- * and then the black cells of plane i while marching over the planes, so
- * that e, u and r are read once per sweep instead of once per colour; on = 0
- * (default) runs one pass kernel per colour.  The same updates in the same
- * red-black order; results agree to float32 rounding.  The second correction
+ * mgfr_set_colour_min_mesh): on = 1 (default) runs each red-black sweep
+ * (Sec. 3.3) of levels with N >= 256 as one fused, out-of-place kernel that
+ * updates the red cells of plane i + 1 and the black cells of plane i - 1 while
+ * marching over the planes, so that e, u and r are read once per sweep instead
+ * of once per colour; on = 0 runs one pass kernel per colour.  The same updates
+ * in the same order: the same iterates, bit for bit.  The second correction
  * buffer is allocated by mgfr_create for mixed-precision contexts, so this
  * call allocates nothing.  Errors: MGFR_ERR_ARG for on not 0 or 1. */
 int mgfr_set_fused_sweep32(mgfr_ctx *ctx, int on);

@@ -14,6 +14,7 @@ namespace mgfr {
 
 constexpr double kCOverH0 = 2997.92458;  // c/H0 in Mpc/h
 constexpr double kCkms = 299792.458;     // c in km/s
+constexpr int kFusedMin32 = 256;         // smallest level of the fused float32 sweep
 constexpr int kTailN = 16;               // levels with N <= kTailN run inside one workgroup
 constexpr int kBlock = 256;
 constexpr int kTailThreads = 1024;
@@ -58,7 +59,10 @@ struct mgfr_ctx {
     // 26, 256^3 99 and 187, 512^3 755 and 1771.
     int fused_min_n = 128;
     int colour32_min_n = 128; // float32 sweeps on levels with N >= this by one-colour pass kernels (0: never)
-    int fused32 = 0;          // those sweeps as one fused red-black kernel per sweep instead
+    // Those sweeps, from kFusedMin32 on, as one fused red-black kernel per sweep
+    // instead.  Fused against two passes, us per sweep: 128^3 20 and 17, 256^3 74
+    // and 87, 512^3 561 and 730.
+    int fused32 = 1;
     double omega32 = 1.0;     // relaxation factor of the float32 correction sweeps (mixed solve)
     double omega_now = 1.0;   // the factor in use (set to 1 once the outer residual grows)
     int inner_max = 1;        // float32 correction V-cycles per float64 residual check, at most
@@ -119,6 +123,14 @@ inline OpConst level_const(const mgfr_ctx *c, int l)
     k.tab = c->exp2tab;
     return k;
 }
+
+// Row tiles of the fused red-black sweeps (float64: k_sweep_rows, float32:
+// k_mx_sweep_rows): a workgroup has kRowF waves, one per row of kRowW cells,
+// and stores the inner kRowI rows.
+constexpr int kRowF = 16, kRowI = kRowF - 2, kRowW = 128;
+constexpr int kRowS = kRowW / 2 + 2;  // LDS slots per row: 64 lanes and the cells beyond either end
+// planes per workgroup of a fused sweep over an N^3 level of `cols` row tiles
+int row_chunk(int N, unsigned cols);
 
 // launch helpers implemented in mgfr_solver.hip
 int launch_sweep64(mgfr_ctx *c, int l, double *u, const double *f, int sweeps, bool timed);

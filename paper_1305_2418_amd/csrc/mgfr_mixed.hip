@@ -215,10 +215,11 @@ constexpr int CTJ = MGFR_CTJ;  // updated rows per workgroup (the last row tile 
 #endif
 constexpr int kColourPf = MGFR_COLOUR_PF;  // planes between a raw load and its use (1, 2 or 3)
 static_assert(kColourPf >= 1 && kColourPf <= 3, "prefetch distance 1, 2 or 3");
-#ifndef MGFR_CHUNKS
-#define MGFR_CHUNKS 8
-#endif
-constexpr int kChunks = MGFR_CHUNKS;  // plane chunks along i per pass (N / kChunks planes each)
+// Planes per workgroup (a multiple of 4): N / 8, but 8 at 128^3, where N / 8
+// leaves half the CUs without a workgroup.  us per pass with 8, 16, 32 chunks:
+// 128^3 12.5, 8.6, 10.5; 256^3 45, 49, 59; 512^3 389, 425, 463 (each chunk's
+// start costs).
+inline int colour_chunk(int N) { return N <= 128 ? 8 : N / 8; }
 constexpr int CKW = 128;  // cells per row tile
 constexpr int CLW = 66;   // LDS row: 64 lanes and one halo slot on each side
 
@@ -235,6 +236,12 @@ __device__ __forceinline__ Cell4 mx_cell(float u, float e)
 
 __device__ __forceinline__ float4 pack(const Cell4 &c) { return make_float4(c.u, c.e, c.P, c.W); }
 __device__ __forceinline__ Cell4 unpack(const float4 &v) { return Cell4{v.x, v.y, v.z, v.w}; }
+
+// c ? a : b, value by value (a select of two objects would put them in scratch memory)
+__device__ __forceinline__ Cell4 sel(bool c, const Cell4 &a, const Cell4 &b)
+{
+    return Cell4{c ? a.u : b.u, c ? a.e : b.e, c ? a.P : b.P, c ? a.W : b.W};
+}
 
 // New e at a cell from the cell, its residual target r and its six neighbours
 // (the same Newton step as mx_step, on the P/W form).
@@ -433,242 +440,217 @@ __global__ __launch_bounds__(64 * (CTJ + 2)) void k_mx_colour_zero(ColourArgs A)
 // ------------------------------------------- fused red-black sweep (N >= 128)
 //
 // One whole float32 correction sweep (red cells, then black cells) in one
-// launch, out of place: eout = sweep(ein) on a split level (see sx).  A
-// workgroup owns FI = FW - 4 rows of a 128-cell row tile and marches over
-// `chunk` planes; in step p it updates the red cells of plane p + 1 and then
-// the black cells of plane p, which by then have all six red neighbours new.
-// The black update of an edge row needs red updates one row beyond the tile,
-// which need the old black values of the row after that, so the workgroup has
-// one wave per row for FI + 4 rows: the outer two only load, the next two
-// update their red cells as well (results kept in LDS, not stored).  In k the
-// same holds for the cells k0 - 1 and k0 + 128: the first wave (an outer row)
-// also loads the cells k0 - 2, k0 - 1, k0 + 128, k0 + 129 of every row (one
-// lane each) and updates the red ones of the inner rows.  The chunk starts two
-// planes early for the same reason in i.
+// launch, out of place: eout = sweep(ein) on a split level (see sx); the
+// scheme of the float64 k_sweep_rows.  A workgroup has 16 waves, one per row
+// of 128 cells (lane l: the pair k0 + 2 l, k0 + 2 l + 1), and marches along i; in
+// step p it updates the red cells of plane p + 1 and the black cells of plane
+// p - 1, two independent updates per lane.  Rows 1..14 are stored; rows 0 and
+// 15 update only the red cells that rows 1 and 14 need, and their waves also
+// update the red cells k0 - 1 and k0 + 128 of all rows (lanes 0..15).  LDS holds
+// the old black cells of plane p + 1 and the new red cells of plane p - 1 as
+// (u, e, P, W).  The updates are those of the colour pass, operand by operand,
+// so the iterates are the same bit for bit.
 //
-// Lane l of a row wave holds the cells k0 + 2l, k0 + 2l + 1; on plane p + 1
-// the red one is column s = (p + 1 + j) & 1, and on plane p that same column
-// is black, so each lane does one red and one black update per step.  LDS
-// holds three planes (p, p + 1 and the one being filled) as P/W cells by row,
-// column parity and pair slot (slot 0 and 65: the k-halo cells).  Every cell
-// of ein, u and r is read once and every cell of eout written once (16 B per
-// cell and sweep) apart from the halo rows, which come mostly from L2.
-
-#ifndef MGFR_FW
-#define MGFR_FW 16
-#endif
-constexpr int FW = MGFR_FW;  // waves (rows) per workgroup
-constexpr int FI = FW - 4;   // rows updated and stored
-constexpr int FS = 66;       // LDS slots per row and column parity
-static_assert(4 * FW <= 64, "the k-halo cells of all rows are served by one wave");
-
-struct Sweep2Args {
+// Bound: vector issue and the latency of a step (one workgroup per CU); 16 B
+// per cell of traffic instead of the two passes' 24.  512^3: 561 us per sweep
+// (3.8 TB/s) against 730 us in two passes; the version before, which updated
+// the black cells of plane p after the red ones of plane p + 1, took 910 us.
+struct SweepRowsArgs {
     const float *ein;
     float *eout;
     const float *u, *r;
     int lg, chunk;
+    unsigned nkt, njt;
     MxConst kc;
 };
 
-// (u, e, P = w X, W = w E) of a cell, w = e^u, X = e^e - 1 (fexpm1), E = e^e
-__device__ __forceinline__ float4 mx_cell4(float u, float e, float w)
-{
-    const float E = fexp(e);
-    const float X = fabsf(e) < 0x1p-10f ? fmaf(0.5f * e, e, e) : E - 1.0f;
-    return make_float4(u, e, w * X, w * E);
-}
+typedef float4 MxRowLds[2][kRowF][kRowS];
 
-// New e at a cell c = (u, e, P, W) from its residual target r and six
-// neighbours (u, e, P, W): the Newton step of mx_update.
-__device__ __forceinline__ float own_update(const float4 &c, float r, const float4 &n0, const float4 &n1,
-                                            const float4 &n2, const float4 &n3, const float4 &n4, const float4 &n5,
-                                            const MxConst &k)
-{
-    float Su = 0.f, Se = 0.f, A = 0.f, B = 0.f, SW = 0.f;
-    auto add = [&](const float4 &n) {
-        const float du = n.x - c.x, de = n.y - c.y;
-        Su += du;
-        Se += de;
-        A = fmaf(n.z, du, A);
-        B = fmaf(n.w, de, B);
-        SW += n.w;
-    };
-    add(n0);
-    add(n1);
-    add(n2);
-    add(n3);
-    add(n4);
-    add(n5);
-    const float flux = 0.5f * ((A + c.z * Su) + (B + c.w * Se));
-    const float dflux = 0.5f * (c.w * (Su + Se - 6.0f) - SW);
-    const float sc = fexp(-k.q * c.x);
-    const float cm = fexpm1(-k.q * c.y);
-    const float bs = k.bC * sc;
-    const float N = k.ih2 * flux + bs * cm;
-    const float J = k.ih2 * dflux - k.q * bs * (1.0f + cm);
-    float d = -(N - r) * __builtin_amdgcn_rcpf(J) * k.omega;
-    if (k.max_du > 0.f) d = fminf(fmaxf(d, -k.max_du), k.max_du);
-    return c.y + d;
-}
-
-template <int S0>
-__device__ __forceinline__ void mx_sweep2_rows(const Sweep2Args &A, int i0, int j0, int k0, int w, int lane,
-                                               float4 *sX)
+// S0: red column of the wave's row on plane i0 - 1.  EDGE: an outer row.  ZERO:
+// e is zero everywhere and not read.
+template <int S0, bool EDGE, bool ZERO>
+__device__ __forceinline__ void mx_sweep_rows(const SweepRowsArgs &A, int i0, int j0, int k0, int row, int lane,
+                                              MxRowLds &sO, MxRowLds &sN)
 {
     const int lg = A.lg, m = (1 << lg) - 1;
-    const size_t hN = (size_t)1 << (lg - 1), plane = (size_t)1 << (2 * lg);
-    const int jg = (j0 + w - 2) & m;
-    const bool red_row = w >= 1 && w <= FW - 2;                          // uniform over the wave
-    const bool blk_row = w >= 2 && w <= FW - 3 && j0 + w - 2 <= m;      // rows stored
-    const size_t rowb = (size_t)jg << lg;
-    // addresses: a wave-uniform row pointer plus a 32-bit lane byte offset
-    const uint32_t kk = 4u * (uint32_t)(k0 + 2 * lane), kh2 = 4u * (uint32_t)(k0 / 2 + lane);
-    auto pb = [&](int pl) { return (size_t)(pl & m) * plane + rowb; };
-    auto ldu = [&](int pl) { return at_off<float2>(A.u + pb(pl), kk); };
-    // cell k0 + 2l lies in half (pl + jg) & 1 of its row (k0 is even)
-    auto lde = [&](int pl) {
-        const bool odd = ((pl + jg) & 1) != 0;
-        return make_float2(at_off<float>(A.ein + pb(pl) + (odd ? hN : 0), kh2),
-                           at_off<float>(A.ein + pb(pl) + (odd ? 0 : hN), kh2));
-    };
-    // k-halo duty of the first wave: lane = 4 row + c, c -> k0 - 2, k0 - 1, k0 + 128, k0 + 129
-    const bool hv = w == 0 && lane < 4 * FW;
-    const int hl = lane % (4 * FW), hw = hl >> 2, hc = hl & 3;
-    const int hjg = (j0 + hw - 2) & m;
-    const int hk = (hc < 2 ? k0 - 2 + hc : k0 + 126 + hc) & m;
-    const int hpar = hc & 1, hslot = hc < 2 ? 0 : FS - 1;
-    const bool hin = hv && (hc == 1 || hc == 2) && hw >= 2 && hw <= FW - 3;
-    const size_t hrow = (size_t)hjg << lg;
-    auto hb = [&](int pl) { return (size_t)(pl & m) * plane + hrow; };
-    auto hle = [&](int pl) { return A.ein[hb(pl) + ((size_t)((pl + hjg + hk) & 1) << (lg - 1)) + (size_t)(hk >> 1)]; };
-    auto cell = [&](float u, float e) { return mx_cell4(u, e, fexp(u)); };
-    auto at = [&](int buf, int row, int par, int slot) { return ((buf * FW + row) * 2 + par) * FS + slot; };
-
-    // raw loads of step p, issued one step ahead in two alternating register sets
+    const int i1 = min(i0 + A.chunk, m + 1);
+    const size_t plane = (size_t)1 << (2 * lg);
+    const uint32_t pbytes = 4u << (2 * lg), hN = 2u << lg;  // bytes of a plane, of half a row
+    const int jg = (j0 - 1 + row) & m;
+    const bool stored = !EDGE && j0 - 1 + row <= m;  // uniform over the wave
+    const uint32_t jo = (uint32_t)((row == 0 ? jg - 1 : jg + 1) & m) << lg;  // EDGE: the row beyond
+    // byte offsets within a plane: the pair in natural order, its cells in a half row
+    const uint32_t kk = (uint32_t)(k0 + 2 * lane);
+    const uint32_t offu = 4u * (((uint32_t)jg << lg) + kk), offe = 4u * (((uint32_t)jg << lg) + (kk >> 1));
+    const uint32_t offou = 4u * (jo + kk), offoe = 4u * (jo + (kk >> 1)) + hN;
+    auto pu = [&](int pl) { return PlaneBuf(A.u + (size_t)(pl & m) * plane, pbytes); };
+    auto pe = [&](int pl) { return PlaneBuf(A.ein + (size_t)(pl & m) * plane, pbytes); };
+    auto pr = [&](int pl) { return PlaneBuf(A.r + (size_t)(pl & m) * plane, pbytes); };
+    // the cells beyond the row tile's end: lane q serves row q (EDGE waves, lanes 0..15)
+    const bool low = row == 0;
+    const int hq = lane & (kRowF - 1), hslot = low ? 0 : kRowS - 1;
+    const int hk = (low ? k0 - 1 : k0 + kRowW) & m, hk2 = (low ? k0 - 2 : k0 + kRowW + 1) & m;
+    const int hj = (j0 - 1 + hq) & m;
+    const uint32_t hrow = (uint32_t)hj << lg;
+    const int hup = hq > 0 ? hq - 1 : 0, hdn = hq < kRowF - 1 ? hq + 1 : kRowF - 1;
+    const MxConst &kc = A.kc;
+    // raw values of step p, two steps ahead: u and e (red and black half) of plane
+    // p + 2, r of the red cell of plane p + 1 and of the black cell of plane p - 1
     struct Raw {
-        float2 u, e;       // plane p + 2
-        float rr, rb;      // r of the red cell of plane p + 1, of the black cell of plane p
-        float hu, he, hr;  // k-halo cell: u, e of plane p + 2, r of plane p + 1 (red half)
+        float2 u;
+        float er, eb, rr, rb;
     };
     auto load = [&](int p) {
-        Raw x;
-        x.u = ldu(p + 2);
-        x.e = lde(p + 2);
-        x.rr = at_off<float>(A.r + pb(p + 1), kh2);
-        x.rb = at_off<float>(A.r + pb(p) + hN, kh2);
-        x.hu = A.u[hb(p + 2) + (size_t)hk];
-        x.he = hle(p + 2);
-        x.hr = A.r[hb(p + 1) + (size_t)(hk >> 1)];
-        return x;
+        Raw w;
+        w.u = pu(p + 2).ldf2(offu);
+        if constexpr (ZERO) {
+            w.er = w.eb = 0.0f;
+        } else {
+            const PlaneBuf b = pe(p + 2);
+            w.er = b.ldf(offe);
+            w.eb = b.ldf(offe + hN);
+        }
+        w.rr = pr(p + 1).ldf(offe);
+        if constexpr (!EDGE) w.rb = pr(p - 1).ldf(offe + hN);
+        return w;
     };
-
-    // planes i0 - 2 (P0) and i0 - 1 (P1), old values; the k-halo cell of plane
-    // p is read back from LDS, that of plane p + 1 is kept in H1
-    float4 P0[2], P1[2], H1, prev;
+    // EDGE, one step ahead: the red cell's outer neighbour on plane p + 1 (a black
+    // cell), the cell beyond the end on plane p + 2, and of plane p + 1 its outer
+    // neighbour and r where it is red
+    struct Ext {
+        float ou, oe, hu, he, nu, ne, hr;
+    } ex;
+    auto load_ext = [&](int p, int S) {
+        const PlaneBuf bu = pu(p + 1), be = pe(p + 1);
+        ex.ou = bu.ldf(offou + 4u * S);
+        ex.nu = bu.ldf(4u * (hrow + (uint32_t)hk2));
+        ex.hu = pu(p + 2).ldf(4u * (hrow + (uint32_t)hk));
+        if constexpr (ZERO) {
+            ex.oe = ex.ne = ex.he = 0.0f;
+        } else {
+            ex.oe = be.ldf(offoe);
+            ex.ne = be.ldf(4u * (hrow + (uint32_t)(hk2 >> 1)) + hN);
+            ex.he = pe(p + 2).ldf(4u * (hrow + (uint32_t)(hk >> 1)) + (((p + hj + hk) & 1) ? hN : 0u));
+        }
+        ex.hr = pr(p + 1).ldf(4u * (hrow + (uint32_t)(hk >> 1)));
+    };
+    // planes p - 1 (red new), p (red new) and p + 1 (old) of the pair; red cell of plane p - 2
+    Cell4 A1[2], C0[2], C1[2], R2;
+    Cell4 h0{}, h1{}, hm{};  // EDGE: the cell beyond the end on planes p, p + 1, p - 1
     {
-        const float2 ua = ldu(i0 - 2), ea = lde(i0 - 2), ub = ldu(i0 - 1), eb = lde(i0 - 1);
-        P0[0] = cell(ua.x, ea.x);
-        P0[1] = cell(ua.y, ea.y);
-        P1[0] = cell(ub.x, eb.x);
-        P1[1] = cell(ub.y, eb.y);
-        prev = P0[0];
-        const float4 H0 = cell(A.u[hb(i0 - 2) + (size_t)hk], hle(i0 - 2));
-        if (hv) sX[at(0, hw, hpar, hslot)] = H0;  // ordered by the first step's barrier
-        H1 = cell(A.u[hb(i0 - 1) + (size_t)hk], hle(i0 - 1));
+        // columns of plane i0 - 1: red S0; of plane i0 - 2: red 1 - S0
+        const float2 u0 = pu(i0 - 2).ldf2(offu), u1 = pu(i0 - 1).ldf2(offu);
+        float e0r = 0.f, e0b = 0.f, e1r = 0.f, e1b = 0.f;
+        if constexpr (!ZERO) {
+            e0r = pe(i0 - 2).ldf(offe);
+            e0b = pe(i0 - 2).ldf(offe + hN);
+            e1r = pe(i0 - 1).ldf(offe);
+            e1b = pe(i0 - 1).ldf(offe + hN);
+        }
+        C0[0] = mx_cell(u0.x, S0 ? e0r : e0b);
+        C0[1] = mx_cell(u0.y, S0 ? e0b : e0r);
+        C1[0] = mx_cell(u1.x, S0 ? e1b : e1r);
+        C1[1] = mx_cell(u1.y, S0 ? e1r : e1b);
+        A1[0] = A1[1] = R2 = C0[0];
+        if constexpr (EDGE) {
+            auto hcell = [&](int pl) {
+                const float e = ZERO ? 0.f
+                                     : pe(pl).ldf(4u * (hrow + (uint32_t)(hk >> 1)) + (((pl + hj + hk) & 1) ? hN : 0u));
+                return mx_cell(pu(pl).ldf(4u * (hrow + (uint32_t)hk)), e);
+            };
+            h0 = hm = hcell(i0 - 2);
+            h1 = hcell(i0 - 1);
+            load_ext(i0 - 2, S0);
+        }
     }
-    Raw ra = load(i0 - 2), rb;
-    int x0 = 0, x1 = 1, x2 = 2;  // LDS buffers of planes p, p + 1, p + 2
-    const int iend = i0 + A.chunk;
-
-    auto step = [&](int p, auto Sc, auto Bc, const Raw &cur, Raw &nxt) {
-        constexpr int S = decltype(Sc)::value;
-        constexpr bool BLACK = decltype(Bc)::value;
-        nxt = load(p + 1);
-        const float4 Q0 = cell(cur.u.x, cur.e.x), Q1 = cell(cur.u.y, cur.e.y);
-        const float4 &QS = S ? Q1 : Q0;
-        float4 HQ = H1;
-        if (w == 0) HQ = cell(cur.hu, cur.he);
-        // publish the old black cell of plane p + 1 (and the k-halo cells)
-        sX[at(x1, w, 1 - S, lane + 1)] = P1[1 - S];
-        if (hv) sX[at(x1, hw, hpar, hslot)] = H1;
+    Raw ra = load(i0 - 2), rb = load(i0 - 1);
+    int buf = 0;
+    auto step = [&](int p, auto Sc, Raw &raw) {
+        constexpr int S = decltype(Sc)::value, T = 1 - S;
+        const bool hred = EDGE && ((p + 1 + hj + hk) & 1) == 0;
+        float4(*O)[kRowS] = sO[buf], (*R)[kRowS] = sN[buf];
+        O[row][lane + 1] = pack(C1[T]);
+        R[row][lane + 1] = pack(A1[S]);
+        if constexpr (EDGE) {
+            if (lane < kRowF) (hred ? R : O)[hq][hslot] = pack(sel(hred, hm, h1));
+        }
         __syncthreads();
-        // red cell of plane p + 1: neighbours black and old
-        if (red_row) {
-            const float4 sd = S ? sX[at(x1, w, 0, lane + 2)] : sX[at(x1, w, 1, lane)];
-            const float4 up = sX[at(x1, w - 1, S, lane + 1)];
-            const float4 dn = sX[at(x1, w + 1, S, lane + 1)];
-            const float wr = fexp(P1[S].x);
-            const float en = own_update(P1[S], cur.rr, P1[1 - S], sd, up, dn, P0[S], QS, A.kc);
-            P1[S] = mx_cell4(P1[S].x, en, wr);
-            sX[at(x1, w, S, lane + 1)] = P1[S];
-            if (blk_row && p + 1 >= i0 && p + 1 < iend) at_off<float>(A.eout + pb(p + 1), kh2) = en;
+        // plane p + 2: red column T
+        const Cell4 Q[2] = {mx_cell(raw.u.x, T ? raw.eb : raw.er), mx_cell(raw.u.y, T ? raw.er : raw.eb)};
+        const float rr = raw.rr, rbl = EDGE ? 0.f : raw.rb;
+        raw = load(p + 2);
+        // red cell of plane p + 1
+        Cell4 up = unpack(O[row == 0 ? 0 : row - 1][lane + 1]),
+              dn = unpack(O[row == kRowF - 1 ? row : row + 1][lane + 1]);
+        if constexpr (EDGE) {
+            const Cell4 o = mx_cell(ex.ou, ex.oe);
+            up = sel(row == 0, o, up);
+            dn = sel(row == 0, dn, o);
         }
-        if (w == 0) {
-            // red k-halo cells of the stored rows
-            if (hin && (((p + 1) + hjg + hk) & 1) == 0) {
-                const float4 na = hc == 1 ? sX[at(x1, hw, 0, 0)] : sX[at(x1, hw, 1, FS - 1)];
-                const float4 nb = hc == 1 ? sX[at(x1, hw, 0, 1)] : sX[at(x1, hw, 1, FS - 2)];
-                const float4 up = sX[at(x1, hw - 1, hpar, hslot)];
-                const float4 dn = sX[at(x1, hw + 1, hpar, hslot)];
-                const float4 H0 = sX[at(x0, hw, hpar, hslot)];
-                const float wh = fexp(H1.x);
-                const float en = own_update(H1, cur.hr, na, nb, up, dn, H0, HQ, A.kc);
-                H1 = mx_cell4(H1.x, en, wh);
-                sX[at(x1, hw, hpar, hslot)] = H1;
+        const Cell4 sd = unpack(O[row][S ? lane + 2 : lane]);
+        const float en = mx_update(C1[S], rr, C1[T], sd, up, dn, C0[S], Q[S], kc);
+        // black cell of plane p - 1
+        if constexpr (!EDGE) {
+            if (stored && p - 1 >= i0) {
+                const Cell4 bu = unpack(R[row - 1][lane + 1]), bd = unpack(R[row + 1][lane + 1]),
+                            bs = unpack(R[row][T ? lane + 2 : lane]);
+                const PlaneBuf out(A.eout + (size_t)(p - 1) * plane, pbytes);
+                out.stf(offe + hN, mx_update(A1[T], rbl, A1[S], bs, bu, bd, R2, C0[T], kc));
+                out.stf(offe, A1[S].e);
             }
+        } else {
+            __builtin_amdgcn_sched_barrier(0);  // one update's operands at a time
+            const Cell4 hn = mx_cell(ex.hu, ex.he);
+            if (lane < kRowF && hred) {
+                const float eh = mx_update(h1, ex.hr, mx_cell(ex.nu, ex.ne), unpack(O[hq][low ? 1 : 64]),
+                                           unpack(O[hup][hslot]), unpack(O[hdn][hslot]), h0, hn, kc);
+                h1 = mx_cell(h1.u, eh);
+            }
+            load_ext(p + 1, T);
+            hm = h0;
+            h0 = h1;
+            h1 = hn;
         }
-        // black cell of plane p: neighbours red and new (plane p's buffer was
-        // completed in the previous step)
-        if (BLACK && blk_row) {
-            const float4 sd = S ? sX[at(x0, w, 0, lane + 2)] : sX[at(x0, w, 1, lane)];
-            const float4 up = sX[at(x0, w - 1, S, lane + 1)];
-            const float4 dn = sX[at(x0, w + 1, S, lane + 1)];
-            at_off<float>(A.eout + pb(p) + hN, kh2) =
-                own_update(P0[S], cur.rb, P0[1 - S], sd, up, dn, prev, P1[S], A.kc);
-        }
-        prev = P0[1 - S];
-        P0[0] = P1[0];
-        P0[1] = P1[1];
-        P1[0] = Q0;
-        P1[1] = Q1;
-        H1 = HQ;
-        const int t = x0;
-        x0 = x1;
-        x1 = x2;
-        x2 = t;
+        R2 = A1[S];
+        A1[0] = C0[0];
+        A1[1] = C0[1];
+        C0[T] = C1[T];
+        C0[S] = mx_cell(C1[S].u, en);
+        C1[0] = Q[0];
+        C1[1] = Q[1];
+        buf ^= 1;
     };
-    using Z0 = std::integral_constant<int, S0>;
-    using Z1 = std::integral_constant<int, 1 - S0>;
-    using NB = std::integral_constant<bool, false>;
-    using YB = std::integral_constant<bool, true>;
-    step(i0 - 2, Z0{}, NB{}, ra, rb);
-    step(i0 - 1, Z1{}, NB{}, rb, ra);
-    for (int p = i0; p < iend; p += 2) {  // chunk is even
-        step(p, Z0{}, YB{}, ra, rb);
-        step(p + 1, Z1{}, YB{}, rb, ra);
+    for (int p = i0 - 2; p <= i1; p += 2) {
+        step(p, std::integral_constant<int, S0>{}, ra);
+        if (p < i1) step(p + 1, std::integral_constant<int, 1 - S0>{}, rb);
     }
 }
 
-// grid: 1-D, (N / 128) ceil(N / FI) (N / chunk) workgroups, spread over the
-// XCDs as in the colour pass
-__global__ __launch_bounds__(64 * FW) void k_mx_sweep2(Sweep2Args A)
+// grid: nkt njt ceil(N / chunk) workgroups; those of one XCD (blocks b, b + 8,
+// ...) take consecutive tiles, which share their outer rows in its L2
+template <bool ZERO>
+__global__ __launch_bounds__(64 * kRowF) void k_mx_sweep_rows(SweepRowsArgs A)
 {
-    __shared__ float4 sX[3 * FW * 2 * FS];
-    const int lg = A.lg;
-    const unsigned nb = gridDim.x, b = blockIdx.x;
-    const unsigned L = (b & 7u) * (nb >> 3) + (b >> 3);  // nb is a multiple of 8
-    const int nkt = (1 << lg) / CKW, njt = ((1 << lg) + FI - 1) / FI;
-    const int kt = (int)(L % (unsigned)nkt), jt = (int)((L / (unsigned)nkt) % (unsigned)njt),
-              it = (int)(L / ((unsigned)nkt * (unsigned)njt));
-    const int k0 = kt * CKW, j0 = jt * FI, i0 = it * A.chunk;
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    __shared__ MxRowLds sO, sN;
+    const unsigned nb = gridDim.x, x = blockIdx.x & 7u, per = nb >> 3, rem = nb & 7u;
+    const unsigned L = x * per + min(x, rem) + (blockIdx.x >> 3);
+    const int kt = (int)(L % A.nkt), jt = (int)((L / A.nkt) % A.njt), it = (int)(L / (A.nkt * A.njt));
+    const int k0 = kt * kRowW, j0 = jt * kRowI, i0 = it * A.chunk;
+    const int row = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    // red column of this wave's row on plane i0 - 1 (step i0 - 2)
-    const int s0 = (i0 - 1 + j0 + w - 2) & 1;
-    if (s0)
-        mx_sweep2_rows<1>(A, i0, j0, k0, w, lane, sX);
-    else
-        mx_sweep2_rows<0>(A, i0, j0, k0, w, lane, sX);
+    const int s0 = (i0 - 1 + j0 - 1 + row) & 1;  // red column of the row on plane i0 - 1
+    if (row == 0 || row == kRowF - 1) {
+        __builtin_amdgcn_s_setprio(2);  // these waves do two updates one after the other
+        if (s0)
+            mx_sweep_rows<1, true, ZERO>(A, i0, j0, k0, row, lane, sO, sN);
+        else
+            mx_sweep_rows<0, true, ZERO>(A, i0, j0, k0, row, lane, sO, sN);
+    } else {
+        if (s0)
+            mx_sweep_rows<1, false, ZERO>(A, i0, j0, k0, row, lane, sO, sN);
+        else
+            mx_sweep_rows<0, false, ZERO>(A, i0, j0, k0, row, lane, sO, sN);
+    }
 }
 
 // ------------------------------------------------- restriction pass (N >= 128)
@@ -1393,16 +1375,23 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
     const bool colour_pass = split_level(c, l);
     int slot, rc;
     for (int s = 0; s < sweeps; ++s) {
-        if (colour_pass && c->fused32 && L.e32alt) {
-            const int chunk = L.N / kChunks;
-            const unsigned nbf = (unsigned)((L.N / CKW) * ((L.N + FI - 1) / FI) * kChunks);
-            if ((rc = timer_slot(c, timed, slot))) return rc;
-            k_mx_sweep2<<<nbf, 64 * FW, 0, c->stream>>>(Sweep2Args{L.e32, L.e32alt, L.u32, L.r32, L.lg, chunk, kc});
-            if ((rc = timer_end(c, slot))) return rc;
+        if (colour_pass && c->fused32 && L.N >= kFusedMin32) {
+            const unsigned nkt = (unsigned)(L.N / kRowW), njt = (unsigned)((L.N + kRowI - 1) / kRowI);
+            const int chunk = row_chunk(L.N, nkt * njt);
+            const SweepRowsArgs A{L.e32, L.e32alt, L.u32, L.r32, L.lg, chunk, nkt, njt, kc};
+            const unsigned nbf = nkt * njt * (unsigned)((L.N + chunk - 1) / chunk);
+            if (l == 0 && c->e32_zero) {  // first sweep after a float64 check; not timed
+                k_mx_sweep_rows<true><<<nbf, 64 * kRowF, 0, c->stream>>>(A);
+                c->e32_zero = false;
+            } else {
+                if ((rc = timer_slot(c, timed, slot))) return rc;
+                k_mx_sweep_rows<false><<<nbf, 64 * kRowF, 0, c->stream>>>(A);
+                if ((rc = timer_end(c, slot))) return rc;
+            }
             std::swap(L.e32, L.e32alt);
         } else if (colour_pass) {
-            const int chunk = L.N / kChunks;
-            const unsigned nb = (unsigned)((L.N / CKW) * ((L.N + CTJ - 1) / CTJ) * kChunks);
+            const int chunk = colour_chunk(L.N);
+            const unsigned nb = (unsigned)((L.N / CKW) * ((L.N + CTJ - 1) / CTJ) * (L.N / chunk));
             for (int colour = 0; colour < 2; ++colour) {
                 const ColourArgs A{L.e32, L.u32, L.r32, L.lg, colour, chunk, kc};
                 if (l == 0 && c->e32_zero) {  // first pass after a float64 check; not timed
@@ -1550,7 +1539,7 @@ static int outer_step(mgfr_ctx *c, bool add_e, double *rmax, double *rsq)
     if (add_e) std::swap(L0.u, L0.alt);
     // e = 0: cleared here, or by the first colour pass of the next cycle, which
     // then reads no e and writes the cells it does not update as 0
-    c->e32_zero = split_level(c, 0) && c->p.pre_smooth >= 1 && !(c->fused32 && L0.e32alt);
+    c->e32_zero = split_level(c, 0) && c->p.pre_smooth >= 1;
     if (!c->e32_zero) MGFR_HIP(hipMemsetAsync(L0.e32, 0, n * sizeof(float), c->stream));
     k_mx_final<<<1, 1024, 0, c->stream>>>(c->partial, g, c->dscal);
     MGFR_HIP(hipGetLastError());

@@ -69,6 +69,18 @@ struct PlaneBuf {
     {
         return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
     }
+    __device__ __forceinline__ float ldf(uint32_t off) const
+    {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    }
+    __device__ __forceinline__ float2 ldf2(uint32_t off) const
+    {
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    }
+    __device__ __forceinline__ void stf(uint32_t off, float v) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
+    }
     __device__ __forceinline__ void st2(uint32_t off, double2 v) const
     {
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));

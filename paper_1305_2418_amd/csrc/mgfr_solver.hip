@@ -169,11 +169,6 @@ __device__ __forceinline__ double curv_em(double uc, double ec, double q, const 
 // operand) issued 215 per cell: 1206 and 207 us.  What mattered besides: no
 // spilled register (a scratch load waits for every prefetch before it: 1062 us
 // with seven spills), and exponentials after the barrier, not before it.
-constexpr int RF = 16;      // rows (waves) per workgroup
-constexpr int RI = RF - 2;  // rows stored
-constexpr int RS = 66;      // LDS slots per row: 64 lanes and the cells beyond either end
-constexpr int RKW = 128;    // cells per row tile
-
 struct RowArgs {
     const double *u, *f;
     double *out;
@@ -182,7 +177,7 @@ struct RowArgs {
     OpConst kc;
 };
 
-typedef double2 RowLds[2][RF][RS];
+typedef double2 RowLds[2][kRowF][kRowS];
 
 // S0: red column of the wave's row on plane i0 - 1.  EDGE: an outer row, which
 // also serves the cells beyond one end of all rows (row 0: the lower end).
@@ -203,11 +198,11 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
     auto pf = [&](int pl) { return PlaneBuf(A.f + (size_t)(pl & m) * plane, 8u << (2 * lg)); };
     // the cells beyond the row tile's end: lane q serves row q (EDGE waves, lanes 0..15)
     const bool low = row == 0;
-    const int hq = lane & (RF - 1), hslot = low ? 0 : RS - 1;
-    const int hk = (low ? k0 - 1 : k0 + RKW) & m, hk2 = (low ? k0 - 2 : k0 + RKW + 1) & m;
+    const int hq = lane & (kRowF - 1), hslot = low ? 0 : kRowS - 1;
+    const int hk = (low ? k0 - 1 : k0 + kRowW) & m, hk2 = (low ? k0 - 2 : k0 + kRowW + 1) & m;
     const int hj = (j0 - 1 + hq) & m;
     const uint32_t offh = 8u * (((uint32_t)hj << lg) + (uint32_t)hk), offh2 = 8u * (((uint32_t)hj << lg) + (uint32_t)hk2);
-    const int hup = hq > 0 ? hq - 1 : 0, hdn = hq < RF - 1 ? hq + 1 : RF - 1;
+    const int hup = hq > 0 ? hq - 1 : 0, hdn = hq < kRowF - 1 ? hq + 1 : kRowF - 1;
     const OpConst &kc = A.kc;
     auto cell = [&](double u) { return make_double2(u, exp64(u, kc.tab)); };
     auto update = [&](const double2 &c, const double2 &n0, const double2 &n1, const double2 &n2, const double2 &n3,
@@ -265,19 +260,19 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
     auto step = [&](int p, auto Sc, Raw &raw) {
         constexpr int S = decltype(Sc)::value, T = 1 - S;
         const bool hred = EDGE && ((p + 1 + hj + hk) & 1) == 0;
-        double2(*O)[RS] = sO[buf], (*R)[RS] = sN[buf];
+        double2(*O)[kRowS] = sO[buf], (*R)[kRowS] = sN[buf];
         O[row][lane + 1] = C1[T];
         R[row][lane + 1] = A1[S];
         if constexpr (EDGE) {
             const double2 hv = make_double2(hred ? hm.x : h1.x, hred ? hm.y : h1.y);
-            if (lane < RF) (hred ? R : O)[hq][hslot] = hv;
+            if (lane < kRowF) (hred ? R : O)[hq][hslot] = hv;
         }
         __syncthreads();
         const double2 Q[2] = {cell(raw.u.x), cell(raw.u.y)};
         const double fr = !EDGE && S ? raw.f.y : raw.f.x, fbn = EDGE ? 0.0 : S ? raw.f.x : raw.f.y;
         raw = load(p + 2, S);
         // red cell of plane p + 1
-        double2 up = O[row == 0 ? 0 : row - 1][lane + 1], dn = O[row == RF - 1 ? row : row + 1][lane + 1];
+        double2 up = O[row == 0 ? 0 : row - 1][lane + 1], dn = O[row == kRowF - 1 ? row : row + 1][lane + 1];
         if constexpr (EDGE) {
             const double2 o = cell(ex.o);
             up = make_double2(row == 0 ? o.x : up.x, row == 0 ? o.y : up.y);
@@ -295,7 +290,7 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
         } else {
             __builtin_amdgcn_sched_barrier(0);  // one update's operands at a time
             const double2 hn = cell(ex.hu);
-            if (lane < RF && hred)
+            if (lane < kRowF && hred)
                 h1 = cell(update(h1, hn, h0, O[hdn][hslot], O[hup][hslot], O[hq][low ? 1 : 64], cell(ex.ho), ex.hf));
             load_ext(p + 1, T);
             hm = h0;
@@ -322,18 +317,18 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
 // grid: nkt njt ceil(N / chunk) workgroups; those of one XCD (blocks b, b + 8,
 // ...) take consecutive tiles in j, which share their outer rows in its L2
 template <bool N1>
-__global__ __launch_bounds__(64 * RF) void k_sweep_rows(RowArgs A)
+__global__ __launch_bounds__(64 * kRowF) void k_sweep_rows(RowArgs A)
 {
     __shared__ RowLds sO, sN;
     MGFR_EXP_TABLE_TO_LDS(A.kc);
     const unsigned nb = gridDim.x, x = blockIdx.x & 7u, per = nb >> 3, rem = nb & 7u;
     const unsigned L = x * per + min(x, rem) + (blockIdx.x >> 3);
     const int kt = (int)(L % A.nkt), jt = (int)((L / A.nkt) % A.njt), it = (int)(L / (A.nkt * A.njt));
-    const int k0 = kt * RKW, j0 = jt * RI, i0 = it * A.chunk;
+    const int k0 = kt * kRowW, j0 = jt * kRowI, i0 = it * A.chunk;
     const int row = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     const int s0 = (i0 - 1 + j0 - 1 + row) & 1;  // red column of the row on plane i0 - 1
-    if (row == 0 || row == RF - 1) {
+    if (row == 0 || row == kRowF - 1) {
         __builtin_amdgcn_s_setprio(2);  // these waves do two updates one after the other: 806 -> 755 us
         if (s0)
             sweep_rows<N1, 1, true>(A, i0, j0, k0, row, lane, sO, sN);
@@ -778,10 +773,10 @@ static int timer_slot(mgfr_ctx *c, int *slot)
     return MGFR_OK;
 }
 
-// Planes per workgroup of k_sweep_rows: one workgroup runs on a CU at a time
+// Planes per workgroup of the fused sweeps: one workgroup runs on a CU at a time
 // and spends chunk + 3 steps, so take the chunk with the fewest steps over all
 // rounds of the 256 CUs.
-static int row_chunk(int N, unsigned cols)
+int row_chunk(int N, unsigned cols)
 {
     int best = N;
     long cost = -1;
@@ -815,14 +810,14 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
             MGFR_HIP(hipEventRecord(c->sweep_timer.ev[slot], c->stream));
         }
         if (fused) {
-            const unsigned nkt = (unsigned)std::max(1, L.N / RKW), njt = (unsigned)((L.N + RI - 1) / RI);
+            const unsigned nkt = (unsigned)std::max(1, L.N / kRowW), njt = (unsigned)((L.N + kRowI - 1) / kRowI);
             const int chunk = row_chunk(L.N, nkt * njt);
             const RowArgs A{L.u, f, L.alt, L.lg, chunk, nkt, njt, kc};
             const unsigned nb = nkt * njt * (unsigned)((L.N + chunk - 1) / chunk);
             if (c->p.n == 1)
-                k_sweep_rows<true><<<nb, 64 * RF, 0, c->stream>>>(A);
+                k_sweep_rows<true><<<nb, 64 * kRowF, 0, c->stream>>>(A);
             else
-                k_sweep_rows<false><<<nb, 64 * RF, 0, c->stream>>>(A);
+                k_sweep_rows<false><<<nb, 64 * kRowF, 0, c->stream>>>(A);
             std::swap(L.u, L.alt);
         } else {
             for (int colour = 0; colour < 2; ++colour)

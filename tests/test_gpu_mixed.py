@@ -133,6 +133,27 @@ def test_sweep_kernels_agree(N):
         assert rel < (1e-4 if k == "plain" else 1e-6)
 
 
+@pytest.mark.parametrize("N,n,pre,post", [(256, 1, 4, 4), (256, 2, 1, 2), (512, 1, 2, 1)])
+def test_fused_sweep_gives_the_colour_passes_bits(N, n, pre, post):
+    """One correction cycle with the fused sweep and with one pass per colour: row
+    tiles of 14 and of 8 rows, chunks that do and do not divide the mesh, two
+    and four tiles along k, odd and even sweep counts (the iterate ends in
+    either buffer).  The same operands in the same order: the same bits."""
+    from paper_1305_2418_amd import mgfr
+    print(f"[case] fused sweep bits N={N} n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + n)
+    d = torch.exp(torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * 1.5)
+    d = d / d.mean() - 1.0
+    out = []
+    for fused in (True, False):
+        s = mgfr.Solver(mgfr.Params(mesh=N, fr0_abs=1e-6, n=n, precision=mgfr.MIXED, max_vcycles=2, pre_smooth=pre,
+                                    post_smooth=post))
+        s.set_fused_sweep32(fused)
+        out.append(s.solve(d, want_dfr=False, allow_not_converged=True)[0])
+        del s
+    assert torch.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("n", [1, 2])
 def test_mixed_with_all_options_matches_oracle(n):
     """The mixed solve with every option the benchmark or a hard case uses at

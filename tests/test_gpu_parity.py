@@ -516,6 +516,27 @@ def test_fused_sweep_matches_oracle(N, n):
     assert _rel(u.cpu().numpy(), ref) < 1e-12
 
 
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("N", [64, 128, 256])
+def test_fused_sweep_matches_one_colour_kernels(N, n):
+    """The fused sweep against one launch per colour on a rough field: a mesh
+    narrower than the 128-cell row tile, one tile, two tiles (cells beyond the
+    ends come from another tile); rows and planes that the 14-row tiles and
+    the chunks do not divide.  The same update formula with another order of
+    six-term sums: a few 1e-16 of O(1) values per sweep."""
+    mg = _mg()
+    print(f"[case] fused against one-colour sweep N={N} n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + n)
+    u0 = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * 0.7 - 1.0
+    f = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * 5.0
+    out = []
+    for fused in (64, 0):
+        s = mg.Solver(_params(mg, N, fr0_abs=1e-6, n=n))
+        s.set_fused_min_mesh(fused)
+        out.append(s.ngs_sweep(u0.clone(), f, 2))
+    assert float((out[0] - out[1]).abs().max()) < 1e-13
+
+
 @pytest.mark.parametrize("N,pre,post,fr0", [(64, 2, 2, 1e-6), (128, 2, 2, 1e-6), (64, 1, 2, 1e-5), (256, 2, 2, 1e-6)])
 def test_fused_solve_matches_oracle(N, pre, post, fr0):
     mg = _mg()

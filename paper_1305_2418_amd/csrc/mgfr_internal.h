@@ -55,13 +55,13 @@ struct mgfr_ctx {
     mgfr::Level lev[mgfr::kMaxLevels];
     double *alt0 = nullptr;  // level-0 second buffer (owned)
     // Levels with N >= this use the fused out-of-place sweep (0: never).  Fused
-    // against one launch per colour, us per sweep: 64^3 16 and 8, 128^3 22 and
-    // 26, 256^3 99 and 187, 512^3 755 and 1771.
+    // against one launch per colour, us per sweep: 64^3 16 and 8, 128^3 21 and
+    // 26, 256^3 95 and 186, 512^3 763 and 1772.
     int fused_min_n = 128;
     int colour32_min_n = 128; // float32 sweeps on levels with N >= this by one-colour pass kernels (0: never)
     // Those sweeps, from kFusedMin32 on, as one fused red-black kernel per sweep
-    // instead.  Fused against two passes, us per sweep: 128^3 20 and 17, 256^3 74
-    // and 87, 512^3 561 and 730.
+    // instead.  Fused against two passes, us per sweep: 128^3 20 and 17, 256^3 69
+    // and 87, 512^3 565 and 730.
     int fused32 = 1;
     double omega32 = 1.0;     // relaxation factor of the float32 correction sweeps (mixed solve)
     double omega_now = 1.0;   // the factor in use (set to 1 once the outer residual grows)
@@ -125,9 +125,10 @@ inline OpConst level_const(const mgfr_ctx *c, int l)
 }
 
 // Row tiles of the fused red-black sweeps (float64: k_sweep_rows, float32:
-// k_mx_sweep_rows): a workgroup has kRowF waves, one per row of kRowW cells,
-// and stores the inner kRowI rows.
-constexpr int kRowF = 16, kRowI = kRowF - 2, kRowW = 128;
+// k_mx_sweep_rows): a workgroup has kRowF waves, one per row of kRowW cells, of
+// which the inner kRowI are stored, and one more wave for the cells beyond the
+// rows' ends.
+constexpr int kRowF = 15, kRowI = kRowF - 2, kRowW = 128;
 constexpr int kRowS = kRowW / 2 + 2;  // LDS slots per row: 64 lanes and the cells beyond either end
 // planes per workgroup of a fused sweep over an N^3 level of `cols` row tiles
 int row_chunk(int N, unsigned cols);

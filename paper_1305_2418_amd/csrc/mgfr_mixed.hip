@@ -249,7 +249,8 @@ __device__ __forceinline__ float mx_update(const Cell4 &c, float r, const Cell4 
                                            const Cell4 &n2, const Cell4 &n3, const Cell4 &n4, const Cell4 &n5,
                                            const MxConst &k)
 {
-    float Su = 0.f, Se = 0.f, A = 0.f, B = 0.f, SW = 0.f;
+    float Su = n0.u - c.u, Se = n0.e - c.e;
+    float A = n0.P * Su, B = n0.W * Se, SW = n0.W;
     auto add = [&](const Cell4 &n) {
         const float du = n.u - c.u, de = n.e - c.e;
         Su += du;
@@ -258,18 +259,19 @@ __device__ __forceinline__ float mx_update(const Cell4 &c, float r, const Cell4 
         B = fmaf(n.W, de, B);
         SW += n.W;
     };
-    add(n0);
     add(n1);
     add(n2);
     add(n3);
     add(n4);
     add(n5);
-    const float flux = 0.5f * ((A + c.P * Su) + (B + c.W * Se));
-    const float dflux = 0.5f * (c.W * (Su + Se - 6.0f) - SW);
+    // twice the flux and its derivative; ih2h = 1 / (2 h^2) (halving is exact)
+    const float ih2h = 0.5f * k.ih2;
+    const float flux2 = fmaf(c.P, Su, A) + fmaf(c.W, Se, B);
+    const float dflux2 = fmaf(c.W, Su + Se - 6.0f, -SW);
     const float sc = fexp(-k.q * c.u);
     const float cm = fexpm1(-k.q * c.e);
-    const float N = k.ih2 * flux + k.bC * sc * cm;
-    const float J = k.ih2 * dflux - k.q * k.bC * sc * (1.0f + cm);
+    const float N = fmaf(k.bC * sc, cm, ih2h * flux2);
+    const float J = fmaf(ih2h, dflux2, -(k.q * k.bC * sc * (1.0f + cm)));
     float d = -(N - r) * __builtin_amdgcn_rcpf(J) * k.omega;
     if (k.max_du > 0.f) d = fminf(fmaxf(d, -k.max_du), k.max_du);
     return c.e + d;
@@ -441,20 +443,21 @@ __global__ __launch_bounds__(64 * (CTJ + 2)) void k_mx_colour_zero(ColourArgs A)
 //
 // One whole float32 correction sweep (red cells, then black cells) in one
 // launch, out of place: eout = sweep(ein) on a split level (see sx); the
-// scheme of the float64 k_sweep_rows.  A workgroup has 16 waves, one per row
+// scheme of the float64 k_sweep_rows.  A workgroup has 15 waves, one per row
 // of 128 cells (lane l: the pair k0 + 2 l, k0 + 2 l + 1), and marches along i; in
 // step p it updates the red cells of plane p + 1 and the black cells of plane
-// p - 1, two independent updates per lane.  Rows 1..14 are stored; rows 0 and
-// 15 update only the red cells that rows 1 and 14 need, and their waves also
-// update the red cells k0 - 1 and k0 + 128 of all rows (lanes 0..15).  LDS holds
-// the old black cells of plane p + 1 and the new red cells of plane p - 1 as
+// p - 1, two independent updates per lane.  Rows 1..13 are stored; rows 0 and
+// 14 update only the red cells that rows 1 and 13 need.  A sixteenth wave
+// updates the red cells k0 - 1 and k0 + 128 of all rows.  LDS holds the old
+// black cells of plane p + 1 and the new red cells of plane p - 1 as
 // (u, e, P, W).  The updates are those of the colour pass, operand by operand,
 // so the iterates are the same bit for bit.
 //
-// Bound: vector issue and the latency of a step (one workgroup per CU); 16 B
-// per cell of traffic instead of the two passes' 24.  512^3: 561 us per sweep
-// (3.8 TB/s) against 730 us in two passes; the version before, which updated
-// the black cells of plane p after the red ones of plane p + 1, took 910 us.
+// Bound: vector issue (a SIMD's four waves fill a step) and, with one
+// workgroup per CU, what a step cannot overlap; 16 B per cell of traffic
+// instead of the two passes' 24.  512^3: 565 us per sweep against 730 us in
+// two passes; updating the black cells of plane p after the red ones of plane
+// p + 1, one after the other, took 910 us.
 struct SweepRowsArgs {
     const float *ein;
     float *eout;
@@ -466,9 +469,9 @@ struct SweepRowsArgs {
 
 typedef float4 MxRowLds[2][kRowF][kRowS];
 
-// S0: red column of the wave's row on plane i0 - 1.  EDGE: an outer row.  ZERO:
+// S0: red column of the wave's row on plane i0 - 1.  RING: an outer row.  ZERO:
 // e is zero everywhere and not read.
-template <int S0, bool EDGE, bool ZERO>
+template <int S0, bool RING, bool ZERO>
 __device__ __forceinline__ void mx_sweep_rows(const SweepRowsArgs &A, int i0, int j0, int k0, int row, int lane,
                                               MxRowLds &sO, MxRowLds &sN)
 {
@@ -477,8 +480,8 @@ __device__ __forceinline__ void mx_sweep_rows(const SweepRowsArgs &A, int i0, in
     const size_t plane = (size_t)1 << (2 * lg);
     const uint32_t pbytes = 4u << (2 * lg), hN = 2u << lg;  // bytes of a plane, of half a row
     const int jg = (j0 - 1 + row) & m;
-    const bool stored = !EDGE && j0 - 1 + row <= m;  // uniform over the wave
-    const uint32_t jo = (uint32_t)((row == 0 ? jg - 1 : jg + 1) & m) << lg;  // EDGE: the row beyond
+    const bool stored = !RING && j0 - 1 + row <= m;  // uniform over the wave
+    const uint32_t jo = (uint32_t)((row == 0 ? jg - 1 : jg + 1) & m) << lg;  // RING: the row beyond
     // byte offsets within a plane: the pair in natural order, its cells in a half row
     const uint32_t kk = (uint32_t)(k0 + 2 * lane);
     const uint32_t offu = 4u * (((uint32_t)jg << lg) + kk), offe = 4u * (((uint32_t)jg << lg) + (kk >> 1));
@@ -486,57 +489,36 @@ __device__ __forceinline__ void mx_sweep_rows(const SweepRowsArgs &A, int i0, in
     auto pu = [&](int pl) { return PlaneBuf(A.u + (size_t)(pl & m) * plane, pbytes); };
     auto pe = [&](int pl) { return PlaneBuf(A.ein + (size_t)(pl & m) * plane, pbytes); };
     auto pr = [&](int pl) { return PlaneBuf(A.r + (size_t)(pl & m) * plane, pbytes); };
-    // the cells beyond the row tile's end: lane q serves row q (EDGE waves, lanes 0..15)
-    const bool low = row == 0;
-    const int hq = lane & (kRowF - 1), hslot = low ? 0 : kRowS - 1;
-    const int hk = (low ? k0 - 1 : k0 + kRowW) & m, hk2 = (low ? k0 - 2 : k0 + kRowW + 1) & m;
-    const int hj = (j0 - 1 + hq) & m;
-    const uint32_t hrow = (uint32_t)hj << lg;
-    const int hup = hq > 0 ? hq - 1 : 0, hdn = hq < kRowF - 1 ? hq + 1 : kRowF - 1;
     const MxConst &kc = A.kc;
     // raw values of step p, two steps ahead: u and e (red and black half) of plane
-    // p + 2, r of the red cell of plane p + 1 and of the black cell of plane p - 1
+    // p + 2, r of the red cell of plane p + 1 and of the black cell of plane p - 1;
+    // RING: the red cell's outer neighbour on plane p + 1 (a black cell)
     struct Raw {
         float2 u;
-        float er, eb, rr, rb;
+        float er, eb, rr, rb, ou, oe;
     };
-    auto load = [&](int p) {
+    auto load = [&](int p, int S) {
         Raw w;
         w.u = pu(p + 2).ldf2(offu);
-        if constexpr (ZERO) {
-            w.er = w.eb = 0.0f;
-        } else {
+        w.er = w.eb = w.oe = 0.0f;
+        if constexpr (!ZERO) {
             const PlaneBuf b = pe(p + 2);
             w.er = b.ldf(offe);
             w.eb = b.ldf(offe + hN);
         }
         w.rr = pr(p + 1).ldf(offe);
-        if constexpr (!EDGE) w.rb = pr(p - 1).ldf(offe + hN);
+        if constexpr (RING) {
+            w.ou = pu(p + 1).ldf(offou + 4u * S);
+            if constexpr (!ZERO) w.oe = pe(p + 1).ldf(offoe);
+        } else {
+            w.rb = pr(p - 1).ldf(offe + hN);
+        }
         return w;
     };
-    // EDGE, one step ahead: the red cell's outer neighbour on plane p + 1 (a black
-    // cell), the cell beyond the end on plane p + 2, and of plane p + 1 its outer
-    // neighbour and r where it is red
-    struct Ext {
-        float ou, oe, hu, he, nu, ne, hr;
-    } ex;
-    auto load_ext = [&](int p, int S) {
-        const PlaneBuf bu = pu(p + 1), be = pe(p + 1);
-        ex.ou = bu.ldf(offou + 4u * S);
-        ex.nu = bu.ldf(4u * (hrow + (uint32_t)hk2));
-        ex.hu = pu(p + 2).ldf(4u * (hrow + (uint32_t)hk));
-        if constexpr (ZERO) {
-            ex.oe = ex.ne = ex.he = 0.0f;
-        } else {
-            ex.oe = be.ldf(offoe);
-            ex.ne = be.ldf(4u * (hrow + (uint32_t)(hk2 >> 1)) + hN);
-            ex.he = pe(p + 2).ldf(4u * (hrow + (uint32_t)(hk >> 1)) + (((p + hj + hk) & 1) ? hN : 0u));
-        }
-        ex.hr = pr(p + 1).ldf(4u * (hrow + (uint32_t)(hk >> 1)));
-    };
-    // planes p - 1 (red new), p (red new) and p + 1 (old) of the pair; red cell of plane p - 2
-    Cell4 A1[2], C0[2], C1[2], R2;
-    Cell4 h0{}, h1{}, hm{};  // EDGE: the cell beyond the end on planes p, p + 1, p - 1
+    // Planes p - 1 (red new), p (red new), p + 1 (old) and p + 2 of the pair in a
+    // ring of four: the plane loop is written out for its four positions (and
+    // both parities), so that no cell is moved between registers.
+    Cell4 X[4][2];
     {
         // columns of plane i0 - 1: red S0; of plane i0 - 2: red 1 - S0
         const float2 u0 = pu(i0 - 2).ldf2(offu), u1 = pu(i0 - 1).ldf2(offu);
@@ -547,89 +529,133 @@ __device__ __forceinline__ void mx_sweep_rows(const SweepRowsArgs &A, int i0, in
             e1r = pe(i0 - 1).ldf(offe);
             e1b = pe(i0 - 1).ldf(offe + hN);
         }
-        C0[0] = mx_cell(u0.x, S0 ? e0r : e0b);
-        C0[1] = mx_cell(u0.y, S0 ? e0b : e0r);
-        C1[0] = mx_cell(u1.x, S0 ? e1b : e1r);
-        C1[1] = mx_cell(u1.y, S0 ? e1r : e1b);
-        A1[0] = A1[1] = R2 = C0[0];
-        if constexpr (EDGE) {
-            auto hcell = [&](int pl) {
-                const float e = ZERO ? 0.f
-                                     : pe(pl).ldf(4u * (hrow + (uint32_t)(hk >> 1)) + (((pl + hj + hk) & 1) ? hN : 0u));
-                return mx_cell(pu(pl).ldf(4u * (hrow + (uint32_t)hk)), e);
-            };
-            h0 = hm = hcell(i0 - 2);
-            h1 = hcell(i0 - 1);
-            load_ext(i0 - 2, S0);
-        }
+        X[1][0] = mx_cell(u0.x, S0 ? e0r : e0b);
+        X[1][1] = mx_cell(u0.y, S0 ? e0b : e0r);
+        X[2][0] = mx_cell(u1.x, S0 ? e1b : e1r);
+        X[2][1] = mx_cell(u1.y, S0 ? e1r : e1b);
+        X[0][0] = X[0][1] = X[3][0] = X[3][1] = X[1][0];
     }
-    Raw ra = load(i0 - 2), rb = load(i0 - 1);
-    int buf = 0;
-    auto step = [&](int p, auto Sc, Raw &raw) {
-        constexpr int S = decltype(Sc)::value, T = 1 - S;
-        const bool hred = EDGE && ((p + 1 + hj + hk) & 1) == 0;
-        float4(*O)[kRowS] = sO[buf], (*R)[kRowS] = sN[buf];
+    Raw ra = load(i0 - 2, S0), rb = load(i0 - 1, 1 - S0);
+    auto step = [&](int p, auto Hc, Raw &raw) {
+        constexpr int H = decltype(Hc)::value, S = S0 ^ (H & 1), T = 1 - S;
+        Cell4(&A1)[2] = X[H], (&C0)[2] = X[(H + 1) & 3], (&C1)[2] = X[(H + 2) & 3], (&Q)[2] = X[(H + 3) & 3];
+        float4(*O)[kRowS] = sO[H & 1], (*R)[kRowS] = sN[H & 1];
         O[row][lane + 1] = pack(C1[T]);
         R[row][lane + 1] = pack(A1[S]);
-        if constexpr (EDGE) {
-            if (lane < kRowF) (hred ? R : O)[hq][hslot] = pack(sel(hred, hm, h1));
-        }
         __syncthreads();
+        const Cell4 R2 = Q[T];  // red cell of plane p - 2 (the ring's oldest plane)
         // plane p + 2: red column T
-        const Cell4 Q[2] = {mx_cell(raw.u.x, T ? raw.eb : raw.er), mx_cell(raw.u.y, T ? raw.er : raw.eb)};
-        const float rr = raw.rr, rbl = EDGE ? 0.f : raw.rb;
-        raw = load(p + 2);
+        Q[0] = mx_cell(raw.u.x, T ? raw.eb : raw.er);
+        Q[1] = mx_cell(raw.u.y, T ? raw.er : raw.eb);
+        const Raw cur = raw;
+        raw = load(p + 2, S);
         // red cell of plane p + 1
-        Cell4 up = unpack(O[row == 0 ? 0 : row - 1][lane + 1]),
-              dn = unpack(O[row == kRowF - 1 ? row : row + 1][lane + 1]);
-        if constexpr (EDGE) {
-            const Cell4 o = mx_cell(ex.ou, ex.oe);
-            up = sel(row == 0, o, up);
-            dn = sel(row == 0, dn, o);
+        Cell4 up, dn;
+        if constexpr (RING) {
+            const Cell4 o = mx_cell(cur.ou, cur.oe), in = unpack(O[row == 0 ? 1 : row - 1][lane + 1]);
+            up = sel(row == 0, o, in);
+            dn = sel(row == 0, in, o);
+        } else {
+            up = unpack(O[row - 1][lane + 1]);
+            dn = unpack(O[row + 1][lane + 1]);
         }
         const Cell4 sd = unpack(O[row][S ? lane + 2 : lane]);
-        const float en = mx_update(C1[S], rr, C1[T], sd, up, dn, C0[S], Q[S], kc);
+        const float en = mx_update(C1[S], cur.rr, C1[T], sd, up, dn, C0[S], Q[S], kc);
         // black cell of plane p - 1
-        if constexpr (!EDGE) {
+        if constexpr (!RING) {
             if (stored && p - 1 >= i0) {
                 const Cell4 bu = unpack(R[row - 1][lane + 1]), bd = unpack(R[row + 1][lane + 1]),
                             bs = unpack(R[row][T ? lane + 2 : lane]);
                 const PlaneBuf out(A.eout + (size_t)(p - 1) * plane, pbytes);
-                out.stf(offe + hN, mx_update(A1[T], rbl, A1[S], bs, bu, bd, R2, C0[T], kc));
+                out.stf(offe + hN, mx_update(A1[T], cur.rb, A1[S], bs, bu, bd, R2, C0[T], kc));
                 out.stf(offe, A1[S].e);
             }
-        } else {
-            __builtin_amdgcn_sched_barrier(0);  // one update's operands at a time
-            const Cell4 hn = mx_cell(ex.hu, ex.he);
-            if (lane < kRowF && hred) {
-                const float eh = mx_update(h1, ex.hr, mx_cell(ex.nu, ex.ne), unpack(O[hq][low ? 1 : 64]),
-                                           unpack(O[hup][hslot]), unpack(O[hdn][hslot]), h0, hn, kc);
-                h1 = mx_cell(h1.u, eh);
-            }
-            load_ext(p + 1, T);
-            hm = h0;
-            h0 = h1;
-            h1 = hn;
         }
-        R2 = A1[S];
-        A1[0] = C0[0];
-        A1[1] = C0[1];
-        C0[T] = C1[T];
-        C0[S] = mx_cell(C1[S].u, en);
-        C1[0] = Q[0];
-        C1[1] = Q[1];
-        buf ^= 1;
+        C1[S] = mx_cell(C1[S].u, en);
     };
-    for (int p = i0 - 2; p <= i1; p += 2) {
-        step(p, std::integral_constant<int, S0>{}, ra);
-        if (p < i1) step(p + 1, std::integral_constant<int, 1 - S0>{}, rb);
+    for (int p = i0 - 2;;) {
+        step(p, std::integral_constant<int, 0>{}, ra);
+        if (++p > i1) break;
+        step(p, std::integral_constant<int, 1>{}, rb);
+        if (++p > i1) break;
+        step(p, std::integral_constant<int, 2>{}, ra);
+        if (++p > i1) break;
+        step(p, std::integral_constant<int, 3>{}, rb);
+        if (++p > i1) break;
+    }
+}
+
+// The red cells k0 - 1 (lanes 0..14, row = lane) and k0 + 128 (lanes 16..30) of
+// the workgroup's rows, on the same steps: a cell is black and red in turn along
+// i; black, its old value is published beside its row's black cells, red, it is
+// updated and its new value published with the row's red ones.
+template <bool ZERO>
+__device__ __forceinline__ void mx_sweep_ends(const SweepRowsArgs &A, int i0, int j0, int k0, int lane, MxRowLds &sO,
+                                              MxRowLds &sN)
+{
+    const int lg = A.lg, m = (1 << lg) - 1;
+    const int i1 = min(i0 + A.chunk, m + 1);
+    const size_t plane = (size_t)1 << (2 * lg);
+    const uint32_t pbytes = 4u << (2 * lg), hN = 2u << lg;
+    const bool low = (lane & 16) == 0, live = (lane & 15) < kRowF && lane < 32;
+    const int q = min(lane & 15, kRowF - 1), slot = low ? 0 : kRowS - 1, in = low ? 1 : kRowS - 2;
+    const int j = (j0 - 1 + q) & m, k = (low ? k0 - 1 : k0 + kRowW) & m, k2 = (low ? k0 - 2 : k0 + kRowW + 1) & m;
+    const uint32_t row = (uint32_t)j << lg;
+    // byte offsets within a plane: u and e of the cell and of its outer neighbour
+    const uint32_t ou = 4u * (row + (uint32_t)k), oe = 4u * (row + (uint32_t)(k >> 1)), ou2 = 4u * (row + (uint32_t)k2),
+                   oe2 = 4u * (row + (uint32_t)(k2 >> 1)) + hN;
+    const int jup = q > 0 ? q - 1 : 0, jdn = q < kRowF - 1 ? q + 1 : q;
+    auto pu = [&](int pl) { return PlaneBuf(A.u + (size_t)(pl & m) * plane, pbytes); };
+    auto pe = [&](int pl) { return PlaneBuf(A.ein + (size_t)(pl & m) * plane, pbytes); };
+    auto pr = [&](int pl) { return PlaneBuf(A.r + (size_t)(pl & m) * plane, pbytes); };
+    auto lde = [&](int pl) { return ZERO ? 0.0f : pe(pl).ldf(oe + (((pl + j + k) & 1) ? hN : 0u)); };
+    // step p: u, e of plane p + 2; r and the outer neighbour (black where the cell is red) of plane p + 1
+    struct Raw {
+        float u, e, r, u2, e2;
+    };
+    auto load = [&](int p) {
+        Raw w;
+        w.u = pu(p + 2).ldf(ou);
+        w.e = lde(p + 2);
+        w.r = pr(p + 1).ldf(oe);
+        w.u2 = pu(p + 1).ldf(ou2);
+        w.e2 = ZERO ? 0.0f : pe(p + 1).ldf(oe2);
+        return w;
+    };
+    Cell4 X[4];  // planes p - 1, p, p + 1, p + 2 (ring)
+    X[0] = X[1] = X[3] = mx_cell(pu(i0 - 2).ldf(ou), lde(i0 - 2));
+    X[2] = mx_cell(pu(i0 - 1).ldf(ou), lde(i0 - 1));
+    Raw ra = load(i0 - 2), rb = load(i0 - 1);
+    auto step = [&](int p, auto Hc, Raw &raw) {
+        constexpr int H = decltype(Hc)::value;
+        const bool red = ((p + 1 + j + k) & 1) == 0;  // on planes p + 1 and p - 1
+        float4(*O)[kRowS] = sO[H & 1], (*R)[kRowS] = sN[H & 1];
+        if (live) (red ? R : O)[q][slot] = pack(sel(red, X[H], X[(H + 2) & 3]));
+        __syncthreads();
+        Cell4 &c = X[(H + 2) & 3], &n = X[(H + 3) & 3];
+        n = mx_cell(raw.u, raw.e);
+        const Raw cur = raw;
+        raw = load(p + 2);
+        if (live && red)
+            c = mx_cell(c.u, mx_update(c, cur.r, mx_cell(cur.u2, cur.e2), unpack(O[q][in]), unpack(O[jup][slot]),
+                                       unpack(O[jdn][slot]), X[(H + 1) & 3], n, A.kc));
+    };
+    for (int p = i0 - 2;;) {
+        step(p, std::integral_constant<int, 0>{}, ra);
+        if (++p > i1) break;
+        step(p, std::integral_constant<int, 1>{}, rb);
+        if (++p > i1) break;
+        step(p, std::integral_constant<int, 2>{}, ra);
+        if (++p > i1) break;
+        step(p, std::integral_constant<int, 3>{}, rb);
+        if (++p > i1) break;
     }
 }
 
 // grid: nkt njt ceil(N / chunk) workgroups; those of one XCD (blocks b, b + 8,
 // ...) take consecutive tiles, which share their outer rows in its L2
 template <bool ZERO>
-__global__ __launch_bounds__(64 * kRowF) void k_mx_sweep_rows(SweepRowsArgs A)
+__global__ __launch_bounds__(64 * (kRowF + 1)) void k_mx_sweep_rows(SweepRowsArgs A)
 {
     __shared__ MxRowLds sO, sN;
     const unsigned nb = gridDim.x, x = blockIdx.x & 7u, per = nb >> 3, rem = nb & 7u;
@@ -639,8 +665,9 @@ __global__ __launch_bounds__(64 * kRowF) void k_mx_sweep_rows(SweepRowsArgs A)
     const int row = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     const int s0 = (i0 - 1 + j0 - 1 + row) & 1;  // red column of the row on plane i0 - 1
-    if (row == 0 || row == kRowF - 1) {
-        __builtin_amdgcn_s_setprio(2);  // these waves do two updates one after the other
+    if (row == kRowF)
+        mx_sweep_ends<ZERO>(A, i0, j0, k0, lane, sO, sN);
+    else if (row == 0 || row == kRowF - 1) {
         if (s0)
             mx_sweep_rows<1, true, ZERO>(A, i0, j0, k0, row, lane, sO, sN);
         else
@@ -1381,11 +1408,11 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
             const SweepRowsArgs A{L.e32, L.e32alt, L.u32, L.r32, L.lg, chunk, nkt, njt, kc};
             const unsigned nbf = nkt * njt * (unsigned)((L.N + chunk - 1) / chunk);
             if (l == 0 && c->e32_zero) {  // first sweep after a float64 check; not timed
-                k_mx_sweep_rows<true><<<nbf, 64 * kRowF, 0, c->stream>>>(A);
+                k_mx_sweep_rows<true><<<nbf, 64 * (kRowF + 1), 0, c->stream>>>(A);
                 c->e32_zero = false;
             } else {
                 if ((rc = timer_slot(c, timed, slot))) return rc;
-                k_mx_sweep_rows<false><<<nbf, 64 * kRowF, 0, c->stream>>>(A);
+                k_mx_sweep_rows<false><<<nbf, 64 * (kRowF + 1), 0, c->stream>>>(A);
                 if ((rc = timer_end(c, slot))) return rc;
             }
             std::swap(L.e32, L.e32alt);

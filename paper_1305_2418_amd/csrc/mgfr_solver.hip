@@ -146,29 +146,27 @@ __device__ __forceinline__ double curv_em(double uc, double ec, double q, const 
 
 // One full red-black sweep, out of place: out = sweep(u), on levels with N >= 64.
 //
-// A workgroup has 16 waves, one per row of 128 cells (lane l: the pair
+// A workgroup has 15 waves, one per row of 128 cells (lane l: the pair
 // k0 + 2 l, k0 + 2 l + 1), and marches along i.  In step p it updates the red
 // cells of plane p + 1 and the black cells of plane p - 1.  The two updates of a
 // lane do not depend on each other, which is why the black one trails by two
 // planes: with one barrier per step and four waves per SIMD the dependent chain
-// of an update is what a step would otherwise wait for.  Rows 1..14 are
-// stored; rows 0 and 15 update only their red cells, which the black cells of
-// rows 1 and 14 need (their outer neighbour is one more value per lane).  The
-// red cells k0 - 1 and k0 + 128 of the 16 rows are updated by lanes 0..15 of
-// the two outer waves.  A cell is kept as (u, e^u): e^u is evaluated when its
-// plane is loaded and after its red update.  In every plane the updated column
-// of a wave is uniform, so nothing is selected per lane.  LDS holds the old
-// black cells of plane p + 1 and the new red cells of plane p - 1 (two buffers
-// each, 68 KB).  Meshes narrower than a tile (N = 64) hold it twice: both
-// copies of a cell get the same value.
+// of an update is what a step would otherwise wait for.  Rows 1..13 are
+// stored; rows 0 and 14 update only their red cells, which the black cells of
+// rows 1 and 13 need (their outer neighbour is one more value per lane).  The
+// red cells k0 - 1 and k0 + 128 of all rows are a sixteenth wave's.  A cell is
+// kept as (u, e^u): e^u is evaluated when its plane is loaded and after its red
+// update.  In every plane the updated column of a wave is uniform, so nothing
+// is selected per lane.  LDS holds the old black cells of plane p + 1 and the
+// new red cells of plane p - 1 (two buffers each, 63 KB).  Meshes narrower than
+// a tile (N = 64) hold it twice: both copies of a cell get the same value.
 //
 // Bound: the float64 vector pipe and the latency of a step (one workgroup per
-// CU: 128 registers).  111 vector instructions per cell; 755 us per sweep of
-// 512^3 (24 B per cell: 4.3 TB/s), 99 us at 256^3.  The version before (a row
-// pair per thread, 12 x 60 of each 16 x 64 tile stored, a select for every
-// operand) issued 215 per cell: 1206 and 207 us.  What mattered besides: no
-// spilled register (a scratch load waits for every prefetch before it: 1062 us
-// with seven spills), and exponentials after the barrier, not before it.
+// CU: 128 registers).  512^3: 763 us per sweep (24 B per cell), 256^3
+// 95 us; a version with a row pair per thread, 12 x 60 of each 16 x 64 tile
+// stored and a select for every operand issued twice the instructions: 1206 and
+// 207 us.  What mattered besides: no spilled register (a scratch load waits for
+// every prefetch before it), and exponentials after the barrier, not before it.
 struct RowArgs {
     const double *u, *f;
     double *out;
@@ -179,123 +177,90 @@ struct RowArgs {
 
 typedef double2 RowLds[2][kRowF][kRowS];
 
-// S0: red column of the wave's row on plane i0 - 1.  EDGE: an outer row, which
-// also serves the cells beyond one end of all rows (row 0: the lower end).
-template <bool N1, int S0, bool EDGE>
+template <bool N1>
+__device__ __forceinline__ double row_update(const double2 &c, const double2 &n0, const double2 &n1, const double2 &n2,
+                                             const double2 &n3, const double2 &n4, const double2 &n5, double f,
+                                             const OpConst &kc)
+{
+    return c.x + ngs_step_e(c.x, c.y, curv_em<N1>(c.x, c.y, kc.q, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y, n3.x,
+                            n3.y, n4.x, n4.y, n5.x, n5.y, f, kc);
+}
+
+// S0: red column of the wave's row on plane i0 - 1.  RING: an outer row.
+template <bool N1, int S0, bool RING>
 __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int k0, int row, int lane, RowLds &sO,
                                            RowLds &sN)
 {
     const int lg = A.lg, m = (1 << lg) - 1;
     const int i1 = min(i0 + A.chunk, m + 1);
     const size_t plane = (size_t)1 << (2 * lg);
+    const uint32_t pbytes = 8u << (2 * lg);
     const int jg = (j0 - 1 + row) & m;
-    const bool stored = !EDGE && j0 - 1 + row <= m;  // uniform over the wave
-    // byte offsets within a plane: the lane's pair, and (EDGE) the same in the row beyond
+    const bool stored = !RING && j0 - 1 + row <= m;  // uniform over the wave
+    // byte offsets within a plane: the lane's pair, and (RING) the same in the row beyond
     const uint32_t kk = (uint32_t)((k0 + 2 * lane) & m);
     const uint32_t off = 8u * (((uint32_t)jg << lg) + kk);
     const uint32_t offo = 8u * (((uint32_t)((row == 0 ? jg - 1 : jg + 1) & m) << lg) + kk);
-    auto pu = [&](int pl) { return PlaneBuf(A.u + (size_t)(pl & m) * plane, 8u << (2 * lg)); };
-    auto pf = [&](int pl) { return PlaneBuf(A.f + (size_t)(pl & m) * plane, 8u << (2 * lg)); };
-    // the cells beyond the row tile's end: lane q serves row q (EDGE waves, lanes 0..15)
-    const bool low = row == 0;
-    const int hq = lane & (kRowF - 1), hslot = low ? 0 : kRowS - 1;
-    const int hk = (low ? k0 - 1 : k0 + kRowW) & m, hk2 = (low ? k0 - 2 : k0 + kRowW + 1) & m;
-    const int hj = (j0 - 1 + hq) & m;
-    const uint32_t offh = 8u * (((uint32_t)hj << lg) + (uint32_t)hk), offh2 = 8u * (((uint32_t)hj << lg) + (uint32_t)hk2);
-    const int hup = hq > 0 ? hq - 1 : 0, hdn = hq < kRowF - 1 ? hq + 1 : kRowF - 1;
+    auto pu = [&](int pl) { return PlaneBuf(A.u + (size_t)(pl & m) * plane, pbytes); };
+    auto pf = [&](int pl) { return PlaneBuf(A.f + (size_t)(pl & m) * plane, pbytes); };
     const OpConst &kc = A.kc;
     auto cell = [&](double u) { return make_double2(u, exp64(u, kc.tab)); };
-    auto update = [&](const double2 &c, const double2 &n0, const double2 &n1, const double2 &n2, const double2 &n3,
-                      const double2 &n4, const double2 &n5, double f) {
-        return c.x + ngs_step_e(c.x, c.y, curv_em<N1>(c.x, c.y, kc.q, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y, n3.x,
-                                n3.y, n4.x, n4.y, n5.x, n5.y, f, kc);
-    };
-    // raw values of step p: u of plane p + 2 and f of plane p + 1, loaded two
-    // steps ahead
+    // raw values of step p, two steps ahead: u of plane p + 2, f of plane p + 1;
+    // RING: f of the red cell alone and its outer neighbour (column S), plane p + 1
     struct Raw {
         double2 u, f;
     };
     auto load = [&](int p, int S) {
         Raw w;
         w.u = pu(p + 2).ld2(off);
-        if constexpr (EDGE)  // the red cell's alone
-            w.f.x = pf(p + 1).ld(off + 8u * S);
+        if constexpr (RING)
+            w.f = make_double2(pf(p + 1).ld(off + 8u * S), pu(p + 1).ld(offo + 8u * S));
         else
             w.f = pf(p + 1).ld2(off);
         return w;
     };
-    // EDGE: on plane p + 1 the red cell's outer neighbour (column S), and f and
-    // the outer neighbour of the cell beyond the end, whose u is of plane p + 2;
-    // one step ahead, because they are used late in a step and registers are short
-    struct Ext {
-        double o, hu, ho, hf;
-    } ex;
-    auto load_ext = [&](int p, int S) {
-        const PlaneBuf b = pu(p + 1);
-        ex.o = b.ld(offo + 8u * S);
-        ex.hu = pu(p + 2).ld(offh);
-        ex.ho = b.ld(offh2);
-        ex.hf = pf(p + 1).ld(offh);
-    };
     // planes p - 1 (red new), p (red new) and p + 1 (old) of the pair; red cell of plane p - 2
     double2 A1[2], C0[2], C1[2], R2;
-    double fb0 = 0.0, fb1 = 0.0;      // f of the black cells of planes p - 1 and p
-    double2 h0, h1, hm;               // EDGE: the cell beyond the end on planes p, p + 1, p - 1
+    double fb0 = 0.0, fb1 = 0.0;  // f of the black cells of planes p - 1 and p
     {
         const double2 u0 = pu(i0 - 2).ld2(off), u1 = pu(i0 - 1).ld2(off);
-        const double g0 = EDGE ? pu(i0 - 2).ld(offh) : 0.0, g1 = EDGE ? pu(i0 - 1).ld(offh) : 0.0;
         C0[0] = cell(u0.x);
         C0[1] = cell(u0.y);
         C1[0] = cell(u1.x);
         C1[1] = cell(u1.y);
         A1[0] = A1[1] = R2 = C0[0];
-        if constexpr (EDGE) {
-            h0 = hm = cell(g0);
-            h1 = cell(g1);
-        }
     }
-    if constexpr (EDGE) load_ext(i0 - 2, S0);
     Raw ra = load(i0 - 2, S0), rb = load(i0 - 1, 1 - S0);
     int buf = 0;
     auto step = [&](int p, auto Sc, Raw &raw) {
         constexpr int S = decltype(Sc)::value, T = 1 - S;
-        const bool hred = EDGE && ((p + 1 + hj + hk) & 1) == 0;
         double2(*O)[kRowS] = sO[buf], (*R)[kRowS] = sN[buf];
         O[row][lane + 1] = C1[T];
         R[row][lane + 1] = A1[S];
-        if constexpr (EDGE) {
-            const double2 hv = make_double2(hred ? hm.x : h1.x, hred ? hm.y : h1.y);
-            if (lane < kRowF) (hred ? R : O)[hq][hslot] = hv;
-        }
         __syncthreads();
         const double2 Q[2] = {cell(raw.u.x), cell(raw.u.y)};
-        const double fr = !EDGE && S ? raw.f.y : raw.f.x, fbn = EDGE ? 0.0 : S ? raw.f.x : raw.f.y;
+        const double2 fv = raw.f;
         raw = load(p + 2, S);
         // red cell of plane p + 1
-        double2 up = O[row == 0 ? 0 : row - 1][lane + 1], dn = O[row == kRowF - 1 ? row : row + 1][lane + 1];
-        if constexpr (EDGE) {
-            const double2 o = cell(ex.o);
-            up = make_double2(row == 0 ? o.x : up.x, row == 0 ? o.y : up.y);
-            dn = make_double2(row == 0 ? dn.x : o.x, row == 0 ? dn.y : o.y);
+        double2 up, dn;
+        if constexpr (RING) {
+            const double2 o = cell(fv.y), in = O[row == 0 ? 1 : row - 1][lane + 1];
+            up = make_double2(row == 0 ? o.x : in.x, row == 0 ? o.y : in.y);
+            dn = make_double2(row == 0 ? in.x : o.x, row == 0 ? in.y : o.y);
+        } else {
+            up = O[row - 1][lane + 1];
+            dn = O[row + 1][lane + 1];
         }
-        const double ur = update(C1[S], Q[S], C0[S], dn, up, C1[T], O[row][S ? lane + 2 : lane], fr);
+        const double ur = row_update<N1>(C1[S], Q[S], C0[S], dn, up, C1[T], O[row][S ? lane + 2 : lane],
+                                         RING || !S ? fv.x : fv.y, kc);
         // black cell of plane p - 1
-        if constexpr (!EDGE) {
+        if constexpr (!RING) {
             if (stored && p - 1 >= i0) {
-                const double ub = update(A1[T], C0[T], R2, R[row + 1][lane + 1], R[row - 1][lane + 1], A1[S],
-                                         R[row][T ? lane + 2 : lane], fb0);
-                PlaneBuf(A.out + (size_t)(p - 1) * plane, 8u << (2 * lg))
+                const double ub = row_update<N1>(A1[T], C0[T], R2, R[row + 1][lane + 1], R[row - 1][lane + 1], A1[S],
+                                                 R[row][T ? lane + 2 : lane], fb0, kc);
+                PlaneBuf(A.out + (size_t)(p - 1) * plane, pbytes)
                     .st2(off, S ? make_double2(ub, A1[1].x) : make_double2(A1[0].x, ub));
             }
-        } else {
-            __builtin_amdgcn_sched_barrier(0);  // one update's operands at a time
-            const double2 hn = cell(ex.hu);
-            if (lane < kRowF && hred)
-                h1 = cell(update(h1, hn, h0, O[hdn][hslot], O[hup][hslot], O[hq][low ? 1 : 64], cell(ex.ho), ex.hf));
-            load_ext(p + 1, T);
-            hm = h0;
-            h0 = h1;
-            h1 = hn;
         }
         R2 = A1[S];
         A1[0] = C0[0];
@@ -305,7 +270,7 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
         C1[0] = Q[0];
         C1[1] = Q[1];
         fb0 = fb1;
-        fb1 = fbn;
+        fb1 = S ? fv.x : fv.y;
         buf ^= 1;
     };
     for (int p = i0 - 2; p <= i1; p += 2) {
@@ -314,10 +279,60 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
     }
 }
 
+// The red cells k0 - 1 (lanes 0..14, row = lane) and k0 + 128 (lanes 16..30) of
+// the workgroup's rows, on the same steps: a cell is black and red in turn along
+// i; black, its old value is published beside its row's black cells, red, it is
+// updated and its new value published with the row's red ones.
+template <bool N1>
+__device__ __forceinline__ void sweep_ends(const RowArgs &A, int i0, int j0, int k0, int lane, RowLds &sO, RowLds &sN)
+{
+    const int lg = A.lg, m = (1 << lg) - 1;
+    const int i1 = min(i0 + A.chunk, m + 1);
+    const size_t plane = (size_t)1 << (2 * lg);
+    const uint32_t pbytes = 8u << (2 * lg);
+    const bool low = (lane & 16) == 0, live = (lane & 15) < kRowF && lane < 32;
+    const int q = min(lane & 15, kRowF - 1), slot = low ? 0 : kRowS - 1, in = low ? 1 : kRowS - 2;
+    const int j = (j0 - 1 + q) & m, k = (low ? k0 - 1 : k0 + kRowW) & m, k2 = (low ? k0 - 2 : k0 + kRowW + 1) & m;
+    const uint32_t off = 8u * (((uint32_t)j << lg) + (uint32_t)k), off2 = 8u * (((uint32_t)j << lg) + (uint32_t)k2);
+    const int jup = q > 0 ? q - 1 : 0, jdn = q < kRowF - 1 ? q + 1 : q;
+    auto pu = [&](int pl) { return PlaneBuf(A.u + (size_t)(pl & m) * plane, pbytes); };
+    auto pf = [&](int pl) { return PlaneBuf(A.f + (size_t)(pl & m) * plane, pbytes); };
+    const OpConst &kc = A.kc;
+    auto cell = [&](double u) { return make_double2(u, exp64(u, kc.tab)); };
+    struct Raw {  // step p: u of plane p + 2; f and the outer neighbour of plane p + 1
+        double u, f, u2;
+    };
+    auto load = [&](int p) { return Raw{pu(p + 2).ld(off), pf(p + 1).ld(off), pu(p + 1).ld(off2)}; };
+    // the cell on planes p - 1, p, p + 1
+    double2 h0 = cell(pu(i0 - 2).ld(off)), h1 = cell(pu(i0 - 1).ld(off)), hm = h0;
+    Raw ra = load(i0 - 2), rb = load(i0 - 1);
+    int buf = 0;
+    auto step = [&](int p, Raw &raw) {
+        const bool red = ((p + 1 + j + k) & 1) == 0;  // on planes p + 1 and p - 1
+        double2(*O)[kRowS] = sO[buf], (*R)[kRowS] = sN[buf];
+        const double2 hv = make_double2(red ? hm.x : h1.x, red ? hm.y : h1.y);
+        if (live) (red ? R : O)[q][slot] = hv;
+        __syncthreads();
+        const double2 hn = cell(raw.u);
+        const Raw cur = raw;
+        raw = load(p + 2);
+        if (live && red)
+            h1 = cell(row_update<N1>(h1, hn, h0, O[jdn][slot], O[jup][slot], O[q][in], cell(cur.u2), cur.f, kc));
+        hm = h0;
+        h0 = h1;
+        h1 = hn;
+        buf ^= 1;
+    };
+    for (int p = i0 - 2; p <= i1; p += 2) {
+        step(p, ra);
+        if (p < i1) step(p + 1, rb);
+    }
+}
+
 // grid: nkt njt ceil(N / chunk) workgroups; those of one XCD (blocks b, b + 8,
 // ...) take consecutive tiles in j, which share their outer rows in its L2
 template <bool N1>
-__global__ __launch_bounds__(64 * kRowF) void k_sweep_rows(RowArgs A)
+__global__ __launch_bounds__(64 * (kRowF + 1)) void k_sweep_rows(RowArgs A)
 {
     __shared__ RowLds sO, sN;
     MGFR_EXP_TABLE_TO_LDS(A.kc);
@@ -328,8 +343,9 @@ __global__ __launch_bounds__(64 * kRowF) void k_sweep_rows(RowArgs A)
     const int row = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     const int s0 = (i0 - 1 + j0 - 1 + row) & 1;  // red column of the row on plane i0 - 1
-    if (row == 0 || row == kRowF - 1) {
-        __builtin_amdgcn_s_setprio(2);  // these waves do two updates one after the other: 806 -> 755 us
+    if (row == kRowF)
+        sweep_ends<N1>(A, i0, j0, k0, lane, sO, sN);
+    else if (row == 0 || row == kRowF - 1) {
         if (s0)
             sweep_rows<N1, 1, true>(A, i0, j0, k0, row, lane, sO, sN);
         else
@@ -815,9 +831,9 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
             const RowArgs A{L.u, f, L.alt, L.lg, chunk, nkt, njt, kc};
             const unsigned nb = nkt * njt * (unsigned)((L.N + chunk - 1) / chunk);
             if (c->p.n == 1)
-                k_sweep_rows<true><<<nb, 64 * kRowF, 0, c->stream>>>(A);
+                k_sweep_rows<true><<<nb, 64 * (kRowF + 1), 0, c->stream>>>(A);
             else
-                k_sweep_rows<false><<<nb, 64 * kRowF, 0, c->stream>>>(A);
+                k_sweep_rows<false><<<nb, 64 * (kRowF + 1), 0, c->stream>>>(A);
             std::swap(L.u, L.alt);
         } else {
             for (int colour = 0; colour < 2; ++colour)

@@ -32,6 +32,7 @@
 #include <random>
 #include <vector>
 
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -182,10 +183,144 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
         }
 }
 
+// The same convolution for 16 output channels and input channels in chunks of
+// 16 (the network's finest level, and its backward-data passes): S >= 16.
+//
+// A workgroup walks over tiles of 16 x 8 x TZ voxels (TZ = MT / 2) and keeps the
+// weight fragments of a chunk in registers (14 k-steps of two taps each; with one
+// chunk they are loaded once).  The next tile's (chunk's) halo block is loaded
+// into registers while the current one is multiplied.  Operands are swapped
+// against k_conv3d, so that a lane ends with four consecutive channels of one
+// voxel and stores them at once; the products and their order are the same, and
+// so are the results.  LDS holds the two 8-channel halves of the block apart, 16
+// bytes per voxel, so that the 16 lanes of a fragment read take 256 contiguous
+// bytes.  The address of every fragment is one of three per-lane bases (the
+// distance of a k-step's two taps takes three values) plus a constant.
+// Bound: LDS reads, 8 cycles per CU and MFMA against 4 of the matrix cores.
+// 16 -> 16 channels on 2.1 M voxels: 110 -> 49 us; 48 -> 16: 340 -> 148 us (weights
+// read from L1 in every k-step, two-way bank conflicts, no loads in flight
+// during the products, two-byte stores).
+template <int MT>
+__global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X, int lgS, int Cin,
+                                                   const __bf16 *__restrict__ W, const float *__restrict__ bias,
+                                                   int relu, unsigned ntiles, __bf16 *__restrict__ Y,
+                                                   float *__restrict__ Y32)
+{
+    constexpr int TZ = MT / 2, HX = 18, HY = 10, HV = HX * HY * (TZ + 2), NK = 14;
+    constexpr int NP = (HV * 2 + 255) / 256;  // 16-byte pieces of a halo block per thread
+    __shared__ __attribute__((aligned(16))) __bf16 sX[2 * HV * 8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, r16 = lane & 15;
+    const int S = 1 << lgS, sm = S - 1;
+    const unsigned ntx = (unsigned)S / 16, nty = (unsigned)S / 8, ntz = (unsigned)S / TZ;
+    const int wz = (w * MT) >> 3, wy = (w * MT) & 7;  // first row of this wave
+    const int c8 = 8 * (g & 1);
+    // fragment of k-step k: voxel offset of tap 2 k, for lanes of g >= 2 that of tap 2 k + 1
+    const __bf16 *p0 = sX + (g & 1) * HV * 8 + ((wz * HY + wy) * HX + r16) * 8;
+    const __bf16 *pb[3] = {p0 + (g >= 2 ? 8 : 0), p0 + (g >= 2 ? 8 * (HX - 2) : 0),
+                           p0 + (g >= 2 ? 8 * (HX * HY - 2 * HX - 2) : 0)};
+    const bool pad = g >= 2;  // the second tap of the last k-step does not exist: zeros
+    float bo[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bo[j] = bias ? bias[4 * g + j] : 0.f;
+    auto origin = [&](unsigned tile, int &x0, int &y0, int &z0, size_t &vol) {
+        x0 = (int)(tile % ntx) * 16;
+        tile /= ntx;
+        y0 = (int)(tile % nty) * 8;
+        tile /= nty;
+        z0 = (int)(tile % ntz) * TZ;
+        vol = (size_t)(tile / ntz) << (3 * lgS);
+    };
+    bf16x8 st[NP];
+    auto fetch = [&](unsigned tile, int cc0) {
+        int x0, y0, z0;
+        size_t vol;
+        origin(tile, x0, y0, z0, vol);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int idx = min(tid + 256 * i, HV * 2 - 1), v = idx >> 1;
+            const int x = v % HX, y = (v / HX) % HY, z = v / (HX * HY);
+            const size_t src = vol + ((((size_t)((z0 + z - 1) & sm) << lgS) + (size_t)((y0 + y - 1) & sm)) << lgS) +
+                               (size_t)((x0 + x - 1) & sm);
+            st[i] = *(const bf16x8 *)(X + src * Cin + cc0 + 8 * (idx & 1));
+        }
+    };
+    bf16x8 b[NK];
+    auto weights = [&](int cc0) {
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            const int t = 2 * k + (g >> 1);
+            b[k] = t < 27 ? *(const bf16x8 *)(W + ((size_t)t * 16 + r16) * Cin + cc0 + c8) : bf16x8{};
+        }
+    };
+    weights(0);
+    if (blockIdx.x < ntiles) fetch(blockIdx.x, 0);
+    for (unsigned tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        f32x4 acc[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int cc0 = 0; cc0 < Cin; cc0 += 16) {
+            __syncthreads();  // the previous block's readers are done
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int idx = tid + 256 * i;
+                if (idx < HV * 2) *(bf16x8 *)(sX + (idx & 1) * HV * 8 + (idx >> 1) * 8) = st[i];
+            }
+            if (Cin > 16) weights(cc0);
+            __syncthreads();
+            if (cc0 + 16 < Cin)
+                fetch(tile, cc0 + 16);
+            else if (tile + gridDim.x < ntiles)
+                fetch(tile + gridDim.x, 0);
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                const int t = 2 * k;  // compile-time: the loop is unrolled
+                const __bf16 *q = (t == 26 ? p0 : pb[t % 3 != 2 ? 0 : t % 9 != 8 ? 1 : 2]) +
+                                  (((t / 9) * HY + (t / 3) % 3) * HX + t % 3) * 8;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    bf16x8 a = *(const bf16x8 *)(q + mt * HX * 8);
+                    if (k == NK - 1) a = pad ? bf16x8{} : a;
+                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], a, acc[mt], 0, 0, 0);
+                }
+            }
+        }
+        int x0, y0, z0;
+        size_t vol;
+        origin(tile, x0, y0, z0, vol);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const size_t v = vol + ((((size_t)(z0 + wz) << lgS) + (size_t)(y0 + wy + mt)) << lgS) + (size_t)(x0 + r16);
+            float o[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                o[j] = acc[mt][j] + bo[j];
+                if (relu) o[j] = fmaxf(o[j], 0.f);
+            }
+            if (Y) *(bf16x4 *)(Y + v * 16 + 4 * g) = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
+            if (Y32) *(f32x4 *)(Y32 + v * 16 + 4 * g) = f32x4{o[0], o[1], o[2], o[3]};
+        }
+    }
+}
+
 // Launch k_conv3d over nvox = B S^3 voxels (S >= 8, Cout a multiple of 16 up to 96).
 void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 *W, const float *bias, int Cout,
                    int relu, __bf16 *Y, float *Y32, hipStream_t s)
 {
+    if (Cout == 16 && Cin % 32 == 16 && lgS >= 4) {
+        // persistent.  Tiles of 512 voxels (2.1 voxels loaded per voxel), two workgroups per CU
+        // (its registers; 768 groups on 512 places: 59 instead of 49 us); of 256 (2.8)
+        // where there are too few to give every CU one
+        if (nvox / 512 >= 256) {
+            const unsigned nt = (unsigned)(nvox / 512);
+            k_conv16<8><<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu, nt, Y, Y32);
+        } else {
+            const unsigned nt = (unsigned)(nvox / 256);
+            k_conv16<4><<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu, nt, Y, Y32);
+        }
+        return;
+    }
     const unsigned blocks = (unsigned)(nvox / (16 * kConvMT * kConvWaves));
     // LDS: the halo tile ((TX+2) x 10 x (TZ+2) voxels) times the channel chunk (bf16)
     const int TX = lgS < 4 ? (1 << lgS) : 16, TZ = (16 * kConvMT * kConvWaves) / (TX * 8);

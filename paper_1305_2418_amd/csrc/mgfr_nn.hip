@@ -79,6 +79,7 @@ template <int NT>
 __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__restrict__ X, int lgS, int Cin,
                                                              const __bf16 *__restrict__ W,
                                                              const float *__restrict__ bias, int Cout, int relu,
+                                                             const __bf16 *__restrict__ M,
                                                              __bf16 *__restrict__ Y, float *__restrict__ Y32)
 {
     extern __shared__ __attribute__((aligned(16))) __bf16 sX[];  // [halo voxels][CC], sized at launch
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
                                       (size_t)(x0 + lx);
                     float val = acc[mt][nt][j] + bo;
                     if (relu) val = fmaxf(val, 0.f);
+                    if (M && !(bf2f(M[v * Cout + o]) > 0.f)) val = 0.f;
                     if (Y) Y[v * Cout + o] = f2bf(val);
                     if (Y32) Y32[v * Cout + o] = val;
                 }
@@ -200,11 +202,11 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
 // 16 -> 16 channels on 2.1 M voxels: 110 -> 49 us; 48 -> 16: 340 -> 148 us (weights
 // read from L1 in every k-step, two-way bank conflicts, no loads in flight
 // during the products, two-byte stores).
-template <int MT>
+template <int MT, bool MASK>
 __global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X, int lgS, int Cin,
                                                    const __bf16 *__restrict__ W, const float *__restrict__ bias,
-                                                   int relu, unsigned ntiles, __bf16 *__restrict__ Y,
-                                                   float *__restrict__ Y32)
+                                                   int relu, const __bf16 *__restrict__ M, unsigned ntiles,
+                                                   __bf16 *__restrict__ Y, float *__restrict__ Y32)
 {
     constexpr int TZ = MT / 2, HX = 18, HY = 10, HV = HX * HY * (TZ + 2), NK = 14;
     constexpr int NP = (HV * 2 + 255) / 256;  // 16-byte pieces of a halo block per thread
@@ -293,10 +295,13 @@ __global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X,
         for (int mt = 0; mt < MT; ++mt) {
             const size_t v = vol + ((((size_t)(z0 + wz) << lgS) + (size_t)(y0 + wy + mt)) << lgS) + (size_t)(x0 + r16);
             float o[4];
+            bf16x4 m = {};
+            if (MASK) m = *(const bf16x4 *)(M + v * 16 + 4 * g);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 o[j] = acc[mt][j] + bo[j];
                 if (relu) o[j] = fmaxf(o[j], 0.f);
+                if (MASK && !(bf2f(m[j]) > 0.f)) o[j] = 0.f;
             }
             if (Y) *(bf16x4 *)(Y + v * 16 + 4 * g) = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
             if (Y32) *(f32x4 *)(Y32 + v * 16 + 4 * g) = f32x4{o[0], o[1], o[2], o[3]};
@@ -305,8 +310,9 @@ __global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X,
 }
 
 // Launch k_conv3d over nvox = B S^3 voxels (S >= 8, Cout a multiple of 16 up to 96).
+// With a mask M (Cout channels, for a gradient through a ReLU) Y is zero where M > 0 does not hold.
 void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 *W, const float *bias, int Cout,
-                   int relu, __bf16 *Y, float *Y32, hipStream_t s)
+                   int relu, const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
 {
     if (Cout == 16 && Cin % 32 == 16 && lgS >= 4) {
         // persistent.  Tiles of 512 voxels (2.1 voxels loaded per voxel), two workgroups per CU
@@ -314,10 +320,12 @@ void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 
         // where there are too few to give every CU one
         if (nvox / 512 >= 256) {
             const unsigned nt = (unsigned)(nvox / 512);
-            k_conv16<8><<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu, nt, Y, Y32);
+            (M ? k_conv16<8, true> : k_conv16<8, false>)<<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu,
+                                                                                            M, nt, Y, Y32);
         } else {
             const unsigned nt = (unsigned)(nvox / 256);
-            k_conv16<4><<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu, nt, Y, Y32);
+            (M ? k_conv16<4, true> : k_conv16<4, false>)<<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu,
+                                                                                            M, nt, Y, Y32);
         }
         return;
     }
@@ -334,12 +342,12 @@ void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 
     }
     const dim3 grid(blocks, groups);
     switch (nt) {
-    case 1: k_conv3d<1><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, Y, Y32); break;
-    case 2: k_conv3d<2><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, Y, Y32); break;
-    case 3: k_conv3d<3><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, Y, Y32); break;
-    case 4: k_conv3d<4><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, Y, Y32); break;
-    case 5: k_conv3d<5><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, Y, Y32); break;
-    default: k_conv3d<6><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, Y, Y32); break;
+    case 1: k_conv3d<1><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 2: k_conv3d<2><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 3: k_conv3d<3><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 4: k_conv3d<4><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 5: k_conv3d<5><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    default: k_conv3d<6><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
     }
 }
 
@@ -512,22 +520,29 @@ __global__ void k_features(const double *__restrict__ delta, size_t nvox, int lg
     }
 }
 
-// 2^3 mean: out has side S/2 (lgS of the output)
-__global__ void k_pool(const __bf16 *__restrict__ in, int lgSo, int C, size_t nout, __bf16 *__restrict__ out)
+// 2^3 mean: out has side S/2 (lgS of the output); 8 channels (16 bytes) per thread
+__global__ __launch_bounds__(256) void k_pool(const __bf16 *__restrict__ in, int lgSo, int C, size_t nout,
+                                              __bf16 *__restrict__ out)
 {
-    const int So = 1 << lgSo, sm = So - 1, lgSi = lgSo + 1;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nout * C; i += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i % C);
-        const size_t v = i / C;
+    const int So = 1 << lgSo, sm = So - 1, lgSi = lgSo + 1, C8 = C >> 3;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nout * C8; i += (size_t)gridDim.x * 256) {
+        const int c = 8 * (int)(i % C8);
+        const size_t v = i / C8;
         const int x = (int)(v & sm), y = (int)((v >> lgSo) & sm), z = (int)((v >> (2 * lgSo)) & sm);
         const size_t b = v >> (3 * lgSo);
-        float s = 0.f;
+        float s[8] = {};
+#pragma unroll
         for (int a = 0; a < 8; ++a) {
             const size_t src = (((b << lgSi) + (2 * z + (a >> 2))) << (2 * lgSi)) + ((size_t)(2 * y + ((a >> 1) & 1)) << lgSi) +
                                (2 * x + (a & 1));
-            s += bf2f(in[src * C + c]);
+            const bf16x8 d = *(const bf16x8 *)(in + src * C + c);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[j] += bf2f(d[j]);
         }
-        out[i] = f2bf(0.125f * s);
+        bf16x8 o;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = f2bf(0.125f * s[j]);
+        *(bf16x8 *)(out + v * C + c) = o;
     }
 }
 
@@ -554,49 +569,57 @@ __global__ void k_concat_up(const __bf16 *__restrict__ in, int Cu, const __bf16 
     }
 }
 
-// d_in[parent][c] = sum_children d_out[child][off + c]
-__global__ void k_upsample_bwd(const __bf16 *__restrict__ dout, int lgSi, int C, size_t nin, int Ctot, int off,
-                               __bf16 *__restrict__ din)
+// The gradients below are taken through the ReLU that made y on the way out:
+// zero where y > 0 does not hold.  Threads take 8 channels (16 bytes) each.
+__device__ __forceinline__ bf16x8 through_relu(const float *d, const __bf16 *y)
 {
-    const int Si = 1 << lgSi, sm = Si - 1, lgSo = lgSi + 1;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nin * C; i += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i % C);
-        const size_t v = i / C;
-        const int x = (int)(v & sm), y = (int)((v >> lgSi) & sm), z = (int)((v >> (2 * lgSi)) & sm);
+    const bf16x8 m = *(const bf16x8 *)y;
+    bf16x8 o;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] = bf2f(m[j]) > 0.f ? f2bf(d[j]) : f2bf(0.f);
+    return o;
+}
+
+// d_in[parent][c] = (y[parent][c] > 0) sum_children d_out[child][c], c < C of Ctot
+__global__ __launch_bounds__(256) void k_upsample_bwd(const __bf16 *__restrict__ dout, int lgSi, int C, size_t nin, int Ctot,
+                                                      const __bf16 *__restrict__ y, __bf16 *__restrict__ din)
+{
+    const int Si = 1 << lgSi, sm = Si - 1, lgSo = lgSi + 1, C8 = C >> 3;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nin * C8; i += (size_t)gridDim.x * 256) {
+        const int c = 8 * (int)(i % C8);
+        const size_t v = i / C8;
+        const int x = (int)(v & sm), yy = (int)((v >> lgSi) & sm), z = (int)((v >> (2 * lgSi)) & sm);
         const size_t b = v >> (3 * lgSi);
-        float s = 0.f;
+        float s[8] = {};
+#pragma unroll
         for (int a = 0; a < 8; ++a) {
-            const size_t src = (((b << lgSo) + (2 * z + (a >> 2))) << (2 * lgSo)) + ((size_t)(2 * y + ((a >> 1) & 1)) << lgSo) +
-                               (2 * x + (a & 1));
-            s += bf2f(dout[src * Ctot + off + c]);
+            const size_t src = (((b << lgSo) + (2 * z + (a >> 2))) << (2 * lgSo)) +
+                               ((size_t)(2 * yy + ((a >> 1) & 1)) << lgSo) + (2 * x + (a & 1));
+            const bf16x8 d = *(const bf16x8 *)(dout + src * Ctot + c);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[j] += bf2f(d[j]);
         }
-        din[i] = f2bf(s);
+        *(bf16x8 *)(din + v * C + c) = through_relu(s, y + v * C + c);
     }
 }
 
-// skip-connection gradient: d_skip[v][c] = d_cat[v][off + c] + d_pool[parent(v)][c] / 8
-__global__ void k_skip_grad(const __bf16 *__restrict__ dcat, int Ctot, int off, const __bf16 *__restrict__ dpool,
-                            int lgS, int C, size_t nvox, __bf16 *__restrict__ dskip)
+// skip-connection gradient: d_skip[v][c] = (y[v][c] > 0) (d_cat[v][off + c] + d_pool[parent(v)][c] / 8)
+__global__ __launch_bounds__(256) void k_skip_grad(const __bf16 *__restrict__ dcat, int Ctot, int off,
+                                                   const __bf16 *__restrict__ dpool, int lgS, int C, size_t nvox,
+                                                   const __bf16 *__restrict__ y, __bf16 *__restrict__ dskip)
 {
-    const int S = 1 << lgS, sm = S - 1, lgP = lgS - 1;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvox * C; i += (size_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i % C);
-        const size_t v = i / C;
-        const int x = (int)(v & sm), y = (int)((v >> lgS) & sm), z = (int)((v >> (2 * lgS)) & sm);
+    const int S = 1 << lgS, sm = S - 1, lgP = lgS - 1, C8 = C >> 3;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvox * C8; i += (size_t)gridDim.x * 256) {
+        const int c = 8 * (int)(i % C8);
+        const size_t v = i / C8;
+        const int x = (int)(v & sm), yy = (int)((v >> lgS) & sm), z = (int)((v >> (2 * lgS)) & sm);
         const size_t b = v >> (3 * lgS);
-        const size_t par = (((b << lgP) + (z >> 1)) << (2 * lgP)) + ((size_t)(y >> 1) << lgP) + (x >> 1);
-        dskip[i] = f2bf(bf2f(dcat[v * Ctot + off + c]) + 0.125f * bf2f(dpool[par * C + c]));
-    }
-}
-
-// dz = dy * (y > 0), reading dy from channels [off, off + C) of a Ctot-channel tensor
-__global__ void k_relu_bwd(const __bf16 *__restrict__ dy, int Ctot, int off, const __bf16 *__restrict__ y, size_t nvox,
-                           int C, __bf16 *__restrict__ dz)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvox * C; i += (size_t)gridDim.x * blockDim.x) {
-        const size_t v = i / C;
-        const int c = (int)(i % C);
-        dz[i] = bf2f(y[i]) > 0.f ? dy[v * Ctot + off + c] : f2bf(0.f);
+        const size_t par = (((b << lgP) + (z >> 1)) << (2 * lgP)) + ((size_t)(yy >> 1) << lgP) + (x >> 1);
+        const bf16x8 dc = *(const bf16x8 *)(dcat + v * Ctot + off + c), dp = *(const bf16x8 *)(dpool + par * C + c);
+        float s[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] = bf2f(dc[j]) + 0.125f * bf2f(dp[j]);
+        *(bf16x8 *)(dskip + v * C + c) = through_relu(s, y + v * C + c);
     }
 }
 
@@ -612,7 +635,7 @@ __global__ void k_head(const __bf16 *__restrict__ h, size_t nvox, const float *_
 }
 
 // Loss and the head's backward pass in one: with d = 2 (y - u / kUScale) / n,
-// loss[0] += sum (y - u / kUScale)^2 / n, dh[v][c] = d wh[c],
+// loss[0] += sum (y - u / kUScale)^2 / n, dh[v][c] = (h[v][c] > 0) d wh[c],
 // dwh[c] += sum_v d h[v][c], dwh[16] += sum_v d.  The sums are formed per
 // workgroup first: atomics on these 18 addresses cost 12 ns each one after
 // the other (one per wave and sum: 1.78 ms on 2.1 M voxels; 256 workgroups,
@@ -640,7 +663,7 @@ __global__ __launch_bounds__(256) void k_loss_head_bwd(const __bf16 *__restrict_
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 s[8 * q + c] += d * bf2f(a[c]);
-                b[c] = f2bf(d * w[8 * q + c]);
+                b[c] = bf2f(a[c]) > 0.f ? f2bf(d * w[8 * q + c]) : f2bf(0.f);
             }
             *(bf16x8 *)(dh + v * 16 + 8 * q) = b;
         }
@@ -815,7 +838,7 @@ int net_alloc(mgfr_net *n)
         (rc = A(&n->p2, V3 * 32)) || (rc = A(&n->h3a, V3 * 64)) || (rc = A(&n->h3, V3 * 64)) ||
         (rc = A(&n->cat4, V2 * 96)) || (rc = A(&n->h4a, V2 * 32)) || (rc = A(&n->h4, V2 * 32)) ||
         (rc = A(&n->cat5, V * 48)) || (rc = A(&n->h5a, V * 16)) || (rc = A(&n->h5, V * 16)) ||
-        (rc = A(&n->gA, V * 48)) || (rc = A(&n->gB, V * 48)) || (rc = A(&n->gC, V * 16)) || (rc = A(&n->gD, V * 16)))
+        (rc = A(&n->gA, V * 48)) || (rc = A(&n->gB, V2 * 96)) || (rc = A(&n->gC, V * 16)) || (rc = A(&n->gD, V * 16)))
         return rc;
     MGFR_HIP(hipMalloc(&n->y32, V * sizeof(float)));
     MGFR_HIP(hipMalloc(&n->cond, 2 * 4096 * sizeof(float)));
@@ -851,22 +874,24 @@ int net_refresh(mgfr_net *n)
 int conv(mgfr_net *n, const __bf16 *x, size_t nvox, int lgS, int layer, bool relu, __bf16 *y)
 {
     const ConvSpec &L = n->L[layer];
-    launch_conv3d(x, nvox, lgS, L.cin, n->wbf + L.woff, n->p + L.boff, L.cout, relu ? 1 : 0, y, nullptr, n->stream);
+    launch_conv3d(x, nvox, lgS, L.cin, n->wbf + L.woff, n->p + L.boff, L.cout, relu ? 1 : 0, nullptr, y, nullptr,
+                  n->stream);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
 
-// Backward through one conv+ReLU layer: dy (channels [off, off+Cout) of a Ctot tensor),
-// its output y and input x; accumulates weight/bias gradients, writes dx if non-null.
-int conv_bwd(mgfr_net *n, const __bf16 *dy, int Ctot, int off, const __bf16 *y, const __bf16 *x, size_t nvox, int lgS,
-             int layer, __bf16 *dz_scratch, __bf16 *dx)
+// Backward through one convolution: from dz, the gradient before the layer's
+// ReLU, and its input x, accumulates weight and bias gradients and writes the
+// input's gradient dx if non-null, with relu_in through the ReLU that made x.
+// (Every gradient passes its ReLU where it is written: a pass of its own over dy,
+// y and dz was 44 us of the 110 us that a layer of 16 channels took on 2.1 M voxels.)
+int conv_bwd(mgfr_net *n, const __bf16 *dz, const __bf16 *x, size_t nvox, int lgS, int layer, __bf16 *dx, bool relu_in)
 {
     const ConvSpec &L = n->L[layer];
-    k_relu_bwd<<<gridn(nvox * L.cout), 256, 0, n->stream>>>(dy, Ctot, off, y, nvox, L.cout, dz_scratch);
-    launch_wgrad(x, dz_scratch, nvox, lgS, L.cin, L.cout, n->g + L.woff, n->g + L.boff, n->stream);
-    if (dx) {
-        launch_conv3d(dz_scratch, nvox, lgS, L.cout, n->wt + L.woff, nullptr, L.cin, 0, dx, nullptr, n->stream);
-    }
+    launch_wgrad(x, dz, nvox, lgS, L.cin, L.cout, n->g + L.woff, n->g + L.boff, n->stream);
+    if (dx)
+        launch_conv3d(dz, nvox, lgS, L.cout, n->wt + L.woff, nullptr, L.cin, 0, relu_in ? x : nullptr, dx, nullptr,
+                      n->stream);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
@@ -880,10 +905,10 @@ int net_forward(mgfr_net *n, const double *delta, int B, int lgS)
     MGFR_HIP(hipMemcpyAsync(n->cond, n->hcond, 2 * B * sizeof(float), hipMemcpyHostToDevice, n->stream));
     k_features<<<gridn(V), 256, 0, n->stream>>>(delta, V, lgS, n->cond, n->x0);
     if ((rc = conv(n, n->x0, V, lgS, 0, true, n->h1a)) || (rc = conv(n, n->h1a, V, lgS, 1, true, n->s1))) return rc;
-    k_pool<<<gridn(V2 * 16), 256, 0, n->stream>>>(n->s1, lgS - 1, 16, V2, n->p1);
+    k_pool<<<gridn(V2 * 2), 256, 0, n->stream>>>(n->s1, lgS - 1, 16, V2, n->p1);
     if ((rc = conv(n, n->p1, V2, lgS - 1, 2, true, n->h2a)) || (rc = conv(n, n->h2a, V2, lgS - 1, 3, true, n->s2)))
         return rc;
-    k_pool<<<gridn(V3 * 32), 256, 0, n->stream>>>(n->s2, lgS - 2, 32, V3, n->p2);
+    k_pool<<<gridn(V3 * 4), 256, 0, n->stream>>>(n->s2, lgS - 2, 32, V3, n->p2);
     if ((rc = conv(n, n->p2, V3, lgS - 2, 4, true, n->h3a)) || (rc = conv(n, n->h3a, V3, lgS - 2, 5, true, n->h3)))
         return rc;
     k_concat_up<<<gridn(V2 * 12), 256, 0, n->stream>>>(n->h3, 64, n->s2, 32, lgS - 1, V2, n->cat4);
@@ -906,35 +931,29 @@ int net_backward(mgfr_net *n, const double *u_target, int B, int lgS)
     // loss and head
     k_loss_head_bwd<<<gridn(V, kHeadBlocks), 256, 0, n->stream>>>(n->h5, n->y32, u_target, V, n->p + n->head_off, n->gC,
                                                                   n->g + n->head_off, n->loss);
-    // level 1 decoder: c5b (dy = gC) -> d(h5a) in gD; c5a -> d(cat5) in gA [V][48]
-    if ((rc = conv_bwd(n, n->gC, 16, 0, n->h5, n->h5a, V, lgS, 9, n->gB, n->gD))) return rc;
-    if ((rc = conv_bwd(n, n->gD, 16, 0, n->h5a, n->cat5, V, lgS, 8, n->gB, n->gA))) return rc;
-    // d(h4) = sum over children of d(cat5)[:, 0:32]  -> gB [V2][32]
-    k_upsample_bwd<<<gridn(V2 * 32), 256, 0, n->stream>>>(n->gA, lgS - 1, 32, V2, 48, 0, n->gB);
-    // keep d(cat5)[:, 32:48] (the s1 part): copy into gD [V][16]
-    // (k_skip_grad below combines it with the pooled gradient later)
-    // level 2 decoder: c4b (dy = gB) -> d(h4a) in gC ; c4a -> d(cat4) in gB?  use separate buffers
-    // gC holds [V2][32]; d(cat4) [V2][96] goes to gD? gD is [V][16] >= V2*96 when V >= 48 V2 ... use gB region after
-    if ((rc = conv_bwd(n, n->gB, 32, 0, n->h4, n->h4a, V2, lgS - 1, 7, n->gC + 0, n->gD))) return rc;  // dz in gC, d(h4a) in gD
-    // c4a: dy = gD [V2][32]; dz scratch gC; d(cat4) -> gB [V2][96] (gB has V*48 >= V2*96 elements)
-    if ((rc = conv_bwd(n, n->gD, 32, 0, n->h4a, n->cat4, V2, lgS - 1, 6, n->gC, n->gB))) return rc;
-    // d(h3) = sum over children of d(cat4)[:, 0:64] -> gC [V3][64]
-    k_upsample_bwd<<<gridn(V3 * 64), 256, 0, n->stream>>>(n->gB, lgS - 2, 64, V3, 96, 0, n->gC);
-    // level 3: c3b (dy = gC) -> d(h3a) in gD ; c3a -> d(p2) in gC
-    __bf16 *dz3 = n->gD + V3 * 64;  // scratch after d(h3a)
-    if ((rc = conv_bwd(n, n->gC, 64, 0, n->h3, n->h3a, V3, lgS - 2, 5, dz3, n->gD))) return rc;
-    if ((rc = conv_bwd(n, n->gD, 64, 0, n->h3a, n->p2, V3, lgS - 2, 4, dz3, n->gC))) return rc;
-    // d(s2) = d(cat4)[:, 64:96] + d(p2)/8 -> gD [V2][32]
-    k_skip_grad<<<gridn(V2 * 32), 256, 0, n->stream>>>(n->gB, 96, 64, n->gC, lgS - 1, 32, V2, n->gD);
-    // level 2 encoder: c2b (dy = gD) -> d(h2a) in gC ; c2a -> d(p1) in gD
-    __bf16 *dz2 = n->gB;  // d(cat4) no longer needed
-    if ((rc = conv_bwd(n, n->gD, 32, 0, n->s2, n->h2a, V2, lgS - 1, 3, dz2, n->gC))) return rc;
-    if ((rc = conv_bwd(n, n->gC, 32, 0, n->h2a, n->p1, V2, lgS - 1, 2, dz2, n->gD))) return rc;
-    // d(s1) = d(cat5)[:, 32:48] + d(p1)/8 -> gC [V][16]
-    k_skip_grad<<<gridn(V * 16), 256, 0, n->stream>>>(n->gA, 48, 32, n->gD, lgS, 16, V, n->gC);
-    // level 1 encoder: c1b (dy = gC) -> d(h1a) in gD ; c1a (no input gradient)
-    if ((rc = conv_bwd(n, n->gC, 16, 0, n->s1, n->h1a, V, lgS, 1, n->gB, n->gD))) return rc;
-    if ((rc = conv_bwd(n, n->gD, 16, 0, n->h1a, n->x0, V, lgS, 0, n->gB, nullptr))) return rc;
+    // level 1 decoder: c5b (dz = gC) -> gD; c5a -> d(cat5) in gA [V][48]
+    if ((rc = conv_bwd(n, n->gC, n->h5a, V, lgS, 9, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, n->cat5, V, lgS, 8, n->gA, false))) return rc;
+    // h4: sum over children of d(cat5)[:, 0:32] -> gB [V2][32]
+    k_upsample_bwd<<<gridn(V2 * 4), 256, 0, n->stream>>>(n->gA, lgS - 1, 32, V2, 48, n->h4, n->gB);
+    // level 2 decoder: c4b (dz = gB) -> gD; c4a -> d(cat4) in gB [V2][96]
+    if ((rc = conv_bwd(n, n->gB, n->h4a, V2, lgS - 1, 7, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, n->cat4, V2, lgS - 1, 6, n->gB, false))) return rc;
+    // h3: sum over children of d(cat4)[:, 0:64] -> gC [V3][64]
+    k_upsample_bwd<<<gridn(V3 * 8), 256, 0, n->stream>>>(n->gB, lgS - 2, 64, V3, 96, n->h3, n->gC);
+    // level 3: c3b (dz = gC) -> gD; c3a -> d(p2) in gC
+    if ((rc = conv_bwd(n, n->gC, n->h3a, V3, lgS - 2, 5, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, n->p2, V3, lgS - 2, 4, n->gC, false))) return rc;
+    // s2: d(cat4)[:, 64:96] + d(p2)/8 -> gD [V2][32]
+    k_skip_grad<<<gridn(V2 * 4), 256, 0, n->stream>>>(n->gB, 96, 64, n->gC, lgS - 1, 32, V2, n->s2, n->gD);
+    // level 2 encoder: c2b (dz = gD) -> gC; c2a -> d(p1) in gD
+    if ((rc = conv_bwd(n, n->gD, n->h2a, V2, lgS - 1, 3, n->gC, true))) return rc;
+    if ((rc = conv_bwd(n, n->gC, n->p1, V2, lgS - 1, 2, n->gD, false))) return rc;
+    // s1: d(cat5)[:, 32:48] + d(p1)/8 -> gC [V][16]
+    k_skip_grad<<<gridn(V * 2), 256, 0, n->stream>>>(n->gA, 48, 32, n->gD, lgS, 16, V, n->s1, n->gC);
+    // level 1 encoder: c1b (dz = gC) -> gD; c1a (no input gradient)
+    if ((rc = conv_bwd(n, n->gC, n->h1a, V, lgS, 1, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, n->x0, V, lgS, 0, nullptr, false))) return rc;
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
@@ -1181,7 +1200,7 @@ extern "C" int mgfr_conv3d_fwd(const void *x, int B, int S, int Cin, const void 
     if ((rc = conv_args(B, S, Cin, Cout, &lgS))) return rc;
     if (!x || !w || (!y && !y32)) return set_error(MGFR_ERR_ARG, "x, w and an output must be non-NULL");
     const size_t V = (size_t)B << (3 * lgS);
-    launch_conv3d((const __bf16 *)x, V, lgS, Cin, (const __bf16 *)w, bias, Cout, relu, (__bf16 *)y, y32,
+    launch_conv3d((const __bf16 *)x, V, lgS, Cin, (const __bf16 *)w, bias, Cout, relu, nullptr, (__bf16 *)y, y32,
                   (hipStream_t)stream);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
@@ -1197,8 +1216,8 @@ extern "C" int mgfr_conv3d_bwd_data(const void *dz, int B, int S, int Cout, cons
     hipStream_t s = (hipStream_t)stream;
     k_wt_transpose<<<gridn((size_t)27 * Cin * Cout), 256, 0, s>>>((const __bf16 *)w, Cin, Cout, (__bf16 *)wt_work);
     const size_t V = (size_t)B << (3 * lgS);
-    launch_conv3d((const __bf16 *)dz, V, lgS, Cout, (const __bf16 *)wt_work, nullptr, Cin, 0, (__bf16 *)dx, nullptr,
-                  s);
+    launch_conv3d((const __bf16 *)dz, V, lgS, Cout, (const __bf16 *)wt_work, nullptr, Cin, 0, nullptr, (__bf16 *)dx,
+                  nullptr, s);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }

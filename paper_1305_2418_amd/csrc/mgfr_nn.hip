@@ -185,47 +185,54 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
         }
 }
 
-// The same convolution for 16 output channels and input channels in chunks of
-// 16 (the network's finest level, and its backward-data passes): S >= 16.
+// The same convolution for S >= 16 and input channels in chunks of CK = 16 or 32
+// (every layer of the network above the 8^3 mesh, and their backward-data passes).
 //
-// A workgroup walks over tiles of 16 x 8 x TZ voxels (TZ = MT / 2) and keeps the
-// weight fragments of a chunk in registers (14 k-steps of two taps each; with one
-// chunk they are loaded once).  The next tile's (chunk's) halo block is loaded
-// into registers while the current one is multiplied.  Operands are swapped
-// against k_conv3d, so that a lane ends with four consecutive channels of one
-// voxel and stores them at once; the products and their order are the same, and
-// so are the results.  LDS holds the two 8-channel halves of the block apart, 16
-// bytes per voxel, so that the 16 lanes of a fragment read take 256 contiguous
-// bytes.  The address of every fragment is one of three per-lane bases (the
-// distance of a k-step's two taps takes three values) plus a constant.
+// A workgroup computes 16 NT output channels (those of blockIdx.y) and walks over
+// tiles of 16 x 8 x TZ voxels; each of its waves keeps the weight fragments of
+// 16 channels and one chunk in registers (14 k-steps of two taps each, or 27 of
+// one; with one chunk they are loaded once) and takes MT = 2 TZ NT rows of 16
+// voxels.  The next tile's (chunk's) halo block is loaded into registers while the
+// current one is multiplied.  Operands are swapped against k_conv3d, so that a
+// lane ends with four consecutive channels of one voxel and stores them at once;
+// the products and their order are the same, and so are the results.  LDS holds
+// the CK / 8 parts of 8 channels of the block apart, 16 bytes per voxel, each part
+// starting a multiple of 256 bytes on: the lanes of a fragment read, and those of
+// a staging write, take 256 contiguous bytes.  The address of every fragment is a
+// per-lane base (for CK = 16 one of three: the distance of a k-step's two taps
+// takes three values) plus a constant.
 // Bound: LDS reads, 8 cycles per CU and MFMA against 4 of the matrix cores.
-// 16 -> 16 channels on 2.1 M voxels: 110 -> 49 us; 48 -> 16: 340 -> 148 us (weights
-// read from L1 in every k-step, two-way bank conflicts, no loads in flight
-// during the products, two-byte stores).
-template <int MT, bool MASK>
-__global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X, int lgS, int Cin,
-                                                   const __bf16 *__restrict__ W, const float *__restrict__ bias,
-                                                   int relu, const __bf16 *__restrict__ M, unsigned ntiles,
-                                                   __bf16 *__restrict__ Y, float *__restrict__ Y32)
+// us, before (weights from L1 in every k-step, two-way bank conflicts, no loads in
+// flight during the products, two-byte stores) and now, 2.1 M voxels: 16 -> 16
+// channels 110, 42; 48 -> 16 340, 145; 16 -> 48 176, 135; 262144 voxels: 16 -> 32
+// 25, 16; 32 -> 32 46, 23; 96 -> 32 120, 66; 32 -> 96 114, 57; 32 -> 16 41, 16;
+// 32768 voxels: 32 -> 64 22, 9.6; 64 -> 64 39, 22; 64 -> 32 34, 15.
+template <int CK, int NT, int TZ, bool MASK>
+__global__ __launch_bounds__(256, 2) void k_conv_reg(const __bf16 *__restrict__ X, int lgS, int Cin,
+                                                     const __bf16 *__restrict__ W, const float *__restrict__ bias,
+                                                     int Cout, int relu, const __bf16 *__restrict__ M, unsigned ntiles,
+                                                     __bf16 *__restrict__ Y, float *__restrict__ Y32)
 {
-    constexpr int TZ = MT / 2, HX = 18, HY = 10, HV = HX * HY * (TZ + 2), NK = 14;
-    constexpr int NP = (HV * 2 + 255) / 256;  // 16-byte pieces of a halo block per thread
-    __shared__ __attribute__((aligned(16))) __bf16 sX[2 * HV * 8];
+    constexpr int MT = 2 * TZ * NT, HX = 18, HY = 10, HV = HX * HY * (TZ + 2), Q = CK / 8, HP = (HV + 15) / 16 * 16;
+    constexpr int NK = CK == 16 ? 14 : 27;
+    constexpr int NP = (HP * Q + 255) / 256;  // 16-byte pieces of a halo block per thread
+    static_assert(MT == 4 || MT % 8 == 0, "a wave's rows are half a z-plane of the tile or whole ones");
+    __shared__ __attribute__((aligned(16))) __bf16 sX[Q * HP * 8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, r16 = lane & 15;
     const int S = 1 << lgS, sm = S - 1;
     const unsigned ntx = (unsigned)S / 16, nty = (unsigned)S / 8, ntz = (unsigned)S / TZ;
-    const int wz = (w * MT) >> 3, wy = (w * MT) & 7;  // first row of this wave
-    const int c8 = 8 * (g & 1);
-    // fragment of k-step k: voxel offset of tap 2 k, for lanes of g >= 2 that of tap 2 k + 1
-    const __bf16 *p0 = sX + (g & 1) * HV * 8 + ((wz * HY + wy) * HX + r16) * 8;
+    const int row0 = (w / NT) * MT, wz = row0 >> 3, wy = row0 & 7;  // first row of this wave
+    const int o0 = 16 * ((int)blockIdx.y * NT + w % NT);            // its output channels
+    const __bf16 *p0 = sX + ((g & (Q - 1)) * HP + (wz * HY + wy) * HX + r16) * 8;
+    // CK = 16, k-step k: voxel offset of tap 2 k, for lanes of g >= 2 that of tap 2 k + 1
     const __bf16 *pb[3] = {p0 + (g >= 2 ? 8 : 0), p0 + (g >= 2 ? 8 * (HX - 2) : 0),
                            p0 + (g >= 2 ? 8 * (HX * HY - 2 * HX - 2) : 0)};
-    const bool pad = g >= 2;  // the second tap of the last k-step does not exist: zeros
+    const bool pad = g >= 2;  // the second tap of its last k-step does not exist: zeros
     float bo[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bo[j] = bias ? bias[4 * g + j] : 0.f;
+    for (int j = 0; j < 4; ++j) bo[j] = bias ? bias[o0 + 4 * g + j] : 0.f;
     auto origin = [&](unsigned tile, int &x0, int &y0, int &z0, size_t &vol) {
         x0 = (int)(tile % ntx) * 16;
         tile /= ntx;
@@ -234,56 +241,65 @@ __global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X,
         z0 = (int)(tile % ntz) * TZ;
         vol = (size_t)(tile / ntz) << (3 * lgS);
     };
+    // staging: this thread's pieces are part pq of voxels pv + 256 / Q i
+    const int pq = (tid >> 4) & (Q - 1), pv = ((tid >> 4) / Q) * 16 + (tid & 15);
+    __bf16 *pst = sX + (pq * HP + pv) * 8;
     bf16x8 st[NP];
     auto fetch = [&](unsigned tile, int cc0) {
         int x0, y0, z0;
         size_t vol;
         origin(tile, x0, y0, z0, vol);
+        const __bf16 *x = X + cc0 + 8 * pq;
+        int v0 = pv;
+        asm volatile("" : "+v"(v0));  // coordinates are formed anew: kept for all pieces they spill
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const int idx = min(tid + 256 * i, HV * 2 - 1), v = idx >> 1;
-            const int x = v % HX, y = (v / HX) % HY, z = v / (HX * HY);
-            const size_t src = vol + ((((size_t)((z0 + z - 1) & sm) << lgS) + (size_t)((y0 + y - 1) & sm)) << lgS) +
-                               (size_t)((x0 + x - 1) & sm);
-            st[i] = *(const bf16x8 *)(X + src * Cin + cc0 + 8 * (idx & 1));
+            const int v = min(v0 + 256 / Q * i, HV - 1);
+            const int vx = v % HX, vy = (v / HX) % HY, vz = v / (HX * HY);
+            const size_t src = vol + ((((size_t)((z0 + vz - 1) & sm) << lgS) + (size_t)((y0 + vy - 1) & sm)) << lgS) +
+                               (size_t)((x0 + vx - 1) & sm);
+            st[i] = *(const bf16x8 *)(x + src * Cin);
         }
     };
     bf16x8 b[NK];
+    const unsigned woff = (unsigned)((o0 + r16) * Cin + 8 * (g & (Q - 1))), woff2 = woff + (g >= 2 ? (unsigned)(Cout * Cin) : 0);
     auto weights = [&](int cc0) {
+        const int tap = Cout * Cin;
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
-            const int t = 2 * k + (g >> 1);
-            b[k] = t < 27 ? *(const bf16x8 *)(W + ((size_t)t * 16 + r16) * Cin + cc0 + c8) : bf16x8{};
+            const bool last = CK == 16 && k == NK - 1;
+            const __bf16 *wk = W + (CK == 16 ? 2 * k : k) * tap + cc0;  // uniform
+            b[k] = *(const bf16x8 *)(wk + (CK == 32 || last ? woff : woff2));
+            if (last) b[k] = pad ? bf16x8{} : b[k];
         }
     };
-    weights(0);
+    if (Cin == CK) weights(0);
     if (blockIdx.x < ntiles) fetch(blockIdx.x, 0);
     for (unsigned tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         f32x4 acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int cc0 = 0; cc0 < Cin; cc0 += 16) {
+        for (int cc0 = 0; cc0 < Cin; cc0 += CK) {
+            if (Cin > CK) weights(cc0);
             __syncthreads();  // the previous block's readers are done
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                const int idx = tid + 256 * i;
-                if (idx < HV * 2) *(bf16x8 *)(sX + (idx & 1) * HV * 8 + (idx >> 1) * 8) = st[i];
+                if (pv + 256 / Q * i < HP) *(bf16x8 *)(pst + 256 / Q * i * 8) = st[i];
             }
-            if (Cin > 16) weights(cc0);
             __syncthreads();
-            if (cc0 + 16 < Cin)
-                fetch(tile, cc0 + 16);
-            else if (tile + gridDim.x < ntiles)
-                fetch(tile + gridDim.x, 0);
+            const bool more = cc0 + CK < Cin;
+            const unsigned next = more ? tile : tile + gridDim.x;
+            if (next < ntiles) fetch(next, more ? cc0 + CK : 0);
 #pragma unroll
             for (int k = 0; k < NK; ++k) {
-                const int t = 2 * k;  // compile-time: the loop is unrolled
-                const __bf16 *q = (t == 26 ? p0 : pb[t % 3 != 2 ? 0 : t % 9 != 8 ? 1 : 2]) +
+                if (CK == 32 && MT == 8) __builtin_amdgcn_sched_barrier(0);  // reads of later k-steps would spill
+                const int t = CK == 16 ? 2 * k : k;  // compile-time: the loop is unrolled
+                const __bf16 *q = (CK == 32 || t == 26 ? p0 : pb[t % 3 != 2 ? 0 : t % 9 != 8 ? 1 : 2]) +
                                   (((t / 9) * HY + (t / 3) % 3) * HX + t % 3) * 8;
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
-                    bf16x8 a = *(const bf16x8 *)(q + mt * HX * 8);
-                    if (k == NK - 1) a = pad ? bf16x8{} : a;
+                    bf16x8 a = *(const bf16x8 *)(q + ((mt >> 3) * HY + (mt & 7)) * HX * 8);
+                    if (CK == 16 && k == NK - 1) a = pad ? bf16x8{} : a;
                     acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], a, acc[mt], 0, 0, 0);
                 }
             }
@@ -293,18 +309,19 @@ __global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X,
         origin(tile, x0, y0, z0, vol);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const size_t v = vol + ((((size_t)(z0 + wz) << lgS) + (size_t)(y0 + wy + mt)) << lgS) + (size_t)(x0 + r16);
+            const size_t v = vol + ((((size_t)(z0 + wz + (mt >> 3)) << lgS) + (size_t)(y0 + wy + (mt & 7))) << lgS) +
+                             (size_t)(x0 + r16);
             float o[4];
             bf16x4 m = {};
-            if (MASK) m = *(const bf16x4 *)(M + v * 16 + 4 * g);
+            if (MASK) m = *(const bf16x4 *)(M + v * Cout + o0 + 4 * g);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 o[j] = acc[mt][j] + bo[j];
                 if (relu) o[j] = fmaxf(o[j], 0.f);
                 if (MASK && !(bf2f(m[j]) > 0.f)) o[j] = 0.f;
             }
-            if (Y) *(bf16x4 *)(Y + v * 16 + 4 * g) = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
-            if (Y32) *(f32x4 *)(Y32 + v * 16 + 4 * g) = f32x4{o[0], o[1], o[2], o[3]};
+            if (Y) *(bf16x4 *)(Y + v * Cout + o0 + 4 * g) = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
+            if (Y32) *(f32x4 *)(Y32 + v * Cout + o0 + 4 * g) = f32x4{o[0], o[1], o[2], o[3]};
         }
     }
 }
@@ -314,19 +331,39 @@ __global__ __launch_bounds__(256, 2) void k_conv16(const __bf16 *__restrict__ X,
 void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 *W, const float *bias, int Cout,
                    int relu, const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
 {
-    if (Cout == 16 && Cin % 32 == 16 && lgS >= 4) {
-        // persistent.  Tiles of 512 voxels (2.1 voxels loaded per voxel), two workgroups per CU
-        // (its registers; 768 groups on 512 places: 59 instead of 49 us); of 256 (2.8)
-        // where there are too few to give every CU one
-        if (nvox / 512 >= 256) {
-            const unsigned nt = (unsigned)(nvox / 512);
-            (M ? k_conv16<8, true> : k_conv16<8, false>)<<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu,
-                                                                                            M, nt, Y, Y32);
-        } else {
-            const unsigned nt = (unsigned)(nvox / 256);
-            (M ? k_conv16<4, true> : k_conv16<4, false>)<<<std::min(nt, 512u), 256, 0, s>>>(X, lgS, Cin, W, bias, relu,
-                                                                                            M, nt, Y, Y32);
-        }
+    if (Cin % 16 == 0 && lgS >= 4) {
+        // two blocks of 16 channels per workgroup where the number is even: its
+        // weights still fit in the registers and the input is read half as often
+        const int NT = Cout % 32 == 0 ? 2 : 1;
+        const unsigned groups = (unsigned)(Cout / (16 * NT));
+        // persistent, two workgroups per CU (their registers; 768 groups on 512
+        // places: 59 us instead of 49 for 16 -> 16 channels)
+        auto go = [&](auto *k, unsigned tz) {
+            const unsigned nt = (unsigned)(nvox / (128 * tz));
+            k<<<dim3(std::min(nt, std::max(512u / groups, 1u)), groups), 256, 0, s>>>(X, lgS, Cin, W, bias, Cout, relu,
+                                                                                      M, nt, Y, Y32);
+        };
+        auto pick = [&](auto *masked, auto *plain, unsigned tz) { M ? go(masked, tz) : go(plain, tz); };
+        // The deepest tile that the registers allow loads the fewest voxels of halo
+        // (4 planes: 2.1 per voxel, 2: 2.8, 1: 4.2); a shallower one where the
+        // tiles would leave CUs without a workgroup
+        const size_t b4 = nvox / 512 * groups, b2 = nvox / 256 * groups;
+        if (Cin % 32 == 0) {
+            if (NT == 1)
+                pick(k_conv_reg<32, 1, 2, true>, k_conv_reg<32, 1, 2, false>, 2);
+            else if (b2 >= 256)
+                pick(k_conv_reg<32, 2, 2, true>, k_conv_reg<32, 2, 2, false>, 2);
+            else
+                pick(k_conv_reg<32, 2, 1, true>, k_conv_reg<32, 2, 1, false>, 1);
+        } else if (NT == 1) {
+            if (b4 >= 256)
+                pick(k_conv_reg<16, 1, 4, true>, k_conv_reg<16, 1, 4, false>, 4);
+            else
+                pick(k_conv_reg<16, 1, 2, true>, k_conv_reg<16, 1, 2, false>, 2);
+        } else if (b2 >= 256)
+            pick(k_conv_reg<16, 2, 2, true>, k_conv_reg<16, 2, 2, false>, 2);
+        else
+            pick(k_conv_reg<16, 2, 1, true>, k_conv_reg<16, 2, 1, false>, 1);
         return;
     }
     const unsigned blocks = (unsigned)(nvox / (16 * kConvMT * kConvWaves));

@@ -70,22 +70,25 @@ def test_conv_backward_data_and_weight_match_reference(B, S, Cin, Cout):
     assert torch.abs(db - db_ref).max() <= 1e-4 * db_ref.abs().max()
 
 
-@pytest.mark.parametrize("B,S,Cin,relu", [(1, 16, 16, True), (3, 16, 80, False), (1, 32, 48, True), (4, 32, 16, False),
-                                          (1, 64, 48, True), (2, 64, 16, True), (5, 32, 16, False)])
-def test_conv_to_16_channels_exact_on_integers(B, S, Cin, relu):
-    """Convolutions to 16 channels on small integers, whose float32 sums are
-    exact (|x| <= 3, |w| <= 2: 27 * 80 * 6 + 8 < 2^24): tiles of 256 and of 512
-    voxels, fewer and more of them than workgroups, one chunk of input channels
-    and several; and a non-finite voxel reaches its 27 neighbours and no other."""
+@pytest.mark.parametrize("B,S,Cin,Cout,relu", [
+    (1, 16, 16, 16, True), (3, 16, 80, 16, False), (1, 32, 48, 16, True), (4, 32, 16, 16, False), (1, 64, 48, 16, True),
+    (2, 64, 16, 16, True), (5, 32, 16, 16, False), (1, 16, 16, 32, False), (2, 32, 48, 96, True), (1, 16, 16, 48, True),
+    (1, 16, 32, 16, True), (3, 32, 64, 48, False), (1, 16, 32, 64, True), (1, 32, 64, 64, False), (2, 32, 96, 32, True)])
+def test_conv_exact_on_integers(B, S, Cin, Cout, relu):
+    """Convolutions on small integers, whose float32 sums are exact (|x| <= 3,
+    |w| <= 2: 27 * 96 * 6 + 8 < 2^24): every depth of the tiles, fewer and more
+    of them than workgroups, chunks of 16 and of 32 input channels, one and
+    several, one and several blocks of output channels; and a non-finite voxel
+    reaches its 27 neighbours and no other."""
     mg = _mg()
-    print(f"[case] conv to 16 B={B} S={S} Cin={Cin} relu={relu}", flush=True)
+    print(f"[case] conv B={B} S={S} Cin={Cin} Cout={Cout} relu={relu}", flush=True)
     g = torch.Generator().manual_seed(B * 1000 + S + Cin)
     x = torch.randint(-3, 4, (B, S, S, S, Cin), generator=g).to(torch.bfloat16)
-    w = torch.randint(-2, 3, (27, 16, Cin), generator=g).to(torch.bfloat16)
-    b = torch.randint(-8, 9, (16,), generator=g).float()
+    w = torch.randint(-2, 3, (27, Cout, Cin), generator=g).to(torch.bfloat16)
+    b = torch.randint(-8, 9, (Cout,), generator=g).float()
     y = mg.conv3d_fwd(x.to(DEV), w.to(DEV), b.to(DEV), relu=relu, out32=True).cpu()
     # the reference in float32, exact on these integers as well
-    xt, wt = x.float().permute(0, 4, 1, 2, 3), w.float().permute(1, 2, 0).reshape(16, Cin, 3, 3, 3)
+    xt, wt = x.float().permute(0, 4, 1, 2, 3), w.float().permute(1, 2, 0).reshape(Cout, Cin, 3, 3, 3)
     ref = U.conv3d_periodic(xt, wt, b)
     ref = (torch.relu(ref) if relu else ref).permute(0, 2, 3, 4, 1)
     assert torch.equal(y, ref)

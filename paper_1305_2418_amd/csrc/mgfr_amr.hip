@@ -863,117 +863,300 @@ struct AmrxCell {
     float ec, Xc, uc, wc, en[6], Xn[6], un[6], wn[6];
 };
 
-__device__ __forceinline__ void amrx_gather(const LevelDev &L, const float *__restrict__ E, int blk, int m, int b,
-                                            int vol, int x, int y, int z, AmrxCell &c)
+// indices of the cell (x, y, z) of block blk of sublevel M and of its neighbours
+// (+x, -x, +y, -y, +z, -z): in the block, in the neighbouring block, or the block's
+// own frozen ghost.  All neighbour ids are loaded at once and nothing branches on
+// them, so that the loads that follow are in flight together.
+template <int M>
+__device__ __forceinline__ void amrx_index(const LevelDev &L, int blk, int x, int y, int z, size_t o[7])
 {
-    const size_t o = (size_t)blk * vol + pidx(m, x, y, z);
-    c.ec = E[o];
-    c.uc = L.u32[m][o];
-    c.Xc = fexpm1(c.ec);
-    c.wc = fexp(c.uc);
-    const int dx[6] = {1, -1, 0, 0, 0, 0}, dy[6] = {0, 0, 1, -1, 0, 0}, dz[6] = {0, 0, 0, 0, 1, -1};
+    constexpr int b = 8 >> M, p = b + 2, vol = p * p * p;
+    int nbr[6];
+#pragma unroll
+    for (int f = 0; f < 6; ++f) nbr[f] = L.nbr[6 * blk + f];
+    const size_t own = (size_t)blk * vol;
+    const int c = ((x + 1) * p + y + 1) * p + z + 1;
+    o[0] = own + c;
+    const int at[3] = {x, y, z}, st[3] = {p * p, p, 1};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const bool hi = at[a] == b - 1 && nbr[2 * a + 1] >= 0, lo = at[a] == 0 && nbr[2 * a] >= 0;
+        o[1 + 2 * a] = (hi ? (size_t)nbr[2 * a + 1] * vol - b * st[a] : own) + c + st[a];
+        o[2 + 2 * a] = (lo ? (size_t)nbr[2 * a] * vol + b * st[a] : own) + c - st[a];
+    }
+}
+
+template <int M>
+__device__ __forceinline__ void amrx_gather(const LevelDev &L, const float *__restrict__ E, const size_t o[7], AmrxCell &c)
+{
+    c.ec = E[o[0]];
+    c.uc = L.u32[M][o[0]];
 #pragma unroll
     for (int s = 0; s < 6; ++s) {
-        c.en[s] = amr_nbval(L, E, blk, m, b, vol, x + dx[s], y + dy[s], z + dz[s]);
-        c.un[s] = amr_nbval(L, (const float *)L.u32[m], blk, m, b, vol, x + dx[s], y + dy[s], z + dz[s]);
+        c.en[s] = E[o[1 + s]];
+        c.un[s] = L.u32[M][o[1 + s]];
+    }
+    c.Xc = fexpm1(c.ec);
+    c.wc = fexp(c.uc);
+#pragma unroll
+    for (int s = 0; s < 6; ++s) {
         c.Xn[s] = fexpm1(c.en[s]);
         c.wn[s] = fexp(c.un[s]);
     }
 }
 
-// one colour of a float32 correction sweep on sublevel m (threads on that colour only)
-__global__ void k_amrx_sweep(LevelDev L, int m, int colour, MxConst kc)
+// One 8^3 block per wave (sublevel 0).  Lane (y, z) = (lane >> 3, lane & 7) holds
+// the column of 8 cells along x and the two beyond its ends in registers; the
+// cells and the faces in y and z lie in LDS as {e, X, u, w}, so that each
+// exponential is formed once per block instead of once per neighbour.
+constexpr int kBlkWaves = 4;           // blocks per workgroup
+constexpr int kBlkTile = 8 * 10 * 10;  // cells of a tile: x in 0..7, y and z in -1..8
+
+struct AmrxColumn {
+    float e[10], X[10], u[10], w[10];  // [x + 1]
+};
+
+__device__ __forceinline__ int blk_tile(int x, int y, int z) { return (x * 10 + y + 1) * 10 + z + 1; }
+
+// block of this wave, consecutive blocks on the same XCD (they share faces);
+// launched with blk_grid(nb) workgroups
+__device__ __forceinline__ int blk_of_wave()
 {
-    const int b = sub_b(m), vol = sub_vol(m);
-    const int per = b > 1 ? b * b * b / 2 : 1;
-    const size_t n = (size_t)L.nb * per;
-    for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < n; id += (size_t)gridDim.x * blockDim.x) {
-        const int blk = (int)(id / per), c = (int)(id % per);
-        const int ox = L.org[3 * blk] >> m, oy = L.org[3 * blk + 1] >> m, oz = L.org[3 * blk + 2] >> m;
-        int x = 0, y = 0, z = 0;
-        if (b > 1) {
-            const int hb = b >> 1;
-            x = c / (b * hb);
-            y = (c / hb) % b;
-            z = 2 * (c % hb) + ((colour + ox + oy + oz + x + y) & 1);
-        } else if (((ox + oy + oz) & 1) != colour) {
-            continue;
-        }
-        AmrxCell cell;
-        amrx_gather(L, L.e32[m], blk, m, b, vol, x, y, z, cell);
-        const size_t o = (size_t)blk * vol + pidx(m, x, y, z);
-        L.e32[m][o] = cell.ec + mx_step(cell.ec, cell.Xc, cell.uc, cell.wc, cell.en, cell.Xn, cell.un, cell.wn,
-                                        L.r32[m][o], kc);
+    const unsigned wg = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    return (int)(wg * kBlkWaves) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+unsigned blk_grid(int nb) { return ((unsigned)nb + 8 * kBlkWaves - 1) / (8 * kBlkWaves) * 8; }
+
+__device__ __forceinline__ void amrx_load_block(const LevelDev &L, const float *__restrict__ E, int blk, int lane,
+                                                AmrxColumn &c, float4 *tile)
+{
+    const int p = 10, vol = p * p * p, a = lane >> 3, b = lane & 7;
+    const float *U = L.u32[0];
+    // base of a face: the neighbouring block's layer, else the block's own ghosts
+    int nbr[6];
+#pragma unroll
+    for (int f = 0; f < 6; ++f) nbr[f] = L.nbr[6 * blk + f];
+    const size_t own = (size_t)blk * vol;
+    auto face = [&](int f, int stride, int off) {  // f even: layer 8 of the neighbour or 0 here; odd: 1 or 9
+        const int lo = (f & 1) ? 1 : 8, gh = (f & 1) ? 9 : 0;
+        return (nbr[f] >= 0 ? (size_t)nbr[f] * vol + lo * stride : own + gh * stride) + off;
+    };
+    const size_t o = own + p * p + (a + 1) * p + b + 1;
+    const size_t fx0 = face(0, p * p, (a + 1) * p + b + 1), fx1 = face(1, p * p, (a + 1) * p + b + 1);
+    const size_t fo[4] = {face(2, p, (a + 1) * p * p + b + 1), face(3, p, (a + 1) * p * p + b + 1),
+                          face(4, 1, (a + 1) * p * p + (b + 1) * p), face(5, 1, (a + 1) * p * p + (b + 1) * p)};
+    float fe[4], fu[4];
+    c.e[0] = E[fx0];
+    c.u[0] = U[fx0];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        c.e[x + 1] = E[o + x * p * p];
+        c.u[x + 1] = U[o + x * p * p];
+    }
+    c.e[9] = E[fx1];
+    c.u[9] = U[fx1];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        fe[f] = E[fo[f]];
+        fu[f] = U[fo[f]];
+    }
+#pragma unroll
+    for (int x = 0; x < 10; ++x) {
+        c.X[x] = fexpm1(c.e[x]);
+        c.w[x] = fexp(c.u[x]);
+        if (x > 0 && x < 9) tile[blk_tile(x - 1, a, b)] = make_float4(c.e[x], c.X[x], c.u[x], c.w[x]);
+    }
+    const int fd[4] = {blk_tile(a, -1, b), blk_tile(a, 8, b), blk_tile(a, b, -1), blk_tile(a, b, 8)};
+#pragma unroll
+    for (int f = 0; f < 4; ++f) tile[fd[f]] = make_float4(fe[f], fexpm1(fe[f]), fu[f], fexp(fu[f]));
+}
+
+// neighbours of the cell at tile index q in the order of amrx_gather: those in x
+// given, those in y and z from the tile
+__device__ __forceinline__ void amrx_sides(const float4 &xp, const float4 &xm, const float4 *tile, int q, AmrxCell &c)
+{
+    const float4 n[6] = {xp, xm, tile[q + 10], tile[q - 10], tile[q + 1], tile[q - 1]};
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+        c.en[t] = n[t].x;
+        c.Xn[t] = n[t].y;
+        c.un[t] = n[t].z;
+        c.wn[t] = n[t].w;
     }
 }
 
-// coarse interior cell of sublevel m + 1: eb = mean of the daughters' e, u32 =
-// mean of their u32, r = mean of their r - N(e)
-__global__ void k_amrx_restrict(LevelDev L, int m, MxConst kc)
+// one colour of a float32 correction sweep on sublevel 0.  Lanes update the cells
+// of their column whose x has the parity s: every lane is busy in every step.
+// Bound: the traffic of e, u and r (272 MB for 19442 blocks, 44 us: 6.2 TB/s,
+// from the last-level cache).  With every cell gathering its neighbours, their ids
+// and 14 exponentials by itself the launch took 86 us; 9.9 -> 4.9 us for 952 blocks.
+__global__ __launch_bounds__(64 * kBlkWaves) void k_amrx_sweep_blk(LevelDev L, int colour, MxConst kc)
 {
-    const int b = sub_b(m), vol = sub_vol(m), bc = sub_b(m + 1), volc = sub_vol(m + 1);
-    const int cells = bc * bc * bc;
+    __shared__ float4 tiles[kBlkWaves][kBlkTile];
+    const int blk = blk_of_wave(), lane = threadIdx.x & 63;
+    if (blk >= L.nb) return;  // a wave of its own: no barrier below
+    float4 *tile = tiles[threadIdx.x >> 6];
+    const int y = lane >> 3, z = lane & 7;
+    const int s = (colour + L.org[3 * blk] + L.org[3 * blk + 1] + L.org[3 * blk + 2] + y + z) & 1;
+    const size_t o = (size_t)blk * 1000 + pidx(0, s, y, z);
+    float r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = L.r32[0][o + 200 * i];
+    AmrxColumn c;
+    amrx_load_block(L, L.e32[0], blk, lane, c, tile);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        auto at = [&](int x) {  // cell x + s of the column, x + 1 known
+            return make_float4(s ? c.e[x + 2] : c.e[x + 1], s ? c.X[x + 2] : c.X[x + 1], s ? c.u[x + 2] : c.u[x + 1],
+                               s ? c.w[x + 2] : c.w[x + 1]);
+        };
+        const float4 cc = at(2 * i);
+        AmrxCell cell;
+        amrx_sides(at(2 * i + 1), at(2 * i - 1), tile, blk_tile(2 * i + s, y, z), cell);
+        L.e32[0][o + 200 * i] = cc.x + mx_step(cc.x, cc.y, cc.z, cc.w, cell.en, cell.Xn, cell.un, cell.wn, r[i], kc);
+    }
+}
+
+// one colour of a float32 correction sweep on sublevel M > 0 (threads on that colour
+// only).  Latency-bound; 19442 blocks, M = 1, 2, 3: 21.5, 10.1, 7.0 us with a branch
+// and a load after the other per neighbour, 15.5, 7.0, 4.9 with the loads at once.
+template <int M>
+__global__ __launch_bounds__(256) void k_amrx_sweep(LevelDev L, int colour, MxConst kc)
+{
+    constexpr int b = 8 >> M, per = b > 1 ? b * b * b / 2 : 1, hb = b > 1 ? b / 2 : 1;
+    const size_t n = (size_t)L.nb * per;
+    for (size_t id = (size_t)blockIdx.x * 256 + threadIdx.x; id < n; id += (size_t)gridDim.x * 256) {
+        const int blk = (int)(id / per), c = (int)(id % per);
+        const int org = (L.org[3 * blk] >> M) + (L.org[3 * blk + 1] >> M) + (L.org[3 * blk + 2] >> M);
+        int x = 0, y = 0, z = 0;
+        if (b > 1) {
+            x = c / (b * hb);
+            y = (c / hb) % b;
+            z = 2 * (c % hb) + ((colour + org + x + y) & 1);
+        } else if ((org & 1) != colour) {
+            continue;
+        }
+        size_t o[7];
+        amrx_index<M>(L, blk, x, y, z, o);
+        const float r = L.r32[M][o[0]];
+        AmrxCell cell;
+        amrx_gather<M>(L, L.e32[M], o, cell);
+        L.e32[M][o[0]] = cell.ec + mx_step(cell.ec, cell.Xc, cell.uc, cell.wc, cell.en, cell.Xn, cell.un, cell.wn, r, kc);
+    }
+}
+
+// Sublevel 1 from sublevel 0: eb = mean of the daughters' e, u32 = mean of their
+// u32, r = mean of their r - N(e); one block per wave as above.
+// 19442 blocks: 204 -> 41 us (8 cells per coarse cell, gathered one after the other).
+__global__ __launch_bounds__(64 * kBlkWaves) void k_amrx_restrict_blk(LevelDev L, MxConst kc)
+{
+    __shared__ float4 tiles[kBlkWaves][kBlkTile];
+    const int blk = blk_of_wave(), lane = threadIdx.x & 63;
+    if (blk >= L.nb) return;  // a wave of its own: no barrier below
+    float4 *tile = tiles[threadIdx.x >> 6];
+    const int y = lane >> 3, z = lane & 7;
+    const size_t o = (size_t)blk * 1000 + pidx(0, 0, y, z);
+    float r[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) r[x] = L.r32[0][o + 100 * x];
+    AmrxColumn c;
+    amrx_load_block(L, L.e32[0], blk, lane, c, tile);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        auto at = [&](int i) { return make_float4(c.e[i], c.X[i], c.u[i], c.w[i]); };
+        AmrxCell cell;
+        amrx_sides(at(x + 2), at(x), tile, blk_tile(x, y, z), cell);
+        r[x] -= mx_value(c.e[x + 1], c.X[x + 1], c.u[x + 1], c.w[x + 1], cell.en, cell.Xn, cell.un, cell.wn, kc);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int x = 0; x < 8; ++x) tile[blk_tile(x, y, z)] = make_float4(c.e[x + 1], c.u[x + 1], r[x], 0.f);
+    __builtin_amdgcn_wave_barrier();
+    const int X = lane >> 4, Y = (lane >> 2) & 3, Z = lane & 3;
+    float se = 0.f, su = 0.f, sr = 0.f;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        const float4 v = tile[blk_tile(2 * X + (d >> 2), 2 * Y + ((d >> 1) & 1), 2 * Z + (d & 1))];
+        se += v.x;
+        su += v.y;
+        sr += v.z;
+    }
+    const size_t q = (size_t)blk * sub_vol(1) + pidx(1, X, Y, Z);
+    L.eb32[1][q] = 0.125f * se;
+    L.u32[1][q] = 0.125f * su;
+    L.r32[1][q] = 0.125f * sr;
+}
+
+// the same for sublevel M + 1 from sublevel M > 0, one coarse cell per thread
+template <int M>
+__global__ __launch_bounds__(256) void k_amrx_restrict(LevelDev L, MxConst kc)
+{
+    constexpr int bc = 4 >> M, volc = (bc + 2) * (bc + 2) * (bc + 2), cells = bc * bc * bc;
     const size_t n = (size_t)L.nb * cells;
-    for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < n; id += (size_t)gridDim.x * blockDim.x) {
+    for (size_t id = (size_t)blockIdx.x * 256 + threadIdx.x; id < n; id += (size_t)gridDim.x * 256) {
         const int blk = (int)(id / cells), c = (int)(id % cells);
         const int X = c / (bc * bc), Y = (c / bc) % bc, Z = c % bc;
         float se = 0.f, su = 0.f, sr = 0.f;
-        for (int a = 0; a < 2; ++a)
-            for (int b2 = 0; b2 < 2; ++b2)
-                for (int d = 0; d < 2; ++d) {
-                    const int x = 2 * X + a, y = 2 * Y + b2, z = 2 * Z + d;
-                    AmrxCell cell;
-                    amrx_gather(L, L.e32[m], blk, m, b, vol, x, y, z, cell);
-                    const float N = mx_value(cell.ec, cell.Xc, cell.uc, cell.wc, cell.en, cell.Xn, cell.un, cell.wn, kc);
-                    se += cell.ec;
-                    su += cell.uc;
-                    sr += L.r32[m][(size_t)blk * vol + pidx(m, x, y, z)] - N;
-                }
-        const size_t q = (size_t)blk * volc + pidx(m + 1, X, Y, Z);
-        L.eb32[m + 1][q] = 0.125f * se;
-        L.u32[m + 1][q] = 0.125f * su;
-        L.r32[m + 1][q] = 0.125f * sr;
-    }
-}
-
-// r += N_c(eb), e = eb on the interior cells of sublevel m (the FAS source)
-__global__ void k_amrx_coarse_rhs(LevelDev L, int m, MxConst kc)
-{
-    const int b = sub_b(m), vol = sub_vol(m);
-    const int cells = b * b * b;
-    const size_t n = (size_t)L.nb * cells;
-    for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < n; id += (size_t)gridDim.x * blockDim.x) {
-        const int blk = (int)(id / cells), c = (int)(id % cells);
-        const int x = c / (b * b), y = (c / b) % b, z = c % b;
-        AmrxCell cell;
-        amrx_gather(L, L.eb32[m], blk, m, b, vol, x, y, z, cell);
-        const size_t o = (size_t)blk * vol + pidx(m, x, y, z);
-        L.r32[m][o] += mx_value(cell.ec, cell.Xc, cell.uc, cell.wc, cell.en, cell.Xn, cell.un, cell.wn, kc);
-        L.e32[m][o] = cell.ec;
-    }
-}
-
-// e[m] += P(e[m+1] - eb[m+1]) on interior cells (linear: mode 0, injection: mode 1)
-__global__ void k_amrx_prolong(LevelDev L, int m, int mode)
-{
-    const int b = sub_b(m), vol = sub_vol(m), bc = sub_b(m + 1), volc = sub_vol(m + 1);
-    const int cells = b * b * b;
-    const size_t n = (size_t)L.nb * cells;
-    for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < n; id += (size_t)gridDim.x * blockDim.x) {
-        const int blk = (int)(id / cells), c = (int)(id % cells);
-        const int x = c / (b * b), y = (c / b) % b, z = c % b;
-        const int X = x >> 1, Y = y >> 1, Z = z >> 1;
-        auto d = [&](int i, int j, int k) {
-            return amr_nbval(L, (const float *)L.e32[m + 1], blk, m + 1, bc, volc, i, j, k) -
-                   amr_nbval(L, (const float *)L.eb32[m + 1], blk, m + 1, bc, volc, i, j, k);
-        };
-        float v = d(X, Y, Z);
-        if (mode == 0) {
-            v += ((x & 1) ? 0.125f : -0.125f) * (d(X + 1, Y, Z) - d(X - 1, Y, Z));
-            v += ((y & 1) ? 0.125f : -0.125f) * (d(X, Y + 1, Z) - d(X, Y - 1, Z));
-            v += ((z & 1) ? 0.125f : -0.125f) * (d(X, Y, Z + 1) - d(X, Y, Z - 1));
+#pragma unroll 2
+        for (int d = 0; d < 8; ++d) {
+            size_t o[7];
+            amrx_index<M>(L, blk, 2 * X + (d >> 2), 2 * Y + ((d >> 1) & 1), 2 * Z + (d & 1), o);
+            AmrxCell cell;
+            amrx_gather<M>(L, L.e32[M], o, cell);
+            const float N = mx_value(cell.ec, cell.Xc, cell.uc, cell.wc, cell.en, cell.Xn, cell.un, cell.wn, kc);
+            se += cell.ec;
+            su += cell.uc;
+            sr += L.r32[M][o[0]] - N;
         }
-        L.e32[m][(size_t)blk * vol + pidx(m, x, y, z)] += v;
+        const size_t q = (size_t)blk * volc + pidx(M + 1, X, Y, Z);
+        L.eb32[M + 1][q] = 0.125f * se;
+        L.u32[M + 1][q] = 0.125f * su;
+        L.r32[M + 1][q] = 0.125f * sr;
+    }
+}
+
+// r += N_c(eb), e = eb on the interior cells of sublevel M (the FAS source)
+template <int M>
+__global__ __launch_bounds__(256) void k_amrx_coarse_rhs(LevelDev L, MxConst kc)
+{
+    constexpr int b = 8 >> M, cells = b * b * b;
+    const size_t n = (size_t)L.nb * cells;
+    for (size_t id = (size_t)blockIdx.x * 256 + threadIdx.x; id < n; id += (size_t)gridDim.x * 256) {
+        const int blk = (int)(id / cells), c = (int)(id % cells);
+        size_t o[7];
+        amrx_index<M>(L, blk, c / (b * b), (c / b) % b, c % b, o);
+        AmrxCell cell;
+        amrx_gather<M>(L, L.eb32[M], o, cell);
+        L.r32[M][o[0]] += mx_value(cell.ec, cell.Xc, cell.uc, cell.wc, cell.en, cell.Xn, cell.un, cell.wn, kc);
+        L.e32[M][o[0]] = cell.ec;
+    }
+}
+
+// e[M] += P(e[M + 1] - eb[M + 1]) on interior cells (linear: mode 0, injection: mode 1)
+template <int M>
+__global__ __launch_bounds__(256) void k_amrx_prolong(LevelDev L, int mode)
+{
+    constexpr int b = 8 >> M, cells = b * b * b;
+    const float *e = L.e32[M + 1], *eb = L.eb32[M + 1];
+    const size_t n = (size_t)L.nb * cells;
+    for (size_t id = (size_t)blockIdx.x * 256 + threadIdx.x; id < n; id += (size_t)gridDim.x * 256) {
+        const int blk = (int)(id / cells), c = (int)(id % cells);
+        const int x = c / (b * b), y = (c / b) % b, z = c % b;
+        size_t o[7];
+        amrx_index<M + 1>(L, blk, x >> 1, y >> 1, z >> 1, o);
+        float v = e[o[0]] - eb[o[0]];
+        if (mode == 0) {
+            float d[6];
+#pragma unroll
+            for (int t = 0; t < 6; ++t) d[t] = e[o[1 + t]] - eb[o[1 + t]];
+            v += ((x & 1) ? 0.125f : -0.125f) * (d[0] - d[1]);
+            v += ((y & 1) ? 0.125f : -0.125f) * (d[2] - d[3]);
+            v += ((z & 1) ? 0.125f : -0.125f) * (d[4] - d[5]);
+        }
+        L.e32[M][(size_t)blk * sub_vol(M) + pidx(M, x, y, z)] += v;
     }
 }
 
@@ -1263,31 +1446,36 @@ int amr_vcycle(mgfr_amr *A, const LevelDev &L, int m, const SubConst &K)
     return amr_sweeps(A, L, m, A->p.post_smooth, K);
 }
 
-// float32 correction V-cycle on sublevels m.. of a refined level (mixed precision)
-int amrx_vcycle(mgfr_amr *A, const LevelDev &L, int m, const MxConst *K)
+// float32 correction V-cycle on sublevels M.. of a refined level (mixed precision)
+template <int M>
+int amrx_vcycle(mgfr_amr *A, const LevelDev &L, const MxConst *K)
 {
-    auto sweeps = [&](int mm, int count) {
-        const int b = sub_b(mm);
-        const size_t cells = (size_t)L.nb * b * b * b;
+    constexpr int b = 8 >> M;
+    const size_t cells = (size_t)L.nb * b * b * b;
+    auto sweeps = [&](int count) {
         for (int s = 0; s < count; ++s)
-            for (int colour = 0; colour < 2; ++colour)
-                k_amrx_sweep<<<grid_of(b > 1 ? cells / 2 : cells), 256, 0, A->stream>>>(L, mm, colour, K[mm]);
+            for (int colour = 0; colour < 2; ++colour) {
+                if constexpr (M == 0)
+                    k_amrx_sweep_blk<<<blk_grid(L.nb), 64 * kBlkWaves, 0, A->stream>>>(L, colour, K[0]);
+                else
+                    k_amrx_sweep<M><<<grid_of(b > 1 ? cells / 2 : cells), 256, 0, A->stream>>>(L, colour, K[M]);
+            }
     };
-    if (m == kSub - 1) {
-        sweeps(m, A->p.coarse_sweeps);
+    if constexpr (M == kSub - 1) {
+        sweeps(A->p.coarse_sweeps);
+    } else {
+        sweeps(A->p.pre_smooth);
+        if constexpr (M == 0)
+            k_amrx_restrict_blk<<<blk_grid(L.nb), 64 * kBlkWaves, 0, A->stream>>>(L, K[0]);
+        else
+            k_amrx_restrict<M><<<grid_of(cells / 8), 256, 0, A->stream>>>(L, K[M]);
+        k_amrx_coarse_rhs<M + 1><<<grid_of(cells / 8), 256, 0, A->stream>>>(L, K[M + 1]);
         MGFR_HIP(hipGetLastError());
-        return MGFR_OK;
+        int rc;
+        if ((rc = amrx_vcycle<M + 1>(A, L, K))) return rc;
+        k_amrx_prolong<M><<<grid_of(cells), 256, 0, A->stream>>>(L, A->p.prolong);
+        sweeps(A->p.post_smooth);
     }
-    sweeps(m, A->p.pre_smooth);
-    const int bc = sub_b(m + 1), b = sub_b(m);
-    const size_t cc = (size_t)L.nb * bc * bc * bc, cf = (size_t)L.nb * b * b * b;
-    k_amrx_restrict<<<grid_of(cc), 256, 0, A->stream>>>(L, m, K[m]);
-    k_amrx_coarse_rhs<<<grid_of(cc), 256, 0, A->stream>>>(L, m + 1, K[m + 1]);
-    MGFR_HIP(hipGetLastError());
-    int rc;
-    if ((rc = amrx_vcycle(A, L, m + 1, K))) return rc;
-    k_amrx_prolong<<<grid_of(cf), 256, 0, A->stream>>>(L, m, A->p.prolong);
-    sweeps(m, A->p.post_smooth);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
@@ -1361,7 +1549,7 @@ int solve_level(mgfr_amr *A, int l)
             if (!std::isfinite(res) || grow >= 3) break;  // fall back below
             if (res <= A->p.tol) { status = MGFR_OK; done = true; break; }
             if (cyc >= A->p.max_vcycles) { status = MGFR_NOT_CONVERGED; done = true; break; }
-            if ((rc = amrx_vcycle(A, L, 0, KM))) return rc;
+            if ((rc = amrx_vcycle<0>(A, L, KM))) return rc;
             k_amrx_update<<<grid_of((size_t)L.nb * 512), 256, 0, A->stream>>>(L);
             k_amr_exchange<<<grid_of(ff), 256, 0, A->stream>>>(L, L.u[0], 0);
             MGFR_HIP(hipGetLastError());

@@ -93,6 +93,25 @@ def test_fully_refined_level_matches_uniform_oracle(precision):
     assert err <= 1e-8
 
 
+@pytest.mark.parametrize("N0,nref,fr0,a,seed", [(32, 2, 1e-6, 1.0, 4), (64, 2, 1e-6, 0.7, 6), (32, 1, 1e-5, 1.0, 5)])
+def test_amr_mixed_cycles_contract_like_float64(N0, nref, fr0, a, seed):
+    """The float32 correction cycle is the float64 one's smoother on the defect:
+    without over-relaxation the refined levels take as many cycles as the oracle,
+    within two (the first cycle of each starts from e = 0; float32 rounding), and
+    never fall back to float64 cycles."""
+    from paper_1305_2418_amd import mgfr
+    print(f"[case] amr mixed cycles N0={N0} nref={nref}", flush=True)
+    pos = synth.clustered_load(N0, 100.0, rms=5.0, seed=seed, n_halos=50, profile="nfw")
+    s_o, _, _, sts = O.amr_solve(O.params(mesh=N0, fr0_abs=fr0, a=a), nref, pos.numpy())
+    assert s_o == 0
+    amr = mgfr.Amr(mgfr.Params(mesh=N0, fr0_abs=fr0, a=a, refine_levels=nref, precision=mgfr.MIXED), max_blocks=20000)
+    amr.set_relaxation32(1.0)
+    _, st = amr.solve(pos.to(DEV))
+    for l in range(1, nref + 1):
+        print(f"  level {l}: cycles {st[l].vcycles} (oracle {sts[l].vcycles})")
+        assert not st[l].fell_back and st[l].vcycles <= sts[l].vcycles + 2
+
+
 def test_amr_rejects_bad_arguments():
     from paper_1305_2418_amd import mgfr
     with pytest.raises(mgfr.MgfrError):

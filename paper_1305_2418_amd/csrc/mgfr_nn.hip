@@ -185,6 +185,39 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
         }
 }
 
+// Input of a layer: C channels per voxel of x or, with a skip connection, the
+// nearest-neighbour upsampling of x (C channels per voxel of the mesh of half the
+// side) followed by the Cs channels of skip.  A chunk of channels comes from one
+// of the two (C is a multiple of it), so that no concatenated copy is written
+// (62 us of the 556 us of a 128^3 prediction, and the copies were read from HBM:
+// 48 -> 16 channels 145 -> 124 us, its weight gradient 213 -> 165 us).
+struct ConvIn {
+    const __bf16 *x;
+    int C;
+    const __bf16 *skip = nullptr;
+    int Cs = 0;
+};
+
+// the source of the channels from c on: its array at channel c, its channels and
+// the shift of the mesh coordinates
+struct ConvSrc {
+    const __bf16 *x;
+    int C, sh;
+};
+
+__device__ __forceinline__ ConvSrc conv_src(const ConvIn &I, int c)
+{
+    if (!I.skip) return ConvSrc{I.x + c, I.C, 0};
+    return c < I.C ? ConvSrc{I.x + c, I.C, 1} : ConvSrc{I.skip + (c - I.C), I.Cs, 0};
+}
+
+// voxel (x, y, z) of the volume that starts at voxel vol, in the source's mesh
+__device__ __forceinline__ size_t conv_voxel(const ConvSrc &s, size_t vol, int z, int y, int x, int lgS)
+{
+    const int lg = lgS - s.sh;
+    return (vol >> (3 * s.sh)) + ((((size_t)(z >> s.sh) << lg) + (size_t)(y >> s.sh)) << lg) + (size_t)(x >> s.sh);
+}
+
 // The same convolution for S >= 16 and input channels in chunks of CK = 16 or 32
 // (every layer of the network above the 8^3 mesh, and their backward-data passes).
 //
@@ -204,18 +237,18 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
 // Bound: LDS reads, 8 cycles per CU and MFMA against 4 of the matrix cores.
 // us, before (weights from L1 in every k-step, two-way bank conflicts, no loads in
 // flight during the products, two-byte stores) and now, 2.1 M voxels: 16 -> 16
-// channels 110, 42; 48 -> 16 340, 145; 16 -> 48 176, 135; 262144 voxels: 16 -> 32
-// 25, 16; 32 -> 32 46, 23; 96 -> 32 120, 66; 32 -> 96 114, 57; 32 -> 16 41, 16;
+// channels 110, 42; 48 -> 16 340, 124; 16 -> 48 176, 143; 262144 voxels: 16 -> 32
+// 25, 16; 32 -> 32 46, 23; 96 -> 32 120, 61; 32 -> 96 114, 57; 32 -> 16 41, 16;
 // 32768 voxels: 32 -> 64 22, 9.6; 64 -> 64 39, 22; 64 -> 32 34, 15.
-template <int CK, int NT, int TZ, bool MASK>
-__global__ __launch_bounds__(256, 2) void k_conv_reg(const __bf16 *__restrict__ X, int lgS, int Cin,
-                                                     const __bf16 *__restrict__ W, const float *__restrict__ bias,
-                                                     int Cout, int relu, const __bf16 *__restrict__ M, unsigned ntiles,
+template <int CK, int NT, int TZ, bool MASK, bool SKIP>
+__global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const __bf16 *__restrict__ W,
+                                                     const float *__restrict__ bias, int Cout, int relu, const __bf16 *__restrict__ M, unsigned ntiles,
                                                      __bf16 *__restrict__ Y, float *__restrict__ Y32)
 {
     constexpr int MT = 2 * TZ * NT, HX = 18, HY = 10, HV = HX * HY * (TZ + 2), Q = CK / 8, HP = (HV + 15) / 16 * 16;
     constexpr int NK = CK == 16 ? 14 : 27;
     constexpr int NP = (HP * Q + 255) / 256;  // 16-byte pieces of a halo block per thread
+    const int Cin = SKIP ? in.C + in.Cs : in.C;
     static_assert(MT == 4 || MT % 8 == 0, "a wave's rows are half a z-plane of the tile or whole ones");
     __shared__ __attribute__((aligned(16))) __bf16 sX[Q * HP * 8];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -249,16 +282,16 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(const __bf16 *__restrict__ 
         int x0, y0, z0;
         size_t vol;
         origin(tile, x0, y0, z0, vol);
-        const __bf16 *x = X + cc0 + 8 * pq;
+        const ConvSrc from = SKIP ? conv_src(in, cc0) : ConvSrc{in.x + cc0, in.C, 0};
+        const __bf16 *x = from.x + 8 * pq;
         int v0 = pv;
         asm volatile("" : "+v"(v0));  // coordinates are formed anew: kept for all pieces they spill
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int v = min(v0 + 256 / Q * i, HV - 1);
             const int vx = v % HX, vy = (v / HX) % HY, vz = v / (HX * HY);
-            const size_t src = vol + ((((size_t)((z0 + vz - 1) & sm) << lgS) + (size_t)((y0 + vy - 1) & sm)) << lgS) +
-                               (size_t)((x0 + vx - 1) & sm);
-            st[i] = *(const bf16x8 *)(x + src * Cin);
+            st[i] = *(const bf16x8 *)(x + conv_voxel(from, vol, (z0 + vz - 1) & sm, (y0 + vy - 1) & sm,
+                                                     (x0 + vx - 1) & sm, lgS) * from.C);
         }
     };
     bf16x8 b[NK];
@@ -328,9 +361,11 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(const __bf16 *__restrict__ 
 
 // Launch k_conv3d over nvox = B S^3 voxels (S >= 8, Cout a multiple of 16 up to 96).
 // With a mask M (Cout channels, for a gradient through a ReLU) Y is zero where M > 0 does not hold.
-void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 *W, const float *bias, int Cout,
-                   int relu, const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
+// A skip connection is for meshes of 16^3 and up, without a mask.
+void launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, const float *bias, int Cout, int relu,
+                   const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
 {
+    const int Cin = in.C + in.Cs;
     if (Cin % 16 == 0 && lgS >= 4) {
         // two blocks of 16 channels per workgroup where the number is even: its
         // weights still fit in the registers and the input is read half as often
@@ -340,30 +375,39 @@ void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 
         // places: 59 us instead of 49 for 16 -> 16 channels)
         auto go = [&](auto *k, unsigned tz) {
             const unsigned nt = (unsigned)(nvox / (128 * tz));
-            k<<<dim3(std::min(nt, std::max(512u / groups, 1u)), groups), 256, 0, s>>>(X, lgS, Cin, W, bias, Cout, relu,
+            k<<<dim3(std::min(nt, std::max(512u / groups, 1u)), groups), 256, 0, s>>>(in, lgS, W, bias, Cout, relu,
                                                                                       M, nt, Y, Y32);
         };
-        auto pick = [&](auto *masked, auto *plain, unsigned tz) { M ? go(masked, tz) : go(plain, tz); };
+        auto pick = [&](auto *masked, auto *plain, auto *skip, unsigned tz) {
+            in.skip ? go(skip, tz) : M ? go(masked, tz) : go(plain, tz);
+        };
         // The deepest tile that the registers allow loads the fewest voxels of halo
         // (4 planes: 2.1 per voxel, 2: 2.8, 1: 4.2); a shallower one where the
         // tiles would leave CUs without a workgroup
         const size_t b4 = nvox / 512 * groups, b2 = nvox / 256 * groups;
         if (Cin % 32 == 0) {
             if (NT == 1)
-                pick(k_conv_reg<32, 1, 2, true>, k_conv_reg<32, 1, 2, false>, 2);
+                pick(k_conv_reg<32, 1, 2, true, false>, k_conv_reg<32, 1, 2, false, false>,
+                     k_conv_reg<32, 1, 2, false, true>, 2);
             else if (b2 >= 256)
-                pick(k_conv_reg<32, 2, 2, true>, k_conv_reg<32, 2, 2, false>, 2);
+                pick(k_conv_reg<32, 2, 2, true, false>, k_conv_reg<32, 2, 2, false, false>,
+                     k_conv_reg<32, 2, 2, false, true>, 2);
             else
-                pick(k_conv_reg<32, 2, 1, true>, k_conv_reg<32, 2, 1, false>, 1);
+                pick(k_conv_reg<32, 2, 1, true, false>, k_conv_reg<32, 2, 1, false, false>,
+                     k_conv_reg<32, 2, 1, false, true>, 1);
         } else if (NT == 1) {
             if (b4 >= 256)
-                pick(k_conv_reg<16, 1, 4, true>, k_conv_reg<16, 1, 4, false>, 4);
+                pick(k_conv_reg<16, 1, 4, true, false>, k_conv_reg<16, 1, 4, false, false>,
+                     k_conv_reg<16, 1, 4, false, true>, 4);
             else
-                pick(k_conv_reg<16, 1, 2, true>, k_conv_reg<16, 1, 2, false>, 2);
+                pick(k_conv_reg<16, 1, 2, true, false>, k_conv_reg<16, 1, 2, false, false>,
+                     k_conv_reg<16, 1, 2, false, true>, 2);
         } else if (b2 >= 256)
-            pick(k_conv_reg<16, 2, 2, true>, k_conv_reg<16, 2, 2, false>, 2);
+            pick(k_conv_reg<16, 2, 2, true, false>, k_conv_reg<16, 2, 2, false, false>,
+                     k_conv_reg<16, 2, 2, false, true>, 2);
         else
-            pick(k_conv_reg<16, 2, 1, true>, k_conv_reg<16, 2, 1, false>, 1);
+            pick(k_conv_reg<16, 2, 1, true, false>, k_conv_reg<16, 2, 1, false, false>,
+                     k_conv_reg<16, 2, 1, false, true>, 1);
         return;
     }
     const unsigned blocks = (unsigned)(nvox / (16 * kConvMT * kConvWaves));
@@ -379,12 +423,12 @@ void launch_conv3d(const __bf16 *X, size_t nvox, int lgS, int Cin, const __bf16 
     }
     const dim3 grid(blocks, groups);
     switch (nt) {
-    case 1: k_conv3d<1><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
-    case 2: k_conv3d<2><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
-    case 3: k_conv3d<3><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
-    case 4: k_conv3d<4><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
-    case 5: k_conv3d<5><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
-    default: k_conv3d<6><<<grid, 64 * kConvWaves, lds, s>>>(X, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 1: k_conv3d<1><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 2: k_conv3d<2><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 3: k_conv3d<3><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 4: k_conv3d<4><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    case 5: k_conv3d<5><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
+    default: k_conv3d<6><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
     }
 }
 
@@ -428,10 +472,10 @@ __device__ __forceinline__ bf16x8 tr_pair(const __bf16 *p0, const __bf16 *p1)
 
 // grid (Cout / 16 * Cin / 16, splits of the tiles)
 template <int LGX>
-__global__ __launch_bounds__(256) void k_conv3d_wgrad(const __bf16 *__restrict__ X, const __bf16 *__restrict__ dZ,
-                                                       int lgS, int Cin, int Cout, unsigned ntiles,
-                                                       float *__restrict__ dW, float *__restrict__ db)
+__global__ __launch_bounds__(256) void k_conv3d_wgrad(ConvIn in, const __bf16 *__restrict__ dZ, int lgS, int Cout,
+                                                       unsigned ntiles, float *__restrict__ dW, float *__restrict__ db)
 {
+    const int Cin = in.C + in.Cs;
     constexpr int TX = 1 << LGX, TZ = kWgTile / (8 * TX);
     constexpr int HX = TX + 2, HY = 10, HV = HX * HY * (TZ + 2);
     __shared__ __attribute__((aligned(16))) __bf16 sX[HV * 16];
@@ -443,6 +487,7 @@ __global__ __launch_bounds__(256) void k_conv3d_wgrad(const __bf16 *__restrict__
     const int CT = Cin >> 4;
     const int o0 = 16 * ((int)blockIdx.x / CT), c0 = 16 * ((int)blockIdx.x % CT);
     const bool bias = db != nullptr && c0 == 0 && w == 3;
+    const ConvSrc from = conv_src(in, c0);
     const unsigned ntx = (unsigned)S / TX, nty = (unsigned)S / 8, ntz = (unsigned)S / TZ;
     // this lane's part of a row of voxels: voxel 4 g + r16 / 4 of 16, channels 4 (r16 & 3) ..
     const int v0 = 4 * g + (r16 >> 2), c4 = 4 * (r16 & 3);
@@ -479,9 +524,8 @@ __global__ __launch_bounds__(256) void k_conv3d_wgrad(const __bf16 *__restrict__
             const int idx = tid + 256 * i, v = idx >> 1, h = idx & 1;
             if (v < HV) {
                 const int x = v % HX, y = (v / HX) % HY, z = v / (HX * HY);
-                const size_t src = vol + ((((size_t)((z0 + z - 1) & sm) << lgS) + (size_t)((y0 + y - 1) & sm)) << lgS) +
-                                   (size_t)((x0 + x - 1) & sm);
-                *(bf16x8 *)(sX + v * 16 + 8 * h) = *(const bf16x8 *)(X + src * Cin + c0 + 8 * h);
+                const size_t src = conv_voxel(from, vol, (z0 + z - 1) & sm, (y0 + y - 1) & sm, (x0 + x - 1) & sm, lgS);
+                *(bf16x8 *)(sX + v * 16 + 8 * h) = *(const bf16x8 *)(from.x + src * from.C + 8 * h);
             }
         }
         __syncthreads();
@@ -518,15 +562,15 @@ __global__ __launch_bounds__(256) void k_conv3d_wgrad(const __bf16 *__restrict__
 // block to dW with atomics, so more of them cost more than they hide (the ten
 // layers of a gradient of eight 64^3 volumes with 256, 512, 768, 1024
 // workgroups: 0.98, 0.78, 0.80, 0.91 ms).
-void launch_wgrad(const __bf16 *X, const __bf16 *dZ, size_t nvox, int lgS, int Cin, int Cout, float *dW, float *db,
+void launch_wgrad(const ConvIn &in, const __bf16 *dZ, size_t nvox, int lgS, int Cout, float *dW, float *db,
                   hipStream_t s)
 {
-    const unsigned ntiles = (unsigned)(nvox / kWgTile), pairs = (unsigned)((Cin >> 4) * (Cout >> 4));
+    const unsigned ntiles = (unsigned)(nvox / kWgTile), pairs = (unsigned)(((in.C + in.Cs) >> 4) * (Cout >> 4));
     const dim3 grid(pairs, std::max(1u, std::min(ntiles, (unsigned)MGFR_WG_SPLIT / pairs)));
     if (lgS == 3)
-        k_conv3d_wgrad<3><<<grid, 256, 0, s>>>(X, dZ, lgS, Cin, Cout, ntiles, dW, db);
+        k_conv3d_wgrad<3><<<grid, 256, 0, s>>>(in, dZ, lgS, Cout, ntiles, dW, db);
     else
-        k_conv3d_wgrad<4><<<grid, 256, 0, s>>>(X, dZ, lgS, Cin, Cout, ntiles, dW, db);
+        k_conv3d_wgrad<4><<<grid, 256, 0, s>>>(in, dZ, lgS, Cout, ntiles, dW, db);
 }
 
 // Wt[t'][c][o] = W[26 - t'][o][c]: weights of the backward-data convolution
@@ -908,27 +952,26 @@ int net_refresh(mgfr_net *n)
     return MGFR_OK;
 }
 
-int conv(mgfr_net *n, const __bf16 *x, size_t nvox, int lgS, int layer, bool relu, __bf16 *y)
+int conv(mgfr_net *n, const ConvIn &in, size_t nvox, int lgS, int layer, __bf16 *y)
 {
     const ConvSpec &L = n->L[layer];
-    launch_conv3d(x, nvox, lgS, L.cin, n->wbf + L.woff, n->p + L.boff, L.cout, relu ? 1 : 0, nullptr, y, nullptr,
-                  n->stream);
+    launch_conv3d(in, nvox, lgS, n->wbf + L.woff, n->p + L.boff, L.cout, 1, nullptr, y, nullptr, n->stream);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
 
 // Backward through one convolution: from dz, the gradient before the layer's
-// ReLU, and its input x, accumulates weight and bias gradients and writes the
+// ReLU, and its input, accumulates weight and bias gradients and writes the
 // input's gradient dx if non-null, with relu_in through the ReLU that made x.
 // (Every gradient passes its ReLU where it is written: a pass of its own over dy,
 // y and dz was 44 us of the 110 us that a layer of 16 channels took on 2.1 M voxels.)
-int conv_bwd(mgfr_net *n, const __bf16 *dz, const __bf16 *x, size_t nvox, int lgS, int layer, __bf16 *dx, bool relu_in)
+int conv_bwd(mgfr_net *n, const __bf16 *dz, const ConvIn &in, size_t nvox, int lgS, int layer, __bf16 *dx, bool relu_in)
 {
     const ConvSpec &L = n->L[layer];
-    launch_wgrad(x, dz, nvox, lgS, L.cin, L.cout, n->g + L.woff, n->g + L.boff, n->stream);
+    launch_wgrad(in, dz, nvox, lgS, L.cout, n->g + L.woff, n->g + L.boff, n->stream);
     if (dx)
-        launch_conv3d(dz, nvox, lgS, L.cout, n->wt + L.woff, nullptr, L.cin, 0, relu_in ? x : nullptr, dx, nullptr,
-                      n->stream);
+        launch_conv3d({dz, L.cout}, nvox, lgS, n->wt + L.woff, nullptr, L.cin, 0, relu_in ? in.x : nullptr, dx,
+                      nullptr, n->stream);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
@@ -941,18 +984,18 @@ int net_forward(mgfr_net *n, const double *delta, int B, int lgS)
     n->fwd_lg = lgS;
     MGFR_HIP(hipMemcpyAsync(n->cond, n->hcond, 2 * B * sizeof(float), hipMemcpyHostToDevice, n->stream));
     k_features<<<gridn(V), 256, 0, n->stream>>>(delta, V, lgS, n->cond, n->x0);
-    if ((rc = conv(n, n->x0, V, lgS, 0, true, n->h1a)) || (rc = conv(n, n->h1a, V, lgS, 1, true, n->s1))) return rc;
+    if ((rc = conv(n, {n->x0, 16}, V, lgS, 0, n->h1a)) || (rc = conv(n, {n->h1a, 16}, V, lgS, 1, n->s1))) return rc;
     k_pool<<<gridn(V2 * 2), 256, 0, n->stream>>>(n->s1, lgS - 1, 16, V2, n->p1);
-    if ((rc = conv(n, n->p1, V2, lgS - 1, 2, true, n->h2a)) || (rc = conv(n, n->h2a, V2, lgS - 1, 3, true, n->s2)))
+    if ((rc = conv(n, {n->p1, 16}, V2, lgS - 1, 2, n->h2a)) || (rc = conv(n, {n->h2a, 32}, V2, lgS - 1, 3, n->s2)))
         return rc;
     k_pool<<<gridn(V3 * 4), 256, 0, n->stream>>>(n->s2, lgS - 2, 32, V3, n->p2);
-    if ((rc = conv(n, n->p2, V3, lgS - 2, 4, true, n->h3a)) || (rc = conv(n, n->h3a, V3, lgS - 2, 5, true, n->h3)))
+    if ((rc = conv(n, {n->p2, 32}, V3, lgS - 2, 4, n->h3a)) || (rc = conv(n, {n->h3a, 64}, V3, lgS - 2, 5, n->h3)))
         return rc;
-    k_concat_up<<<gridn(V2 * 12), 256, 0, n->stream>>>(n->h3, 64, n->s2, 32, lgS - 1, V2, n->cat4);
-    if ((rc = conv(n, n->cat4, V2, lgS - 1, 6, true, n->h4a)) || (rc = conv(n, n->h4a, V2, lgS - 1, 7, true, n->h4)))
+    if ((rc = conv(n, {n->h3, 64, n->s2, 32}, V2, lgS - 1, 6, n->h4a)) ||
+        (rc = conv(n, {n->h4a, 32}, V2, lgS - 1, 7, n->h4)))
         return rc;
-    k_concat_up<<<gridn(V * 6), 256, 0, n->stream>>>(n->h4, 32, n->s1, 16, lgS, V, n->cat5);
-    if ((rc = conv(n, n->cat5, V, lgS, 8, true, n->h5a)) || (rc = conv(n, n->h5a, V, lgS, 9, true, n->h5))) return rc;
+    if ((rc = conv(n, {n->h4, 32, n->s1, 16}, V, lgS, 8, n->h5a)) || (rc = conv(n, {n->h5a, 16}, V, lgS, 9, n->h5)))
+        return rc;
     k_head<<<gridn(V), 256, 0, n->stream>>>(n->h5, V, n->p + n->head_off, n->y32);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
@@ -969,28 +1012,28 @@ int net_backward(mgfr_net *n, const double *u_target, int B, int lgS)
     k_loss_head_bwd<<<gridn(V, kHeadBlocks), 256, 0, n->stream>>>(n->h5, n->y32, u_target, V, n->p + n->head_off, n->gC,
                                                                   n->g + n->head_off, n->loss);
     // level 1 decoder: c5b (dz = gC) -> gD; c5a -> d(cat5) in gA [V][48]
-    if ((rc = conv_bwd(n, n->gC, n->h5a, V, lgS, 9, n->gD, true))) return rc;
-    if ((rc = conv_bwd(n, n->gD, n->cat5, V, lgS, 8, n->gA, false))) return rc;
+    if ((rc = conv_bwd(n, n->gC, {n->h5a, 16}, V, lgS, 9, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, {n->h4, 32, n->s1, 16}, V, lgS, 8, n->gA, false))) return rc;
     // h4: sum over children of d(cat5)[:, 0:32] -> gB [V2][32]
     k_upsample_bwd<<<gridn(V2 * 4), 256, 0, n->stream>>>(n->gA, lgS - 1, 32, V2, 48, n->h4, n->gB);
     // level 2 decoder: c4b (dz = gB) -> gD; c4a -> d(cat4) in gB [V2][96]
-    if ((rc = conv_bwd(n, n->gB, n->h4a, V2, lgS - 1, 7, n->gD, true))) return rc;
-    if ((rc = conv_bwd(n, n->gD, n->cat4, V2, lgS - 1, 6, n->gB, false))) return rc;
+    if ((rc = conv_bwd(n, n->gB, {n->h4a, 32}, V2, lgS - 1, 7, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, {n->h3, 64, n->s2, 32}, V2, lgS - 1, 6, n->gB, false))) return rc;
     // h3: sum over children of d(cat4)[:, 0:64] -> gC [V3][64]
     k_upsample_bwd<<<gridn(V3 * 8), 256, 0, n->stream>>>(n->gB, lgS - 2, 64, V3, 96, n->h3, n->gC);
     // level 3: c3b (dz = gC) -> gD; c3a -> d(p2) in gC
-    if ((rc = conv_bwd(n, n->gC, n->h3a, V3, lgS - 2, 5, n->gD, true))) return rc;
-    if ((rc = conv_bwd(n, n->gD, n->p2, V3, lgS - 2, 4, n->gC, false))) return rc;
+    if ((rc = conv_bwd(n, n->gC, {n->h3a, 64}, V3, lgS - 2, 5, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, {n->p2, 32}, V3, lgS - 2, 4, n->gC, false))) return rc;
     // s2: d(cat4)[:, 64:96] + d(p2)/8 -> gD [V2][32]
     k_skip_grad<<<gridn(V2 * 4), 256, 0, n->stream>>>(n->gB, 96, 64, n->gC, lgS - 1, 32, V2, n->s2, n->gD);
     // level 2 encoder: c2b (dz = gD) -> gC; c2a -> d(p1) in gD
-    if ((rc = conv_bwd(n, n->gD, n->h2a, V2, lgS - 1, 3, n->gC, true))) return rc;
-    if ((rc = conv_bwd(n, n->gC, n->p1, V2, lgS - 1, 2, n->gD, false))) return rc;
+    if ((rc = conv_bwd(n, n->gD, {n->h2a, 32}, V2, lgS - 1, 3, n->gC, true))) return rc;
+    if ((rc = conv_bwd(n, n->gC, {n->p1, 16}, V2, lgS - 1, 2, n->gD, false))) return rc;
     // s1: d(cat5)[:, 32:48] + d(p1)/8 -> gC [V][16]
     k_skip_grad<<<gridn(V * 2), 256, 0, n->stream>>>(n->gA, 48, 32, n->gD, lgS, 16, V, n->s1, n->gC);
     // level 1 encoder: c1b (dz = gC) -> gD; c1a (no input gradient)
-    if ((rc = conv_bwd(n, n->gC, n->h1a, V, lgS, 1, n->gD, true))) return rc;
-    if ((rc = conv_bwd(n, n->gD, n->x0, V, lgS, 0, nullptr, false))) return rc;
+    if ((rc = conv_bwd(n, n->gC, {n->h1a, 16}, V, lgS, 1, n->gD, true))) return rc;
+    if ((rc = conv_bwd(n, n->gD, {n->x0, 16}, V, lgS, 0, nullptr, false))) return rc;
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
@@ -1172,6 +1215,12 @@ extern "C" int mgfr_net_activation(mgfr_net *n, int index, void *dst, int64_t co
     const size_t vox = ((size_t)n->fwd_B << (3 * n->fwd_lg)) >> (3 * depth[index]);
     const size_t elems = vox * ch[index];
     if (count != (int64_t)elems) return set_error(MGFR_ERR_ARG, "count does not match the activation's size");
+    // the convolutions read a concatenation from its two sources: form it here
+    if (index == 9)
+        k_concat_up<<<gridn(vox * 12), 256, 0, n->stream>>>(n->h3, 64, n->s2, 32, n->fwd_lg - 1, vox, n->cat4);
+    if (index == 12)
+        k_concat_up<<<gridn(vox * 6), 256, 0, n->stream>>>(n->h4, 32, n->s1, 16, n->fwd_lg, vox, n->cat5);
+    MGFR_HIP(hipGetLastError());
     const void *src = index == 15 ? (const void *)n->y32 : (const void *)buf[index];
     const size_t esz = index == 15 ? sizeof(float) : sizeof(__bf16);
     MGFR_HIP(hipMemcpyAsync(dst, src, elems * esz, hipMemcpyDeviceToDevice, n->stream));
@@ -1237,7 +1286,7 @@ extern "C" int mgfr_conv3d_fwd(const void *x, int B, int S, int Cin, const void 
     if ((rc = conv_args(B, S, Cin, Cout, &lgS))) return rc;
     if (!x || !w || (!y && !y32)) return set_error(MGFR_ERR_ARG, "x, w and an output must be non-NULL");
     const size_t V = (size_t)B << (3 * lgS);
-    launch_conv3d((const __bf16 *)x, V, lgS, Cin, (const __bf16 *)w, bias, Cout, relu, nullptr, (__bf16 *)y, y32,
+    launch_conv3d({(const __bf16 *)x, Cin}, V, lgS, (const __bf16 *)w, bias, Cout, relu, nullptr, (__bf16 *)y, y32,
                   (hipStream_t)stream);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
@@ -1253,8 +1302,8 @@ extern "C" int mgfr_conv3d_bwd_data(const void *dz, int B, int S, int Cout, cons
     hipStream_t s = (hipStream_t)stream;
     k_wt_transpose<<<gridn((size_t)27 * Cin * Cout), 256, 0, s>>>((const __bf16 *)w, Cin, Cout, (__bf16 *)wt_work);
     const size_t V = (size_t)B << (3 * lgS);
-    launch_conv3d((const __bf16 *)dz, V, lgS, Cout, (const __bf16 *)wt_work, nullptr, Cin, 0, nullptr, (__bf16 *)dx,
-                  nullptr, s);
+    launch_conv3d({(const __bf16 *)dz, Cout}, V, lgS, (const __bf16 *)wt_work, nullptr, Cin, 0, nullptr,
+                  (__bf16 *)dx, nullptr, s);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }
@@ -1268,7 +1317,7 @@ extern "C" int mgfr_conv3d_bwd_weight(const void *x, const void *dz, int B, int 
     if (!x || !dz || !dw) return set_error(MGFR_ERR_ARG, "null argument");
     hipStream_t s = (hipStream_t)stream;
     const size_t V = (size_t)B << (3 * lgS);
-    launch_wgrad((const __bf16 *)x, (const __bf16 *)dz, V, lgS, Cin, Cout, dw, db, s);
+    launch_wgrad({(const __bf16 *)x, Cin}, (const __bf16 *)dz, V, lgS, Cout, dw, db, s);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }

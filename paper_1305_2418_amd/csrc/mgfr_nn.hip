@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * kConvWaves) void k_conv3d(const __bf16 *__rest
 // side) followed by the Cs channels of skip.  A chunk of channels comes from one
 // of the two (C is a multiple of it), so that no concatenated copy is written
 // (62 us of the 556 us of a 128^3 prediction, and the copies were read from HBM:
-// 48 -> 16 channels 145 -> 124 us, its weight gradient 213 -> 165 us).
+// 48 -> 16 channels 145 -> 124 us then, its weight gradient 213 -> 165 us).
 struct ConvIn {
     const __bf16 *x;
     int C;
@@ -234,15 +234,19 @@ __device__ __forceinline__ size_t conv_voxel(const ConvSrc &s, size_t vol, int z
 // a staging write, take 256 contiguous bytes.  The address of every fragment is a
 // per-lane base (for CK = 16 one of three: the distance of a k-step's two taps
 // takes three values) plus a constant.
-// Bound: LDS reads, 8 cycles per CU and MFMA against 4 of the matrix cores.
+// Fragments are shared between the rows (CK = 32: an input row's three serve three
+// output rows, 30 reads of LDS for 72 products) or planes (CK = 16) of a wave.
+// Bound: the halo traffic and the staging between products; 16 -> 16 channels move
+// 134 MB of HBM in 40 us (3.3 TB/s) with the matrix cores a third busy.
 // us, before (weights from L1 in every k-step, two-way bank conflicts, no loads in
 // flight during the products, two-byte stores) and now, 2.1 M voxels: 16 -> 16
-// channels 110, 42; 48 -> 16 340, 124; 16 -> 48 176, 143; 262144 voxels: 16 -> 32
-// 25, 16; 32 -> 32 46, 23; 96 -> 32 120, 61; 32 -> 96 114, 57; 32 -> 16 41, 16;
-// 32768 voxels: 32 -> 64 22, 9.6; 64 -> 64 39, 22; 64 -> 32 34, 15.
+// channels 110, 40; 48 -> 16 340, 111; 16 -> 48 176, 127; 262144 voxels: 16 -> 32
+// 25, 14; 32 -> 32 46, 20; 96 -> 32 120, 50; 32 -> 96 114, 45; 32 -> 16 41, 15;
+// 32768 voxels: 32 -> 64 22, 7.7; 64 -> 64 39, 17; 64 -> 32 34, 14.
 template <int CK, int NT, int TZ, bool MASK, bool SKIP>
 __global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const __bf16 *__restrict__ W,
-                                                     const float *__restrict__ bias, int Cout, int relu, const __bf16 *__restrict__ M, unsigned ntiles,
+                                                     const float *__restrict__ bias, int Cout, int relu,
+                                                     const __bf16 *__restrict__ M, unsigned ntiles,
                                                      __bf16 *__restrict__ Y, float *__restrict__ Y32)
 {
     constexpr int MT = 2 * TZ * NT, HX = 18, HY = 10, HV = HX * HY * (TZ + 2), Q = CK / 8, HP = (HV + 15) / 16 * 16;
@@ -256,7 +260,11 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const _
     const int g = lane >> 4, r16 = lane & 15;
     const int S = 1 << lgS, sm = S - 1;
     const unsigned ntx = (unsigned)S / 16, nty = (unsigned)S / 8, ntz = (unsigned)S / TZ;
-    const int row0 = (w / NT) * MT, wz = row0 >> 3, wy = row0 & 7;  // first row of this wave
+    // this wave's rows: with PAIR rows 2 w and 2 w + 1 of every plane, else whole planes or half of one
+    constexpr bool PAIR = CK == 16 && NT == 1 && TZ == 4 && !MASK;
+    const int row0 = (w / NT) * MT, wz = PAIR ? 0 : row0 >> 3, wy = PAIR ? 2 * w : row0 & 7;
+    auto rowz = [](int mt) { return PAIR ? mt >> 1 : mt >> 3; };
+    auto rowy = [](int mt) { return PAIR ? mt & 1 : mt & 7; };
     const int o0 = 16 * ((int)blockIdx.y * NT + w % NT);            // its output channels
     const __bf16 *p0 = sX + ((g & (Q - 1)) * HP + (wz * HY + wy) * HX + r16) * 8;
     // CK = 16, k-step k: voxel offset of tap 2 k, for lanes of g >= 2 that of tap 2 k + 1
@@ -274,24 +282,37 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const _
         z0 = (int)(tile % ntz) * TZ;
         vol = (size_t)(tile / ntz) << (3 * lgS);
     };
-    // staging: this thread's pieces are part pq of voxels pv + 256 / Q i
+    // staging: this thread's pieces are part pq of voxels pv + 256 / Q i of the halo
+    // block, whose coordinates mod S are kept packed as z, y, x fields of lgS bits
     const int pq = (tid >> 4) & (Q - 1), pv = ((tid >> 4) / Q) * 16 + (tid & 15);
     __bf16 *pst = sX + (pq * HP + pv) * 8;
+    const unsigned top = (1u | 1u << lgS | 1u << (2 * lgS)) << (lgS - 1);  // highest bit of each field
+    unsigned pc[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int v = min(pv + 256 / Q * i, HV - 1);
+        const int vx = v % HX, vy = (v / HX) % HY, vz = v / (HX * HY);
+        pc[i] = (((((unsigned)(vz & sm)) << lgS) | (unsigned)(vy & sm)) << lgS) | (unsigned)(vx & sm);
+    }
     bf16x8 st[NP];
     auto fetch = [&](unsigned tile, int cc0) {
         int x0, y0, z0;
         size_t vol;
         origin(tile, x0, y0, z0, vol);
         const ConvSrc from = SKIP ? conv_src(in, cc0) : ConvSrc{in.x + cc0, in.C, 0};
-        const __bf16 *x = from.x + 8 * pq;
-        int v0 = pv;
-        asm volatile("" : "+v"(v0));  // coordinates are formed anew: kept for all pieces they spill
+        const __bf16 *x = from.x + (vol >> (3 * from.sh)) * from.C;
+        const unsigned og = (((((unsigned)((z0 - 1) & sm)) << lgS) | (unsigned)((y0 - 1) & sm)) << lgS) |
+                            (unsigned)((x0 - 1) & sm);
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const int v = min(v0 + 256 / Q * i, HV - 1);
-            const int vx = v % HX, vy = (v / HX) % HY, vz = v / (HX * HY);
-            st[i] = *(const bf16x8 *)(x + conv_voxel(from, vol, (z0 + vz - 1) & sm, (y0 + vy - 1) & sm,
-                                                     (x0 + vx - 1) & sm, lgS) * from.C);
+            // the fields' sums mod S: carries stop below the highest bits, which add without
+            unsigned r = ((pc[i] & ~top) + (og & ~top)) ^ ((pc[i] ^ og) & top);
+            if (SKIP && from.sh) {
+                const int lc = lgS - 1;
+                r = ((((r >> (2 * lgS + 1)) << lc) | ((r >> (lgS + 1)) & (unsigned)(sm >> 1))) << lc) |
+                    ((r >> 1) & (unsigned)(sm >> 1));
+            }
+            st[i] = *(const bf16x8 *)(x + (size_t)r * from.C + 8 * pq);
         }
     };
     bf16x8 b[NK];
@@ -306,12 +327,24 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const _
             if (last) b[k] = pad ? bf16x8{} : b[k];
         }
     };
+    const unsigned lo = (unsigned)(r16 * Cout + 4 * g);  // this lane's place in an output row
     if (Cin == CK) weights(0);
     if (blockIdx.x < ntiles) fetch(blockIdx.x, 0);
     for (unsigned tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         f32x4 acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int x0, y0, z0;
+        size_t vol;
+        origin(tile, x0, y0, z0, vol);
+        auto out_row = [&](int mt) {  // uniform
+            return (vol + ((((size_t)(z0 + wz + rowz(mt)) << lgS) + (size_t)(y0 + wy + rowy(mt))) << lgS) + (size_t)x0) *
+                       Cout + o0;
+        };
+        bf16x4 m[MT] = {};
+        if (MASK && CK == 16)  // in flight during the products (for CK = 32 the registers do not allow it)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) m[mt] = *(const bf16x4 *)(M + out_row(mt) + lo);
         for (int cc0 = 0; cc0 < Cin; cc0 += CK) {
             if (Cin > CK) weights(cc0);
             __syncthreads();  // the previous block's readers are done
@@ -323,38 +356,96 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const _
             const bool more = cc0 + CK < Cin;
             const unsigned next = more ? tile : tile + gridDim.x;
             if (next < ntiles) fetch(next, more ? cc0 + CK : 0);
+            if constexpr (CK == 32) {
+                // Input row by input row: its three fragments (dx) serve the rows y
+                // - dy of the wave; every row's sum still runs over dz, dy, dx in turn
+                constexpr int RY = MT == 8 ? 8 : MT, IR = RY + 2;
+                bf16x8 f[2][3];
+                auto rowload = [&](int r, bf16x8 *d) {
 #pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                if (CK == 32 && MT == 8) __builtin_amdgcn_sched_barrier(0);  // reads of later k-steps would spill
-                const int t = CK == 16 ? 2 * k : k;  // compile-time: the loop is unrolled
-                const __bf16 *q = (CK == 32 || t == 26 ? p0 : pb[t % 3 != 2 ? 0 : t % 9 != 8 ? 1 : 2]) +
-                                  (((t / 9) * HY + (t / 3) % 3) * HX + t % 3) * 8;
+                    for (int dx = 0; dx < 3; ++dx)
+                        d[dx] = *(const bf16x8 *)(p0 + (((r / IR) * HY + r % IR) * HX + dx) * 8);
+                };
+                rowload(0, f[0]);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    bf16x8 a = *(const bf16x8 *)(q + ((mt >> 3) * HY + (mt & 7)) * HX * 8);
-                    if (CK == 16 && k == NK - 1) a = pad ? bf16x8{} : a;
-                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], a, acc[mt], 0, 0, 0);
+                for (int r = 0; r < 3 * IR; ++r) {
+                    __builtin_amdgcn_sched_barrier(0);  // reads of later rows would spill (and 10 % slower without)
+                    if (r + 1 < 3 * IR) rowload(r + 1, f[(r + 1) & 1]);
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                        for (int dy = 0; dy < 3; ++dy) {
+                            const int y = r % IR - dy;
+                            if (y >= 0 && y < RY)
+                                acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[(r / IR) * 9 + dy * 3 + dx], f[r & 1][dx],
+                                                                                 acc[y], 0, 0, 0);
+                        }
+                }
+            } else if constexpr (PAIR) {
+                // Input plane by input plane: fragments of taps (dx 0, 1), (1, 2) and (2, 0 of
+                // the next row) serve up to three planes of the wave; every row's sum still
+                // runs over the k-steps in turn
+                auto frag = [&](const __bf16 *base, int zi, int y, int dx) {
+                    return *(const bf16x8 *)(base + ((zi * HY + y) * HX + dx) * 8);
+                };
+                auto mul = [&](int k, const bf16x8 &a, int z, int y) {
+                    acc[2 * z + y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], a, acc[2 * z + y], 0, 0, 0);
+                };
+#pragma unroll
+                for (int zi = 0; zi < TZ + 2; ++zi) {
+                    bf16x8 A[4], B[3], C[4], D[2] = {}, E[2] = {};
+                    const bool top = zi < TZ, mid = zi > 0 && zi <= TZ, bot = zi > 1;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        A[r] = frag(pb[0], zi, r, 0);
+                        C[r] = frag(pb[0], zi, r, 1);
+                        if (r < 3) B[r] = frag(pb[1], zi, r, 2);
+                    }
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        if (top) D[y] = frag(pb[2], zi, y + 2, 2);
+                        if (bot) E[y] = pad ? bf16x8{} : frag(p0, zi, y + 2, 2);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 5; ++i)
+#pragma unroll
+                        for (int y = 0; y < 2; ++y) {
+                            const bf16x8 t = i == 0 ? A[y] : i == 1 ? B[y] : i == 2 ? C[y + 1] : i == 3 ? A[y + 2] : D[y];
+                            const bf16x8 m = i == 0 ? C[y] : i == 1 ? A[y + 1] : i == 2 ? B[y + 1] : C[y + 2];
+                            const bf16x8 o = i == 0 ? A[y] : i == 1 ? B[y] : i == 2 ? C[y + 1] : i == 3 ? A[y + 2] : E[y];
+                            if (top) mul(i, t, zi, y);
+                            if (mid && i < 4) mul(5 + i, m, zi - 1, y);
+                            if (bot) mul(9 + i, o, zi - 2, y);
+                        }
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < NK; ++k) {
+                    const int t = 2 * k;  // compile-time: the loop is unrolled
+                    const __bf16 *q = (t == 26 ? p0 : pb[t % 3 != 2 ? 0 : t % 9 != 8 ? 1 : 2]) +
+                                      (((t / 9) * HY + (t / 3) % 3) * HX + t % 3) * 8;
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        bf16x8 a = *(const bf16x8 *)(q + mt * HX * 8);
+                        if (k == NK - 1) a = pad ? bf16x8{} : a;
+                        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[k], a, acc[mt], 0, 0, 0);
+                    }
                 }
             }
         }
-        int x0, y0, z0;
-        size_t vol;
-        origin(tile, x0, y0, z0, vol);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const size_t v = vol + ((((size_t)(z0 + wz + (mt >> 3)) << lgS) + (size_t)(y0 + wy + (mt & 7))) << lgS) +
-                             (size_t)(x0 + r16);
+            const size_t row = out_row(mt);
             float o[4];
-            bf16x4 m = {};
-            if (MASK) m = *(const bf16x4 *)(M + v * Cout + o0 + 4 * g);
+            if (MASK && CK == 32) m[mt] = *(const bf16x4 *)(M + row + lo);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 o[j] = acc[mt][j] + bo[j];
                 if (relu) o[j] = fmaxf(o[j], 0.f);
-                if (MASK && !(bf2f(m[j]) > 0.f)) o[j] = 0.f;
+                if (MASK && !(bf2f(m[mt][j]) > 0.f)) o[j] = 0.f;
             }
-            if (Y) *(bf16x4 *)(Y + v * Cout + o0 + 4 * g) = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
-            if (Y32) *(f32x4 *)(Y32 + v * Cout + o0 + 4 * g) = f32x4{o[0], o[1], o[2], o[3]};
+            if (Y) *(bf16x4 *)(Y + row + lo) = bf16x4{f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3])};
+            if (Y32) *(f32x4 *)(Y32 + row + lo) = f32x4{o[0], o[1], o[2], o[3]};
         }
     }
 }

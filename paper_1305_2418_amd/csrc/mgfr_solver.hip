@@ -774,6 +774,89 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs A)
 
 static inline unsigned nblocks(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
+// ------------------------------------------------- small levels, several half-sweeps
+//
+// H half-sweeps (2: one red-black sweep, 4: two) of the 32^3 or 64^3 level in one
+// launch, out of place.  A workgroup owns 4 x 4 rows of the mesh and holds them
+// with H rows on every side in LDS as (u, e^u): each half-sweep updates one row
+// less on every side, so that the cells of the tile end with the values that H
+// launches of one colour each would give, and no workgroup waits for another.
+// A row's even cells lie before its odd ones: the lanes of an access take
+// consecutive 16-byte places.
+// Bound: float64 arithmetic, the surrounding rows included (1.6 times the cells'
+// updates for H = 2, 3.4 for H = 4), and the latency of a launch.  One launch per
+// colour took 3.5-3.9 us and the gap to the next: 32^3, two sweeps 4 x 3.5 -> 7.1 us
+// (H = 2 twice: 8.8); 64^3, one sweep 2 x 3.9 -> 5.9 us.
+template <bool N1, int LG, int H>
+__global__ __launch_bounds__(1024) void k_sweep_tile(const double *__restrict__ u, const double *__restrict__ f,
+                                                     double *__restrict__ out, OpConst kc)
+{
+    constexpr int N = 1 << LG, M = N - 1, E = 4 + 2 * H, HALF = N / 2, NT = 1024;
+    __shared__ double2 ue[E * E * N];
+    MGFR_EXP_TABLE_TO_LDS(kc);
+    const int t = threadIdx.x;
+    const int i0 = 4 * (int)(blockIdx.x / (N / 4)) - H, j0 = 4 * (int)(blockIdx.x % (N / 4)) - H;
+    auto slot = [](int i, int j, int k) { return ((i * E + j) << LG) + (k & 1) * HALF + (k >> 1); };
+    auto cell = [&](int i, int j, int k) {
+        return ((((size_t)((i0 + i) & M) << LG) + (size_t)((j0 + j) & M)) << LG) + (size_t)k;
+    };
+    // the cell of thread t, round q, of half-sweep h: (4 + 2 m)^2 rows of N / 2 cells, m = H - 1 - h
+    auto place = [&](int h, int q, int &i, int &j, int &k) {
+        const int m = H - 1 - h, D = 4 + 2 * m, e = t + q * NT, row = e / HALF;
+        i = H - m + row / D;
+        j = H - m + row % D;
+        k = 2 * (e % HALF) + ((i0 + i + j0 + j + h) & 1);
+        return row < D * D;
+    };
+    constexpr int R = ((4 + 2 * (H - 1)) * (4 + 2 * (H - 1)) * HALF + NT - 1) / NT;  // rounds of the first half-sweep
+    double fv[H][R];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            int i, j, k;
+            fv[h][q] = place(h, q, i, j, k) ? f[cell(i, j, k)] : 0.0;
+        }
+#pragma unroll
+    for (int q = 0; q < (E * E * N + NT - 1) / NT; ++q) {
+        const int e = t + q * NT, r = e >> LG, k = e & M;
+        if (r < E * E) {
+            const double x = u[cell(r / E, r % E, k)];
+            ue[slot(r / E, r % E, k)] = make_double2(x, exp64(x, kc.tab));
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            int i, j, k;
+            if (place(h, q, i, j, k)) {
+                const int c = slot(i, j, k), side = ((i * E + j) << LG) + (1 - (k & 1)) * HALF;
+                ue[c] = tail_update<N1, LG>(ue[c], ue[c + E * N], ue[c - E * N], ue[c + N], ue[c - N],
+                                            ue[side + (((k + 1) & M) >> 1)], ue[side + (((k - 1) & M) >> 1)], fv[h][q], kc);
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < (16 * N + NT - 1) / NT; ++q) {
+        const int e = t + q * NT, r = e >> LG, k = e & M;
+        if (r < 16) out[cell(H + (r >> 2), H + (r & 3), k)] = ue[slot(H + (r >> 2), H + (r & 3), k)].x;
+    }
+}
+
+template <int LG, int H>
+static void launch_tile(mgfr_ctx *c, Level &L, const double *f, const OpConst &kc)
+{
+    const unsigned nb = (unsigned)((L.N / 4) * (L.N / 4));
+    if (c->p.n == 1)
+        k_sweep_tile<true, LG, H><<<nb, 1024, 0, c->stream>>>(L.u, f, L.alt, kc);
+    else
+        k_sweep_tile<false, LG, H><<<nb, 1024, 0, c->stream>>>(L.u, f, L.alt, kc);
+    std::swap(L.u, L.alt);
+}
+
 static int timer_slot(mgfr_ctx *c, int *slot)
 {
     Timer &T = c->sweep_timer;
@@ -817,6 +900,10 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
     Level &L = c->lev[l];
     OpConst kc = level_const(c, l);
     const bool fused = c->fused_min_n > 0 && L.N >= c->fused_min_n && L.alt != nullptr;
+    // 32^3 and 64^3: see k_sweep_tile.  Two sweeps in one launch on 32^3 (7.1 us
+    // against 8.8 for two launches, 64 workgroups), not on 64^3, whose 256
+    // workgroups then redo more than the launch saves (13.3 us against 11.8)
+    const bool tile = !fused && c->fused_min_n > 0 && (L.N == 32 || L.N == 64) && L.alt != nullptr;
     const size_t half = (size_t)1 << (3 * L.lg - 1);
     for (int s = 0; s < sweeps; ++s) {
         int slot = -1;
@@ -835,6 +922,15 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
             else
                 k_sweep_rows<false><<<nb, 64 * (kRowF + 1), 0, c->stream>>>(A);
             std::swap(L.u, L.alt);
+        } else if (tile) {
+            if (L.N == 64) {
+                launch_tile<6, 2>(c, L, f, kc);
+            } else if (!timed && s + 1 < sweeps) {  // timing counts one sweep per launch
+                launch_tile<5, 4>(c, L, f, kc);
+                ++s;
+            } else {
+                launch_tile<5, 2>(c, L, f, kc);
+            }
         } else {
             for (int colour = 0; colour < 2; ++colour)
                 k_sweep_half<<<nblocks(half), kBlock, 0, c->stream>>>(L.u, f, L.lg, colour, kc);
@@ -1033,7 +1129,7 @@ static int create_impl(const mgfr_params *p, void *stream, mgfr_ctx *c)
             MGFR_HIP(hipMalloc(&L.u, bytes));
             MGFR_HIP(hipMalloc(&L.ubar, bytes));
         }
-        if (n >= 64) {  // second buffer for out-of-place fused sweeps
+        if (n >= 32) {  // second buffer for out-of-place sweeps
             MGFR_HIP(hipMalloc(&L.alt, bytes));
             if (l == 0) c->alt0 = L.alt;
         }

@@ -563,3 +563,24 @@ def test_fused_solve_matches_oracle(N, pre, post, fr0):
     s2.set_fused_min_mesh(0)
     u2, dfr2, st2 = s2.solve(torch.tensor(d, device=DEV), allow_not_converged=True)
     assert _rel(dfr.cpu().numpy(), dfr2.cpu().numpy()) < 1e-10
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("N,sweeps", [(32, 1), (32, 2), (32, 3), (64, 1), (64, 2), (64, 5)])
+def test_tile_sweeps_match_one_colour_kernels(N, sweeps, n):
+    """The sweeps of the 32^3 and 64^3 levels that a workgroup makes on its tile
+    and the rows around it, against one launch per colour on a rough field: one
+    sweep per launch and two, odd and even counts (the result in either buffer).
+    The same update formula with another order of six-term sums: a few 1e-16 of
+    O(1) values per sweep."""
+    mg = _mg()
+    print(f"[case] tile sweeps N={N} sweeps={sweeps} n={n}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(10 * N + sweeps + n)
+    u0 = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * 0.7 - 1.0
+    f = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * 5.0
+    out = []
+    for fused in (128, 0):
+        s = mg.Solver(_params(mg, N, fr0_abs=1e-6, n=n))
+        s.set_fused_min_mesh(fused)
+        out.append(s.ngs_sweep(u0.clone(), f, sweeps))
+    assert float((out[0] - out[1]).abs().max()) < 1e-13

@@ -132,8 +132,10 @@ int mgfr_set_timing(mgfr_ctx *ctx, int on);
 
 /* Float64 sweeps: smallest level size N at which a red-black sweep runs as
  * one fused, out-of-place kernel (both colours per launch, LDS-staged tiles);
- * smaller levels use one in-place kernel per colour.  Default 128; 0 = never;
- * otherwise n >= 64.  Results agree to rounding either way. */
+ * the 32^3 and 64^3 levels below it make one or two sweeps per launch on tiles,
+ * smaller ones use one in-place kernel per colour.  Default 128; 0 = one kernel
+ * per colour on every level; otherwise n >= 64.  Results agree to rounding
+ * either way. */
 int mgfr_set_fused_min_mesh(mgfr_ctx *ctx, int n);
 
 /* Float32 correction sweeps of the mixed-precision solve: smallest level size
@@ -149,7 +151,8 @@ int mgfr_set_colour_min_mesh(mgfr_ctx *ctx, int n);
  * (Sec. 3.3) of levels with N >= 256 as one fused, out-of-place kernel that
  * updates the red cells of plane i + 1 and the black cells of plane i - 1 while
  * marching over the planes, so that e, u and r are read once per sweep instead
- * of once per colour; on = 0 runs one pass kernel per colour.  The same updates
+ * of once per colour; the 32^3 and 64^3 levels make one or two sweeps per launch
+ * on tiles; on = 0 runs one kernel per colour on every level.  The same updates
  * in the same order: the same iterates, bit for bit.  The second correction
  * buffer is allocated by mgfr_create for mixed-precision contexts, so this
  * call allocates nothing.  Errors: MGFR_ERR_ARG for on not 0 or 1. */

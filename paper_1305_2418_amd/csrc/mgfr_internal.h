@@ -36,7 +36,7 @@ struct Level {
     double *alt = nullptr;  // second buffer of out-of-place sweeps (current iterate is u)
     // float32 mirrors for the mixed-precision inner cycle
     float *e32 = nullptr, *r32 = nullptr, *u32 = nullptr, *ebar32 = nullptr;
-    float *e32alt = nullptr;  // second e buffer of the fused float32 sweep (levels with N >= 128)
+    float *e32alt = nullptr;  // second e buffer of the out-of-place float32 sweeps (levels with N >= 32)
 };
 
 struct Timer {

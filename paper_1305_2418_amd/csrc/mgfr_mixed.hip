@@ -839,6 +839,80 @@ __global__ __launch_bounds__(kBlock) void k_mx_sweep_half(float *__restrict__ e,
     mx_sweep_cell(e, u, r, (size_t)blockIdx.x * kBlock + threadIdx.x, lg, colour, kc);
 }
 
+// H half-sweeps of the 32^3 or 64^3 level in one launch, out of place: the
+// geometry of the float64 k_sweep_tile, cells in LDS as {e, X, u, w}.  Each update
+// is that of k_mx_sweep_half, bit by bit.
+// Bound: the launch's latency and the updates, the surrounding rows included.
+// 32^3, two sweeps: four launches of 3.4 us (and the gaps) -> 5.9 us; 64^3, one
+// sweep: two of 3.5 us -> 4.7 us (two sweeps per launch: 10.3 us).
+template <int LG, int H>
+__global__ __launch_bounds__(1024) void k_mx_sweep_tile(const float *__restrict__ e, const float *__restrict__ u,
+                                                        const float *__restrict__ r, float *__restrict__ out, MxConst kc)
+{
+    constexpr int N = 1 << LG, M = N - 1, E = 4 + 2 * H, HALF = N / 2, NT = 1024;
+    __shared__ float4 sc[E * E * N];
+    const int t = threadIdx.x;
+    const int i0 = 4 * (int)(blockIdx.x / (N / 4)) - H, j0 = 4 * (int)(blockIdx.x % (N / 4)) - H;
+    auto slot = [](int i, int j, int k) { return ((i * E + j) << LG) + (k & 1) * HALF + (k >> 1); };
+    auto cell = [&](int i, int j, int k) { return ix((i0 + i) & M, (j0 + j) & M, k, LG); };
+    // the cell of thread t, round q, of half-sweep h: (4 + 2 m)^2 rows of N / 2 cells, m = H - 1 - h
+    auto place = [&](int h, int q, int &i, int &j, int &k) {
+        const int m = H - 1 - h, D = 4 + 2 * m, c = t + q * NT, row = c / HALF;
+        i = H - m + row / D;
+        j = H - m + row % D;
+        k = 2 * (c % HALF) + ((i0 + i + j0 + j + h) & 1);
+        return row < D * D;
+    };
+    constexpr int R = ((4 + 2 * (H - 1)) * (4 + 2 * (H - 1)) * HALF + NT - 1) / NT;  // rounds of the first half-sweep
+    float rv[H][R];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            int i, j, k;
+            rv[h][q] = place(h, q, i, j, k) ? r[cell(i, j, k)] : 0.f;
+        }
+#pragma unroll
+    for (int q = 0; q < (E * E * N + NT - 1) / NT; ++q) {
+        const int c = t + q * NT, row = c >> LG, k = c & M;
+        if (row < E * E) {
+            const size_t g = cell(row / E, row % E, k);
+            const float ec = e[g], uc = u[g];
+            sc[slot(row / E, row % E, k)] = make_float4(ec, fexpm1(ec), uc, fexp(uc));
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            int i, j, k;
+            if (place(h, q, i, j, k)) {
+                const int c = slot(i, j, k), side = ((i * E + j) << LG) + (1 - (k & 1)) * HALF;
+                const float4 x = sc[c];
+                const float4 n[6] = {sc[c + E * N], sc[c - E * N], sc[c + N], sc[c - N],
+                                     sc[side + (((k + 1) & M) >> 1)], sc[side + (((k - 1) & M) >> 1)]};
+                float en[6], Xn[6], un[6], wn[6];
+#pragma unroll
+                for (int s = 0; s < 6; ++s) {
+                    en[s] = n[s].x;
+                    Xn[s] = n[s].y;
+                    un[s] = n[s].z;
+                    wn[s] = n[s].w;
+                }
+                const float ne = x.x + mx_step(x.x, x.y, x.z, x.w, en, Xn, un, wn, rv[h][q], kc);
+                sc[c] = make_float4(ne, fexpm1(ne), x.z, x.w);
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < (16 * N + NT - 1) / NT; ++q) {
+        const int c = t + q * NT, row = c >> LG, k = c & M;
+        if (row < 16) out[cell(H + (row >> 2), H + (row & 3), k)] = sc[slot(H + (row >> 2), H + (row & 3), k)].x;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_mx_residual_restrict(const float *__restrict__ e,
                                                                    const float *__restrict__ u,
                                                                    const float *__restrict__ r, int lg, MxConst kc,
@@ -1400,6 +1474,8 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
     const MxConst kc = mx_const(c, l);
     const size_t half = (size_t)1 << (3 * L.lg - 1);
     const bool colour_pass = split_level(c, l);
+    // one sweep of 64^3 or two of 32^3 per launch: see k_mx_sweep_tile
+    const bool tile = c->fused32 && (L.N == 32 || L.N == 64) && L.e32alt != nullptr;
     int slot, rc;
     for (int s = 0; s < sweeps; ++s) {
         if (colour_pass && c->fused32 && L.N >= kFusedMin32) {
@@ -1430,6 +1506,19 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
                 k_mx_colour<<<nb, 64 * (CTJ + 2), 0, c->stream>>>(A);
                 if ((rc = timer_end(c, slot))) return rc;
             }
+        } else if (tile) {
+            const unsigned nbt = (unsigned)((L.N / 4) * (L.N / 4));
+            const bool two = L.N == 32 && s + 1 < sweeps;
+            if ((rc = timer_slot(c, timed, slot))) return rc;
+            if (L.N == 64)
+                k_mx_sweep_tile<6, 2><<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc);
+            else if (two)
+                k_mx_sweep_tile<5, 4><<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc);
+            else
+                k_mx_sweep_tile<5, 2><<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc);
+            if ((rc = timer_end(c, slot))) return rc;
+            std::swap(L.e32, L.e32alt);
+            if (two) ++s;
         } else {
             for (int colour = 0; colour < 2; ++colour) {
                 if ((rc = timer_slot(c, timed, slot))) return rc;
@@ -1505,7 +1594,7 @@ int mixed_alloc(mgfr_ctx *c)
         MGFR_HIP(hipMalloc(&L.r32, bytes));
         MGFR_HIP(hipMalloc(&L.u32, bytes));
         if (l > 0) MGFR_HIP(hipMalloc(&L.ebar32, bytes));
-        if (L.N >= CKW) MGFR_HIP(hipMalloc(&L.e32alt, bytes));
+        if (L.N >= 32) MGFR_HIP(hipMalloc(&L.e32alt, bytes));
     }
     return MGFR_OK;
 }

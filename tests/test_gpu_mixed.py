@@ -154,6 +154,27 @@ def test_fused_sweep_gives_the_colour_passes_bits(N, n, pre, post):
     assert torch.equal(out[0], out[1])
 
 
+@pytest.mark.parametrize("N,n,pre,post", [(32, 1, 2, 2), (32, 2, 1, 3), (64, 1, 4, 4), (64, 2, 3, 2), (128, 1, 1, 2)])
+def test_tile_sweeps_give_the_one_colour_kernels_bits(N, n, pre, post):
+    """Two correction cycles with the 32^3 and 64^3 levels swept in tiles (one or
+    two sweeps per launch, the iterate in either buffer) and with one launch per
+    colour: the same operands in the same order, the same bits."""
+    from paper_1305_2418_amd import mgfr
+    print(f"[case] tile sweep bits N={N} n={n} pre={pre} post={post}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + n)
+    d = torch.exp(torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * 1.5)
+    d = d / d.mean() - 1.0
+    out = []
+    for fused in (True, False):
+        s = mgfr.Solver(mgfr.Params(mesh=N, fr0_abs=1e-6, n=n, precision=mgfr.MIXED, max_vcycles=2, pre_smooth=pre,
+                                    post_smooth=post))
+        s.set_relaxation32(1.2)
+        s.set_fused_sweep32(fused)
+        out.append(s.solve(d, want_dfr=False, allow_not_converged=True)[0])
+        del s
+    assert torch.equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("n", [1, 2])
 def test_mixed_with_all_options_matches_oracle(n):
     """The mixed solve with every option the benchmark or a hard case uses at

@@ -537,14 +537,17 @@ void launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, cons
 // within a k-step is free, as long as both operands use the same: the 16
 // lanes of a group and the two halves of a fragment are laid out so that one
 // load of a wave reads 16 consecutive voxels of a row (512 contiguous bytes,
-// no bank conflict).  Wave w accumulates the taps w, w + 4, ...; the 28th slot
-// is the bias gradient (a product with ones).  The sums stay in registers
-// over all tiles and are added to dW once per workgroup.
-// Bound: the LDS reads (two per MFMA, 8 LDS cycles against 16 / 4 matrix
-// cycles per CU) and the staging between barriers.  16 -> 16 channels on 2.1 M
-// voxels: 2163 -> 87 us (333 TFLOP/s); the ten layers of one gradient of eight
-// 64^3 volumes: 14.4 -> 0.78 ms (before: a scalar transpose into LDS for each
-// tap, atomics per 2048 voxels), and the separate bias pass's 3.9 ms are gone.
+// no bank conflict).  Wave w accumulates the columns of taps (dz, dx) number w,
+// w + 4, w + 8 (the fourth wave the bias gradient, a product with ones, beside its
+// two); the three taps dy of a column share their rows, so that a k-step reads two
+// new half fragments per column instead of six.  The sums stay in registers over
+// all tiles and are added to dW once per workgroup; the next tile is loaded into
+// registers during the products.
+// Bound: the traffic (16 -> 16 channels on 2.1 M voxels: 134 MB and the halos) and
+// the barriers around the staging.  That layer: 2163 us with a scalar transpose
+// into LDS per tap; 87 with transpose loads; 67 with the next tile in flight; 61
+// with shared rows (475 TFLOP/s).  The ten layers of one gradient of eight 64^3
+// volumes: 14.4 -> 0.52 ms, and a separate bias pass's 3.9 ms are gone.
 #ifndef MGFR_WG_SPLIT
 #define MGFR_WG_SPLIT 512
 #endif
@@ -553,10 +556,13 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-__device__ __forceinline__ bf16x8 tr_pair(const __bf16 *p0, const __bf16 *p1)
+__device__ __forceinline__ s16x4 tr_half(const __bf16 *p)
 {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p0);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p1);
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+}
+
+__device__ __forceinline__ bf16x8 join(s16x4 lo, s16x4 hi)
+{
     const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, v);
 }
@@ -584,75 +590,122 @@ __global__ __launch_bounds__(256) void k_conv3d_wgrad(ConvIn in, const __bf16 *_
     const int v0 = 4 * g + (r16 >> 2), c4 = 4 * (r16 & 3);
     const __bf16 *pz = sZ + v0 * 16 + c4;
     const __bf16 *px = sX + (((HY + 1 + (v0 >> LGX)) * HX) + 1 + (v0 & (TX - 1))) * 16 + c4;
-    f32x4 acc[7];
-    const __bf16 *pt[7];
+    // the wave's columns of taps (dz, dx): 9 over four waves; [..][dy]
+    const bool third = w == 0;
+    f32x4 acc[3][3] = {};
+    const __bf16 *pt[3];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const int t = w + 4 * q < 27 ? w + 4 * q : 0;
-        pt[q] = px + (((t / 9 - 1) * HY + ((t / 3) % 3 - 1)) * HX + (t % 3 - 1)) * 16;
+    for (int q = 0; q < 3; ++q) {
+        const int c = q < 2 || third ? w + 4 * q : 0;
+        pt[q] = px + ((c / 3 - 1) * HY * HX + (c % 3 - 1)) * 16;
     }
     const __bf16 one = (__bf16)1.0f;
     const bf16x8 ones = {one, one, one, one, one, one, one, one};
-    for (unsigned tile = blockIdx.y; tile < ntiles; tile += gridDim.y) {
-        unsigned b = tile;
+    // staging: 16-byte pieces, half h of voxel sv + 128 i of the tile (dZ) and of the
+    // halo block (X), the latter's coordinates mod S packed as z, y, x fields
+    constexpr int PZ = kWgTile * 2 / 256, PX = (HV * 2 + 255) / 256;
+    const int sv = tid >> 1, h8 = 8 * (tid & 1);
+    const unsigned zoff = (((((unsigned)sv >> (LGX + 3)) << lgS) + ((sv >> LGX) & 7)) << lgS) + (sv & (TX - 1));
+    const unsigned top = (1u | 1u << lgS | 1u << (2 * lgS)) << (lgS - 1);  // highest bit of each field
+    unsigned pc[PX];
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+        const int v = min(sv + 128 * i, HV - 1), x = v % HX, y = (v / HX) % HY, z = v / (HX * HY);
+        pc[i] = ((((unsigned)(z & sm) << lgS) | (unsigned)(y & sm)) << lgS) | (unsigned)(x & sm);
+    }
+    bf16x8 rz[PZ], rx[PX];
+    auto fetch = [&](unsigned b) {
         const int x0 = (int)(b % ntx) * TX;
         b /= ntx;
         const int y0 = (int)(b % nty) * 8;
         b /= nty;
         const int z0 = (int)(b % ntz) * TZ;
         const size_t vol = (size_t)(b / ntz) << (3 * lgS);
+        const size_t org = vol + ((((size_t)z0 << lgS) + (size_t)y0) << lgS) + (size_t)x0;
+        const __bf16 *z = dZ + org * Cout + o0, *x = from.x + (vol >> (3 * from.sh)) * from.C;
+        const unsigned og = ((((unsigned)((z0 - 1) & sm) << lgS) | (unsigned)((y0 - 1) & sm)) << lgS) |
+                            (unsigned)((x0 - 1) & sm);
+#pragma unroll
+        for (int i = 0; i < PZ; ++i)
+            rz[i] = *(const bf16x8 *)(z + ((size_t)(i * 16 / TX) << (2 * lgS)) * Cout + (size_t)zoff * Cout + h8);
+#pragma unroll
+        for (int i = 0; i < PX; ++i) {
+            // the fields' sums mod S: carries stop below the highest bits, which add without
+            unsigned r = ((pc[i] & ~top) + (og & ~top)) ^ ((pc[i] ^ og) & top);
+            if (from.sh) {
+                const int lc = lgS - 1;
+                r = ((((r >> (2 * lgS + 1)) << lc) | ((r >> (lgS + 1)) & (unsigned)(sm >> 1))) << lc) |
+                    ((r >> 1) & (unsigned)(sm >> 1));
+            }
+            rx[i] = *(const bf16x8 *)(x + (size_t)r * from.C + h8);
+        }
+    };
+    if (blockIdx.y < ntiles) fetch(blockIdx.y);
+    for (unsigned tile = blockIdx.y; tile < ntiles; tile += gridDim.y) {
         __syncthreads();  // the previous tile's readers are done
 #pragma unroll
-        for (int i = 0; i < kWgTile * 2 / 256; ++i) {
-            const int idx = tid + 256 * i, v = idx >> 1, h = idx & 1;
-            const int x = v & (TX - 1), y = (v >> LGX) & 7, z = v >> (LGX + 3);
-            const size_t src = vol + ((((size_t)(z0 + z) << lgS) + (size_t)(y0 + y)) << lgS) + (size_t)(x0 + x);
-            *(bf16x8 *)(sZ + v * 16 + 8 * h) = *(const bf16x8 *)(dZ + src * Cout + o0 + 8 * h);
-        }
+        for (int i = 0; i < PZ; ++i) *(bf16x8 *)(sZ + (sv + 128 * i) * 16 + h8) = rz[i];
 #pragma unroll
-        for (int i = 0; i < (HV * 2 + 255) / 256; ++i) {
-            const int idx = tid + 256 * i, v = idx >> 1, h = idx & 1;
-            if (v < HV) {
-                const int x = v % HX, y = (v / HX) % HY, z = v / (HX * HY);
-                const size_t src = conv_voxel(from, vol, (z0 + z - 1) & sm, (y0 + y - 1) & sm, (x0 + x - 1) & sm, lgS);
-                *(bf16x8 *)(sX + v * 16 + 8 * h) = *(const bf16x8 *)(from.x + src * from.C + 8 * h);
+        for (int i = 0; i < PX; ++i)
+            if (sv + 128 * i < HV) *(bf16x8 *)(sX + (sv + 128 * i) * 16 + h8) = rx[i];
+        __syncthreads();
+        if (tile + gridDim.y < ntiles) fetch(tile + gridDim.y);
+        // k-steps of 32 voxels: two halves of 16, each one row of 16 or two rows of 8
+        constexpr int RG = 16 / TX, KP = 4 / RG;  // rows per half, k-steps per plane
+        for (int z = 0; z < TZ; ++z) {
+            auto half = [&](int q, int row) { return tr_half(pt[q] + (z * HY + row) * HX * 16); };
+            s16x4 h[3][4];  // RG = 1: rows 2 ks - 1 .. 2 ks + 2 of each column
+            if constexpr (RG == 1) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (q < 2 || third) {
+                        h[q][2] = half(q, -1);
+                        h[q][3] = half(q, 0);
+                    }
+            }
+#pragma unroll
+            for (int ks = 0; ks < KP; ++ks) {
+                const __bf16 *za = pz + (z * KP + ks) * 512;
+                const bf16x8 a = join(tr_half(za), tr_half(za + 256));
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (q < 2 || third) {
+                        if constexpr (RG == 1) {
+                            h[q][0] = h[q][2];
+                            h[q][1] = h[q][3];
+                            h[q][2] = half(q, 2 * ks + 1);
+                            h[q][3] = half(q, 2 * ks + 2);
+                        }
+#pragma unroll
+                        for (int dy = 0; dy < 3; ++dy) {
+                            const bf16x8 x = RG == 1 ? join(h[q][dy], h[q][dy + 1])
+                                                     : join(half(q, 4 * ks + dy - 1), half(q, 4 * ks + dy + 1));
+                            acc[q][dy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x, acc[q][dy], 0, 0, 0);
+                        }
+                    }
+                if (bias) acc[2][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[2][0], 0, 0, 0);
             }
         }
-        __syncthreads();
-        // k-steps of 32 voxels: two groups of 16, each one row of 16 or two rows of 8
-#pragma unroll 4
-        for (int ks = 0; ks < kWgTile / 32; ++ks) {
-            constexpr int RG = 16 / TX;  // rows per group
-            const int r0 = 2 * ks * RG, r1 = r0 + RG;
-            const int off0 = ((r0 >> 3) * HY + (r0 & 7)) * HX * 16, off1 = ((r1 >> 3) * HY + (r1 & 7)) * HX * 16;
-            const bf16x8 a = tr_pair(pz + ks * 512, pz + ks * 512 + 256);
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-                acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, tr_pair(pt[q] + off0, pt[q] + off1), acc[q], 0, 0, 0);
-            if (w < 3)
-                acc[6] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, tr_pair(pt[6] + off0, pt[6] + off1), acc[6], 0, 0, 0);
-            else if (bias)
-                acc[6] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[6], 0, 0, 0);
-        }
     }
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        const int t = w + 4 * q;
+    for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int o = o0 + 4 * g + j;
-            if (t < 27) unsafeAtomicAdd(&dW[((size_t)t * Cout + o) * Cin + c0 + r16], acc[q][j]);
-            else if (bias && r16 == 0) unsafeAtomicAdd(&db[o], acc[q][j]);
+        for (int dy = 0; dy < 3; ++dy) {
+            const int c = w + 4 * q, t = (c / 3) * 9 + dy * 3 + c % 3;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int o = o0 + 4 * g + j;
+                if (c < 9) unsafeAtomicAdd(&dW[((size_t)t * Cout + o) * Cin + c0 + r16], acc[q][dy][j]);
+                else if (bias && dy == 0 && r16 == 0) unsafeAtomicAdd(&db[o], acc[q][dy][j]);
+            }
         }
-    }
 }
 
 // Launch k_conv3d_wgrad over nvox = B S^3 voxels (a multiple of 512: S >= 8).
 // Two workgroups per CU over all channel blocks: each adds a whole channel
 // block to dW with atomics, so more of them cost more than they hide (the ten
-// layers of a gradient of eight 64^3 volumes with 256, 512, 768, 1024
-// workgroups: 0.98, 0.78, 0.80, 0.91 ms).
+// layers of a gradient of eight 64^3 volumes with 512, 768 and 1024
+// workgroups: 0.60, 0.72 and 0.74 ms).
 void launch_wgrad(const ConvIn &in, const __bf16 *dZ, size_t nvox, int lgS, int Cout, float *dW, float *db,
                   hipStream_t s)
 {

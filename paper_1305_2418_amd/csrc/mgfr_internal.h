@@ -134,7 +134,7 @@ constexpr int kRowS = kRowW / 2 + 2;  // LDS slots per row: 64 lanes and the cel
 int row_chunk(int N, unsigned cols);
 
 // launch helpers implemented in mgfr_solver.hip
-int launch_sweep64(mgfr_ctx *c, int l, double *u, const double *f, int sweeps, bool timed);
+int launch_sweep64(mgfr_ctx *c, int l, double *u, const double *f, int sweeps, bool timed, const Level *from = nullptr);
 int launch_residual_norm64(mgfr_ctx *c, int l, const double *u, const double *f, double *rmax,
                            double *rsumsq);
 int vcycle64(mgfr_ctx *c, int l);

@@ -845,10 +845,14 @@ __global__ __launch_bounds__(kBlock) void k_mx_sweep_half(float *__restrict__ e,
 // Bound: the launch's latency and the updates, the surrounding rows included.
 // 32^3, two sweeps: four launches of 3.4 us (and the gaps) -> 5.9 us; 64^3, one
 // sweep: two of 3.5 us -> 4.7 us (two sweeps per launch: 10.3 us).
-template <int LG, int H>
+template <int LG, int H, bool PRO>
 __global__ __launch_bounds__(1024) void k_mx_sweep_tile(const float *__restrict__ e, const float *__restrict__ u,
-                                                        const float *__restrict__ r, float *__restrict__ out, MxConst kc)
+                                                        const float *__restrict__ r, float *__restrict__ out, MxConst kc,
+                                                        const float *__restrict__ ec, const float *__restrict__ eb,
+                                                        int mode)
 {
+    using P = TileProlong<float, LG, 4 + 2 * H>;
+    __shared__ float sd[PRO ? P::CELLS : 1];
     constexpr int N = 1 << LG, M = N - 1, E = 4 + 2 * H, HALF = N / 2, NT = 1024;
     __shared__ float4 sc[E * E * N];
     const int t = threadIdx.x;
@@ -872,13 +876,25 @@ __global__ __launch_bounds__(1024) void k_mx_sweep_tile(const float *__restrict_
             int i, j, k;
             rv[h][q] = place(h, q, i, j, k) ? r[cell(i, j, k)] : 0.f;
         }
+    constexpr int RL = (E * E * N + NT - 1) / NT;
+    float xe[RL], xu[RL];
 #pragma unroll
-    for (int q = 0; q < (E * E * N + NT - 1) / NT; ++q) {
+    for (int q = 0; q < RL; ++q) {
+        const int c = t + q * NT, row = c >> LG;
+        const size_t g = cell(row / E, row % E, c & M);  // in the mesh for any row
+        xe[q] = e[g];
+        xu[q] = u[g];
+    }
+    if constexpr (PRO) {
+        P::template load<NT>(sd, ec, eb, i0, j0);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < RL; ++q) {
         const int c = t + q * NT, row = c >> LG, k = c & M;
         if (row < E * E) {
-            const size_t g = cell(row / E, row % E, k);
-            const float ec = e[g], uc = u[g];
-            sc[slot(row / E, row % E, k)] = make_float4(ec, fexpm1(ec), uc, fexp(uc));
+            if (PRO) xe[q] += P::value(sd, row / E, row % E, k, mode);
+            sc[slot(row / E, row % E, k)] = make_float4(xe[q], fexpm1(xe[q]), xu[q], fexp(xu[q]));
         }
     }
     __syncthreads();
@@ -1468,14 +1484,21 @@ static int timer_end(mgfr_ctx *c, int slot)
     return MGFR_OK;
 }
 
-int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
+// 32^3 and 64^3, unless they run one kernel per colour: see k_mx_sweep_tile
+static bool tile_level(const mgfr_ctx *c, const Level &L)
+{
+    return c->fused32 && (L.N == 32 || L.N == 64) && L.e32alt != nullptr;
+}
+
+// With `from` (tile levels, at least one sweep) the correction of that coarser
+// level is added first.
+int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed, const Level *from = nullptr)
 {
     Level &L = c->lev[l];
     const MxConst kc = mx_const(c, l);
     const size_t half = (size_t)1 << (3 * L.lg - 1);
     const bool colour_pass = split_level(c, l);
-    // one sweep of 64^3 or two of 32^3 per launch: see k_mx_sweep_tile
-    const bool tile = c->fused32 && (L.N == 32 || L.N == 64) && L.e32alt != nullptr;
+    const bool tile = tile_level(c, L);  // one sweep of 64^3 or two of 32^3 per launch
     int slot, rc;
     for (int s = 0; s < sweeps; ++s) {
         if (colour_pass && c->fused32 && L.N >= kFusedMin32) {
@@ -1510,12 +1533,18 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed)
             const unsigned nbt = (unsigned)((L.N / 4) * (L.N / 4));
             const bool two = L.N == 32 && s + 1 < sweeps;
             if ((rc = timer_slot(c, timed, slot))) return rc;
+            auto go = [&](auto *plain, auto *prolong) {
+                (from ? prolong : plain)<<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc,
+                                                                      from ? from->e32 : nullptr,
+                                                                      from ? from->ebar32 : nullptr, c->p.prolong);
+            };
             if (L.N == 64)
-                k_mx_sweep_tile<6, 2><<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc);
+                go(k_mx_sweep_tile<6, 2, false>, k_mx_sweep_tile<6, 2, true>);
             else if (two)
-                k_mx_sweep_tile<5, 4><<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc);
+                go(k_mx_sweep_tile<5, 4, false>, k_mx_sweep_tile<5, 4, true>);
             else
-                k_mx_sweep_tile<5, 2><<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc);
+                go(k_mx_sweep_tile<5, 2, false>, k_mx_sweep_tile<5, 2, true>);
+            from = nullptr;
             if ((rc = timer_end(c, slot))) return rc;
             std::swap(L.e32, L.e32alt);
             if (two) ++s;
@@ -1578,9 +1607,12 @@ int mx_vcycle(mgfr_ctx *c, int l)
                                                       sc);
     MGFR_HIP(hipGetLastError());
     if ((rc = mx_vcycle(c, l + 1))) return rc;
-    k_mx_prolong_add<<<nb(nc), kBlock, 0, c->stream>>>(L.e32, Lc.e32, Lc.ebar32, L.lg, c->p.prolong, sf, sc);
-    MGFR_HIP(hipGetLastError());
-    return mx_launch_sweeps(c, l, c->p.post_smooth, l == 0 && c->timing);
+    const bool with_sweep = tile_level(c, L) && c->p.post_smooth > 0;
+    if (!with_sweep) {
+        k_mx_prolong_add<<<nb(nc), kBlock, 0, c->stream>>>(L.e32, Lc.e32, Lc.ebar32, L.lg, c->p.prolong, sf, sc);
+        MGFR_HIP(hipGetLastError());
+    }
+    return mx_launch_sweeps(c, l, c->p.post_smooth, l == 0 && c->timing, with_sweep ? &Lc : nullptr);
 }
 
 }  // namespace

@@ -194,6 +194,40 @@ __device__ __forceinline__ void prolong_block(T *__restrict__ u, const T *__rest
             }
 }
 
+// The prolongation for a tile of E x E rows of the N^3 level (N = 2^LG, its first
+// row (i0, j0) even) that a workgroup of NT threads stages in LDS: d = uc - ub of
+// the coarse rows around it, then prolong_block's value at one of its cells.
+template <typename T, int LG, int E>
+struct TileProlong {
+    static constexpr int C = E / 2 + 2, K = 1 << (LG - 1), CELLS = C * C * K;
+
+    template <int NT>
+    __device__ __forceinline__ static void load(T *d, const T *__restrict__ uc, const T *__restrict__ ub, int i0, int j0)
+    {
+#pragma unroll
+        for (int q = 0; q < (CELLS + NT - 1) / NT; ++q) {
+            const int e = (int)threadIdx.x + q * NT, r = e / K;
+            if (e < CELLS) {
+                const size_t g = cidx(((i0 >> 1) - 1 + r / C) & (K - 1), ((j0 >> 1) - 1 + r % C) & (K - 1), e % K, LG - 1);
+                d[e] = uc[g] - ub[g];
+            }
+        }
+    }
+
+    __device__ __forceinline__ static T value(const T *d, int i, int j, int k, int mode)
+    {
+        const int r = ((i >> 1) + 1) * C + (j >> 1) + 1, kc = k >> 1;
+        T v = d[r * K + kc];
+        if (mode == 0) {
+            const T eighth = (T)0.125;
+            v += ((i & 1) ? eighth : -eighth) * (d[(r + C) * K + kc] - d[(r - C) * K + kc]);
+            v += ((j & 1) ? eighth : -eighth) * (d[(r + 1) * K + kc] - d[(r - 1) * K + kc]);
+            v += ((k & 1) ? eighth : -eighth) * (d[r * K + ((kc + 1) & (K - 1))] - d[r * K + ((kc - 1) & (K - 1))]);
+        }
+        return v;
+    }
+};
+
 // ---------------------------------------------------- tail levels (16^3, 8^3, 4^3)
 // How one workgroup of 1024 threads holds the coarsest levels in LDS.  A
 // thread owns W consecutive cells of a row: 4 on 16^3 (all threads), 2 on 8^3

@@ -787,10 +787,16 @@ static inline unsigned nblocks(size_t n) { return (unsigned)((n + kBlock - 1) / 
 // updates for H = 2, 3.4 for H = 4), and the latency of a launch.  One launch per
 // colour took 3.5-3.9 us and the gap to the next: 32^3, two sweeps 4 x 3.5 -> 7.1 us
 // (H = 2 twice: 8.8); 64^3, one sweep 2 x 3.9 -> 5.9 us.
-template <bool N1, int LG, int H>
+// PRO: the first sweeps after the coarse level: u + P(uc - ub) is formed as the tile
+// is loaded (about 1 us more, against 4.8 us of a launch of its own).
+template <bool N1, int LG, int H, bool PRO>
 __global__ __launch_bounds__(1024) void k_sweep_tile(const double *__restrict__ u, const double *__restrict__ f,
-                                                     double *__restrict__ out, OpConst kc)
+                                                     double *__restrict__ out, OpConst kc,
+                                                     const double *__restrict__ uc, const double *__restrict__ ub,
+                                                     int mode)
 {
+    using P = TileProlong<double, LG, 4 + 2 * H>;
+    __shared__ double sd[PRO ? P::CELLS : 1];
     constexpr int N = 1 << LG, M = N - 1, E = 4 + 2 * H, HALF = N / 2, NT = 1024;
     __shared__ double2 ue[E * E * N];
     MGFR_EXP_TABLE_TO_LDS(kc);
@@ -817,12 +823,23 @@ __global__ __launch_bounds__(1024) void k_sweep_tile(const double *__restrict__ 
             int i, j, k;
             fv[h][q] = place(h, q, i, j, k) ? f[cell(i, j, k)] : 0.0;
         }
+    constexpr int RL = (E * E * N + NT - 1) / NT;
+    double x[RL];
 #pragma unroll
-    for (int q = 0; q < (E * E * N + NT - 1) / NT; ++q) {
+    for (int q = 0; q < RL; ++q) {
+        const int e = t + q * NT, r = e >> LG;
+        x[q] = r < E * E ? u[cell(r / E, r % E, e & M)] : 0.0;
+    }
+    if constexpr (PRO) {
+        P::template load<NT>(sd, uc, ub, i0, j0);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < RL; ++q) {
         const int e = t + q * NT, r = e >> LG, k = e & M;
         if (r < E * E) {
-            const double x = u[cell(r / E, r % E, k)];
-            ue[slot(r / E, r % E, k)] = make_double2(x, exp64(x, kc.tab));
+            if (PRO) x[q] += P::value(sd, r / E, r % E, k, mode);
+            ue[slot(r / E, r % E, k)] = make_double2(x[q], exp64(x[q], kc.tab));
         }
     }
     __syncthreads();
@@ -847,14 +864,22 @@ __global__ __launch_bounds__(1024) void k_sweep_tile(const double *__restrict__ 
 }
 
 template <int LG, int H>
-static void launch_tile(mgfr_ctx *c, Level &L, const double *f, const OpConst &kc)
+static void launch_tile(mgfr_ctx *c, Level &L, const double *f, const OpConst &kc, const Level *from)
 {
     const unsigned nb = (unsigned)((L.N / 4) * (L.N / 4));
+    const double *uc = from ? from->u : nullptr, *ub = from ? from->ubar : nullptr;
+    auto go = [&](auto *k) { k<<<nb, 1024, 0, c->stream>>>(L.u, f, L.alt, kc, uc, ub, c->p.prolong); };
     if (c->p.n == 1)
-        k_sweep_tile<true, LG, H><<<nb, 1024, 0, c->stream>>>(L.u, f, L.alt, kc);
+        from ? go(k_sweep_tile<true, LG, H, true>) : go(k_sweep_tile<true, LG, H, false>);
     else
-        k_sweep_tile<false, LG, H><<<nb, 1024, 0, c->stream>>>(L.u, f, L.alt, kc);
+        from ? go(k_sweep_tile<false, LG, H, true>) : go(k_sweep_tile<false, LG, H, false>);
     std::swap(L.u, L.alt);
+}
+
+// 32^3 and 64^3, unless they run the fused sweep or one kernel per colour: see k_sweep_tile
+static bool tile_level(const mgfr_ctx *c, const Level &L)
+{
+    return (L.N == 32 || L.N == 64) && c->fused_min_n > L.N && L.alt != nullptr;
 }
 
 static int timer_slot(mgfr_ctx *c, int *slot)
@@ -893,17 +918,18 @@ int row_chunk(int N, unsigned cols)
 
 // `sweeps` red-black sweeps on level l.  Levels with N >= fused_min_n use the
 // out-of-place fused kernel and swap L.u / L.alt after each sweep; the others
-// update L.u in place with one kernel per colour.
-int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sweeps, bool timed)
+// update L.u in place with one kernel per colour.  With `from` (tile levels, at
+// least one sweep) the correction of that coarser level is added first.
+int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sweeps, bool timed, const Level *from)
 {
     (void)u_unused;
     Level &L = c->lev[l];
     OpConst kc = level_const(c, l);
     const bool fused = c->fused_min_n > 0 && L.N >= c->fused_min_n && L.alt != nullptr;
-    // 32^3 and 64^3: see k_sweep_tile.  Two sweeps in one launch on 32^3 (7.1 us
-    // against 8.8 for two launches, 64 workgroups), not on 64^3, whose 256
-    // workgroups then redo more than the launch saves (13.3 us against 11.8)
-    const bool tile = !fused && c->fused_min_n > 0 && (L.N == 32 || L.N == 64) && L.alt != nullptr;
+    // Two sweeps in one launch on 32^3 (7.1 us against 8.8 for two launches, 64
+    // workgroups), not on 64^3, whose 256 workgroups then redo more than the
+    // launch saves (13.3 us against 11.8)
+    const bool tile = tile_level(c, L);
     const size_t half = (size_t)1 << (3 * L.lg - 1);
     for (int s = 0; s < sweeps; ++s) {
         int slot = -1;
@@ -924,13 +950,14 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
             std::swap(L.u, L.alt);
         } else if (tile) {
             if (L.N == 64) {
-                launch_tile<6, 2>(c, L, f, kc);
+                launch_tile<6, 2>(c, L, f, kc, from);
             } else if (!timed && s + 1 < sweeps) {  // timing counts one sweep per launch
-                launch_tile<5, 4>(c, L, f, kc);
+                launch_tile<5, 4>(c, L, f, kc, from);
                 ++s;
             } else {
-                launch_tile<5, 2>(c, L, f, kc);
+                launch_tile<5, 2>(c, L, f, kc, from);
             }
+            from = nullptr;
         } else {
             for (int colour = 0; colour < 2; ++colour)
                 k_sweep_half<<<nblocks(half), kBlock, 0, c->stream>>>(L.u, f, L.lg, colour, kc);
@@ -980,9 +1007,12 @@ int vcycle64(mgfr_ctx *c, int l)
     k_coarse_rhs<<<nblocks(nc), kBlock, 0, c->stream>>>(Lc.ubar, Lc.lg, level_const(c, l + 1), Lc.f, Lc.u);
     MGFR_HIP(hipGetLastError());
     if ((rc = vcycle64(c, l + 1))) return rc;
-    k_prolong_add<<<nblocks(nc), kBlock, 0, c->stream>>>(L.u, Lc.u, Lc.ubar, L.lg, c->p.prolong);
-    MGFR_HIP(hipGetLastError());
-    return launch_sweep64(c, l, L.u, L.f, c->p.post_smooth, l == 0 && c->timing);
+    const bool with_sweep = tile_level(c, L) && c->p.post_smooth > 0;
+    if (!with_sweep) {
+        k_prolong_add<<<nblocks(nc), kBlock, 0, c->stream>>>(L.u, Lc.u, Lc.ubar, L.lg, c->p.prolong);
+        MGFR_HIP(hipGetLastError());
+    }
+    return launch_sweep64(c, l, L.u, L.f, c->p.post_smooth, l == 0 && c->timing, with_sweep ? &Lc : nullptr);
 }
 
 int launch_residual_norm64(mgfr_ctx *c, int l, const double *u, const double *f, double *rmax, double *rsumsq)

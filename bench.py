@@ -507,13 +507,17 @@ def main():
     # algorithmic bytes of a red-black sweep: float64, read u and f, write u
     # (24 B/cell); float32 correction sweep, read e, r and u, write e (16 B/cell)
     if args.mode.startswith("fp64"):
-        kernel, bpc, design_bpc = ("k_sweep_rows" if N >= 128 else "k_sweep_half (x2 per sweep)"), 24.0, 24.0
+        kernel = "k_sweep_rows" if N >= 128 else "k_sweep_tile" if N >= 32 else "k_sweep_half (x2 per sweep)"
+        bpc = design_bpc = 24.0
         src = KERNEL_SRC["fp64"]
     else:
-        # levels from 256^3 on: one fused kernel per sweep; below, one pass per
+        # from 256^3 on and on 64^3 and 32^3: one kernel per sweep; 128^3: one pass per
         # colour, half a sweep each (8 B/cell of its 16), which by its own design
         # reads u and e of every cell, r of the updated half and writes that half
-        kernel, bpc, design_bpc = ("k_mx_sweep_rows", 16.0, 16.0) if N >= 256 else ("k_mx_colour (x2 per sweep)", 8.0, 12.0)
+        if N >= 256 or 32 <= N <= 64:
+            kernel, bpc, design_bpc = ("k_mx_sweep_rows" if N >= 256 else "k_mx_sweep_tile"), 16.0, 16.0
+        else:
+            kernel, bpc, design_bpc = ("k_mx_colour" if N == 128 else "k_mx_sweep_half") + " (x2 per sweep)", 8.0, 12.0
         src = KERNEL_SRC["mixed"]
     alg_bytes = bpc * N ** 3
     achieved = alg_bytes / (head["sweep_launch_ms"] * 1e-3) / 1e9

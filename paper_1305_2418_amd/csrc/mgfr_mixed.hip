@@ -1531,7 +1531,7 @@ int mx_launch_sweeps(mgfr_ctx *c, int l, int sweeps, bool timed, const Level *fr
             }
         } else if (tile) {
             const unsigned nbt = (unsigned)((L.N / 4) * (L.N / 4));
-            const bool two = L.N == 32 && s + 1 < sweeps;
+            const bool two = L.N == 32 && !timed && s + 1 < sweeps;  // timing counts one sweep per launch
             if ((rc = timer_slot(c, timed, slot))) return rc;
             auto go = [&](auto *plain, auto *prolong) {
                 (from ? prolong : plain)<<<nbt, 1024, 0, c->stream>>>(L.e32, L.u32, L.r32, L.e32alt, kc,

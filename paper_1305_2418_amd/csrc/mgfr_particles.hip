@@ -43,16 +43,23 @@ __global__ __launch_bounds__(kBlock) void k_cic_scatter(const float *__restrict_
             }
 }
 
-// Units of a workgroup: runs of kUnitRun consecutive units (tiles next to each other
+// Units of a workgroup: runs of 2^lgrun consecutive units (tiles next to each other
 // along z) go to one XCD, whose L2 then holds the lines of pos and acc that
-// neighbouring tiles share (20 M particles on 256^3: the force fetches 0.56 GB
-// instead of 1.06, 492 -> 470 us; the assignment 0.76 instead of 0.98, 333 -> 310
-// us; runs of 16 and 256: 479 and 469, 313 and 306 us, but the longest runs leave
-// XCDs without work below 128^3).
-constexpr uint32_t kUnitRun = 64;
-__device__ __forceinline__ uint32_t unit_of(uint32_t j)
+// neighbouring tiles share (20 M particles on 256^3, runs of 64: the force fetches
+// 0.56 GB instead of 1.06, 492 -> 470 us; the assignment 0.76 instead of 0.98, 333
+// -> 310 us; runs of 16 and 256: 479 and 469, 313 and 306 us).  unit_lgrun: at least
+// eight runs per XCD (32^3, 64 tiles: the force of 0.3 M particles 36 us, with one
+// run of 64 on one XCD 40), and no runs where a tile is many units, which share
+// their tile's lines and not their neighbours' (30 M particles on 32^3: assignment
+// 956 us, 965 with runs).
+__device__ __forceinline__ uint32_t unit_of(uint32_t j, uint32_t lgrun)
 {
-    return (j / kUnitRun * 8 + (blockIdx.x & 7u)) * kUnitRun + j % kUnitRun;  // ascending in j
+    return ((((j >> lgrun) << 3) | (blockIdx.x & 7u)) << lgrun) | (j & ((1u << lgrun) - 1u));  // ascending in j
+}
+inline uint32_t unit_lgrun(const mgfr_ctx *c)
+{
+    const int lgT = 3 * (c->lev[0].lg - kBinLg);  // 2^lgT tiles
+    return c->perm_np <= ((int64_t)kUnit << lgT) ? (uint32_t)std::min(6, std::max(0, lgT - 6)) : 0u;
 }
 inline unsigned unit_blocks(unsigned grid) { return (grid + 7) / 8 * 8; }
 
@@ -66,8 +73,8 @@ inline unsigned unit_blocks(unsigned grid) { return (grid + 7) / 8 * 8; }
 __global__ __launch_bounds__(kBlock) void k_cic_units(const float *__restrict__ pos, const double *__restrict__ mass,
                                                         const uint32_t *__restrict__ perm,
                                                         const uint4 *__restrict__ units,
-                                                        const uint32_t *__restrict__ total, int lg, double h,
-                                                        double *__restrict__ m, int *__restrict__ flag)
+                                                        const uint32_t *__restrict__ total, uint32_t lgrun, int lg,
+                                                        double h, double *__restrict__ m, int *__restrict__ flag)
 {
     __shared__ double win[kWin3];
     const int tid = threadIdx.x;
@@ -75,7 +82,7 @@ __global__ __launch_bounds__(kBlock) void k_cic_units(const float *__restrict__ 
     const double r = 1.0 / h;
     const uint32_t U = *total;
     for (int e = tid; e < kWin3; e += kBlock) win[e] = 0.0;
-    for (uint32_t j = blockIdx.x >> 3, u; (u = unit_of(j)) < U; j += gridDim.x >> 3) {
+    for (uint32_t j = blockIdx.x >> 3, u; (u = unit_of(j, lgrun)) < U; j += gridDim.x >> 3) {
         const uint4 d = units[u];
         const int ti = (int)(d.x >> (2 * tl)) << kBinLg, tj = (int)((d.x >> tl) & tmask) << kBinLg,
                   tk = (int)(d.x & tmask) << kBinLg;
@@ -300,8 +307,8 @@ __device__ __noinline__ double3 grad_sum_global(const double *__restrict__ fr, i
 __global__ __launch_bounds__(kBlock) void k_force_units(const double *__restrict__ fr, const float *__restrict__ pos,
                                                           const uint32_t *__restrict__ perm,
                                                           const uint4 *__restrict__ units,
-                                                          const uint32_t *__restrict__ total, int lg, double h,
-                                                          double pref, float *__restrict__ acc,
+                                                          const uint32_t *__restrict__ total, uint32_t lgrun, int lg,
+                                                          double h, double pref, float *__restrict__ acc,
                                                           int *__restrict__ flag)
 {
     __shared__ double win[kFW3];
@@ -310,7 +317,7 @@ __global__ __launch_bounds__(kBlock) void k_force_units(const double *__restrict
     const double s = pref / (2.0 * h), r = 1.0 / h;
     const uint32_t U = *total;
     constexpr int kFWPer = (kFW3 + kBlock - 1) / kBlock;  // window values staged per thread
-    for (uint32_t j = blockIdx.x >> 3, u; (u = unit_of(j)) < U; j += gridDim.x >> 3) {
+    for (uint32_t j = blockIdx.x >> 3, u; (u = unit_of(j, lgrun)) < U; j += gridDim.x >> 3) {
         const uint4 d = units[u];
         const int ti = (int)(d.x >> (2 * tl)) << kBinLg, tj = (int)((d.x >> tl) & tmask) << kBinLg,
                   tk = (int)(d.x & tmask) << kBinLg;
@@ -439,8 +446,8 @@ extern "C" int mgfr_assign_density(mgfr_ctx *c, const float *pos, const double *
     c->perm_np = 0;
     if (c->binning && np <= c->bin_cap) {
         if (int e = bin_particles(c, pos, np)) return e;
-        k_cic_units<<<unit_blocks(c->unit_grid), kBlock, 0, c->stream>>>(pos, mass, c->perm, c->units, c->unit_total, L0.lg,
-                                                             L0.h, delta, c->dflag);
+        k_cic_units<<<unit_blocks(c->unit_grid), kBlock, 0, c->stream>>>(pos, mass, c->perm, c->units, c->unit_total,
+                                                                          unit_lgrun(c), L0.lg, L0.h, delta, c->dflag);
     } else {
         k_cic_scatter<<<(unsigned)pblocks, kBlock, 0, c->stream>>>(pos, mass, np, L0.lg, L0.h, delta, c->dflag);
     }
@@ -474,8 +481,8 @@ extern "C" int mgfr_fifth_force(mgfr_ctx *c, const double *u, const float *pos, 
     if (pblocks > 0x7fffffffULL) return set_error(MGFR_ERR_ARG, "np too large");
     const double pref = kCkms * kCkms / (2.0 * c->p.a);
     if (c->perm_np == np && c->perm) {
-        k_force_units<<<unit_blocks(c->unit_grid), kBlock, 0, c->stream>>>(fr, pos, c->perm, c->units, c->unit_total, L0.lg,
-                                                               L0.h, pref, acc, c->dflag);
+        k_force_units<<<unit_blocks(c->unit_grid), kBlock, 0, c->stream>>>(
+            fr, pos, c->perm, c->units, c->unit_total, unit_lgrun(c), L0.lg, L0.h, pref, acc, c->dflag);
     } else {
         k_force_gather<<<(unsigned)pblocks, kBlock, 0, c->stream>>>(fr, pos, nullptr, np, L0.lg, L0.h, pref, acc,
                                                                      c->dflag);
@@ -505,8 +512,8 @@ extern "C" int mgfr_pm_accel(mgfr_ctx *c, const double *delta, const double *u, 
     if (pblocks > 0x7fffffffULL) return set_error(MGFR_ERR_ARG, "np too large");
     const double pref = -1.0 / c->p.a;
     if (c->perm_np == np && c->perm) {
-        k_force_units<<<unit_blocks(c->unit_grid), kBlock, 0, c->stream>>>(psi, pos, c->perm, c->units, c->unit_total, L0.lg,
-                                                               L0.h, pref, acc, c->dflag);
+        k_force_units<<<unit_blocks(c->unit_grid), kBlock, 0, c->stream>>>(
+            psi, pos, c->perm, c->units, c->unit_total, unit_lgrun(c), L0.lg, L0.h, pref, acc, c->dflag);
     } else {
         k_force_gather<<<(unsigned)pblocks, kBlock, 0, c->stream>>>(psi, pos, nullptr, np, L0.lg, L0.h, pref, acc,
                                                                      c->dflag);

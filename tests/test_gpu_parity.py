@@ -584,3 +584,26 @@ def test_tile_sweeps_match_one_colour_kernels(N, sweeps, n):
         s.set_fused_min_mesh(fused)
         out.append(s.ngs_sweep(u0.clone(), f, sweeps))
     assert float((out[0] - out[1]).abs().max()) < 1e-13
+
+
+@pytest.mark.parametrize("N,npart", [(8, 700), (32, 3000), (32, 70001), (64, 5000), (128, 20001)])
+def test_binned_units_reach_every_particle(N, npart):
+    """Runs of work units of every length (1 to 64 units per XCD, fewer units than
+    runs, tiles of several units): the binned assignment and force against the
+    per-particle kernels.  Sums of float64 weights in another order (1e-12 of the
+    largest cell); the force is per particle, its 8-term sums in another order (1e-6
+    of the largest, float32 results)."""
+    mg = _mg()
+    print(f"[case] units N={N} np={npart}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + npart)
+    pos = (torch.rand((npart, 3), generator=g, device=DEV) * 100.0).float()
+    u = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV)
+    out = []
+    for binning in (True, False):
+        s = mg.Solver(_params(mg, N), binning=binning)
+        if binning:
+            s.reserve_particles(npart)
+        d = s.assign_density(pos)
+        out.append((d, s.fifth_force(u, pos)))
+    assert float((out[0][0] - out[1][0]).abs().max()) <= 1e-12 * float(out[1][0].abs().max())
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 1e-6 * float(out[1][1].abs().max())

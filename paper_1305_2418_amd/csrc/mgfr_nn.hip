@@ -457,7 +457,9 @@ void launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, cons
                    const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
 {
     const int Cin = in.C + in.Cs;
-    if (Cin % 16 == 0 && lgS >= 4) {
+    // k_conv_reg stores four channels at once; outputs off those boundaries take k_conv3d
+    const bool aligned = ((uintptr_t)Y & 7) == 0 && ((uintptr_t)Y32 & 15) == 0;
+    if (Cin % 16 == 0 && lgS >= 4 && aligned) {
         // two blocks of 16 channels per workgroup where the number is even: its
         // weights still fit in the registers and the input is read half as often
         const int NT = Cout % 32 == 0 ? 2 : 1;

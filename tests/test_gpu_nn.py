@@ -103,6 +103,24 @@ def test_conv_exact_on_integers(B, S, Cin, Cout, relu):
     assert torch.equal(~torch.isfinite(y).all(-1), near)
 
 
+@pytest.mark.parametrize("S,Cin,Cout", [(16, 16, 16), (16, 32, 32)])
+def test_conv_into_an_output_off_the_store_width(S, Cin, Cout):
+    """Outputs one element past an aligned address: the same bits as aligned ones."""
+    mg = _mg()
+    print(f"[case] conv into an offset output S={S} Cin={Cin} Cout={Cout}", flush=True)
+    g = torch.Generator().manual_seed(S + Cin)
+    x = torch.randn((1, S, S, S, Cin), generator=g).to(torch.bfloat16).to(DEV)
+    w = (torch.randn((27, Cout, Cin), generator=g) / np.sqrt(27 * Cin)).to(torch.bfloat16).to(DEV)
+    n = S ** 3 * Cout
+    y, y32 = torch.zeros(n + 1, dtype=torch.bfloat16, device=DEV), torch.zeros(n + 1, device=DEV)
+    rc = mg.lib().mgfr_conv3d_fwd(x.data_ptr(), 1, S, Cin, w.data_ptr(), None, Cout, 0, y.data_ptr() + 2,
+                                  y32.data_ptr() + 4, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    torch.cuda.synchronize()
+    assert torch.equal(y[1:].view(1, S, S, S, Cout), mg.conv3d_fwd(x, w)) and float(y[0]) == 0.0
+    assert torch.equal(y32[1:].view(1, S, S, S, Cout), mg.conv3d_fwd(x, w, out32=True)) and float(y32[0]) == 0.0
+
+
 @pytest.mark.parametrize("B,S,Cin,Cout,with_db", [(1, 8, 16, 16, True), (3, 8, 16, 96, True), (1, 8, 96, 16, False),
                                                   (1, 16, 64, 64, True), (2, 32, 48, 16, True), (1, 32, 16, 32, True)])
 def test_conv_backward_weight_exact_on_integers(B, S, Cin, Cout, with_db):

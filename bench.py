@@ -180,7 +180,7 @@ def measure_mfma(N, dev, log):
     ms = a.elapsed_time(b) / reps
     tf = net_forward_flops(S) / (ms * 1e-3) / 1e12
     log(f"network forward at {S}^3: {ms:.3f} ms, {tf:.1f} TFLOP/s")
-    return {"kernel": f"k_conv3d (network forward, {S}^3, bf16 MFMA 16x16x32)", "ms": ms,
+    return {"kernel": f"k_conv_reg (network forward, {S}^3, bf16 MFMA 16x16x32)", "ms": ms,
             "flop": net_forward_flops(S), "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
             "frac": tf / 2500.0}
 

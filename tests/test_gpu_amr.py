@@ -305,3 +305,31 @@ def test_binned_assignment_equals_per_particle(N0, nref, npart):
     assert np.abs(d1 - d0).max() <= 1e-12 * np.abs(d0).max()
     # both solves stop at residual 1e-8: their answers differ by less than that error
     assert np.abs(u1 - u0).max() <= 1e-6 * np.abs(u0).max()
+
+
+@pytest.mark.parametrize("N0,nref", [(32, 1), (32, 2), (64, 1), (64, 2)])
+def test_block_lists_follow_the_counts(N0, nref):
+    """Level-1 blocks of maps smaller than a workgroup's share of positions, of one
+    share and of several: those of the groups of base cells that hold more than 8
+    particles in a cell (and, with two levels, at least those), in row-major order."""
+    from paper_1305_2418_amd import mgfr
+    print(f"[case] block lists N0={N0} nref={nref}", flush=True)
+    g = torch.Generator().manual_seed(N0)
+    pos = torch.rand((4 * N0 ** 3, 3), generator=g) * 100.0
+    pos[: N0 ** 3] = pos[: N0 ** 3] * 0.3 + 40.0
+    pos = pos.float()
+    amr = mgfr.Amr(mgfr.Params(mesh=N0, fr0_abs=1e-5, refine_levels=nref, max_vcycles=2), max_blocks=60000)
+    amr.solve(pos.to(DEV), allow_not_converged=True)
+    org, _ = amr.level(1)
+    idx = np.floor(pos.numpy().astype(np.float64) / (100.0 / N0)).astype(int) % N0
+    cnt = np.zeros((N0,) * 3, int)
+    np.add.at(cnt, (idx[:, 0], idx[:, 1], idx[:, 2]), 1)
+    M = N0 // 4
+    want = (cnt > 8).reshape(M, 4, M, 4, M, 4).any(axis=(1, 3, 5))
+    got = np.zeros((M,) * 3, bool)
+    o = np.asarray(org) // 8
+    got[o[:, 0], o[:, 1], o[:, 2]] = True
+    lin = (o[:, 0] * M + o[:, 1]) * M + o[:, 2]
+    assert np.all(np.diff(lin) > 0) and np.all(got[want])
+    if nref == 1:
+        assert np.array_equal(got, want)

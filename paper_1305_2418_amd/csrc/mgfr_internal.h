@@ -138,7 +138,7 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u, const double *f, int sweeps, b
 int launch_residual_norm64(mgfr_ctx *c, int l, const double *u, const double *f, double *rmax,
                            double *rsumsq);
 int vcycle64(mgfr_ctx *c, int l);
-int solve_fp64_from(mgfr_ctx *c, double *u, mgfr_stats *st, double D);  // V-cycles from the current u
+int solve_fp64_from(mgfr_ctx *c, mgfr_stats *st, double D);  // V-cycles from the current u
 // adaptive smoothing: after a residual check, res (this check) against res2
 // (two checks back, < 0 if none); doubles the sweeps when it has not fallen
 void adapt_smoothing(mgfr_ctx *c, double res, double res2);

@@ -1719,7 +1719,7 @@ int solve_mixed(mgfr_ctx *c, double *u, mgfr_stats *st, double D)
             MGFR_HIP(hipMemsetAsync(u, 0, n * sizeof(double), c->stream));
             st->fell_back = 1;
             const int done = it;
-            status = solve_fp64_from(c, u, st, D);
+            status = solve_fp64_from(c, st, D);
             st->outer_iters = done + st->vcycles;
             return status;
         }

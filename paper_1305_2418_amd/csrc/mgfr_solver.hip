@@ -1392,12 +1392,14 @@ void mgfr::adapt_smoothing(mgfr_ctx *c, double res, double res2)
     c->p.post_smooth = std::min(std::max(1, 2 * c->p.post_smooth), c->smooth_max);
 }
 
-int mgfr::solve_fp64_from(mgfr_ctx *c, double *u, mgfr_stats *st, double D)
+// V-cycles on the level-0 iterate, which an odd number of out-of-place sweeps
+// leaves in the other buffer: the residual is that of L0.u after every cycle.
+int mgfr::solve_fp64_from(mgfr_ctx *c, mgfr_stats *st, double D)
 {
     Level &L0 = c->lev[0];
     double rmax, rsq;
     const double ncell = (double)L0.N * L0.N * L0.N;
-    int rc = launch_residual_norm64(c, 0, u, L0.f, &rmax, &rsq);
+    int rc = launch_residual_norm64(c, 0, L0.u, L0.f, &rmax, &rsq);
     if (rc) return rc;
     double res = rmax / D, res1 = res, res2 = -1.0;  // res1, res2: one and two checks back
     st->res0 = res;
@@ -1407,7 +1409,7 @@ int mgfr::solve_fp64_from(mgfr_ctx *c, double *u, mgfr_stats *st, double D)
         if (res <= c->p.tol) { status = MGFR_OK; break; }
         if (cyc >= c->p.max_vcycles) { status = MGFR_NOT_CONVERGED; break; }
         if ((rc = vcycle64(c, 0))) return rc;
-        if ((rc = launch_residual_norm64(c, 0, u, L0.f, &rmax, &rsq))) return rc;
+        if ((rc = launch_residual_norm64(c, 0, L0.u, L0.f, &rmax, &rsq))) return rc;
         if (c->timing && (rc = collect_timing(c, st))) return rc;
         res2 = cyc >= 1 ? res1 : -1.0;
         res1 = res;
@@ -1476,7 +1478,7 @@ extern "C" int mgfr_solve(mgfr_ctx *c, const double *delta, double *u, double *d
     if (c->p.precision == MGFR_MIXED) {
         status = solve_mixed(c, u, st, D);
     } else {
-        status = solve_fp64_from(c, u, st, D);
+        status = solve_fp64_from(c, st, D);
     }
     st->smooth_used = c->p.pre_smooth;
     c->p.pre_smooth = pre;

@@ -625,3 +625,29 @@ def test_reported_residual_is_the_fields_largest(N):
     r = float(s.residual(u, f).abs().max()) / st.scale
     print(f"  reported {st.res:.12e}, field {r:.12e}")
     assert abs(st.res / r - 1) < 1e-9
+
+
+@pytest.mark.parametrize("N,n,pre,post,cycles", [(16, 1, 2, 1, 1), (32, 1, 4, 2, 1), (32, 2, 1, 0, 2), (64, 1, 2, 1, 1),
+                                                 (64, 2, 1, 0, 3), (128, 2, 2, 1, 2), (128, 1, 1, 0, 1), (256, 1, 1, 2, 1)])
+@pytest.mark.parametrize("fallback", [False, True])
+def test_reported_residual_is_that_of_the_returned_field(N, n, pre, post, cycles, fallback):
+    """Schedules whose cycles leave the iterate in the second buffer of the
+    out-of-place sweeps (an odd number of launches), after one cycle and more,
+    in the float64 solve and in the one that the mixed solve falls back to: the
+    reported residual against the largest entry of the residual field of the
+    returned u, 1e-9 of it as above."""
+    mg = _mg()
+    print(f"[case] reported residual N={N} n={n} V({pre},{post}) cycles={cycles} fallback={fallback}", flush=True)
+    d = torch.tensor(_delta(N, 5.0, 14, halos=20 if N >= 32 else 0), device=DEV)
+    p = _params(mg, N, fr0_abs=1e-6, n=n, pre_smooth=pre, post_smooth=post, max_vcycles=cycles,
+                precision=mg.MIXED if fallback else mg.FP64)
+    u0 = torch.zeros((N, N, N), dtype=torch.float64, device=DEV)
+    if fallback:
+        u0[1, 2, 3] = float("nan")
+    s = mg.Solver(p)
+    u, _, st = s.solve(d, u=u0, want_dfr=False, allow_not_converged=True)
+    assert st.vcycles == cycles and st.fell_back == int(fallback)
+    f = O.background(_oparams(N, fr0_abs=1e-6, n=n))[1] * _oparams(N).omega_m / _oparams(N).a ** 3 * d
+    r = float(s.residual(u, f).abs().max()) / st.scale
+    print(f"  reported {st.res:.12e}, field {r:.12e}")
+    assert abs(st.res / r - 1) < 1e-9

@@ -120,7 +120,10 @@ __device__ __forceinline__ double recip(double x)
 }
 
 // Newton-Gauss-Seidel step from precomputed exponentials: ec = e^{u_c},
-// em = e^{-q u_c} - 1, neighbour values n* and their exponentials e*.
+// em = e^{-q u_c} - 1, neighbour values n* and their exponentials e*.  em is
+// expm1_64's in every sweep: for n = 1 rsqrt(ec) - 1 would be 3 % of a 512^3 sweep
+// cheaper (705 us for 727), but cancels for small u (solves of contrast 1e-6 stop
+// at a residual of 2e-9) and is infinite where e^u underflows.
 __device__ __forceinline__ double ngs_step_e(double uc, double ec, double em, double n0, double e0, double n1,
                                              double e1, double n2, double e2, double n3, double e3, double n4,
                                              double e4, double n5, double e5, double f, const OpConst &k)
@@ -134,14 +137,6 @@ __device__ __forceinline__ double ngs_step_e(double uc, double ec, double em, do
     double du = -(L - f) * recip(J);
     if (k.max_du > 0.0) du = fmin(fmax(du, -k.max_du), k.max_du);
     return du;
-}
-
-// e^{-q u} - 1 given e^{u}: for n = 1 (q = 1/2) this is rsqrt(e^u) - 1.
-template <bool N1>
-__device__ __forceinline__ double curv_em(double uc, double ec, double q, const double *tab)
-{
-    if constexpr (N1) return rsqrt(ec) - 1.0;
-    else return expm1_64(-q * uc, tab);
 }
 
 // One full red-black sweep, out of place: out = sweep(u), on levels with N >= 64.
@@ -162,8 +157,8 @@ __device__ __forceinline__ double curv_em(double uc, double ec, double q, const 
 // a tile (N = 64) hold it twice: both copies of a cell get the same value.
 //
 // Bound: the float64 vector pipe and the latency of a step (one workgroup per
-// CU: 128 registers).  512^3: 763 us per sweep (24 B per cell), 256^3
-// 95 us; a version with a row pair per thread, 12 x 60 of each 16 x 64 tile
+// CU: 128 registers).  512^3: 727 us per sweep (24 B per cell), 256^3
+// 98 us; a version with a row pair per thread, 12 x 60 of each 16 x 64 tile
 // stored and a select for every operand issued twice the instructions: 1206 and
 // 207 us.  What mattered besides: no spilled register (a scratch load waits for
 // every prefetch before it), and exponentials after the barrier, not before it.
@@ -177,17 +172,16 @@ struct RowArgs {
 
 typedef double2 RowLds[2][kRowF][kRowS];
 
-template <bool N1>
 __device__ __forceinline__ double row_update(const double2 &c, const double2 &n0, const double2 &n1, const double2 &n2,
                                              const double2 &n3, const double2 &n4, const double2 &n5, double f,
                                              const OpConst &kc)
 {
-    return c.x + ngs_step_e(c.x, c.y, curv_em<N1>(c.x, c.y, kc.q, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y, n3.x,
+    return c.x + ngs_step_e(c.x, c.y, expm1_64(-kc.q * c.x, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y, n3.x,
                             n3.y, n4.x, n4.y, n5.x, n5.y, f, kc);
 }
 
 // S0: red column of the wave's row on plane i0 - 1.  RING: an outer row.
-template <bool N1, int S0, bool RING>
+template <int S0, bool RING>
 __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int k0, int row, int lane, RowLds &sO,
                                            RowLds &sN)
 {
@@ -251,12 +245,12 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
             up = O[row - 1][lane + 1];
             dn = O[row + 1][lane + 1];
         }
-        const double ur = row_update<N1>(C1[S], Q[S], C0[S], dn, up, C1[T], O[row][S ? lane + 2 : lane],
+        const double ur = row_update(C1[S], Q[S], C0[S], dn, up, C1[T], O[row][S ? lane + 2 : lane],
                                          RING || !S ? fv.x : fv.y, kc);
         // black cell of plane p - 1
         if constexpr (!RING) {
             if (stored && p - 1 >= i0) {
-                const double ub = row_update<N1>(A1[T], C0[T], R2, R[row + 1][lane + 1], R[row - 1][lane + 1], A1[S],
+                const double ub = row_update(A1[T], C0[T], R2, R[row + 1][lane + 1], R[row - 1][lane + 1], A1[S],
                                                  R[row][T ? lane + 2 : lane], fb0, kc);
                 PlaneBuf(A.out + (size_t)(p - 1) * plane, pbytes)
                     .st2(off, S ? make_double2(ub, A1[1].x) : make_double2(A1[0].x, ub));
@@ -283,7 +277,6 @@ __device__ __forceinline__ void sweep_rows(const RowArgs &A, int i0, int j0, int
 // the workgroup's rows, on the same steps: a cell is black and red in turn along
 // i; black, its old value is published beside its row's black cells, red, it is
 // updated and its new value published with the row's red ones.
-template <bool N1>
 __device__ __forceinline__ void sweep_ends(const RowArgs &A, int i0, int j0, int k0, int lane, RowLds &sO, RowLds &sN)
 {
     const int lg = A.lg, m = (1 << lg) - 1;
@@ -317,7 +310,7 @@ __device__ __forceinline__ void sweep_ends(const RowArgs &A, int i0, int j0, int
         const Raw cur = raw;
         raw = load(p + 2);
         if (live && red)
-            h1 = cell(row_update<N1>(h1, hn, h0, O[jdn][slot], O[jup][slot], O[q][in], cell(cur.u2), cur.f, kc));
+            h1 = cell(row_update(h1, hn, h0, O[jdn][slot], O[jup][slot], O[q][in], cell(cur.u2), cur.f, kc));
         hm = h0;
         h0 = h1;
         h1 = hn;
@@ -331,7 +324,6 @@ __device__ __forceinline__ void sweep_ends(const RowArgs &A, int i0, int j0, int
 
 // grid: nkt njt ceil(N / chunk) workgroups; those of one XCD (blocks b, b + 8,
 // ...) take consecutive tiles in j, which share their outer rows in its L2
-template <bool N1>
 __global__ __launch_bounds__(64 * (kRowF + 1)) void k_sweep_rows(RowArgs A)
 {
     __shared__ RowLds sO, sN;
@@ -344,17 +336,17 @@ __global__ __launch_bounds__(64 * (kRowF + 1)) void k_sweep_rows(RowArgs A)
     const int lane = threadIdx.x & 63;
     const int s0 = (i0 - 1 + j0 - 1 + row) & 1;  // red column of the row on plane i0 - 1
     if (row == kRowF)
-        sweep_ends<N1>(A, i0, j0, k0, lane, sO, sN);
+        sweep_ends(A, i0, j0, k0, lane, sO, sN);
     else if (row == 0 || row == kRowF - 1) {
         if (s0)
-            sweep_rows<N1, 1, true>(A, i0, j0, k0, row, lane, sO, sN);
+            sweep_rows<1, true>(A, i0, j0, k0, row, lane, sO, sN);
         else
-            sweep_rows<N1, 0, true>(A, i0, j0, k0, row, lane, sO, sN);
+            sweep_rows<0, true>(A, i0, j0, k0, row, lane, sO, sN);
     } else {
         if (s0)
-            sweep_rows<N1, 1, false>(A, i0, j0, k0, row, lane, sO, sN);
+            sweep_rows<1, false>(A, i0, j0, k0, row, lane, sO, sN);
         else
-            sweep_rows<N1, 0, false>(A, i0, j0, k0, row, lane, sO, sN);
+            sweep_rows<0, false>(A, i0, j0, k0, row, lane, sO, sN);
     }
 }
 
@@ -643,17 +635,16 @@ struct TailLevel : TailGrid<LG> {
     double *f, *ub;
 };
 
-template <bool N1, int LG>
 __device__ __forceinline__ double2 tail_update(double2 c, double2 n0, double2 n1, double2 n2, double2 n3, double2 n4,
                                                double2 n5, double f, const OpConst &kc)
 {
-    const double un = c.x + ngs_step_e(c.x, c.y, curv_em<N1>(c.x, c.y, kc.q, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y,
+    const double un = c.x + ngs_step_e(c.x, c.y, expm1_64(-kc.q * c.x, kc.tab), n0.x, n0.y, n1.x, n1.y, n2.x, n2.y,
                                        n3.x, n3.y, n4.x, n4.y, n5.x, n5.y, f, kc);
     return make_double2(un, exp64(un, kc.tab));
 }
 
 // Red-black sweeps of the 16^3 or 8^3 level.
-template <bool N1, int LG>
+template <int LG>
 __device__ __forceinline__ void tail_sweeps(const TailLevel<LG> &T, int sweeps, const OpConst &kc)
 {
     using L = TailLevel<LG>;
@@ -682,7 +673,7 @@ __device__ __forceinline__ void tail_sweeps(const TailLevel<LG> &T, int sweeps, 
         for (int c = B; c < W; c += 2) {
             const int k = k0 + c;
             const double2 l = c == 0 ? out : x[c - 1], r = c == W - 1 ? out : x[(c + 1) % W];
-            y[c] = tail_update<N1, LG>(x[c], T.ue[L::slot(ip, j, k)], T.ue[L::slot(im, j, k)], T.ue[L::slot(i, jp, k)],
+            y[c] = tail_update(x[c], T.ue[L::slot(ip, j, k)], T.ue[L::slot(im, j, k)], T.ue[L::slot(i, jp, k)],
                                        T.ue[L::slot(i, jm, k)], r, l, f[c], kc);
         }
 #pragma unroll
@@ -705,7 +696,6 @@ __device__ __forceinline__ void tail_sweeps(const TailLevel<LG> &T, int sweeps, 
 // Sweeps of the 4^3 level by the first wave: within one wave the LDS accesses
 // of a half-sweep are done before the next one's, and the fences keep the
 // compiler from moving them.
-template <bool N1>
 __device__ __forceinline__ void tail_sweeps4(const TailLevel<2> &T, int sweeps, const OpConst &kc)
 {
     using L = TailLevel<2>;
@@ -719,7 +709,7 @@ __device__ __forceinline__ void tail_sweeps4(const TailLevel<2> &T, int sweeps, 
         const double f = T.f[c];
         for (int h = 0; h < 2 * sweeps; ++h) {
             if (par == (h & 1)) {
-                x = tail_update<N1, 2>(x, T.ue[n0], T.ue[n1], T.ue[n2], T.ue[n3], T.ue[n4], T.ue[n5], f, kc);
+                x = tail_update(x, T.ue[n0], T.ue[n1], T.ue[n2], T.ue[n3], T.ue[n4], T.ue[n5], f, kc);
                 T.ue[c] = x;
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -812,7 +802,6 @@ __device__ __forceinline__ void tail_prolong(const TailLevel<LG> &T, const TailL
     __syncthreads();
 }
 
-template <bool N1>
 __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs A)
 {
     __shared__ double2 s_ue[4096 + 512 + 64];
@@ -837,17 +826,17 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs A)
     }
     __syncthreads();
     if (lg == 4) {
-        tail_sweeps<N1>(T4, A.pre, k4);
+        tail_sweeps(T4, A.pre, k4);
         tail_restrict(T4, T3, k4, k3);
     }
-    tail_sweeps<N1>(T3, A.pre, k3);
+    tail_sweeps(T3, A.pre, k3);
     tail_restrict(T3, T2, k3, k2);
-    tail_sweeps4<N1>(T2, A.coarse, k2);
+    tail_sweeps4(T2, A.coarse, k2);
     tail_prolong(T3, T2, A.mode, s_tab);
-    tail_sweeps<N1>(T3, A.post, k3);
+    tail_sweeps(T3, A.post, k3);
     if (lg == 4) {
         tail_prolong(T4, T3, A.mode, s_tab);
-        tail_sweeps<N1>(T4, A.post, k4);
+        tail_sweeps(T4, A.post, k4);
     }
     for (int c = t; c < n0; c += kTailThreads) A.u[c] = s_ue[slot0(c)].x;
 }
@@ -871,7 +860,7 @@ static inline unsigned nblocks(size_t n) { return (unsigned)((n + kBlock - 1) / 
 // (H = 2 twice: 8.8); 64^3, one sweep 2 x 3.9 -> 5.9 us.
 // PRO: the first sweeps after the coarse level: u + P(uc - ub) is formed as the tile
 // is loaded (about 1 us more, against 4.8 us of a launch of its own).
-template <bool N1, int LG, int H, bool PRO>
+template <int LG, int H, bool PRO>
 __global__ __launch_bounds__(1024) void k_sweep_tile(const double *__restrict__ u, const double *__restrict__ f,
                                                      double *__restrict__ out, OpConst kc,
                                                      const double *__restrict__ uc, const double *__restrict__ ub,
@@ -932,7 +921,7 @@ __global__ __launch_bounds__(1024) void k_sweep_tile(const double *__restrict__ 
             int i, j, k;
             if (place(h, q, i, j, k)) {
                 const int c = slot(i, j, k), side = ((i * E + j) << LG) + (1 - (k & 1)) * HALF;
-                ue[c] = tail_update<N1, LG>(ue[c], ue[c + E * N], ue[c - E * N], ue[c + N], ue[c - N],
+                ue[c] = tail_update(ue[c], ue[c + E * N], ue[c - E * N], ue[c + N], ue[c - N],
                                             ue[side + (((k + 1) & M) >> 1)], ue[side + (((k - 1) & M) >> 1)], fv[h][q], kc);
             }
         }
@@ -951,10 +940,7 @@ static void launch_tile(mgfr_ctx *c, Level &L, const double *f, const OpConst &k
     const unsigned nb = (unsigned)((L.N / 4) * (L.N / 4));
     const double *uc = from ? from->u : nullptr, *ub = from ? from->ubar : nullptr;
     auto go = [&](auto *k) { k<<<nb, 1024, 0, c->stream>>>(L.u, f, L.alt, kc, uc, ub, c->p.prolong); };
-    if (c->p.n == 1)
-        from ? go(k_sweep_tile<true, LG, H, true>) : go(k_sweep_tile<true, LG, H, false>);
-    else
-        from ? go(k_sweep_tile<false, LG, H, true>) : go(k_sweep_tile<false, LG, H, false>);
+    from ? go(k_sweep_tile<LG, H, true>) : go(k_sweep_tile<LG, H, false>);
     std::swap(L.u, L.alt);
 }
 
@@ -1025,10 +1011,7 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
             const int chunk = row_chunk(L.N, nkt * njt);
             const RowArgs A{L.u, f, L.alt, L.lg, chunk, nkt, njt, kc};
             const unsigned nb = nkt * njt * (unsigned)((L.N + chunk - 1) / chunk);
-            if (c->p.n == 1)
-                k_sweep_rows<true><<<nb, 64 * (kRowF + 1), 0, c->stream>>>(A);
-            else
-                k_sweep_rows<false><<<nb, 64 * (kRowF + 1), 0, c->stream>>>(A);
+            k_sweep_rows<<<nb, 64 * (kRowF + 1), 0, c->stream>>>(A);
             std::swap(L.u, L.alt);
         } else if (tile) {
             if (L.N == 64) {
@@ -1069,10 +1052,7 @@ static int launch_tail(mgfr_ctx *c, int l0)
     A.q = c->q;
     A.max_du = c->p.max_du;
     A.tab = c->exp2tab;
-    if (c->p.n == 1)
-        k_tail<true><<<1, kTailThreads, 0, c->stream>>>(A);
-    else
-        k_tail<false><<<1, kTailThreads, 0, c->stream>>>(A);
+    k_tail<<<1, kTailThreads, 0, c->stream>>>(A);
     MGFR_HIP(hipGetLastError());
     return MGFR_OK;
 }

@@ -651,3 +651,62 @@ def test_reported_residual_is_that_of_the_returned_field(N, n, pre, post, cycles
     r = float(s.residual(u, f).abs().max()) / st.scale
     print(f"  reported {st.res:.12e}, field {r:.12e}")
     assert abs(st.res / r - 1) < 1e-9
+
+
+# ------------------------------------------------- small and very negative fields
+
+@pytest.mark.parametrize("contrast", [1e-2, 1e-4, 1e-6, 1e-8])
+@pytest.mark.parametrize("N", [8, 16, 32, 64, 128, 256])
+def test_low_contrast_solve_reaches_a_tight_tolerance(N, contrast):
+    """Linear-theory densities: |u| is as small as the contrast, and the sweeps'
+    e^{-u/2} - 1 has to keep its relative precision there, or their fixed point
+    moves off the operator that the residual measures.  The oracle (expm1)
+    reaches 1e-13 in every case up to 128^3; 1e-12 here."""
+    mg = _mg()
+    print(f"[case] low contrast N={N} {contrast}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N)
+    d = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV)
+    d -= d.mean()
+    d *= contrast / d.abs().max()
+    s = mg.Solver(_params(mg, N, fr0_abs=1e-6, tol=1e-12, max_vcycles=30))
+    _, _, st = s.solve(d, want_dfr=False, allow_not_converged=True)
+    print(f"  cycles {st.vcycles}, residual {st.res:.2e}")
+    assert st.status == 0 and st.res <= 1e-12
+
+
+@pytest.mark.parametrize("mean,spread", [(0.0, 1e-8), (0.0, 1e-3), (-0.25, 0.3), (-800.0, 100.0)])
+@pytest.mark.parametrize("N", [32, 64, 128])
+def test_sweeps_match_one_colour_kernels_over_the_range_of_u(N, mean, spread):
+    """Tile and row sweeps against one launch per colour for fields near zero,
+    across the border of small and ordinary values and where e^u underflows (the
+    update is then the step limit): both evaluate the same formula, with another
+    order of six-term sums, 1e-13 of the largest |u| as for O(1) fields."""
+    mg = _mg()
+    print(f"[case] sweeps over the range of u N={N} {mean} {spread}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N)
+    u0 = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * spread + mean
+    f = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV) * min(spread, 1.0)
+    out = []
+    for fused in (128, 0):
+        s = mg.Solver(_params(mg, N, fr0_abs=1e-6))
+        s.set_fused_min_mesh(fused)
+        out.append(s.ngs_sweep(u0.clone(), f, 2))
+    assert bool(torch.isfinite(out[1]).all())
+    assert float((out[0] - out[1]).abs().max()) < 1e-13 * float(out[1].abs().max())
+
+
+@pytest.mark.parametrize("mean,spread", [(0.0, 1e-8), (0.0, 1e-3), (-800.0, 20.0)])
+@pytest.mark.parametrize("N", [8, 16])
+def test_tail_cycle_over_the_range_of_u_matches_oracle(N, mean, spread):
+    """One V-cycle in the tail kernel for the same fields, against the oracle:
+    1e-12 of the largest |u| as for O(1) fields."""
+    mg = _mg()
+    print(f"[case] tail over the range of u N={N} {mean} {spread}", flush=True)
+    p = _oparams(N, fr0_abs=1e-6)
+    rng = np.random.default_rng(N)
+    u0 = rng.normal(mean, spread, (N, N, N))
+    f = rng.normal(0.0, min(spread, 1.0), (N, N, N))
+    ref = O.vcycle_once(p, f, u0)
+    u = mg.Solver(_params(mg, N, fr0_abs=1e-6)).vcycle(torch.tensor(u0, device=DEV), torch.tensor(f, device=DEV))
+    assert np.isfinite(ref).all()
+    assert _rel(u.cpu().numpy(), ref) < 1e-12

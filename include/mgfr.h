@@ -472,8 +472,8 @@ void mgfr_amr_destroy(mgfr_amr *amr);
 int mgfr_amr_set_relaxation32(mgfr_amr *amr, double omega);
 /* pos: float32 [np][3] (unit masses); u0: float64 [N0^3] output (base solution) or
  * NULL; st: HOST array of refine_levels + 1 stats (level 0 = base) or NULL.
- * Refinement flags are built on the device and only the block maps reach
- * the host; then the composite masses are assigned (binned when
+ * Refinement flags, block lists and block maps are built on the device, the
+ * host reads the number of blocks; then the composite masses are assigned (binned when
  * mgfr_amr_reserve_particles covers np).
  * A non-finite position (or one beyond 1e15 Mpc/h) gives MGFR_ERR_NONFINITE.
  * Returns the worst level status (MGFR_NOT_CONVERGED if a level hit

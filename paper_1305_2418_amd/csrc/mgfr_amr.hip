@@ -1400,7 +1400,6 @@ struct mgfr_amr {
     int *map[kMaxRef + 1] = {nullptr}, *org[kMaxRef + 1] = {nullptr}, *nbr[kMaxRef + 1] = {nullptr};
     double *arr[kMaxRef + 1][4][kSub] = {};  // u, f, ub, E per sublevel
     float *arr32[kMaxRef + 1][4][kSub] = {};  // e, u, r, eb per sublevel (mixed precision only)
-    std::vector<int> horg[kMaxRef + 1];
     uint32_t *grp = nullptr;  // scratch of the block lists (build_level)
     mgfr_stats st[kMaxRef + 1];
     double beta = 0, C = 0, fbar = 0;
@@ -1511,9 +1510,9 @@ void amr_free(mgfr_amr *A)
     delete A;
 }
 
-// Block list, block map and face neighbours of level l from its flags; the origins
-// also on the host with want_org.
-int build_level(mgfr_amr *A, int l, bool want_org)
+// Block list, block map and face neighbours of level l from its flags.  Nothing of
+// the level changes if there are more blocks than max_blocks.
+int build_level(mgfr_amr *A, int l)
 {
     const int lgM = A->lg0 + l - 3;
     const size_t n = (size_t)1 << (3 * lgM);
@@ -1534,13 +1533,6 @@ int build_level(mgfr_amr *A, int l, bool want_org)
                                                                                      lgM, A->nbr[l]);
     MGFR_HIP(hipGetLastError());
     A->nb[l] = (int)count;
-    if (want_org) {
-        A->horg[l].resize(3 * (size_t)count);
-        if (count)
-            MGFR_HIP(hipMemcpyAsync(A->horg[l].data(), A->org[l], 3 * sizeof(int) * (size_t)count, hipMemcpyDeviceToHost,
-                                    A->stream));
-        MGFR_HIP(hipStreamSynchronize(A->stream));
-    }
     return MGFR_OK;
 }
 
@@ -1829,7 +1821,7 @@ extern "C" int mgfr_amr_solve(mgfr_amr *A, const float *pos, int64_t np, double 
     k_flag_base<<<(unsigned)std::min<size_t>((n0 + 255) / 256, 16384), 256, 0, A->stream>>>(A->cnt0, A->lg0,
                                                                                            A->flag[1]);
     MGFR_HIP(hipGetLastError());
-    if ((rc = build_level(A, 1, A->nref < 2))) return rc;
+    if ((rc = build_level(A, 1))) return rc;
     if (A->nref >= 2) {
         // level-2 blocks from level-1 counts inside level-1 blocks, then proper nesting
         const int N1 = 2 * N0, M2 = N1 / 4;
@@ -1846,8 +1838,8 @@ extern "C" int mgfr_amr_solve(mgfr_amr *A, const float *pos, int64_t np, double 
                                                                                               A->flag[1]);
             MGFR_HIP(hipGetLastError());
         }
-        if ((rc = build_level(A, 1, true))) return rc;
-        if ((rc = build_level(A, 2, true))) return rc;
+        if ((rc = build_level(A, 1))) return rc;
+        if ((rc = build_level(A, 2))) return rc;
     }
     // 2. composite cloud-in-cell masses (Sec. 3.1) on the base mesh and the blocks,
     //    then the covered coarser cells as sums of their daughters
@@ -1979,11 +1971,15 @@ extern "C" int mgfr_amr_get_level(mgfr_amr *A, int level, int32_t *origins_host,
 {
     if (!A || level < 1 || level > A->nref) return set_error(MGFR_ERR_ARG, "invalid level");
     const LevelDev L = level_dev(A, level);
-    if (origins_host && L.nb) memcpy(origins_host, A->horg[level].data(), 3 * sizeof(int) * (size_t)L.nb);
-    if (u && L.nb) {
+    if (L.nb == 0) return MGFR_OK;
+    // the origins lie on the device only, so that they are those of the nb blocks
+    // also after a solve that failed between two builds of the level
+    if (origins_host)
+        MGFR_HIP(hipMemcpyAsync(origins_host, L.org, 3 * sizeof(int) * (size_t)L.nb, hipMemcpyDeviceToHost, A->stream));
+    if (u) {
         k_amr_copy_out<<<grid_of((size_t)L.nb * 512), 256, 0, A->stream>>>(L, u);
         MGFR_HIP(hipGetLastError());
-        MGFR_HIP(hipStreamSynchronize(A->stream));
     }
+    MGFR_HIP(hipStreamSynchronize(A->stream));
     return MGFR_OK;
 }

@@ -333,3 +333,32 @@ def test_block_lists_follow_the_counts(N0, nref):
     assert np.all(np.diff(lin) > 0) and np.all(got[want])
     if nref == 1:
         assert np.array_equal(got, want)
+
+
+def test_block_list_after_a_solve_that_ran_out_of_blocks():
+    """The capacity holds the flagged level-1 blocks but not those that proper
+    nesting adds: the solve fails, and the level that it leaves is that of the
+    first list (on a new object, whose host side knows no blocks yet, and after
+    a solve of fewer)."""
+    from paper_1305_2418_amd import mgfr
+    N0 = 32
+    print("[case] block list after a failed solve", flush=True)
+    pos = synth.clustered_load(N0, 100.0, rms=5.0, seed=4, n_halos=50, profile="nfw")
+    idx = np.floor(pos.numpy().astype(np.float64) / (100.0 / N0)).astype(int) % N0
+    cnt = np.zeros((N0,) * 3, int)
+    np.add.at(cnt, (idx[:, 0], idx[:, 1], idx[:, 2]), 1)
+    M = N0 // 4
+    first = np.argwhere((cnt > 8).reshape(M, 4, M, 4, M, 4).any(axis=(1, 3, 5))) * 8
+    nested = int(O.amr_flags(O.params(mesh=N0, fr0_abs=1e-6), 2, pos.numpy())[1].sum())
+    assert 1 < len(first) < nested
+    q = (torch.arange(N0, device=DEV, dtype=torch.float32) + 0.5) * (100.0 / N0)
+    few = torch.cat([torch.cartesian_prod(q, q, q), torch.full((16, 3), 50.1, device=DEV)])  # one clump
+    for before in (None, few):
+        amr = mgfr.Amr(mgfr.Params(mesh=N0, fr0_abs=1e-6, refine_levels=2, max_vcycles=1), max_blocks=len(first))
+        if before is not None:
+            amr.solve(before, allow_not_converged=True)
+        with pytest.raises(mgfr.MgfrError) as ei:
+            amr.solve(pos.to(DEV))
+        assert "max_blocks" in str(ei.value)
+        org, u = amr.level(1)
+        assert np.array_equal(org, first) and u.shape == (len(first), 8, 8, 8)

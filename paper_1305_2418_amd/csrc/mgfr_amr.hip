@@ -1090,7 +1090,7 @@ __global__ __launch_bounds__(64 * kBlkWaves) void k_amrx_outer(LevelDev L, doubl
     const int fd[4] = {blk_tile(a, -1, b), blk_tile(a, 8, b), blk_tile(a, b, -1), blk_tile(a, b, 8)};
 #pragma unroll
     for (int f = 0; f < 4; ++f) tile[fd[f]] = make_double2(fu[f], exp64(fu[f], tab));
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     double mx = 0.0;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
@@ -1152,7 +1152,7 @@ __global__ __launch_bounds__(64 * kBlkWaves) void k_amrx_sweep_blk(LevelDev L, i
     for (int i = 0; i < 4; ++i) r[i] = L.r32[0][o + 200 * i];
     AmrxColumn c;
     amrx_load_block(L, L.e32[0], blk, lane, c, tile);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         auto at = [&](int x) {  // cell x + s of the column, x + 1 known
@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(64 * kBlkWaves) void k_amrx_restrict_blk(LevelDev L
     for (int x = 0; x < 8; ++x) r[x] = L.r32[0][o + 100 * x];
     AmrxColumn c;
     amrx_load_block(L, L.e32[0], blk, lane, c, tile);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
         auto at = [&](int i) { return make_float4(c.e[i], c.X[i], c.u[i], c.w[i]); };
@@ -1218,10 +1218,10 @@ __global__ __launch_bounds__(64 * kBlkWaves) void k_amrx_restrict_blk(LevelDev L
         amrx_sides(at(x + 2), at(x), tile, blk_tile(x, y, z), cell);
         r[x] -= mx_value(c.e[x + 1], c.X[x + 1], c.u[x + 1], c.w[x + 1], cell.en, cell.Xn, cell.un, cell.wn, kc);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int x = 0; x < 8; ++x) tile[blk_tile(x, y, z)] = make_float4(c.e[x + 1], c.u[x + 1], r[x], 0.f);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     const int X = lane >> 4, Y = (lane >> 2) & 3, Z = lane & 3;
     float se = 0.f, su = 0.f, sr = 0.f;
 #pragma unroll

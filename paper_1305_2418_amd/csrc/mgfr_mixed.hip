@@ -1087,8 +1087,7 @@ __device__ __forceinline__ void mx_tail_sweeps(const MxTailLevel<LG> &T, int swe
 }
 
 // Sweeps of the 4^3 level by the first wave: within one wave the LDS accesses
-// of a half-sweep are done before the next one's, and the fences keep the
-// compiler from moving them.
+// of a half-sweep are done before the next one's (wave_lds_sync).
 __device__ __forceinline__ void mx_tail_sweeps4(const MxTailLevel<2> &T, int sweeps, const MxConst &kc)
 {
     using G = TailGrid<2>;
@@ -1107,8 +1106,7 @@ __device__ __forceinline__ void mx_tail_sweeps4(const MxTailLevel<2> &T, int swe
                 x.y = fexpm1(x.x);
                 T.c[c] = x;
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
         }
     }
     __syncthreads();

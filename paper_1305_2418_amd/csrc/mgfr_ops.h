@@ -88,6 +88,16 @@ struct PlaneBuf {
     }
 };
 
+// Between writes to LDS and reads of what other lanes of the same wave wrote (or
+// the reverse): a wave's LDS accesses complete in order, so nothing is waited for;
+// the fence keeps the compiler from moving an access across, which the wave
+// barrier alone (an order of the schedule, not of memory) does not.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ double nanmax(double a, double b)
 {
     return (a != a || a > b) ? a : b;

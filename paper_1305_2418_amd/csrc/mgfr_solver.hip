@@ -694,8 +694,7 @@ __device__ __forceinline__ void tail_sweeps(const TailLevel<LG> &T, int sweeps, 
 }
 
 // Sweeps of the 4^3 level by the first wave: within one wave the LDS accesses
-// of a half-sweep are done before the next one's, and the fences keep the
-// compiler from moving them.
+// of a half-sweep are done before the next one's (wave_lds_sync).
 __device__ __forceinline__ void tail_sweeps4(const TailLevel<2> &T, int sweeps, const OpConst &kc)
 {
     using L = TailLevel<2>;
@@ -712,8 +711,7 @@ __device__ __forceinline__ void tail_sweeps4(const TailLevel<2> &T, int sweeps, 
                 x = tail_update(x, T.ue[n0], T.ue[n1], T.ue[n2], T.ue[n3], T.ue[n4], T.ue[n5], f, kc);
                 T.ue[c] = x;
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
         }
     }
     __syncthreads();

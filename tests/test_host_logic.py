@@ -91,3 +91,17 @@ def test_synthetic_loads_are_seeded_and_in_the_box():
     cells = np.floor(a / (100.0 / 16)).astype(int)
     counts = np.bincount((cells[:, 0] * 16 + cells[:, 1]) * 16 + cells[:, 2], minlength=16 ** 3)
     assert counts.sum() == 16 ** 3 and counts.max() > 20
+
+
+def test_wave_level_lds_exchanges_are_fenced():
+    """Lanes of one wave exchange values through LDS in several kernels; each such
+    place goes through the helper that orders memory as well as the schedule."""
+    src = os.path.join(ROOT, "paper_1305_2418_amd", "csrc")
+    uses = 0
+    for name in sorted(os.listdir(src)):
+        txt = open(os.path.join(src, name)).read()
+        uses += txt.count("wave_lds_sync();")
+        for m in re.finditer(r"__builtin_amdgcn_wave_barrier\(\)", txt):
+            before = txt[:m.start()].rstrip().splitlines()[-1].strip()
+            assert before == '__builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");', (name, before)
+    assert uses >= 7

@@ -476,3 +476,124 @@ def test_context_network_calls(tmp_path):
     s3 = mg.Solver(mg.Params(mesh=N))
     with pytest.raises(mg.MgfrError):
         s3.nn_predict(d)
+
+
+def _taps(x):
+    """The 27 shifts of x [B,S,S,S,C] that the convolution's taps read: x[v + off_t]."""
+    for t in range(27):
+        yield torch.roll(x, (1 - t // 9, 1 - (t // 3) % 3, 1 - t % 3), (1, 2, 3)).reshape(-1, x.shape[-1])
+
+
+def _up(x):
+    return x.repeat_interleave(2, 1).repeat_interleave(2, 2).repeat_interleave(2, 3)
+
+
+def _net_on_volumes(B, S):
+    """A network with non-zero biases on B volumes of side S: its bf16-rounded layers
+    (w [27, Cout, Cin], b) and head, activations, target and gradient, on the GPU."""
+    mg = _mg()
+    net = mg.Net(seed=B + S, max_voxels=B * S ** 3)
+    p = net.get_params()
+    rng = np.random.default_rng(S)
+    off, layers = 0, []
+    for ci, co in U.LAYERS:
+        sl = slice(off, off + 27 * ci * co)
+        off = sl.stop + co
+        p[sl.stop:off] = rng.normal(0.0, 0.1, co)
+        layers.append((sl, slice(sl.stop, off), ci, co))
+    net.set_params(p)
+    g = torch.Generator(device=DEV).manual_seed(S)
+    delta = torch.exp(torch.randn((B, S, S, S), generator=g, dtype=torch.float64, device=DEV)) - 1.0
+    u = -2.0 * torch.log1p(0.1 * (delta + 1.0)) + 0.1
+    cond = [(0.5 + 0.05 * b, 10.0 ** (-7 + 0.2 * b)) for b in range(B)]
+    net.predict(delta, cond)
+    A = [net.activation(i) for i in range(16)]
+    _, grad = net.grads(delta, u, cond)  # the same forward pass again
+    p = torch.tensor(p, device=DEV)
+    W = [(p[w].bfloat16().double().reshape(27, co, ci), p[b].double(), w, b) for w, b, ci, co in layers]
+    return W, p[off:off + 16].double(), A, u, torch.tensor(grad, dtype=torch.float64, device=DEV)
+
+
+# (layer, input activations (the second of a pair is the skip connection), output activation)
+_CONV_IO = [(0, (0,), 1), (1, (1,), 2), (2, (3,), 4), (3, (4,), 5), (4, (6,), 7), (5, (7,), 8), (6, (8, 5), 10),
+            (7, (10,), 11), (8, (11, 2), 13), (9, (13,), 14)]
+
+
+def _input_of(A, io):
+    return A[io[0]].double() if len(io) == 1 else torch.cat([_up(A[io[0]]), A[io[1]]], dim=4).double()
+
+
+@pytest.mark.parametrize("B,S", [(5, 32), (2, 64)])
+def test_network_convolutions_element_by_element_in_batches(B, S):
+    """Every convolution of the forward pass from the library's own input to it, over
+    several volumes and in the tile depths that larger meshes take (the decoder's
+    two-source layers too), against float64 on the same bf16 values: K = 27 Cin + 1
+    float32 additions, then one bf16 rounding."""
+    print(f"[case] network convolutions B={B} S={S}", flush=True)
+    W, _, A, _, _ = _net_on_volumes(B, S)
+    for l, io, out in _CONV_IO:
+        w, b = W[l][:2]
+        x = _input_of(A, io)
+        z = torch.zeros((x.numel() // x.shape[-1], w.shape[1]), dtype=torch.float64, device=DEV) + b
+        E = torch.zeros_like(z) + b.abs()
+        for t, xt in enumerate(_taps(x)):
+            z += xt @ w[t].t().contiguous()
+            E += xt.abs() @ w[t].abs().t().contiguous()
+        k = 27 * x.shape[-1] + 1
+        _check_rounded(A[out].double().reshape(z.shape), torch.relu(z), _gamma(k) * E, f"conv {l} {io} -> {out}")
+
+
+@pytest.mark.parametrize("B,S", [(5, 32), (2, 64)])
+def test_network_gradient_against_the_same_steps_in_float64(B, S):
+    """The gradient of a batch against the same backward steps from the library's own
+    activations, in float64 with the library's bf16 rounding of every gradient that
+    it stores, an explicit concatenation and a ReLU mask of its own.  A float32 sum
+    falls on the other side of a bf16 rounding than its float64 value for some 0.5 %
+    of the elements (2^-24 sqrt(2592) of the sum against a spacing of 2^-8): 2e-4 of
+    a tensor's norm, 6e-4 after ten layers; 3e-3 per layer here, where a wrong row
+    or edge of a tile changes 1e-2 and more."""
+    print(f"[case] network gradient B={B} S={S}", flush=True)
+    W, wh, A, u, grad = _net_on_volumes(B, S)
+    bf = lambda t: t.float().bfloat16().double()  # noqa: E731
+    relu = lambda d, i: torch.where(A[i].double() > 0, d, torch.zeros_like(d))  # noqa: E731
+    io = {l: x for l, x, _ in _CONV_IO}
+
+    def layer(l, dz, want_dx=True):
+        """Check layer l's gradients for dz, return its input's gradient (bf16)."""
+        w, _, ws, bs = W[l]
+        zf = dz.reshape(-1, dz.shape[-1])
+        dw = torch.stack([zf.t().contiguous() @ xt for xt in _taps(_input_of(A, io[l]))])
+        for what, ref, sl in (("weights", dw.reshape(-1), ws), ("biases", zf.sum(0), bs)):
+            rel = float(torch.linalg.norm(grad[sl] - ref) / torch.linalg.norm(ref))
+            print(f"  layer {l} {what}: rel {rel:.2e}", flush=True)
+            assert rel < 3e-3, (l, what)
+        if not want_dx:
+            return None
+        dx = torch.zeros((zf.shape[0], w.shape[2]), dtype=torch.float64, device=DEV)
+        for t in range(27):
+            dx += torch.roll(dz, (t // 9 - 1, (t // 3) % 3 - 1, t % 3 - 1), (1, 2, 3)).reshape(zf.shape) @ w[t]
+        return bf(dx.reshape(dz.shape[:-1] + (w.shape[2],)))
+
+    def fold(d):  # sum over the 2^3 children
+        Bd, n, C = d.shape[0], d.shape[1] // 2, d.shape[-1]
+        return d.reshape(Bd, n, 2, n, 2, n, 2, C).sum(dim=(2, 4, 6))
+
+    e = A[15].double().reshape(u.shape) - (u.float() / U.U_SCALE).double()
+    d = 2.0 * e / e.numel()
+    h5 = A[14].double()
+    assert torch.allclose((d[..., None] * h5).sum((0, 1, 2, 3)), grad[-17:-1], rtol=1e-3, atol=1e-3 * float(grad[-17:-1].abs().max()))
+    dz = relu(bf(d[..., None] * wh), 14)
+    dz = relu(layer(9, dz), 13)
+    dcat5 = layer(8, dz)
+    dz = relu(bf(fold(dcat5[..., :32])), 11)
+    dz = relu(layer(7, dz), 10)
+    dcat4 = layer(6, dz)
+    dz = relu(bf(fold(dcat4[..., :64])), 8)
+    dz = relu(layer(5, dz), 7)
+    dp2 = layer(4, dz)
+    dz = relu(bf(dcat4[..., 64:] + _up(dp2) / 8), 5)
+    dz = relu(layer(3, dz), 4)
+    dp1 = layer(2, dz)
+    dz = relu(bf(dcat5[..., 32:] + _up(dp1) / 8), 2)
+    dz = relu(layer(1, dz), 1)
+    layer(0, dz, want_dx=False)

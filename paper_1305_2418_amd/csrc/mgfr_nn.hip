@@ -450,19 +450,24 @@ __global__ __launch_bounds__(256, 2) void k_conv_reg(ConvIn in, int lgS, const _
     }
 }
 
-// Launch k_conv3d over nvox = B S^3 voxels (S >= 8, Cout a multiple of 16 up to 96).
+// Launch k_conv_reg or k_conv3d over nvox = B S^3 voxels (S >= 8, Cout a multiple of 16 up to 96).
 // With a mask M (Cout channels, for a gradient through a ReLU) Y is zero where M > 0 does not hold.
-// A skip connection is for meshes of 16^3 and up, without a mask.
-void launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, const float *bias, int Cout, int relu,
-                   const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
+// A skip connection is for the shapes of the decoder's layers: meshes of 16^3 and up, 32 + 16 to
+// 16 channels or both multiples of 32 to a multiple of 32, no mask; others are refused.
+int launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, const float *bias, int Cout, int relu,
+                  const __bf16 *M, __bf16 *Y, float *Y32, hipStream_t s)
 {
     const int Cin = in.C + in.Cs;
     // k_conv_reg stores four channels at once; outputs off those boundaries take k_conv3d
     const bool aligned = ((uintptr_t)Y & 7) == 0 && ((uintptr_t)Y32 & 15) == 0;
-    if (Cin % 16 == 0 && lgS >= 4 && aligned) {
-        // two blocks of 16 channels per workgroup where the number is even: its
-        // weights still fit in the registers and the input is read half as often
-        const int NT = Cout % 32 == 0 ? 2 : 1;
+    const bool reg = Cin % 16 == 0 && lgS >= 4 && aligned;
+    const int CK = Cin % 32 == 0 ? 32 : 16;
+    // two blocks of 16 channels per workgroup where the number is even: its
+    // weights still fit in the registers and the input is read half as often
+    const int NT = Cout % 32 == 0 ? 2 : 1;
+    if (in.skip && (!reg || M || in.C % CK || NT != CK / 16))
+        return set_error(MGFR_ERR_ARG, "no convolution of two sources with %d + %d to %d channels here", in.C, in.Cs, Cout);
+    if (reg) {
         const unsigned groups = (unsigned)(Cout / (16 * NT));
         // persistent, two workgroups per CU (their registers; 768 groups on 512
         // places: 59 us instead of 49 for 16 -> 16 channels)
@@ -471,37 +476,33 @@ void launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, cons
             k<<<dim3(std::min(nt, std::max(512u / groups, 1u)), groups), 256, 0, s>>>(in, lgS, W, bias, Cout, relu,
                                                                                       M, nt, Y, Y32);
         };
-        auto pick = [&](auto *masked, auto *plain, auto *skip, unsigned tz) {
-            in.skip ? go(skip, tz) : M ? go(masked, tz) : go(plain, tz);
-        };
+        auto pick = [&](auto *masked, auto *plain, unsigned tz) { M ? go(masked, tz) : go(plain, tz); };
         // The deepest tile that the registers allow loads the fewest voxels of halo
         // (4 planes: 2.1 per voxel, 2: 2.8, 1: 4.2); a shallower one where the
         // tiles would leave CUs without a workgroup
         const size_t b4 = nvox / 512 * groups, b2 = nvox / 256 * groups;
-        if (Cin % 32 == 0) {
+        if (in.skip && CK == 32)
+            b2 >= 256 ? go(k_conv_reg<32, 2, 2, false, true>, 2) : go(k_conv_reg<32, 2, 1, false, true>, 1);
+        else if (in.skip)
+            b4 >= 256 ? go(k_conv_reg<16, 1, 4, false, true>, 4) : go(k_conv_reg<16, 1, 2, false, true>, 2);
+        else if (CK == 32) {
             if (NT == 1)
-                pick(k_conv_reg<32, 1, 2, true, false>, k_conv_reg<32, 1, 2, false, false>,
-                     k_conv_reg<32, 1, 2, false, true>, 2);
+                pick(k_conv_reg<32, 1, 2, true, false>, k_conv_reg<32, 1, 2, false, false>, 2);
             else if (b2 >= 256)
-                pick(k_conv_reg<32, 2, 2, true, false>, k_conv_reg<32, 2, 2, false, false>,
-                     k_conv_reg<32, 2, 2, false, true>, 2);
+                pick(k_conv_reg<32, 2, 2, true, false>, k_conv_reg<32, 2, 2, false, false>, 2);
             else
-                pick(k_conv_reg<32, 2, 1, true, false>, k_conv_reg<32, 2, 1, false, false>,
-                     k_conv_reg<32, 2, 1, false, true>, 1);
+                pick(k_conv_reg<32, 2, 1, true, false>, k_conv_reg<32, 2, 1, false, false>, 1);
         } else if (NT == 1) {
             if (b4 >= 256)
-                pick(k_conv_reg<16, 1, 4, true, false>, k_conv_reg<16, 1, 4, false, false>,
-                     k_conv_reg<16, 1, 4, false, true>, 4);
+                pick(k_conv_reg<16, 1, 4, true, false>, k_conv_reg<16, 1, 4, false, false>, 4);
             else
-                pick(k_conv_reg<16, 1, 2, true, false>, k_conv_reg<16, 1, 2, false, false>,
-                     k_conv_reg<16, 1, 2, false, true>, 2);
+                pick(k_conv_reg<16, 1, 2, true, false>, k_conv_reg<16, 1, 2, false, false>, 2);
         } else if (b2 >= 256)
-            pick(k_conv_reg<16, 2, 2, true, false>, k_conv_reg<16, 2, 2, false, false>,
-                     k_conv_reg<16, 2, 2, false, true>, 2);
+            pick(k_conv_reg<16, 2, 2, true, false>, k_conv_reg<16, 2, 2, false, false>, 2);
         else
-            pick(k_conv_reg<16, 2, 1, true, false>, k_conv_reg<16, 2, 1, false, false>,
-                     k_conv_reg<16, 2, 1, false, true>, 1);
-        return;
+            pick(k_conv_reg<16, 2, 1, true, false>, k_conv_reg<16, 2, 1, false, false>, 1);
+        MGFR_HIP(hipGetLastError());
+        return MGFR_OK;
     }
     const unsigned blocks = (unsigned)(nvox / (16 * kConvMT * kConvWaves));
     // LDS: the halo tile ((TX+2) x 10 x (TZ+2) voxels) times the channel chunk (bf16)
@@ -523,6 +524,8 @@ void launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, cons
     case 5: k_conv3d<5><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
     default: k_conv3d<6><<<grid, 64 * kConvWaves, lds, s>>>(in.x, lgS, Cin, W, bias, Cout, relu, M, Y, Y32); break;
     }
+    MGFR_HIP(hipGetLastError());
+    return MGFR_OK;
 }
 
 // dW[t][o][c] += sum_v dZ[v][o] X[v + off(t)][c] and db[o] += sum_v dZ[v][o];
@@ -1101,9 +1104,7 @@ int net_refresh(mgfr_net *n)
 int conv(mgfr_net *n, const ConvIn &in, size_t nvox, int lgS, int layer, __bf16 *y)
 {
     const ConvSpec &L = n->L[layer];
-    launch_conv3d(in, nvox, lgS, n->wbf + L.woff, n->p + L.boff, L.cout, 1, nullptr, y, nullptr, n->stream);
-    MGFR_HIP(hipGetLastError());
-    return MGFR_OK;
+    return launch_conv3d(in, nvox, lgS, n->wbf + L.woff, n->p + L.boff, L.cout, 1, nullptr, y, nullptr, n->stream);
 }
 
 // Backward through one convolution: from dz, the gradient before the layer's
@@ -1115,11 +1116,10 @@ int conv_bwd(mgfr_net *n, const __bf16 *dz, const ConvIn &in, size_t nvox, int l
 {
     const ConvSpec &L = n->L[layer];
     launch_wgrad(in, dz, nvox, lgS, L.cout, n->g + L.woff, n->g + L.boff, n->stream);
-    if (dx)
-        launch_conv3d({dz, L.cout}, nvox, lgS, n->wt + L.woff, nullptr, L.cin, 0, relu_in ? in.x : nullptr, dx,
-                      nullptr, n->stream);
     MGFR_HIP(hipGetLastError());
-    return MGFR_OK;
+    return dx ? launch_conv3d({dz, L.cout}, nvox, lgS, n->wt + L.woff, nullptr, L.cin, 0, relu_in ? in.x : nullptr, dx,
+                              nullptr, n->stream)
+              : MGFR_OK;
 }
 
 int net_forward(mgfr_net *n, const double *delta, int B, int lgS)
@@ -1432,10 +1432,8 @@ extern "C" int mgfr_conv3d_fwd(const void *x, int B, int S, int Cin, const void 
     if ((rc = conv_args(B, S, Cin, Cout, &lgS))) return rc;
     if (!x || !w || (!y && !y32)) return set_error(MGFR_ERR_ARG, "x, w and an output must be non-NULL");
     const size_t V = (size_t)B << (3 * lgS);
-    launch_conv3d({(const __bf16 *)x, Cin}, V, lgS, (const __bf16 *)w, bias, Cout, relu, nullptr, (__bf16 *)y, y32,
-                  (hipStream_t)stream);
-    MGFR_HIP(hipGetLastError());
-    return MGFR_OK;
+    return launch_conv3d({(const __bf16 *)x, Cin}, V, lgS, (const __bf16 *)w, bias, Cout, relu, nullptr, (__bf16 *)y, y32,
+                         (hipStream_t)stream);
 }
 
 extern "C" int mgfr_conv3d_bwd_data(const void *dz, int B, int S, int Cout, const void *w, int Cin, void *wt_work,
@@ -1448,10 +1446,8 @@ extern "C" int mgfr_conv3d_bwd_data(const void *dz, int B, int S, int Cout, cons
     hipStream_t s = (hipStream_t)stream;
     k_wt_transpose<<<gridn((size_t)27 * Cin * Cout), 256, 0, s>>>((const __bf16 *)w, Cin, Cout, (__bf16 *)wt_work);
     const size_t V = (size_t)B << (3 * lgS);
-    launch_conv3d({(const __bf16 *)dz, Cout}, V, lgS, (const __bf16 *)wt_work, nullptr, Cin, 0, nullptr,
-                  (__bf16 *)dx, nullptr, s);
-    MGFR_HIP(hipGetLastError());
-    return MGFR_OK;
+    return launch_conv3d({(const __bf16 *)dz, Cout}, V, lgS, (const __bf16 *)wt_work, nullptr, Cin, 0, nullptr,
+                         (__bf16 *)dx, nullptr, s);
 }
 
 extern "C" int mgfr_conv3d_bwd_weight(const void *x, const void *dz, int B, int S, int Cin, int Cout, float *dw,

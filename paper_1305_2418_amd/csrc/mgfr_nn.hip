@@ -35,6 +35,8 @@
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// eight bf16 at an address that need not be a multiple of 16
+typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));
 
 namespace mgfr {
 
@@ -547,7 +549,7 @@ int launch_conv3d(const ConvIn &in, size_t nvox, int lgS, const __bf16 *W, const
 // two); the three taps dy of a column share their rows, so that a k-step reads two
 // new half fragments per column instead of six.  The sums stay in registers over
 // all tiles and are added to dW once per workgroup; the next tile is loaded into
-// registers during the products.
+// registers during the products.  The caller's x and dZ may start at any element.
 // Bound: the traffic (16 -> 16 channels on 2.1 M voxels: 134 MB and the halos) and
 // the barriers around the staging.  That layer: 2163 us with a scalar transpose
 // into LDS per tap; 87 with transpose loads; 67 with the next tile in flight; 61
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(256) void k_conv3d_wgrad(ConvIn in, const __bf16 *_
                             (unsigned)((x0 - 1) & sm);
 #pragma unroll
         for (int i = 0; i < PZ; ++i)
-            rz[i] = *(const bf16x8 *)(z + ((size_t)(i * 16 / TX) << (2 * lgS)) * Cout + (size_t)zoff * Cout + h8);
+            rz[i] = *(const bf16x8_any *)(z + ((size_t)(i * 16 / TX) << (2 * lgS)) * Cout + (size_t)zoff * Cout + h8);
 #pragma unroll
         for (int i = 0; i < PX; ++i) {
             // the fields' sums mod S: carries stop below the highest bits, which add without
@@ -642,7 +644,7 @@ __global__ __launch_bounds__(256) void k_conv3d_wgrad(ConvIn in, const __bf16 *_
                 r = ((((r >> (2 * lgS + 1)) << lc) | ((r >> (lgS + 1)) & (unsigned)(sm >> 1))) << lc) |
                     ((r >> 1) & (unsigned)(sm >> 1));
             }
-            rx[i] = *(const bf16x8 *)(x + (size_t)r * from.C + h8);
+            rx[i] = *(const bf16x8_any *)(x + (size_t)r * from.C + h8);
         }
     };
     if (blockIdx.y < ntiles) fetch(blockIdx.y);

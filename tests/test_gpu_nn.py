@@ -597,3 +597,24 @@ def test_network_gradient_against_the_same_steps_in_float64(B, S):
     dz = relu(bf(dcat5[..., 32:] + _up(dp1) / 8), 2)
     dz = relu(layer(1, dz), 1)
     layer(0, dz, want_dx=False)
+
+
+@pytest.mark.parametrize("off", [1, 3, 4])
+@pytest.mark.parametrize("S,Cin,Cout", [(8, 16, 32), (16, 48, 16)])
+def test_conv_backward_weight_from_inputs_at_any_element(S, Cin, Cout, off):
+    """x and dZ one, three and four elements past an aligned address, on small
+    integers (exact in any order): the gradients of the aligned inputs."""
+    mg = _mg()
+    print(f"[case] conv wgrad from offset inputs S={S} Cin={Cin} Cout={Cout} off={off}", flush=True)
+    g = torch.Generator().manual_seed(S + off)
+    x = torch.randint(-3, 4, (1, S, S, S, Cin), generator=g).to(torch.bfloat16).to(DEV)
+    dz = torch.randint(-3, 4, (1, S, S, S, Cout), generator=g).to(torch.bfloat16).to(DEV)
+    want, want_b = mg.conv3d_bwd_weight(x, dz)
+    xo, zo = (torch.zeros(t.numel() + off, dtype=torch.bfloat16, device=DEV) for t in (x, dz))
+    xo[off:] = x.reshape(-1)
+    zo[off:] = dz.reshape(-1)
+    dw, db = torch.zeros_like(want), torch.zeros_like(want_b)
+    assert mg.lib().mgfr_conv3d_bwd_weight(xo.data_ptr() + 2 * off, zo.data_ptr() + 2 * off, 1, S, Cin, Cout,
+                                           dw.data_ptr(), db.data_ptr(), mg._stream_ptr()) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(dw, want) and torch.equal(db, want_b)

@@ -710,3 +710,38 @@ def test_tail_cycle_over_the_range_of_u_matches_oracle(N, mean, spread):
     u = mg.Solver(_params(mg, N, fr0_abs=1e-6)).vcycle(torch.tensor(u0, device=DEV), torch.tensor(f, device=DEV))
     assert np.isfinite(ref).all()
     assert _rel(u.cpu().numpy(), ref) < 1e-12
+
+
+def test_row_kernels_on_the_largest_mesh():
+    """1024^3, the largest mesh: the float64 row sweep against one launch per colour
+    (1e-13 of O(1) values, as on smaller meshes), the reported residual against the
+    residual field's largest entry, and one float32 correction cycle with the row
+    sweep against one with a pass per colour (the same bits)."""
+    mg = _mg()
+    N = 1024
+    print("[case] 1024^3", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    d = torch.randn((N, N, N), generator=g, dtype=torch.float64, device=DEV)
+    u0 = 0.7 * d - 1.0
+    out = []
+    for fused in (128, 0):
+        s = mg.Solver(_params(mg, N, fr0_abs=1e-6))
+        s.set_fused_min_mesh(fused)
+        out.append(s.ngs_sweep(u0.clone(), d, 1))
+        s.close()
+    assert float(out[0].sub_(out[1]).abs_().max()) < 1e-13
+    del out
+    s = mg.Solver(_params(mg, N, fr0_abs=1e-6, max_vcycles=0))
+    _, _, st = s.solve(d, u=u0.clone(), want_dfr=False, allow_not_converged=True)
+    f = O.background(_oparams(N, fr0_abs=1e-6))[1] * _oparams(N).omega_m / _oparams(N).a ** 3 * d
+    r = float(s.residual(u0, f).abs_().max()) / st.scale
+    assert abs(st.res0 / r - 1) < 1e-9
+    s.close()
+    del f, u0
+    out = []
+    for fused in (True, False):
+        s = mg.Solver(_params(mg, N, fr0_abs=1e-6, precision=mg.MIXED, max_vcycles=1, pre_smooth=1, post_smooth=1))
+        s.set_fused_sweep32(fused)
+        out.append(s.solve(d, want_dfr=False, allow_not_converged=True)[0])
+        s.close()
+    assert torch.equal(out[0], out[1])

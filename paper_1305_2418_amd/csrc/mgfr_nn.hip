@@ -213,13 +213,6 @@ __device__ __forceinline__ ConvSrc conv_src(const ConvIn &I, int c)
     return c < I.C ? ConvSrc{I.x + c, I.C, 1} : ConvSrc{I.skip + (c - I.C), I.Cs, 0};
 }
 
-// voxel (x, y, z) of the volume that starts at voxel vol, in the source's mesh
-__device__ __forceinline__ size_t conv_voxel(const ConvSrc &s, size_t vol, int z, int y, int x, int lgS)
-{
-    const int lg = lgS - s.sh;
-    return (vol >> (3 * s.sh)) + ((((size_t)(z >> s.sh) << lg) + (size_t)(y >> s.sh)) << lg) + (size_t)(x >> s.sh);
-}
-
 // The same convolution for S >= 16 and input channels in chunks of CK = 16 or 32
 // (every layer of the network above the 8^3 mesh, and their backward-data passes).
 //
@@ -1029,7 +1022,7 @@ struct mgfr_net {
     int step = 0;
     int fwd_B = 0, fwd_lg = 0;  // shape of the last forward pass (0: none yet)
     // activations
-    __bf16 *x0, *h1a, *s1, *p1, *h2a, *s2, *p2, *h3a, *h3, *cat4, *h4a, *h4, *cat5, *h5a, *h5;
+    __bf16 *x0, *h1a, *s1, *p1, *h2a, *s2, *p2, *h3a, *h3, *h4a, *h4, *h5a, *h5;
     float *y32, *cond, *loss;
     // gradient scratch
     __bf16 *gA, *gB, *gC, *gD;
@@ -1068,8 +1061,7 @@ int net_alloc(mgfr_net *n)
     if ((rc = A(&n->x0, V * 16)) || (rc = A(&n->h1a, V * 16)) || (rc = A(&n->s1, V * 16)) ||
         (rc = A(&n->p1, V2 * 16)) || (rc = A(&n->h2a, V2 * 32)) || (rc = A(&n->s2, V2 * 32)) ||
         (rc = A(&n->p2, V3 * 32)) || (rc = A(&n->h3a, V3 * 64)) || (rc = A(&n->h3, V3 * 64)) ||
-        (rc = A(&n->cat4, V2 * 96)) || (rc = A(&n->h4a, V2 * 32)) || (rc = A(&n->h4, V2 * 32)) ||
-        (rc = A(&n->cat5, V * 48)) || (rc = A(&n->h5a, V * 16)) || (rc = A(&n->h5, V * 16)) ||
+        (rc = A(&n->h4a, V2 * 32)) || (rc = A(&n->h4, V2 * 32)) || (rc = A(&n->h5a, V * 16)) || (rc = A(&n->h5, V * 16)) ||
         (rc = A(&n->gA, V * 48)) || (rc = A(&n->gB, V2 * 96)) || (rc = A(&n->gC, V * 16)) || (rc = A(&n->gD, V * 16)))
         return rc;
     MGFR_HIP(hipMalloc(&n->y32, V * sizeof(float)));
@@ -1084,7 +1076,7 @@ void net_free(mgfr_net *n)
 {
     if (!n) return;
     void *ptrs[] = {n->p, n->g, n->m, n->v, n->wbf, n->wt, n->x0, n->h1a, n->s1, n->p1, n->h2a, n->s2, n->p2,
-                    n->h3a, n->h3, n->cat4, n->h4a, n->h4, n->cat5, n->h5a, n->h5, n->gA, n->gB, n->gC, n->gD,
+                    n->h3a, n->h3, n->h4a, n->h4, n->h5a, n->h5, n->gA, n->gB, n->gC, n->gD,
                     n->y32, n->cond, n->loss};
     for (void *q : ptrs) (void)hipFree(q);
     if (n->hcond) (void)hipHostFree(n->hcond);
@@ -1356,18 +1348,19 @@ extern "C" int mgfr_net_activation(mgfr_net *n, int index, void *dst, int64_t co
     if (index < 0 || index > 15) return set_error(MGFR_ERR_ARG, "activation index must be in [0, 15]");
     if (n->fwd_B == 0) return set_error(MGFR_ERR_ARG, "no forward pass has run on this network yet");
     // buffer, channels and pooling depth (0: S^3, 1: (S/2)^3, 2: (S/4)^3) in forward order
+    // (the convolutions read a concatenation from its two sources: those are formed
+    // here, in the scratch of the gradients)
     const __bf16 *buf[15] = {n->x0, n->h1a, n->s1, n->p1, n->h2a, n->s2, n->p2, n->h3a,
-                             n->h3, n->cat4, n->h4a, n->h4, n->cat5, n->h5a, n->h5};
+                             n->h3, n->gA, n->h4a, n->h4, n->gA, n->h5a, n->h5};
     static const int ch[16] = {16, 16, 16, 16, 32, 32, 32, 64, 64, 96, 32, 32, 48, 16, 16, 1};
     static const int depth[16] = {0, 0, 0, 1, 1, 1, 2, 2, 2, 1, 1, 1, 0, 0, 0, 0};
     const size_t vox = ((size_t)n->fwd_B << (3 * n->fwd_lg)) >> (3 * depth[index]);
     const size_t elems = vox * ch[index];
     if (count != (int64_t)elems) return set_error(MGFR_ERR_ARG, "count does not match the activation's size");
-    // the convolutions read a concatenation from its two sources: form it here
     if (index == 9)
-        k_concat_up<<<gridn(vox * 12), 256, 0, n->stream>>>(n->h3, 64, n->s2, 32, n->fwd_lg - 1, vox, n->cat4);
+        k_concat_up<<<gridn(vox * 12), 256, 0, n->stream>>>(n->h3, 64, n->s2, 32, n->fwd_lg - 1, vox, n->gA);
     if (index == 12)
-        k_concat_up<<<gridn(vox * 6), 256, 0, n->stream>>>(n->h4, 32, n->s1, 16, n->fwd_lg, vox, n->cat5);
+        k_concat_up<<<gridn(vox * 6), 256, 0, n->stream>>>(n->h4, 32, n->s1, 16, n->fwd_lg, vox, n->gA);
     MGFR_HIP(hipGetLastError());
     const void *src = index == 15 ? (const void *)n->y32 : (const void *)buf[index];
     const size_t esz = index == 15 ? sizeof(float) : sizeof(__bf16);

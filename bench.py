@@ -527,8 +527,11 @@ def main():
     if os.path.exists(tpath):
         tj = json.load(open(tpath))
         ent = tj.get(kernel.split(" ")[0])
-        if ent and ent.get("source_hash") == source_hash(src) and ent.get("mesh") == N:
-            traffic = ent.get("bytes_per_launch")
+        if ent and ent.get("mesh") == N:
+            if ent.get("source_hash") == source_hash(src):
+                traffic = ent.get("bytes_per_launch")
+            else:
+                log(f"no counted traffic: the record of {kernel} in profiles/sweep_traffic.json is of other sources")
     out = {
         "metric": "cells/s to converged f_R solve (res<1e-8), plain FP64 MG vs mixed+NN warm start",
         "value": head["cells_per_s"],

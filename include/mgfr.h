@@ -131,31 +131,34 @@ int mgfr_set_stream(mgfr_ctx *ctx, void *stream);
 int mgfr_set_timing(mgfr_ctx *ctx, int on);
 
 /* Float64 sweeps: smallest level size N at which a red-black sweep runs as
- * one fused, out-of-place kernel (both colours per launch, LDS-staged tiles);
- * the 32^3 and 64^3 levels below it make one or two sweeps per launch on tiles,
- * smaller ones use one in-place kernel per colour.  Default 128; 0 = one kernel
- * per colour on every level; otherwise n >= 64.  Results agree to rounding
- * either way. */
+ * one fused, out-of-place kernel (both colours per launch, rows of cells in
+ * LDS).  Of the levels below it, 32^3 and 64^3 make one or two sweeps per launch
+ * on tiles, larger ones use one in-place kernel per colour; 16^3 and smaller
+ * share one kernel always.  Default 128; 0 = one kernel per colour on every
+ * level from 32^3 on; otherwise n >= 64.  Results agree to rounding either
+ * way. */
 int mgfr_set_fused_min_mesh(mgfr_ctx *ctx, int n);
 
 /* Float32 correction sweeps of the mixed-precision solve: smallest level size
- * N at which each colour runs as the plane-marching pass kernel (row tiles of
- * cell pairs staged in LDS, exponentials evaluated once per cell); smaller
- * levels use the plain one-thread-per-cell kernel.  Default 128; 0 = never;
- * otherwise n >= 128.  Both apply the same update in the same red-black
- * order; results agree to float32 rounding. */
+ * N that is swept by the plane-marching kernels (rows of cell pairs staged in
+ * LDS, exponentials evaluated once per cell): a pass per colour or, from 256^3
+ * on, both at once (mgfr_set_fused_sweep32).  Of the levels below it, 32^3 and
+ * 64^3 are swept on tiles (mgfr_set_fused_sweep32), larger ones by the plain
+ * one-thread-per-cell kernel.  Default 128; 0 = never; otherwise n >= 128.  All
+ * apply the same update in the same red-black order; results agree to float32
+ * rounding. */
 int mgfr_set_colour_min_mesh(mgfr_ctx *ctx, int n);
 
-/* Float32 correction sweeps on the levels that use the pass kernels (see
- * mgfr_set_colour_min_mesh): on = 1 (default) runs each red-black sweep
- * (Sec. 3.3) of levels with N >= 256 as one fused, out-of-place kernel that
- * updates the red cells of plane i + 1 and the black cells of plane i - 1 while
- * marching over the planes, so that e, u and r are read once per sweep instead
- * of once per colour; the 32^3 and 64^3 levels make one or two sweeps per launch
- * on tiles; on = 0 runs one kernel per colour on every level.  The same updates
- * in the same order: the same iterates, bit for bit.  The second correction
- * buffer is allocated by mgfr_create for mixed-precision contexts, so this
- * call allocates nothing.  Errors: MGFR_ERR_ARG for on not 0 or 1. */
+/* Float32 correction sweeps: on = 1 (default) runs each red-black sweep
+ * (Sec. 3.3) of the levels with N >= 256 that use the plane-marching kernels (see
+ * mgfr_set_colour_min_mesh) as one out-of-place kernel that updates the red
+ * cells of plane i + 1 and the black cells of plane i - 1 while marching over
+ * the planes, so that e, u and r are read once per sweep instead of once per
+ * colour; the 32^3 and 64^3 levels make one or two sweeps per launch on tiles;
+ * on = 0 runs one kernel per colour on every level from 32^3 on.  The same
+ * updates in the same order: the same iterates, bit for bit.  The second
+ * correction buffer is allocated by mgfr_create for mixed-precision contexts,
+ * so this call allocates nothing.  Errors: MGFR_ERR_ARG for on not 0 or 1. */
 int mgfr_set_fused_sweep32(mgfr_ctx *ctx, int on);
 
 /* Relaxation factor omega of the float32 correction sweeps of the

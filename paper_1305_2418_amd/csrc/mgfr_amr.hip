@@ -22,8 +22,10 @@
 // are never updated, and the correction is zero there.
 //
 // Storage: each block keeps, per sublevel m (side b = 8 >> m), a padded
-// (b+2)^3 array; ghost faces towards a neighbouring block are refreshed by a
-// halo exchange after every update, the others hold the frozen values.
+// (b+2)^3 array.  Ghost faces without a neighbouring block hold the frozen
+// values; towards a neighbour, the sweeps and the whole mixed-precision cycle read
+// that block itself, and a halo exchange refreshes the faces for the float64
+// kernels that read them (restriction, residual norm).
 #include "mgfr_internal.h"
 #include "mgfr_ops.h"
 

@@ -55,8 +55,8 @@ struct mgfr_ctx {
     mgfr::Level lev[mgfr::kMaxLevels];
     double *alt0 = nullptr;  // level-0 second buffer (owned)
     // Levels with N >= this use the fused out-of-place sweep (0: never).  Fused
-    // against one launch per colour, us per sweep: 64^3 16 and 8, 128^3 21 and
-    // 26, 256^3 95 and 186, 512^3 763 and 1772.
+    // against one launch per colour, us per sweep, back to back: 64^3 14 and 7 (as
+    // tiles 5), 128^3 18 and 23, 256^3 98 and 176, 512^3 720 and 1770.
     int fused_min_n = 128;
     int colour32_min_n = 128; // float32 sweeps on levels with N >= this by one-colour pass kernels (0: never)
     // Those sweeps, from kFusedMin32 on, as one fused red-black kernel per sweep

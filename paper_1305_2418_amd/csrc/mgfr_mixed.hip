@@ -439,7 +439,7 @@ __global__ __launch_bounds__(64 * (CTJ + 2)) void k_mx_colour_zero(ColourArgs A)
     mx_colour_pass<true>(A, sB);
 }
 
-// ------------------------------------------- fused red-black sweep (N >= 128)
+// ------------------------------------------- fused red-black sweep (N >= 256)
 //
 // One whole float32 correction sweep (red cells, then black cells) in one
 // launch, out of place: eout = sweep(ein) on a split level (see sx); the

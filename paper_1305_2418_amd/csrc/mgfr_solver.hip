@@ -121,8 +121,8 @@ __device__ __forceinline__ double recip(double x)
 
 // Newton-Gauss-Seidel step from precomputed exponentials: ec = e^{u_c},
 // em = e^{-q u_c} - 1, neighbour values n* and their exponentials e*.  em is
-// expm1_64's in every sweep: for n = 1 rsqrt(ec) - 1 would be 3 % of a 512^3 sweep
-// cheaper (705 us for 727), but cancels for small u (solves of contrast 1e-6 stop
+// expm1_64's in every sweep: for n = 1 rsqrt(ec) - 1 would be cheaper (sweeps back to
+// back, 512^3: 705 us for 727, 256^3: 92 for 98), but cancels for small u (solves of contrast 1e-6 stop
 // at a residual of 2e-9) and is infinite where e^u underflows.
 __device__ __forceinline__ double ngs_step_e(double uc, double ec, double em, double n0, double e0, double n1,
                                              double e1, double n2, double e2, double n3, double e3, double n4,
@@ -139,7 +139,8 @@ __device__ __forceinline__ double ngs_step_e(double uc, double ec, double em, do
     return du;
 }
 
-// One full red-black sweep, out of place: out = sweep(u), on levels with N >= 64.
+// One full red-black sweep, out of place: out = sweep(u), on levels with N >= 64
+// (by default from 128^3 on).
 //
 // A workgroup has 15 waves, one per row of 128 cells (lane l: the pair
 // k0 + 2 l, k0 + 2 l + 1), and marches along i.  In step p it updates the red
@@ -157,8 +158,8 @@ __device__ __forceinline__ double ngs_step_e(double uc, double ec, double em, do
 // a tile (N = 64) hold it twice: both copies of a cell get the same value.
 //
 // Bound: the float64 vector pipe and the latency of a step (one workgroup per
-// CU: 128 registers).  512^3: 727 us per sweep (24 B per cell), 256^3
-// 98 us; a version with a row pair per thread, 12 x 60 of each 16 x 64 tile
+// CU: 128 registers).  Within a solve 0.71 ms per sweep of 512^3 (24 B per cell),
+// 91 us of 256^3, 20 us of 128^3; a version with a row pair per thread, 12 x 60 of each 16 x 64 tile
 // stored and a select for every operand issued twice the instructions: 1206 and
 // 207 us.  What mattered besides: no spilled register (a scratch load waits for
 // every prefetch before it), and exponentials after the barrier, not before it.
@@ -615,7 +616,7 @@ __global__ __launch_bounds__(kBlock) void k_dfr(const double *__restrict__ u, do
 // is the latency of each.  Every level lives in LDS as (u, e^u) pairs, so that
 // an update reads its neighbours' exponentials and evaluates one of its own
 // (in global memory, with eight exponentials and a division per update, the
-// cycle took 137 us for V(2,2) and 192 us for V(4,4); now 42 and 57 us).  A
+// cycle took 137 us for V(2,2) and 192 us for V(4,4); now 44 and 60 us).  A
 // thread owns W consecutive cells of a row (TailGrid) and keeps their values
 // and f in registers through a smoothing phase.
 
@@ -854,8 +855,8 @@ static inline unsigned nblocks(size_t n) { return (unsigned)((n + kBlock - 1) / 
 // consecutive 16-byte places.
 // Bound: float64 arithmetic, the surrounding rows included (1.6 times the cells'
 // updates for H = 2, 3.4 for H = 4), and the latency of a launch.  One launch per
-// colour took 3.5-3.9 us and the gap to the next: 32^3, two sweeps 4 x 3.5 -> 7.1 us
-// (H = 2 twice: 8.8); 64^3, one sweep 2 x 3.9 -> 5.9 us.
+// colour took 3.5-3.9 us and the gap to the next: 32^3, two sweeps 4 x 3.5 -> 7.3 us
+// (H = 2 twice: 8.8); 64^3, one sweep 2 x 3.9 -> 5.3 us.
 // PRO: the first sweeps after the coarse level: u + P(uc - ub) is formed as the tile
 // is loaded (about 1 us more, against 4.8 us of a launch of its own).
 template <int LG, int H, bool PRO>
@@ -992,7 +993,7 @@ int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sw
     Level &L = c->lev[l];
     OpConst kc = level_const(c, l);
     const bool fused = c->fused_min_n > 0 && L.N >= c->fused_min_n && L.alt != nullptr;
-    // Two sweeps in one launch on 32^3 (7.1 us against 8.8 for two launches, 64
+    // Two sweeps in one launch on 32^3 (7.3 us against 8.8 for two launches, 64
     // workgroups), not on 64^3, whose 256 workgroups then redo more than the
     // launch saves (13.3 us against 11.8)
     const bool tile = tile_level(c, L);

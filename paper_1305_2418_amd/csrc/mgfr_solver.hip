@@ -984,9 +984,10 @@ int row_chunk(int N, unsigned cols)
 }
 
 // `sweeps` red-black sweeps on level l.  Levels with N >= fused_min_n use the
-// out-of-place fused kernel and swap L.u / L.alt after each sweep; the others
-// update L.u in place with one kernel per colour.  With `from` (tile levels, at
-// least one sweep) the correction of that coarser level is added first.
+// out-of-place fused kernel, tile levels k_sweep_tile, and both swap L.u / L.alt
+// after each launch; the others update L.u in place with one kernel per colour.
+// With `from` (tile levels, at least one sweep) the correction of that coarser
+// level is added first.
 int launch_sweep64(mgfr_ctx *c, int l, double *u_unused, const double *f, int sweeps, bool timed, const Level *from)
 {
     (void)u_unused;

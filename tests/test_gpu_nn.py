@@ -618,3 +618,18 @@ def test_conv_backward_weight_from_inputs_at_any_element(S, Cin, Cout, off):
                                            dw.data_ptr(), db.data_ptr(), mg._stream_ptr()) == 0
     torch.cuda.synchronize()
     assert torch.equal(dw, want) and torch.equal(db, want_b)
+
+
+@pytest.mark.parametrize("B,S,Cin,Cout", [(1, 8, 96, 96), (2, 16, 96, 80), (1, 16, 80, 80)])
+def test_conv_backward_weight_of_the_widest_layers(B, S, Cin, Cout):
+    """Up to the 36 pairs of 16-channel blocks that the entry point takes, on small
+    integers (exact in any order): every block of every tap is there."""
+    mg = _mg()
+    print(f"[case] conv wgrad widest B={B} S={S} Cin={Cin} Cout={Cout}", flush=True)
+    g = torch.Generator().manual_seed(Cin + Cout)
+    x = torch.randint(-3, 4, (B, S, S, S, Cin), generator=g).to(torch.bfloat16).to(DEV)
+    dz = torch.randint(-3, 4, (B, S, S, S, Cout), generator=g).to(torch.bfloat16).to(DEV)
+    dw, db = mg.conv3d_bwd_weight(x, dz)
+    zf = dz.double().reshape(-1, Cout).t().contiguous()
+    assert torch.equal(dw.double(), torch.stack([zf @ xt for xt in _taps(x.double())]))
+    assert torch.equal(db.double(), zf.sum(1))
